@@ -88,8 +88,10 @@ int32_t attn_kv_spill(const attn_shape *shape, int32_t n_req, const int32_t *n_r
  * every suffix token over positions 1 .. its own (two launches on `stream`; three when the call
  * is small enough for key walks of 1024 keys and more to be split over workgroups, after which a
  * merge pass writes o).  Results do not depend on the batch a request is packed with as long as
- * its walk is not split.  attn_tune_split(0) keeps every walk whole; attn_tune_pack(0) keeps one
- * query head per workgroup also where suffixes are short (otherwise the heads of a key/value group
+ * its walk is not split.  A call whose requests all have at most 16 (token, query head of a group)
+ * rows behind 1024 keys or more (decoding) is walked by a kernel of its own, whole or split, with
+ * the sums over the keys in another order than the 128-row kernel's.  attn_tune_split(0) keeps every walk whole; attn_tune_pack(0) keeps one
+ * query head per workgroup also where suffixes are short, and either keeps such calls on the 128-row kernel (otherwise the heads of a key/value group
  * then share a workgroup's rows; results are bitwise the same either way).
  *   q            device, bf16, [T][H_q][d] (T = cu_seqlens[n_req]);  k_new, v_new: [T][H_kv][d]
  *   out_gate     device, bf16, [T][H_q][d], or NULL (no gate)

@@ -74,6 +74,7 @@ struct AttnArgs {
     const int32_t* unit_t0;   // device: first key tile of the unit
     const int32_t* unit_t1;   // device: one past its last key tile
     const int32_t* unit_part; // device: workspace slot of a partial result, or -1: the unit is a whole walk
+    const int32_t* unit_rec;  // device, few-rows kernel instead of the five arrays: NAR_REC ints per unit
     float* part_o;            // [slot][H_q][ATT_BQ][D] unnormalised partial outputs
     float* part_ml;           // [slot][H_q][ATT_BQ][2] running maximum (raw logits) and normaliser
     int64_t slot_stride;      // elements
@@ -106,9 +107,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // One wave-wide 16-byte-per-lane buffer load to LDS: lane i's chunk lands at lds + 16 i.  The descriptor covers
 // `bytes` from `base`; a lane whose byte offset voff + soff lies past it writes zeros.
+// CPOL 2: a non-temporal access.
+template <int CPOL = 0>
 __device__ __forceinline__ void load_to_lds(const void* base, int bytes, char* lds, int voff, int soff) {
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, CPOL);
 }
 
 // max / sum of a value with the lane 32 up or down (one swap instruction, no LDS)
@@ -121,6 +124,39 @@ __device__ __forceinline__ float sum_with_other_half(float x) {
     const unsigned u = __builtin_bit_cast(unsigned, x);
     const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);
+}
+
+// One 16-byte chunk of a key row copied and of a value row widened from bf16 to fp16.
+__device__ __forceinline__ void append_chunk(const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_dst, uint16_t* v_dst) {
+    *reinterpret_cast<u32x4*>(k_dst) = *reinterpret_cast<const u32x4*>(k_new);
+    const u32x4 vb = *reinterpret_cast<const u32x4*>(v_new);
+    half8 vh;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        vh[2 * i] = (_Float16)__builtin_bit_cast(float, vb[i] << 16);
+        vh[2 * i + 1] = (_Float16)__builtin_bit_cast(float, vb[i] & 0xffff0000u);
+    }
+    *reinterpret_cast<u32x4*>(v_dst) = __builtin_bit_cast(u32x4, vh);
+}
+
+// Four consecutive outputs of one row: gated, rounded to the output type, stored at element `at`.
+template <typename OT>
+__device__ __forceinline__ void store_out(void* o, const uint16_t* gate, int64_t at, f32x4 y) {
+    if (gate) {
+        const u32x2 gb = *reinterpret_cast<const u32x2*>(gate + at);
+        const float g0 = __builtin_bit_cast(float, gb[0] << 16), g1 = __builtin_bit_cast(float, gb[0] & 0xffff0000u);
+        const float g2 = __builtin_bit_cast(float, gb[1] << 16), g3 = __builtin_bit_cast(float, gb[1] & 0xffff0000u);
+        y[0] *= 1.f / (1.f + __expf(-g0));
+        y[1] *= 1.f / (1.f + __expf(-g1));
+        y[2] *= 1.f / (1.f + __expf(-g2));
+        y[3] *= 1.f / (1.f + __expf(-g3));
+    }
+    if constexpr (sizeof(OT) == 4) {
+        *reinterpret_cast<f32x4*>(static_cast<float*>(o) + at) = y;
+    } else {
+        const bf16x4 yb = __builtin_convertvector(y, bf16x4);
+        *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(o) + at) = __builtin_bit_cast(u32x2, yb);
+    }
 }
 
 // Appends the suffix's key and value rows to the cache rows start .. start+n-1 of each request's
@@ -139,15 +175,7 @@ __global__ void __launch_bounds__(APPEND_THREADS) attn_append_kernel(AppendArgs 
     const int64_t row = (int64_t)a.start[r] + (t - a.cu[r]);
     const int64_t dst = (int64_t)a.slot[r] * a.slot_stride + (row * a.row_chunks + c) * 8;
     const int64_t src = ((int64_t)t * a.row_chunks + c) * 8;
-    *reinterpret_cast<u32x4*>(a.k_cache + dst) = *reinterpret_cast<const u32x4*>(a.k_new + src);
-    const u32x4 vb = *reinterpret_cast<const u32x4*>(a.v_new + src);
-    half8 vh;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        vh[2 * i] = (_Float16)__builtin_bit_cast(float, vb[i] << 16);
-        vh[2 * i + 1] = (_Float16)__builtin_bit_cast(float, vb[i] & 0xffff0000u);
-    }
-    *reinterpret_cast<u32x4*>(a.v_cache + dst) = __builtin_bit_cast(u32x4, vh);
+    append_chunk(a.k_new + src, a.v_new + src, a.k_cache + dst, a.v_cache + dst);
 }
 
 template <int D>
@@ -403,23 +431,251 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
                 const int dv = 32 * rb + 8 * b + 4 * g;
-                f32x4 y = {O[rb][4 * b] * inv, O[rb][4 * b + 1] * inv, O[rb][4 * b + 2] * inv, O[rb][4 * b + 3] * inv};
-                if (a.gate) {
-                    const u32x2 gb = *reinterpret_cast<const u32x2*>(a.gate + base + dv);
-                    const float g0 = __builtin_bit_cast(float, gb[0] << 16), g1 = __builtin_bit_cast(float, gb[0] & 0xffff0000u);
-                    const float g2 = __builtin_bit_cast(float, gb[1] << 16), g3 = __builtin_bit_cast(float, gb[1] & 0xffff0000u);
-                    y[0] *= 1.f / (1.f + __expf(-g0));
-                    y[1] *= 1.f / (1.f + __expf(-g1));
-                    y[2] *= 1.f / (1.f + __expf(-g2));
-                    y[3] *= 1.f / (1.f + __expf(-g3));
-                }
-                if constexpr (sizeof(OT) == 4) {
-                    *reinterpret_cast<f32x4*>(static_cast<float*>(a.o) + base + dv) = y;
-                } else {
-                    const bf16x4 yb = __builtin_convertvector(y, bf16x4);
-                    *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.o) + base + dv) = __builtin_bit_cast(u32x2, yb);
-                }
+                store_out<OT>(a.o, a.gate, base + dv, f32x4{O[rb][4 * b] * inv, O[rb][4 * b + 1] * inv, O[rb][4 * b + 2] * inv, O[rb][4 * b + 3] * inv});
             }
+    }
+}
+
+// ---------------------------------------------------------------- few rows: the decode shape
+// Calls whose requests have at most NAR_ROWS rows (tokens x query heads of a key/value group) behind at least
+// 1024 keys: decoding, and suffixes of a few tokens.  Bound: HBM (every key and value is read once for 16 rows at
+// most), so nothing is spent on sharing a tile between waves: each of the four waves of a workgroup walks its own blocks of
+// 32 keys (every fourth one of the unit's range) without a barrier, the keys straight into registers as matrix operands, the
+// values by loads to LDS into a ring of two blocks of its own (the transposing reads need them there), always one block
+// ahead: 16 KiB in flight per wave at d = 128, 128 KiB per compute unit, where about 50 KiB cover the latency of the
+// memory at its full rate.  The 16 rows are the columns of 16x16x32 products, both contractions transposed as in
+// attn_suffix_kernel.  The four results are merged through LDS.  The kernel appends the suffix rows that lie in its own
+// range of keys itself, in front of the walk (nobody else reads them), so such a call has no append launch.
+constexpr int NAR_ROWS = 16;
+constexpr int NAR_KEYS = 32;      // keys per block
+constexpr int NAR_REC = 8;        // a unit's record: first token, tokens, start, slot, first key, one past the last, workspace slot or -1
+__host__ __device__ constexpr int narrow_wgs_per_cu(int d) { return d == 64 ? 3 : d == 128 ? 2 : 1; }
+
+template <int D>
+struct NarrowSmem {
+    static constexpr int CPR = D / 8;                        // 16-byte chunks per row
+    static constexpr int ROW_BYTES = D * 2;
+    static constexpr int BLOCK_BYTES = NAR_KEYS * ROW_BYTES; // one block of values
+    static constexpr int PIECES = BLOCK_BYTES / 1024;        // wave-wide loads per block
+    static constexpr int OROW = D + 4;                       // floats per row of a wave's result (padded)
+    static_assert(2 * NAR_ROWS * OROW * 4 <= 4 * BLOCK_BYTES, "the waves' results take the place of the value blocks");
+    // 16-byte chunk c of a value row is stored at c ^ f(row)
+    static __device__ __forceinline__ int f(int row) { return CPR >= 16 ? (row & 15) : ((row >> 1) & 7); }
+};
+
+__device__ __forceinline__ float max_over_groups(float x) {   // over the four groups of 16 lanes
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return max_with_other_half(fmaxf(__builtin_bit_cast(float, (unsigned)p[0]), __builtin_bit_cast(float, (unsigned)p[1])));
+}
+__device__ __forceinline__ float sum_over_groups(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return sum_with_other_half(__builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]));
+}
+
+template <int D, typename OT, bool NT>
+__global__ void __launch_bounds__(ATT_THREADS, narrow_wgs_per_cu(D)) attn_narrow_kernel(AttnArgs a, AppendArgs ap) {
+    typedef NarrowSmem<D> SM;
+    constexpr int KS = D / 32;      // contraction steps of S^T
+    constexpr int DB = D / 16;      // 16-column tiles of O^T
+    constexpr int NV = SM::PIECES;  // loads to LDS per block
+    constexpr int NK = 2 * KS;      // key loads per block
+    // the two halves of the rings are variables of their own: the compiler then sees that the transposing reads of one half
+    // do not depend on the loads to LDS in flight to the other, for which it would wait otherwise
+    __shared__ __attribute__((aligned(1024))) char ring0[4][SM::BLOCK_BYTES], ring1[4][SM::BLOCK_BYTES];
+    __shared__ float ml[4][NAR_ROWS][2];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    const int G = a.pack;                                   // query heads per key/value head
+    const int item = blockIdx.x / a.H_kv, kvh = blockIdx.x % a.H_kv;
+    // one record per unit, through the scalar cache: the first loads of a walk wait for one round trip to memory only
+    const int32_t* const rec = a.unit_rec + item * NAR_REC;
+    const int tok0 = rec[0], n = rec[1], c0 = rec[2], slot = rec[3], k0 = rec[4], k1 = rec[5], part = rec[6];
+    const int kv_len = c0 + n;
+    const int rows = n * G;
+    const int row_bytes = a.H_kv * D * 2;
+    uint16_t* const kslot = ap.k_cache + (int64_t)slot * a.slot_stride;
+    uint16_t* const vslot = ap.v_cache + (int64_t)slot * a.slot_stride;
+
+    // ---- loads of one block: values to LDS (a wave's 1 KiB per load, the chunk swizzle on the global side), keys to registers
+    const int nb = (k1 - k0 + NAR_KEYS - 1) / NAR_KEYS;
+    const int my = wave < nb ? (nb - wave + 3) / 4 : 0;     // blocks wave, wave + 4, ...
+    const int slot_bytes = kv_len * row_bytes;              // rows past kv_len read as zeros, which the mask never weighs
+    int voff[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int s = i * 64 + lane, row = s / SM::CPR, pos = s % SM::CPR;
+        voff[i] = row * row_bytes + kvh * D * 2 + ((pos ^ SM::f(row)) << 4);
+    }
+    const int koff = i16 * row_bytes + kvh * D * 2 + 16 * g;
+    auto load_values = [&](int j, char* st) {                // block j of this wave; past the last one the descriptor is empty
+        const int soff = __builtin_amdgcn_readfirstlane((k0 + (wave + 4 * j) * NAR_KEYS) * row_bytes);
+        const int bytes = j < my ? slot_bytes : 0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) load_to_lds<NT ? 2 : 0>(vslot, bytes, st + i * 1024, voff[i], soff);
+    };
+    auto load_keys = [&](int j, u32x4* kf) {
+        const int soff = __builtin_amdgcn_readfirstlane((k0 + (wave + 4 * j) * NAR_KEYS) * row_bytes);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(kslot, 0, j < my ? slot_bytes : 0, 0x00020000);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                kf[KS * b + s] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, koff + 16 * b * row_bytes + 64 * s, soff, NT ? 2 : 0);
+    };
+
+    // ---- the suffix rows inside [k0, k1) go to the cache (usually none, or those of the request's last unit)
+    const int new0 = max(c0, k0);
+    if (new0 < k1) {                 // uniform over the workgroup
+        for (int i = threadIdx.x; i < (k1 - new0) * SM::CPR; i += ATT_THREADS) {
+            const int row = new0 + i / SM::CPR, c = i % SM::CPR;
+            const int64_t dst = (int64_t)row * (a.H_kv * D) + kvh * D + 8 * c;
+            const int64_t src = (int64_t)(tok0 + row - c0) * (a.H_kv * D) + kvh * D + 8 * c;
+            append_chunk(ap.k_new + src, ap.v_new + src, kslot + dst, vslot + dst);
+        }
+        __syncthreads();             // (waits for the stores: the walk below reads these rows)
+    }
+    u32x4 ka[NK], kb[NK];
+    load_values(0, ring0[wave]);
+    load_keys(0, ka);
+
+    // ---- query fragments: B operand of S^T, column i16 = row of the workgroup, d = 32 s + 8 g + {0..7}
+    const int tl = min(i16, rows - 1) / G;
+    bf16x8 qf[KS];
+    {
+        const int hd = min(i16, rows - 1) - tl * G;
+        const uint16_t* const qp = a.q + ((int64_t)(tok0 + tl) * a.H_q + kvh * G + hd) * D + 8 * g;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + 32 * s));
+    }
+    const int lim = c0 + tl;         // last visible key of this lane's row
+
+    f32x4 O[DB];
+#pragma unroll
+    for (int i = 0; i < DB; ++i) O[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;    // m: of this lane's row; l: this lane's share of the row's normaliser
+    const float c = a.scale_log2e;
+    const int vrow = 4 * g + (i16 >> 2);                     // + 16: row of the transposing reads
+    const int vbase = vrow * SM::ROW_BYTES + 8 * (i16 & 1);
+    const int vch = (i16 & 3) >> 1;                          // + 2 db: chunk
+
+    auto block = [&](int j, const u32x4* kf, const char* st) {
+        // ---- S^T = K Q^T: register 4 b + e of group g is key 16 b + 4 g + e
+        f32x4 S[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                S[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[KS * b + s]), qf[s], S[b], 0, 0, 0);
+        }
+        const int kv0 = k0 + (wave + 4 * j) * NAR_KEYS;
+        if (kv0 + NAR_KEYS - 1 > c0) {                       // the block reaches past the first row's limit
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (kv0 + 16 * b + 4 * g + e > lim) S[b][e] = -INFINITY;
+        }
+        // ---- online softmax
+        float mx = fmaxf(fmaxf(fmaxf(S[0][0], S[0][1]), fmaxf(S[0][2], S[0][3])), fmaxf(fmaxf(S[1][0], S[1][1]), fmaxf(S[1][2], S[1][3])));
+        const float m_new = fmaxf(m, max_over_groups(mx));
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f((m - m_ref) * c);
+        const float mc = m_ref * c;
+        m = m_new;
+        half2 h[4];
+        float lsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f32x2 e;
+            e[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i >> 1][2 * (i & 1)], c, -mc));
+            e[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i >> 1][2 * (i & 1) + 1], c, -mc));
+            h[i] = __builtin_convertvector(e, half2);
+            const half2 one = {(_Float16)1.0f, (_Float16)1.0f};
+            lsum = __builtin_amdgcn_fdot2(h[i], one, lsum, false);   // the sum of the ROUNDED weights
+        }
+        const half8 pf = __builtin_shufflevector(__builtin_shufflevector(h[0], h[1], 0, 1, 2, 3),
+                                                 __builtin_shufflevector(h[2], h[3], 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
+        l = l * alpha + lsum;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+            for (int i = 0; i < DB; ++i) O[i] *= alpha;
+        }
+        // ---- O^T += V^T P^T
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(
+                st + vbase + (((2 * db + vch) ^ SM::f(vrow)) << 4)));
+            const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(
+                st + vbase + 16 * SM::ROW_BYTES + (((2 * db + vch) ^ SM::f(vrow + 16)) << 4)));
+            O[db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)), pf,
+                                                           O[db], 0, 0, 0);
+        }
+    };
+
+    // block j is here, block j + 1 on its way; nothing of a block's work moves up between the loads of the next one, and
+    // no load to a half of the ring is issued before this wave's reads of that half are done (lgkmcnt(0))
+    auto arrived = [] {
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmcnt<NV + NK>();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto half_free = [] {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int j = 0; j < my; j += 2) {
+        half_free();
+        load_values(j + 1, ring1[wave]);
+        load_keys(j + 1, kb);
+        arrived();
+        block(j, ka, ring0[wave]);
+        half_free();
+        load_values(j + 2, ring0[wave]);
+        load_keys(j + 2, ka);
+        arrived();
+        if (j + 1 < my) block(j + 1, kb, ring1[wave]);
+    }
+
+    // ---- merge of the four waves: each leaves its result in LDS, in the place of the value blocks
+    wait_vmcnt<0>();
+    __syncthreads();
+    auto om = [&](int w, int row) {                          // a row of wave w's result: waves 0, 1 in one half, 2, 3 in the other
+        return reinterpret_cast<float*>(w < 2 ? &ring0[0][0] : &ring1[0][0]) + ((w & 1) * NAR_ROWS + row) * SM::OROW;
+    };
+    {
+        const float lt = sum_over_groups(l);
+        if (g == 0) { ml[wave][i16][0] = m; ml[wave][i16][1] = lt; }
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+            *reinterpret_cast<f32x4*>(om(wave, i16) + 16 * db + 4 * g) = O[db];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < rows * (D / 4); i += ATT_THREADS) {
+        const int row = i / (D / 4), dv = 4 * (i % (D / 4));
+        const float M = fmaxf(fmaxf(ml[0][row][0], ml[1][row][0]), fmaxf(ml[2][row][0], ml[3][row][0]));
+        const float ref = M == -INFINITY ? 0.f : M;           // no key of this part is visible to this row
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float wt = __builtin_amdgcn_exp2f((ml[w][row][0] - ref) * c);
+            acc += wt * *reinterpret_cast<const f32x4*>(om(w, row) + dv);
+            L += wt * ml[w][row][1];
+        }
+        if (part >= 0) {
+            const int64_t prow = ((int64_t)part * a.H_kv + kvh) * ATT_BQ + row;
+            if (dv == 0) *reinterpret_cast<f32x2*>(a.part_ml + prow * 2) = f32x2{M, L};
+            *reinterpret_cast<f32x4*>(a.part_o + prow * D + dv) = acc;
+        } else {
+            const int t = row / G;
+            store_out<OT>(a.o, a.gate, ((int64_t)(tok0 + t) * a.H_q + kvh * G + row - t * G) * D + dv, acc * (1.f / L));
+        }
     }
 }
 
@@ -435,23 +691,18 @@ struct CombineArgs {
     const int32_t* piece_parts; // its number of parts (consecutive slots)
     int32_t H_q;
     int32_t pack;               // as in AttnArgs
+    int32_t subs;               // workgroups per (piece, head): enough threads for the rows of the fullest piece
     float scale_log2e;
 };
 
 // Merges the parts of one split piece for one query head: o = sum_p w_p O_p / sum_p w_p l_p with
 // w_p = 2^((m_p - max_p m_p) * scale * log2 e); a part that saw no key has m_p = -inf, weight 0 and O_p = 0.
-// One thread per (row, four value columns), COMBINE_SUBS workgroups per (piece, head); the loads of all
+// One thread per (row, four value columns), `subs` workgroups per (piece, head); the loads of all
 // parts are independent of each other, so the pass costs a few memory round trips, not one per part.
-template <int D>
-struct CombineShape {
-    static constexpr int CH = D / 4;                               // threads per row
-    static constexpr int SUBS = ATT_BQ * CH / ATT_THREADS;         // workgroups per (piece, head)
-};
-
 template <int D, typename OT>
 __global__ void __launch_bounds__(ATT_THREADS) attn_combine_kernel(CombineArgs a) {
-    constexpr int CH = CombineShape<D>::CH, SUBS = CombineShape<D>::SUBS;
-    const int ph = blockIdx.x / SUBS, sub = blockIdx.x % SUBS;
+    constexpr int CH = D / 4;                  // threads per row
+    const int ph = blockIdx.x / a.subs, sub = blockIdx.x % a.subs;
     const int R = a.pack, HB = a.H_q / R, TPW = ATT_BQ / R;
     const int piece = ph / HB, hb = ph % HB;
     const int r = a.piece_req[piece];
@@ -481,23 +732,8 @@ __global__ void __launch_bounds__(ATT_THREADS) attn_combine_kernel(CombineArgs a
             L += w * ml[1];
         }
         const float inv = 1.f / L;
-        f32x4 y = {acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
-        const int64_t at = ((int64_t)(tok0 + q0 + tl) * a.H_q + hq) * D + 4 * ch;
-        if (a.gate) {
-            const u32x2 gb = *reinterpret_cast<const u32x2*>(a.gate + at);
-            const float g0 = __builtin_bit_cast(float, gb[0] << 16), g1 = __builtin_bit_cast(float, gb[0] & 0xffff0000u);
-            const float g2 = __builtin_bit_cast(float, gb[1] << 16), g3 = __builtin_bit_cast(float, gb[1] & 0xffff0000u);
-            y[0] *= 1.f / (1.f + __expf(-g0));
-            y[1] *= 1.f / (1.f + __expf(-g1));
-            y[2] *= 1.f / (1.f + __expf(-g2));
-            y[3] *= 1.f / (1.f + __expf(-g3));
-        }
-        if constexpr (sizeof(OT) == 4) {
-            *reinterpret_cast<f32x4*>(static_cast<float*>(a.o) + at) = y;
-        } else {
-            const bf16x4 yb = __builtin_convertvector(y, bf16x4);
-            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.o) + at) = __builtin_bit_cast(u32x2, yb);
-        }
+        store_out<OT>(a.o, a.gate, ((int64_t)(tok0 + q0 + tl) * a.H_q + hq) * D + 4 * ch,
+                      f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv});
     }
 }
 

@@ -57,13 +57,18 @@ int32_t check_slots(const int32_t* ids, int32_t n, int32_t n_slots, bool skip_em
 constexpr int SPLIT_BELOW = 512;       // two workgroups per compute unit
 constexpr int SPLIT_MIN_KEYS = 512;
 constexpr int SPLIT_MAX_WGS = 768;
+// The few-rows kernel's walks are cut so that its workgroups fit the chip in one round, two per compute unit (64 one-token
+// requests behind 4 to 10 thousand keys, d = 128: at most 256 / 384 / 512 / 640 / 768 / 1024 workgroups 104 / 109 / 91 / 98 / 90 /
+// 107 us; four such requests 24 / 24 / 20 / 20 / 20 / 20 us).
+constexpr int NARROW_WGS = 512;
 
-// ints of the uploaded index arrays: cu (n_req+1), start, slot (n_req each), five per unit, four per split piece
+// ints of the uploaded index arrays: cu (n_req+1), start, slot (n_req each), five or eight per unit, four per split piece
 // (with packed rows a piece is 128 / G tokens, G the heads per key/value head: at most G times as many pieces)
+constexpr int UNIT_INTS = NAR_REC;
 inline int64_t max_items(int32_t n_req, int64_t T, int G) { return T * G / ATT_BQ + n_req; }
 inline int64_t max_units(int32_t n_req, int64_t T, int G) { return max_items(n_req, T, G) + SPLIT_MAX_WGS; }
 inline int64_t plan_ints(int32_t n_req, int64_t T, int G) {
-    return 3 * (int64_t)n_req + 1 + 5 * max_units(n_req, T, G) + 4 * max_items(n_req, T, G);
+    return 3 * (int64_t)n_req + 1 + NAR_REC + UNIT_INTS * max_units(n_req, T, G) + 4 * max_items(n_req, T, G);
 }
 inline int64_t plan_bytes(int32_t n_req, int64_t T, int G) {
     return (plan_ints(n_req, T, G) * (int64_t)sizeof(int32_t) + 255) / 256 * 256;
@@ -93,12 +98,28 @@ hipError_t launch_attn_d(int d, const AttnArgs& a, unsigned blocks, hipStream_t 
     }
 }
 
-template <typename OT>
-hipError_t launch_combine_d(int d, const CombineArgs& a, unsigned blocks /* (piece, head) pairs */, hipStream_t stream) {
+template <int D, typename OT, bool NT>
+hipError_t launch_narrow(const AttnArgs& a, const AppendArgs& ap, unsigned blocks, hipStream_t stream) {
+    hipLaunchKernelGGL((attn_narrow_kernel<D, OT, NT>), dim3(blocks), dim3(ATT_THREADS), 0, stream, a, ap);
+    return hipGetLastError();
+}
+
+template <typename OT, bool NT>
+hipError_t launch_narrow_d(int d, const AttnArgs& a, const AppendArgs& ap, unsigned blocks, hipStream_t stream) {
     switch (d) {
-        case 64: hipLaunchKernelGGL((attn_combine_kernel<64, OT>), dim3(blocks * CombineShape<64>::SUBS), dim3(ATT_THREADS), 0, stream, a); break;
-        case 128: hipLaunchKernelGGL((attn_combine_kernel<128, OT>), dim3(blocks * CombineShape<128>::SUBS), dim3(ATT_THREADS), 0, stream, a); break;
-        default: hipLaunchKernelGGL((attn_combine_kernel<256, OT>), dim3(blocks * CombineShape<256>::SUBS), dim3(ATT_THREADS), 0, stream, a); break;
+        case 64: return launch_narrow<64, OT, NT>(a, ap, blocks, stream);
+        case 128: return launch_narrow<128, OT, NT>(a, ap, blocks, stream);
+        default: return launch_narrow<256, OT, NT>(a, ap, blocks, stream);
+    }
+}
+
+template <typename OT>
+hipError_t launch_combine_d(int d, const CombineArgs& a, unsigned pairs /* (piece, head) */, hipStream_t stream) {
+    const dim3 grid(pairs * (unsigned)a.subs), block(ATT_THREADS);
+    switch (d) {
+        case 64: hipLaunchKernelGGL((attn_combine_kernel<64, OT>), grid, block, 0, stream, a); break;
+        case 128: hipLaunchKernelGGL((attn_combine_kernel<128, OT>), grid, block, 0, stream, a); break;
+        default: hipLaunchKernelGGL((attn_combine_kernel<256, OT>), grid, block, 0, stream, a); break;
     }
     return hipGetLastError();
 }
@@ -109,6 +130,8 @@ std::atomic<int32_t> g_allow_split{1}, g_allow_pack{1};   // attn_tune_split / a
 struct Unit { int32_t req, tile, t0, t1, part; };
 struct UnitPlan {
     int pack = 1;                     // query heads per token in a workgroup's rows: 1, or H_q / H_kv
+    bool narrow = false;              // the few-rows kernel
+    int max_rows = 0;                 // rows of the fullest piece
     std::vector<Unit> units;          // those with the most key tiles first
     std::vector<int32_t> piece_req, piece_tile, piece_base, piece_parts;   // the split pieces and their workspace slots
 };
@@ -128,8 +151,24 @@ void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const 
         }
         if (rows_packed * 5 <= rows_plain * 4 && g_allow_pack.load() != 0) pack = G;
     }
+    // ---- the few-rows kernel: every request has at most 16 rows, and a walk long enough for the split below (shorter walks
+    // stay whole and on the 128-row kernel, where a row's result does not depend on the batch or on the suffix around it).
+    // Measured, whole call, one-token requests, 128-row kernel against this one: 64 of 8 heads per key/value head behind 4 to 10
+    // thousand keys 130 against 91 us (465 MB read: 73 us at the rate of a plain copy), d = 64 127 against 87, d = 256 119
+    // against 81, four of them 32 against 20.
+    bool narrow = ATT_BQ % G == 0 && g_allow_pack.load() != 0 && g_allow_split.load() != 0;
+    int32_t longest = 0;
+    for (int32_t r = 0; r < n_req; ++r) {
+        if (len[r] == 0) continue;
+        longest = std::max(longest, len[r]);
+        if ((int64_t)len[r] * G > NAR_ROWS || start_pos[r] + len[r] < 2 * SPLIT_MIN_KEYS) narrow = false;
+    }
+    if (longest == 0) narrow = false;
+    if (narrow) pack = G;
     const int TPW = ATT_BQ / pack;        // tokens per workgroup
     const int HB = s->H_q / pack;         // head blocks (workgroups) per unit
+    out.narrow = narrow;
+    out.max_rows = (int)std::min<int64_t>(longest, TPW) * pack;
     // ---- pieces: one per TPW suffix tokens of a request
     struct Piece { int32_t req, tile, n_tiles, parts; };
     std::vector<Piece> pieces;
@@ -143,7 +182,20 @@ void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const 
     const int64_t n_items = (int64_t)pieces.size();
     // ---- too few workgroups for the chip: cut long key walks into parts
     int64_t split_wgs = 0;
-    if (n_items * HB < SPLIT_BELOW && g_allow_split.load() != 0) {
+    if (narrow) {
+        auto count = [&](int64_t tp) {
+            int64_t n = 0;
+            for (const Piece& p : pieces) n += (p.n_tiles + tp - 1) / tp;
+            return n * HB;
+        };
+        int64_t lo = SPLIT_MIN_KEYS / KT, hi = lo;
+        for (const Piece& p : pieces) hi = std::max<int64_t>(hi, p.n_tiles);
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (count(mid) <= NARROW_WGS) hi = mid; else lo = mid + 1;
+        }
+        for (Piece& p : pieces) p.parts = (int32_t)((p.n_tiles + lo - 1) / lo);      // (more requests than slots: lo is the longest walk)
+    } else if (n_items * HB < SPLIT_BELOW && g_allow_split.load() != 0) {
         int64_t tp = std::max<int64_t>(SPLIT_MIN_KEYS / KT, (total_tiles * HB + SPLIT_BELOW - 1) / SPLIT_BELOW);
         for (;; tp *= 2) {
             split_wgs = 0;
@@ -298,10 +350,12 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     if (!cu_seqlens || !start_pos || !seq_slot) return GDN_ERR_NULL;
     if (cu_seqlens[0] != 0) return GDN_ERR_SEQLENS;
     std::vector<int32_t> len(n_req);
+    int64_t kv_rows = 0;
     for (int32_t r = 0; r < n_req; ++r) {
         if (cu_seqlens[r + 1] < cu_seqlens[r]) return GDN_ERR_SEQLENS;
         len[r] = cu_seqlens[r + 1] - cu_seqlens[r];
         if (start_pos[r] < 0 || (int64_t)start_pos[r] + len[r] > cap) return GDN_ERR_START;
+        if (len[r] > 0) kv_rows += start_pos[r] + len[r];
     }
     rc = check_slots(seq_slot, n_req, n_slots, true, len.data());
     if (rc != GDN_OK) return rc;
@@ -335,21 +389,31 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     // the uploaded image is packed to what this call uses (the workspace is sized for the most a call can need):
     // a copy of a few hundred bytes takes the runtime's short path, one of 16 KiB and more does not
     const int64_t MU = n_units, MI = n_pieces;
-    std::vector<int32_t> img((size_t)(3 * (int64_t)n_req + 1 + 5 * MU + 4 * MI), 0);
+    const int64_t unit_ints = plan.narrow ? NAR_REC * MU : 5 * MU;
+    const int64_t unit_at = plan.narrow ? (3 * (int64_t)n_req + 1 + NAR_REC - 1) / NAR_REC * NAR_REC : 3 * (int64_t)n_req + 1;   // records: aligned
+    std::vector<int32_t> img((size_t)(unit_at + unit_ints + 4 * MI), 0);
     int32_t* p_cu = img.data();
     int32_t* p_start = p_cu + n_req + 1;
     int32_t* p_slot = p_start + n_req;
-    int32_t* p_unit = p_slot + n_req;          // five arrays of n_units
-    int32_t* p_piece = p_unit + 5 * MU;        // four arrays of n_pieces
+    int32_t* p_unit = p_cu + unit_at;          // five arrays of n_units, or records
+    int32_t* p_piece = p_unit + unit_ints;     // four arrays of n_pieces
     std::memcpy(p_cu, cu_seqlens, sizeof(int32_t) * (n_req + 1));
     std::memcpy(p_start, start_pos, sizeof(int32_t) * n_req);
     std::memcpy(p_slot, seq_slot, sizeof(int32_t) * n_req);
+    const int KT = att_kt(s->d);
     for (int64_t i = 0; i < n_units; ++i) {
-        p_unit[i] = units[i].req;
-        p_unit[MU + i] = units[i].tile;
-        p_unit[2 * MU + i] = units[i].t0;
-        p_unit[3 * MU + i] = units[i].t1;
-        p_unit[4 * MU + i] = units[i].part;
+        const Unit& u = units[i];
+        if (plan.narrow) {
+            const int32_t kv = start_pos[u.req] + len[u.req];
+            const int32_t rec[NAR_REC] = {cu_seqlens[u.req], len[u.req], start_pos[u.req], seq_slot[u.req], u.t0 * KT, std::min(u.t1 * KT, kv), u.part, 0};
+            std::memcpy(p_unit + NAR_REC * i, rec, sizeof rec);
+            continue;
+        }
+        p_unit[i] = u.req;
+        p_unit[MU + i] = u.tile;
+        p_unit[2 * MU + i] = u.t0;
+        p_unit[3 * MU + i] = u.t1;
+        p_unit[4 * MU + i] = u.part;
     }
     for (int64_t i = 0; i < n_pieces; ++i) {
         p_piece[i] = piece_req[i];
@@ -373,11 +437,14 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     ap.row_chunks = s->H_kv * s->d / 8;
     ap.n_chunks = T * ap.row_chunks;
     ap.n_req = n_req;
+    hipError_t e = hipSuccess;
     const int64_t ablocks = (ap.n_chunks + APPEND_THREADS - 1) / APPEND_THREADS;
     if (ablocks > INT32_MAX) return GDN_ERR_COUNT;
-    hipLaunchKernelGGL(attn_append_kernel, dim3((unsigned)ablocks), dim3(APPEND_THREADS), 0, stream, ap);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_err(e);
+    if (!plan.narrow) {                        // (the few-rows kernel appends its own rows)
+        hipLaunchKernelGGL(attn_append_kernel, dim3((unsigned)ablocks), dim3(APPEND_THREADS), 0, stream, ap);
+        e = hipGetLastError();
+        if (e != hipSuccess) return hip_err(e);
+    }
 
     AttnArgs a;
     a.q = static_cast<const uint16_t*>(q);
@@ -388,7 +455,8 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     a.cu = ap.cu;
     a.start = ap.start;
     a.slot = ap.slot;
-    a.unit_req = d + 3 * (int64_t)n_req + 1;
+    a.unit_rec = d + unit_at;
+    a.unit_req = d + unit_at;
     a.unit_tile = a.unit_req + MU;
     a.unit_t0 = a.unit_req + 2 * MU;
     a.unit_t1 = a.unit_req + 3 * MU;
@@ -402,8 +470,17 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     a.xcd_split = xcd_split ? 1 : 0;
     a.pack = pack;
     a.scale_log2e = s->scale * 1.4426950408889634f;
-    e = s->o_dtype == GDN_F32 ? launch_attn_d<float>(s->d, a, (unsigned)blocks, stream)
-                              : launch_attn_d<uint16_t>(s->d, a, (unsigned)blocks, stream);
+    if (plan.narrow) {
+        // non-temporal reads where a call reads more keys and values than the memory-side cache would hold for the next one
+        // (465 MB 91 against 99 us with ordinary reads; 16 requests, 92 MB read again and again, 32 against 28)
+        const unsigned nb = (unsigned)(n_units * HB);
+        const bool nt = kv_rows * s->H_kv * s->d * 4 > ((int64_t)128 << 20);
+        e = s->o_dtype == GDN_F32 ? (nt ? launch_narrow_d<float, true>(s->d, a, ap, nb, stream) : launch_narrow_d<float, false>(s->d, a, ap, nb, stream))
+                                  : (nt ? launch_narrow_d<uint16_t, true>(s->d, a, ap, nb, stream) : launch_narrow_d<uint16_t, false>(s->d, a, ap, nb, stream));
+    }
+    else
+        e = s->o_dtype == GDN_F32 ? launch_attn_d<float>(s->d, a, (unsigned)blocks, stream)
+                                  : launch_attn_d<uint16_t>(s->d, a, (unsigned)blocks, stream);
     if (e != hipSuccess || n_pieces == 0) return hip_err(e);
 
     CombineArgs ca;
@@ -412,12 +489,13 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     ca.gate = a.gate;
     ca.o = o;
     ca.cu = a.cu;
-    ca.piece_req = a.unit_req + 5 * MU;
+    ca.piece_req = d + unit_at + unit_ints;
     ca.piece_tile = ca.piece_req + MI;
     ca.piece_base = ca.piece_req + 2 * MI;
     ca.piece_parts = ca.piece_req + 3 * MI;
     ca.H_q = s->H_q;
     ca.pack = pack;
+    ca.subs = (plan.max_rows * (s->d / 4) + ATT_THREADS - 1) / ATT_THREADS;
     ca.scale_log2e = a.scale_log2e;
     e = s->o_dtype == GDN_F32 ? launch_combine_d<float>(s->d, ca, (unsigned)(n_pieces * HB), stream)
                               : launch_combine_d<uint16_t>(s->d, ca, (unsigned)(n_pieces * HB), stream);

@@ -332,6 +332,37 @@ def test_split_key_walks_agree_with_whole_walks(monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("H_q,H_kv,d,lens,starts", [
+    (16, 2, 128, [1, 2, 1, 0, 1], [1023, 1022, 4000, 7, 1100]),      # 8 and 16 rows, the shortest walks, an empty request, several parts
+    (4, 4, 64, [1, 15, 16, 3], [1087, 1085, 2047, 1024]),            # one head per group: 1 to 16 rows, new rows across key tiles
+    (32, 2, 64, [1, 1], [1023, 2600]),                               # 16 heads per group
+    (8, 2, 256, [4, 1, 3], [1500, 1023, 2046]),                      # d = 256, new rows across the parts of a walk
+    (16, 4, 128, [1, 4, 2] * 60, [1023, 1100, 1300] * 60),           # more requests than one round of workgroups: whole walks
+    (8, 4, 256, [1, 2, 1, 1, 2], [8200, 7000, 9001, 8191, 1030]),    # over 128 MiB of keys and values: the non-temporal reads
+])
+def test_few_rows_behind_long_prefixes(H_q, H_kv, d, lens, starts):
+    """The few-rows kernel (at most 16 rows behind 1024 keys or more) against the oracle and against the 128-row kernel:
+    the same weights, rounded to fp16 against another running maximum (2^-12 relative each) and summed in another order."""
+    c = wl.attn_case(3800 + len(lens) + d, H_q, H_kv, d, lens, starts, spare_slots=1)
+    AT.attn_tune_pack(False)
+    try:
+        wide, _, _ = gpu_prefill(c, gate=True)
+    finally:
+        AT.attn_tune_pack(True)
+    got, k_after, v_after = gpu_prefill(c, gate=True)
+    assert not np.array_equal(got, wide)                             # the other kernel did run
+    assert np.abs(got - wide).max() <= 2.0 ** -11 * np.abs(wide).max()
+    k_want, v_want = pools_with_prefix(c)
+    for r, s in enumerate(c.seq_slot):
+        k_want[s, :len(c.k_full[r])], v_want[s, :len(c.v_full[r])] = c.k_full[r], v_bits(c.v_full[r])
+    assert np.array_equal(k_after, k_want) and np.array_equal(v_after, v_want)
+    if sum(lens) < 100:
+        check_o(got, oracle_o(c, d ** -0.5, True), "f32")
+        bf, _, _ = gpu_prefill(c, "bf16")
+        check_o(bf, oracle_o(c, d ** -0.5), "bf16")
+
+
+@pytest.mark.gpu
 def test_rows_packed_by_head_group_give_bitwise_the_unpacked_result(monkeypatch):
     """Short suffixes put the query heads of a key/value group into one workgroup's rows; a row's arithmetic does not
     depend on the lane that carries it, so the outputs equal the one-head-per-workgroup run bit for bit (walks under
