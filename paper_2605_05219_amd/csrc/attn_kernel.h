@@ -59,6 +59,7 @@ constexpr int ATT_BQ = 128;       // rows (query columns of the accumulators) pe
 __host__ __device__ constexpr int att_kt(int d) { return d == 256 ? 32 : 64; }
 constexpr int ATT_THREADS = 256;
 constexpr int APPEND_THREADS = 256;
+constexpr float RESCALE_LOG2 = 8.f;
 
 struct AttnArgs {
     const uint16_t* q;        // [T][H_q][D]
@@ -186,7 +187,6 @@ struct AttnSmem {
     static constexpr int TILE_BYTES = KT * ROW_BYTES;
     static constexpr int K_OFF = 0, V_OFF = TILE_BYTES;
     static constexpr int STAGE_BYTES = 2 * TILE_BYTES;
-    static constexpr int BYTES = 2 * STAGE_BYTES;
     static constexpr int PIECES = TILE_BYTES / 1024;      // 1 KiB wave-wide loads per tile
     static_assert(D == 64 || D == 128 || D == 256, "head size");
     static_assert(PIECES % 4 == 0, "pieces split evenly over four waves");
@@ -201,9 +201,12 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     constexpr int CPR = SM::CPR;
     constexpr int KB = D / 16;      // contraction steps of S^T
     constexpr int RB = D / 32;      // row tiles of O^T
+    constexpr int FA = D == 256 ? 2 : 4;   // operand fragments read ahead of the matrix instructions
     constexpr int ATT_KT = SM::KT;
     constexpr int ATT_KVB = ATT_KT / 32;   // 32-row accumulator tiles of S^T per key tile
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    // the two stages are variables of their own: the compiler then sees that reads of one do not depend on the loads to LDS in
+    // flight to the other (in one array, it put a wait for the NEXT tile in front of the transposing reads of this one)
+    __shared__ __attribute__((aligned(1024))) char stage0[SM::STAGE_BYTES], stage1[SM::STAGE_BYTES];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -267,8 +270,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
         koff[i] = in_piece + ((pos ^ SM::fk(row)) << 4);
         voff[i] = in_piece + ((pos ^ SM::fv(row)) << 4);
     }
-    auto issue = [&](int t, int stage) {
-        char* const sb = smem + stage * SM::STAGE_BYTES;
+    auto issue = [&](int t, char* sb) {
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             const int p = wave * PPW + i;
@@ -277,7 +279,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
             load_to_lds(vslot, slot_bytes, sb + SM::V_OFF + p * 1024, voff[i], soff);
         }
     };
-    issue(t0, 0);
+    issue(t0, stage0);
 
     // ---- query fragments: B operand of S^T, d = 16*kb + 8*g + {0..7}
     bf16x8 qf[KB];
@@ -292,7 +294,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) O[rb][i] = 0.f;
-    float m = -INFINITY;     // running maximum of the raw logits of this lane's query (both half-waves agree)
+    float m = -INFINITY;     // reference of this lane's query: within 2^RESCALE_LOG2 of its running maximum (both half-waves agree)
     float l = 0.f;           // this half-wave's share of the normaliser
     const float c = a.scale_log2e;
 
@@ -305,36 +307,37 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     const int vrow_off = SM::V_OFF + vrow * SM::ROW_BYTES + 8 * (i16 & 1);
     const int vchunk = 2 * b4 + ((i16 & 3) >> 1);                   // + 4*rb
 
-    for (int t = t0; t < t1; ++t) {
-        const int stage = (t - t0) & 1;
+    // one key tile: this wave's part of tile t in stage sb, the loads of tile t + 1 to the other stage
+    auto tile = [&](int t, const char* sb, char* other) {
         wait_vmcnt<0>();
         __syncthreads();                       // tile t has landed; everyone has left the other stage
         if (t >= n_tiles_w) {                  // wave-uniform: nothing of this tile is visible to this wave
-            issue(t + 1, stage ^ 1);
-            continue;
+            asm volatile("");                  // (keeps the compiler from issuing the loads of both branches in front of the branch)
+            issue(t + 1, other);
+            return;
         }
-        const char* const sb = smem + stage * SM::STAGE_BYTES;
         const int kv0 = t * ATT_KT;
         // The next tile's loads are issued in between the matrix instructions of S^T (issuing one takes some
         // tens of cycles, which a matrix instruction in flight covers).  Past the unit's last tile the loads
         // are issued all the same: they stay inside the slot, or are cut to zeros by the descriptor, and land
         // in the stage nobody reads.
-        issue(t + 1, stage ^ 1);
+        issue(t + 1, other);
 
         // ---- S^T = K Q^T, in 32-row tiles
         f32x16 S[ATT_KVB];
 #pragma unroll
-        for (int kvb = 0; kvb < ATT_KVB; ++kvb) {
+        for (int kvb = 0; kvb < ATT_KVB; ++kvb)
 #pragma unroll
             for (int i = 0; i < 16; ++i) S[kvb][i] = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int kvb = 0; kvb < ATT_KVB; ++kvb) {
                 const bf16x8 kf = __builtin_bit_cast(
                     bf16x8, *reinterpret_cast<const u32x4*>(sb + SM::K_OFF + kvb * 32 * SM::ROW_BYTES + krow_off + (((2 * kb) ^ kz) << 4)));
                 S[kvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kb], S[kvb], 0, 0, 0);
             }
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);            // four key fragments ahead
+        __builtin_amdgcn_sched_group_barrier(0x100, FA, 0);           // FA key fragments ahead
 #pragma unroll
         for (int i = 0; i < ATT_KVB * KB; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);        // one matrix instruction
@@ -358,7 +361,11 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[kvb][i]);
         mx = max_with_other_half(mx);
-        const float m_new = fmaxf(m, mx);
+        // The reference of the weights follows the running maximum only when that has grown by more than 2^RESCALE_LOG2: the
+        // weights are then at most that large (fp16 and the fp32 sums hold them with the same relative precision), and most
+        // tiles need no pass over O (64 multiplications a lane, before that in nearly every tile of a walk's first half:
+        // some query of 32 nearly always sees a new maximum).  A row's own decision: nothing depends on its neighbours.
+        const float m_new = (mx - m) * c > RESCALE_LOG2 ? mx : m;
         // -inf only in a part of a split walk whose first tiles lie past this query's limit: nothing to weigh yet
         const float m_ref = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = __builtin_amdgcn_exp2f((m - m_ref) * c);
@@ -404,6 +411,16 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
                 O[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[s], O[rb], 0, 0, 0);
             }
         }
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * FA, 1);       // FA value fragments (two reads each) ahead
+#pragma unroll
+        for (int i = 0; i < RB * 2 * ATT_KVB; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
+        }
+    };
+    for (int t = t0; t < t1; t += 2) {
+        tile(t, stage0, stage1);
+        if (t + 1 < t1) tile(t + 1, stage1, stage0);
     }
 
     wait_vmcnt<0>();                           // no load to LDS may be in flight when the workgroup's LDS is given back

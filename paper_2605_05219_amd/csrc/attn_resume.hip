@@ -78,14 +78,7 @@ inline int64_t part_o_bytes(int d) { return (int64_t)SPLIT_MAX_WGS * ATT_BQ * d 
 
 template <int D, typename OT>
 hipError_t launch_attn(const AttnArgs& a, unsigned blocks, hipStream_t stream) {
-    constexpr int smem = AttnSmem<D>::BYTES;
-    // once per process, also when several host threads make their first call together
-    static std::once_flag once;
-    static hipError_t once_err = hipSuccess;
-    std::call_once(once, [] { once_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_suffix_kernel<D, OT>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem); });
-    if (once_err != hipSuccess) return once_err;
-    hipLaunchKernelGGL((attn_suffix_kernel<D, OT>), dim3(blocks), dim3(ATT_THREADS), smem, stream, a);
+    hipLaunchKernelGGL((attn_suffix_kernel<D, OT>), dim3(blocks), dim3(ATT_THREADS), 0, stream, a);
     return hipGetLastError();
 }
 
