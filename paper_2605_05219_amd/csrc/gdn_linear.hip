@@ -10,9 +10,10 @@
 //   2: 256 x 256 x 64, 2 stages, eight waves of 128 tokens x 64 outputs, two per SIMD: while one wave of a SIMD is held up
 //      issuing its loads to LDS the other feeds the matrix pipe, and a barrier covers 64 of k (the default for large
 //      problems; 1 is kept for comparison)
-//   3: 64 x 64 x 128, 4 stages, four waves of one 32 x 32 tile: problems so small that their 64 x 64 tiles fit the chip in two
-//      rounds (a 512-token out-projection: 64 workgroups of shape 0 would walk k one after the other, each step waiting for
-//      its loads; 256 small workgroups with three steps of 128 in flight take 11 us against 18)
+//   3: 64 x 64 x 64, 5 stages, four waves of one 32 x 32 tile, two workgroups per compute unit: problems whose 64 x 64 tiles fit
+//      the chip in one round, where a larger tile would walk k on too few compute units (512 x 2048 x 2048 11.7 us against 17 of
+//      shape 0; 64 x 64 x 128 in 4 stages with one workgroup per compute unit, the form before this one, 12.1, and with 257 to
+//      512 tiles, its second round, 21 against 14 us)
 // A load to LDS writes a wave's 1 KiB contiguously (lane i at 16 i), so rows are unpadded (2 BK bytes) and bank
 // conflicts are avoided by choosing WHICH 16-byte piece of its row a lane fetches: piece p of row r is stored at
 // position p ^ swz(r), swz(r) = (r / rows per 256 bytes) % pieces per row, which makes the 16 lanes that read the
@@ -49,7 +50,8 @@ struct LinearArgs {
     int64_t ldx, ldw, ldy;
     int64_t T;
     int32_t N, K;
-    int32_t tiles_n;
+    int32_t tiles_m, tiles_n;
+    int32_t per_xcd;                    // tiles per XCD
     // gdn_linear_split: the outputs go to n_seg destinations by column range; n_seg = 0: everything to y
     int32_t n_seg;
     int32_t seg_col[LIN_MAX_SEG + 1];   // segment s holds outputs seg_col[s] .. seg_col[s + 1] - 1
@@ -86,7 +88,7 @@ struct LinCfg {
 typedef LinCfg<128, 128, 64, 2, 2, 2, 2> LinSmall;
 typedef LinCfg<256, 256, 32, 4, 1, 2, 2> LinBig;      // four waves, 128 x 128 outputs each
 typedef LinCfg<256, 256, 64, 2, 1, 2, 4> LinBig8;     // eight waves, 128 tokens x 64 outputs each: two waves per SIMD
-typedef LinCfg<64, 64, 128, 4, 1, 2, 2> LinTiny;      // four waves of one 32 x 32 tile each, three k steps of 128 in flight
+typedef LinCfg<64, 64, 64, 5, 2, 2, 2> LinTiny;       // four waves of one 32 x 32 tile each, four k steps of 64 in flight
 
 // The loads of one wave for one stage: 1 KiB each, XL of its quarter of the x tile, then WL of the w tile.
 template <typename CFG>
@@ -122,7 +124,15 @@ gdn_linear_kernel(LinearArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / CFG::WAVES_N, wn = wave % CFG::WAVES_N;   // the wave's part: tokens WM wm .., outputs WN wn ..
     const int lr = lane & 31, g = lane >> 5;
-    const int tile_m = (int)blockIdx.x / a.tiles_n, tile_n = (int)blockIdx.x % a.tiles_n;
+    // ---- which tile.  Workgroups are dealt to the 8 XCDs (each with an L2 of its own) in turn: XCD x takes a consecutive run of the
+    // tiles, which are numbered GROUP_M tile rows at a time, down the rows first, so that the tiles an XCD works on together
+    // share their rows of x and of w in its L2.  (Row by row over the whole output, an XCD's 32 tiles touched nearly every row of w.)
+    constexpr int GROUP_M = CFG::BM == 256 ? 4 : 8;
+    const int seq = ((int)blockIdx.x & 7) * a.per_xcd + ((int)blockIdx.x >> 3);
+    if (seq >= a.tiles_m * a.tiles_n || ((int)blockIdx.x >> 3) >= a.per_xcd) return;
+    const int grp = seq / (GROUP_M * a.tiles_n), in_grp = seq % (GROUP_M * a.tiles_n);
+    const int grp_rows = min(a.tiles_m - grp * GROUP_M, GROUP_M);
+    const int tile_m = grp * GROUP_M + in_grp % grp_rows, tile_n = in_grp / grp_rows;
     const int64_t m0 = (int64_t)tile_m * BM;
     const int n0 = tile_n * BN;
 
@@ -353,7 +363,9 @@ hipError_t launch_linear(LinearArgs a, hipStream_t stream) {
     if (attr_err != hipSuccess) return attr_err;
     const int64_t tiles_m = (a.T + CFG::BM - 1) / CFG::BM;
     a.tiles_n = (a.N + CFG::BN - 1) / CFG::BN;
-    hipLaunchKernelGGL((gdn_linear_kernel<CFG, OUT_BF16>), dim3((unsigned)(tiles_m * a.tiles_n)), dim3(CFG::THREADS), CFG::SMEM, stream, a);
+    a.tiles_m = (int32_t)tiles_m;
+    a.per_xcd = (int32_t)((tiles_m * a.tiles_n + 7) / 8);
+    hipLaunchKernelGGL((gdn_linear_kernel<CFG, OUT_BF16>), dim3((unsigned)(8 * (int64_t)a.per_xcd)), dim3(CFG::THREADS), CFG::SMEM, stream, a);
     return hipGetLastError();
 }
 
@@ -371,25 +383,48 @@ int chip_cus_linear() {
     return n;
 }
 
-// Which tile shape a problem gets: the estimated time of each shape is its number of rounds of workgroups over the
-// chip times the work of one workgroup over the shape's measured rate (relative figures).
-int choose_linear_shape(int64_t T, int32_t N, int32_t K) {
+// The estimated time of a problem in a tile shape, in us at K = 2048: full rounds of workgroups over the chip, and a last one that
+// costs its latency (a workgroup alone walks k no faster) and more the fuller it is: the compute units share power and memory.
+// Fitted to T = 64 .. 8192, N = 32 .. 8224 (estimate against measured: 8192 x 8192 in shape 2 216 / 213, 8192 x 2560 91 / 93,
+// 4096 x 2560 43 / 43; in shape 0 8192 x 2560 87 / 84, 2048 x 8224 80 / 80, 512 x 8224 24 / 26; in shape 3 1024 x 2048 14.5 / 15.5).
+struct ShapeCost { int id, bm, bn, per_cu; double full, alone; bool square; };
+constexpr ShapeCost SHAPES[3] = {{3, 64, 64, 2, 14.5, 10.0, false}, {0, 128, 128, 2, 31.5, 16.0, false}, {2, 256, 256, 1, 54.0, 36.0, true}};
+double shape_cost(const ShapeCost& c, int64_t T, int64_t N) {
+    const int64_t tiles = ((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), slots = (int64_t)chip_cus_linear() * c.per_cu;
+    const double f = (double)(tiles % slots) / (double)slots;
+    return (double)(tiles / slots) * c.full + (f > 0 ? c.alone + (c.full - c.alone) * (c.square ? f * f : f) : 0.0);
+}
+
+// Which tile shape a problem gets, and how many of its columns: a problem whose tiles leave a last round nearly empty may be cut
+// into columns that fill whole rounds of 256 x 256 tiles and a rest in a smaller shape, a launch of its own.  Measured in a layer
+// group's pass: 8192 x 8224 (33 tile columns where 32 fill four rounds) 284 us whole, 244 + 12 cut; 8192 x 2560 114 whole, 63 + 35 cut (alone: 2048 x 8224 90 / 68, 4096 x 8224 142 / 122).
+struct LinearPlan { int shape, rest_shape; int32_t cols; };   // outputs 0 .. cols - 1 in `shape`, the others in `rest_shape`
+LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
     const int forced = g_linear_shape.load();
-    if (forced >= 0) return (forced == 3 && K % 128 != 0) ? 0 : forced;      // shape 3 walks k in steps of 128
-    const double cus = (double)chip_cus_linear();
-    // at most two rounds of 64 x 64 tiles, one per compute unit (measured, shape 3 against shape 0: 512 x 2048 11 against 17 us,
-    // 512 x 2560 19 against 23, 1024 x 2048 19 against 23; 256 x 8224, three rounds, 32 against 23)
-    if (K % 128 == 0 && (double)((T + 63) / 64) * (double)((N + 63) / 64) <= 2.0 * cus) return 3;
-    const struct { int id, bm, bn, per_cu; double rate; } shapes[2] = {{0, 128, 128, 2, 0.34}, {2, 256, 256, 1, 0.53}};
-    int best = 0;
-    double best_t = 0;
-    for (int i = 0; i < 2; ++i) {
-        const double wgs = (double)((T + shapes[i].bm - 1) / shapes[i].bm) * (double)((N + shapes[i].bn - 1) / shapes[i].bn);
-        const double rounds = std::ceil(wgs / (cus * shapes[i].per_cu));
-        const double t = rounds * shapes[i].per_cu * shapes[i].bm * shapes[i].bn / shapes[i].rate;
-        if (i == 0 || t < best_t) { best = shapes[i].id; best_t = t; }
+    if (forced >= 0) return {forced, 0, N};
+    auto best_of = [&](int64_t n, int shapes, double* t) {
+        int best = 0;
+        for (int i = 0; i < shapes; ++i) {
+            const double ti = shape_cost(SHAPES[i], T, n);
+            if (i == 0 || ti < *t) { best = SHAPES[i].id; *t = ti; }
+        }
+        return best;
+    };
+    double whole = 0.0;
+    LinearPlan p = {best_of(N, 3, &whole), 0, N};
+    const double launch = 4.0 * 2048.0 / (double)K;      // a second launch: about 4 us whatever K
+    double least = 0.97 * whole;                         // (a cut has to be worth it)
+    const int64_t tiles_m = (T + 255) / 256, cus = chip_cus_linear();
+    for (int64_t r = 1; r <= 64; ++r) {                  // the most columns that r rounds of 256 x 256 tiles hold
+        const int64_t cols = r * cus / tiles_m * 256;
+        if (cols >= N) break;
+        if (cols == 0) continue;
+        double rest = 0.0;
+        const int rest_shape = best_of(N - cols, 2, &rest);
+        const double t = shape_cost(SHAPES[2], T, cols) + rest + launch;
+        if (t < least) { least = t; p = {2, rest_shape, (int32_t)cols}; }
     }
-    return best;
+    return p;
 }
 
 }  // namespace linear
@@ -416,17 +451,47 @@ int32_t linear_checks(const void* x, int64_t ldx, const void* w, int64_t ldw, co
     return GDN_OK;
 }
 
-int32_t linear_launch(LinearArgs& a, int32_t out_dtype, hipStream_t stream) {
-    a.tiles_n = 0;
-    const bool bf = out_dtype == GDN_BF16;
+int32_t launch_shape(const LinearArgs& a, int shape, bool bf, hipStream_t stream) {
     hipError_t e;
-    switch (choose_linear_shape(a.T, a.N, a.K)) {
+    switch (shape) {
         case 1: e = bf ? launch_linear<LinBig, true>(a, stream) : launch_linear<LinBig, false>(a, stream); break;
         case 2: e = bf ? launch_linear<LinBig8, true>(a, stream) : launch_linear<LinBig8, false>(a, stream); break;
         case 3: e = bf ? launch_linear<LinTiny, true>(a, stream) : launch_linear<LinTiny, false>(a, stream); break;
         default: e = bf ? launch_linear<LinSmall, true>(a, stream) : launch_linear<LinSmall, false>(a, stream); break;
     }
     return hip_err(e);
+}
+
+// Columns c0 .. c1 - 1 of a projection as a projection of its own (c0 a multiple of 256: every alignment holds).
+LinearArgs column_range(const LinearArgs& a, int32_t c0, int32_t c1, int es) {
+    LinearArgs b = a;
+    b.w = static_cast<const char*>(a.w) + (int64_t)c0 * a.ldw * 2;
+    if (a.bias) b.bias = a.bias + c0;
+    b.N = c1 - c0;
+    if (a.n_seg == 0) {
+        b.y = static_cast<char*>(a.y) + (int64_t)c0 * es;
+        return b;
+    }
+    b.n_seg = 0;
+    for (int32_t sg = 0; sg < a.n_seg; ++sg) {
+        const int32_t lo = std::max(a.seg_col[sg], c0), hi = std::min(a.seg_col[sg + 1], c1);
+        if (lo >= hi) continue;
+        b.seg_col[b.n_seg] = lo - c0;
+        b.seg_y[b.n_seg] = static_cast<char*>(a.seg_y[sg]) + (int64_t)(lo - a.seg_col[sg]) * es;
+        b.seg_ld[b.n_seg] = a.seg_ld[sg];
+        ++b.n_seg;
+    }
+    for (int32_t sg = b.n_seg; sg <= LIN_MAX_SEG; ++sg) b.seg_col[sg] = b.N;
+    return b;
+}
+
+int32_t linear_launch(const LinearArgs& a, int32_t out_dtype, hipStream_t stream) {
+    const bool bf = out_dtype == GDN_BF16;
+    const LinearPlan p = plan_linear(a.T, a.N, a.K);
+    if (p.cols == a.N) return launch_shape(a, p.shape, bf, stream);
+    const int es = bf ? 2 : 4;
+    const int32_t rc = launch_shape(column_range(a, 0, p.cols, es), p.shape, bf, stream);
+    return rc != GDN_OK ? rc : launch_shape(column_range(a, p.cols, a.N, es), p.rest_shape, bf, stream);
 }
 }  // namespace
 

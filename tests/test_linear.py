@@ -216,6 +216,38 @@ def test_split_outputs_equal_the_whole_projection(shape, out):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("T,widths", [
+    (8192, [6144, 2048, 16, 16]),              # 33 columns of large tiles where 32 fill four rounds: the rest is two whole segments
+    (8100, [2048, 256, 256]),                  # eight columns of large tiles and a rest; a ragged last tile row
+    (8192, [2000, 304, 256]),                  # the cut (column 2048) inside the second segment
+])
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+def test_large_projection_cut_into_two_column_ranges(T, widths, out):
+    """Problems whose last round of large tiles would be nearly empty run as two launches; every shape computes the same
+    sums in the same order, so whole and split outputs equal one launch of the 128 x 128 shape bit for bit."""
+    import torch
+    K, N = 2048, sum(widths)
+    g = torch.Generator(device="cuda"); g.manual_seed(T + N)
+    x = torch.randn((T, K), device="cuda", generator=g).bfloat16()
+    w = (torch.randn((N, K), device="cuda", generator=g) / K ** 0.5).bfloat16()
+    b = torch.randn((N,), device="cuda", generator=g)
+    dt = torch.bfloat16 if out == "bf16" else torch.float32
+    new = lambda n: torch.full((T, n), float("nan"), dtype=dt, device="cuda")
+    want, whole, parts = new(N), new(N), [new(n + 8) for n in widths]
+    prev = LN.gdn_linear_tune(0)
+    try:
+        LN.gdn_linear(x, w, b, want, None)
+    finally:
+        LN.gdn_linear_tune(prev)
+    LN.gdn_linear(x, w, b, whole, None)
+    LN.gdn_linear_split(x, w, b, [p[:, :n] for p, n in zip(parts, widths)], None)
+    torch.cuda.synchronize()
+    assert torch.equal(whole, want)
+    assert torch.equal(torch.cat([p[:, :n] for p, n in zip(parts, widths)], 1), want)
+    assert all(torch.isnan(p[:, n:]).all() for p, n in zip(parts, widths))          # nothing written past a segment
+
+
+@pytest.mark.gpu
 def test_strided_inputs():
     import torch
     from paper_2605_05219_amd.device_call import to_device
