@@ -791,12 +791,20 @@ struct WsLayout {
     int32_t R, n_bufs;
     int64_t plan, carry, slab, total;
 };
-// n_chunks: chunks of the whole call; max_rounds: chunks of its longest request (or a bound)
-static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_rounds, int32_t n_req) {
+// Latency variant with launches apart: a call whose operand images come to more than this cuts its slabs of 64 rounds in half.  The
+// preparation's stores and the recurrence's loads of a slab then stay in the 256 MiB memory-side cache (48 chains of 128 chunks
+// 437 against 349 us, 64 chains of up to 125 chunks 325 against 286); a call that fits it as a whole pays for every further
+// slab (48 chains of up to 86 chunks 149 against 153, 32 chunks 84 against 85; d = 64, 128 chains 140 against 152).
+constexpr int64_t SLAB_CACHE_BYTES = (int64_t)192 << 20;
+// n_chunks: chunks of the whole call; max_rounds: chunks of its longest request (or a bound).  for_call: the layout a call uses, in
+// place of the size that is enough for every call of these bounds.
+static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_rounds, int32_t n_req, bool for_call = false) {
     const int64_t units = (int64_t)s.L * s.H_v, n_chains = units * n_req, ub = unit_bytes(s);
     const int nw = pick_waves(n_chains, s.d_v / 32, s.in_dtype != GDN_F32);
     WsLayout w;
     w.R = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slab_rounds(n_chains, ub, nw, s.d_v / 32), max_rounds));
+    if (for_call && g_forced_rounds.load() == 0 && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && n_chunks * units * ub > SLAB_CACHE_BYTES)
+        w.R = std::min(w.R, 32);
     w.plan = plan_bytes(n_chunks, n_req);
     w.carry = align_up(n_chains * s.d_v * s.d_k * (int64_t)sizeof(float), 256);
     w.slab = n_chains * w.R * ub;
@@ -896,7 +904,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     // The fused kernel needs the plan image only; the two-kernel path needs the carried states and a slab as well.
     // A workspace too small for the two-kernel path but large enough for the fused kernel gets the fused kernel
     // whatever the estimate says (gdn_workspace_bytes_fused is the size that asks for this).
-    WsLayout wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req);
+    WsLayout wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, true);
     int32_t n_staged = 0;
     if (src_on_host)
         for (int32_t r = 0; r < n_req; ++r) n_staged += src_slot[r] >= 0;
