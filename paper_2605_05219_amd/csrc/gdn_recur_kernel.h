@@ -274,6 +274,188 @@ __global__ void __launch_bounds__(64 * NW) gdn_recur_kernel(RecurArgs a) {
 #undef GDN_PREFETCH_IMAGE
 #undef GDN_PREFETCH_UT
 
+// Latency variant for fp32 operands (d_k = d_v = 64), for calls with at most one such workgroup per compute unit.
+// Bound: the fp32 matrix instructions of a chunk's dependent chain (32 clocks per 2048 flop and SIMD).  The
+// throughput variant gives a wave 32 columns of U, S and O: 240 products of 64 clocks one after the other, 9 us a chunk.
+// Here a workgroup of four waves, one per SIMD, takes 32 columns of a chain and splits them twice: 16 columns a wave on
+// v_mfma_f32_16x16x4_f32, and the chain (U, then S) on waves 0 and 1 apart from the outputs (S Q^T beside U, U P^T beside S) on
+// waves 2 and 3: 128 products of 32 clocks a chunk on the chain.  Measured: 2 chains of
+// 4 chunks 18.7 against 36.8 us, a chunk of a long chain about 3.3 against 8.
+//
+// The images are those of UnitLayout.  Step (t, e) of a product contracts over the indices 16 t + 4 g4 + e of the four groups of
+// 16 lanes, which is how an accumulator tile holds its rows (element e of lane (n, g4): row 4 g4 + e, column n), so S and U are
+// operands as they stand, for the wave that owns them and, through LDS, for the output wave.
+struct RecurF32Smem {
+    typedef UnitLayout<float, 64, 64> U;
+    static constexpr int S_OFF = U::STAGED_BYTES;            // [slice][t][lane] f32x4: S at the chunk start
+    static constexpr int U_OFF = S_OFF + 2 * 4 * 64 * 16;    // [slice][t][lane] f32x4: U of the chunk
+    static constexpr int BYTES = U_OFF + 2 * 4 * 64 * 16;
+};
+
+__global__ void __launch_bounds__(256) gdn_recur_f32_kernel(RecurArgs a) {
+    typedef UnitLayout<float, 64, 64> U;
+    typedef RecurF32Smem SM;
+    constexpr int C = 64, DK = 64, DV = 64, NT = 256;
+    constexpr int NK = U::NKD;               // steps of an image's row tile (over d_k and over the chunk's tokens alike)
+    static_assert(U::NKD == U::NKC, "one step count");
+    extern __shared__ __align__(16) char smem[];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, g4 = lane >> 4;
+    const int half = wave & 1;               // 16-column slice of the workgroup's 32 columns
+    const bool chain_wave = wave < 2;
+
+    const int units = a.L * a.H_v;
+    const int sl = blockIdx.x % 2;           // 32-column slice of d_v
+    const int chain = blockIdx.x / 2;
+    const int r = a.req_order[chain / units];
+    const int lh = chain % units;
+    const int l = lh / a.H_v;
+    const int hv = lh % a.H_v;
+    const int c_last = a.req_chunk_cu[r + 1];
+    const int c_begin = a.req_chunk_cu[r] + a.slab_begin;
+    if (c_begin >= c_last) return;
+    const int c_end = min(c_last, c_begin + a.R);
+
+    const int64_t unit_stride = (int64_t)units * U::UNIT_BYTES;
+    const char* unit = a.ws_units + ((int64_t)r * a.R * units + lh) * U::UNIT_BYTES;
+
+    // the next chunk's image waits in registers, and (chain waves) the next U~
+    constexpr int NVEC = U::STAGED_BYTES / 16, NFULL = NVEC / NT, TAIL = NVEC % NT;
+    u32x4 pre[NFULL], pre_tail = {0, 0, 0, 0};
+    f32x4 ut_pre[4];
+    auto fetch = [&](const char* u) {
+        const u32x4* src = reinterpret_cast<const u32x4*>(u) + tid;
+#pragma unroll
+        for (int i = 0; i < NFULL; ++i) pre[i] = src[i * NT];
+        if (TAIL > 0 && tid < TAIL) pre_tail = src[NFULL * NT];
+        const f32x4* ut = reinterpret_cast<const f32x4*>(u + U::UT_OFF) + (sl * 8 + (g4 >> 1)) * 64 + (g4 & 1) * 32 + 16 * half + n16;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) ut_pre[t] = ut[2 * t * 64];
+    };
+    fetch(unit);
+
+    // ---- start state: tile t of this slice: element e = S[32 sl + 16 half + n16][16 t + 4 g4 + e]
+    f32x4 S[4];
+    const int64_t head_off = ((int64_t)l * a.H_v + hv) * DV * DK + (int64_t)(32 * sl + 16 * half + n16) * DK + 4 * g4;
+    float* const carry = a.carry + (int64_t)r * units * DV * DK + head_off;
+    f32x4* const s_pub = reinterpret_cast<f32x4*>(smem + SM::S_OFF) + half * 4 * 64 + lane;
+    f32x4* const u_pub = reinterpret_cast<f32x4*>(smem + SM::U_OFF) + half * 4 * 64 + lane;
+    if (chain_wave) {
+        const int slot = a.req_src_slot[r];
+        const float* const from = a.slab_begin > 0 ? carry : slot >= 0 ? a.state_src + slot * a.src_slot_stride + head_off : nullptr;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            S[t] = from ? *reinterpret_cast<const f32x4*>(from + 16 * t) : f32x4{0.f, 0.f, 0.f, 0.f};
+            s_pub[t * 64] = S[t];
+        }
+    }
+
+    // an image's element for row 16 rt + n16, step (t, e)
+    const int frag0 = (4 * (g4 >> 1)) * 64 + (g4 & 1) * 32 + n16;
+    auto at = [&](const float* img, int rt, int t, int e) {
+        return img[frag0 + ((rt >> 1) * NK + 8 * t + e) * 64 + (rt & 1) * 16];
+    };
+    const float* const w_img = reinterpret_cast<const float*>(smem + U::W_OFF);
+    const float* const kt_img = reinterpret_cast<const float*>(smem + U::KT_OFF);
+    const float* const q_img = reinterpret_cast<const float*>(smem + U::Q_OFF);
+    const float* const p_img = reinterpret_cast<const float*>(smem + U::P_OFF);
+    const float* const gam = reinterpret_cast<const float*>(smem + U::AUX_OFF);
+    const int32_t* const meta = reinterpret_cast<const int32_t*>(gam + 2 * C);
+
+    for (int c = c_begin; c < c_end; ++c) {
+        {   // (the last barrier of the previous chunk is behind every read of its image)
+            u32x4* dst = reinterpret_cast<u32x4*>(smem) + tid;
+#pragma unroll
+            for (int i = 0; i < NFULL; ++i) dst[i * NT] = pre[i];
+            if (TAIL > 0 && tid < TAIL) dst[NFULL * NT] = pre_tail;
+        }
+        f32x4 acc[4];                        // chain waves: U by token tiles; output waves: O^T by token tiles
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = chain_wave ? ut_pre[t] : f32x4{0.f, 0.f, 0.f, 0.f};
+        if (c + 1 < c_end) unit += unit_stride;      // (the last chunk re-reads its own image)
+        fetch(unit);
+        __syncthreads();                     // the image and S are in LDS
+        const int eslot = meta[AUX_EMIT_SLOT], n = meta[AUX_LEN];
+        const int64_t row0 = (int64_t)l * a.T_alloc + meta[AUX_TOK0];
+        if (chain_wave) {
+            // ---- U = U~ + W S^T
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(w_img, rt, t, e), S[t][e], acc[rt], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) u_pub[t * 64] = acc[t];
+        } else {
+            // ---- O^T = (S Q^T) diag(gam scale): lane n16 of tile rt is token 16 rt + n16
+            f32x4 s[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s[t] = s_pub[t * 64];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(s[t][e], at(q_img, rt, t, e), acc[rt], 0, 0, 0);
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) acc[rt] *= gam[16 * rt + n16] * a.scale;
+        }
+        __syncthreads();                     // U is in LDS, S has been read
+        if (chain_wave) {
+            // ---- S^T = gam_C S^T + (K^T diag(dec)) U
+            const float gam_last = gam[C - 1];
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) S[rt] *= gam_last;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt) S[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(kt_img, rt, t, e), acc[t][e], S[rt], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s_pub[t * 64] = S[t];
+            if (eslot >= 0) {                // checkpoint emission: exact state after the last token of this chunk
+                float* const out = a.state_dst + eslot * a.dst_slot_stride + head_off;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(out + 16 * t) = S[t];
+            }
+        } else {
+            // ---- O^T += U^T P^T (P is lower triangular: token tile rt sees key tiles 0 .. rt), and out
+            f32x4 u[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) u[t] = u_pub[t * 64];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int rt = t; rt < 4; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t][e], at(p_img, rt, t, e), acc[rt], 0, 0, 0);
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) {
+                const int tok = 16 * rt + n16;
+                if (tok >= n) continue;
+                const int64_t off = ((row0 + tok) * a.H_v + hv) * DV + 32 * sl + 16 * half + 4 * g4;
+                if (a.o_bf16) {
+                    const uint32_t lo = f32_to_bf16_rne(acc[rt][0]) | ((uint32_t)f32_to_bf16_rne(acc[rt][1]) << 16);
+                    const uint32_t hi = f32_to_bf16_rne(acc[rt][2]) | ((uint32_t)f32_to_bf16_rne(acc[rt][3]) << 16);
+                    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.o) + off) = make_uint2(lo, hi);
+                } else {
+                    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.o) + off) = acc[rt];
+                }
+            }
+        }
+        __syncthreads();                     // the image and U have been read, S is in LDS
+    }
+    if (chain_wave && c_end < c_last) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(carry + 16 * t) = S[t];
+    }
+}
+
 // s_waitcnt vmcnt(N) (gfx9 encoding: vmcnt in bits 3:0 and 15:14; other counters left alone)
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -226,6 +226,42 @@ def test_fused_and_two_kernel_paths_both_meet_the_oracle(mode, H_qk, H_v, L, o_d
         B.gdn_tune_fused(prev)
 
 
+@pytest.mark.parametrize("L,H_qk,H_v", [(1, 1, 2), (2, 2, 4), (2, 8, 8), (3, 2, 6)])
+@pytest.mark.parametrize("o_dtype,scale", [("f32", 1.0), ("bf16", 0.125)])
+def test_fp32_recurrence_variants(L, H_qk, H_v, o_dtype, scale):
+    """fp32 inputs: token counts around the 16-token tiles and the 64-token chunks, emissions inside and at the end, 16 to 128
+    chains (two workgroups each: at most one per compute unit) and 144 (the throughput variant)."""
+    rng = np.random.default_rng(700 + L * H_v)
+    lens, starts = [1, 15, 16, 17, 63, 65, 200, 0], [0, 3, 64, 100, 7, 0, 1000, 5]
+    n_slots = 20
+    pool = (rng.standard_normal((n_slots, L, H_v, 64, 64)) * 0.5).astype(np.float32)
+    src = [-1, 0, 1, 2, 0, -1, 3, 3]
+    emits = [[1], [18], [], [101, 117], [70], [64, 65], [1001, 1064, 1200], []]
+    per = [wl.token_streams(rng, L, n, H_qk, H_v, 64, 64, "f32", "slow") for n in lens]
+    slots, nxt = [], 4
+    for e in emits:
+        slots.append(list(range(nxt, nxt + len(e)))); nxt += len(e)
+    call = wl.pack_call(L, H_qk, H_v, 64, 64, "f32", per, starts, src, emits, slots, n_slots)
+    check_call(call, pool, TOL["f32"], o_dtype=o_dtype, scale=scale)
+
+
+def test_halved_slabs_of_a_long_call_are_bitwise_the_whole_ones():
+    """48 chains whose operand images exceed the memory-side cache's share: slabs of 32 rounds instead of 64."""
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(41)
+    lens, starts = [4100, 3900, 4000], [0, 128, 64]
+    per = [wl.token_streams(rng, 1, n, 16, 16, 128, 128, "bf16", "slow") for n in lens]
+    pool = (rng.standard_normal((8, 1, 16, 128, 128)) * 0.1).astype(np.float32)
+    call = wl.pack_call(1, 16, 16, 128, 128, "bf16", per, starts, [-1, 0, 1], [[2048, 4100], [4028], []], [[2, 3], [4], []], 8)
+    o_auto, pool_auto = run_call_gpu(call, pool)
+    prev = B.gdn_tune_slab_rounds(64)
+    try:
+        o_64, pool_64 = run_call_gpu(call, pool)
+    finally:
+        B.gdn_tune_slab_rounds(prev)
+    assert np.array_equal(o_auto, o_64) and np.array_equal(pool_auto, pool_64)
+
+
 def test_bf16_output_and_scale():
     sc = wl.config1(orc.deepest_ckpt, seed=5, n_draws=2, N=1024, M=4, H=4, d=128)
     pool, _, _ = fill_pool_from_oracle(sc)
