@@ -303,45 +303,54 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, const int wg, const
         if (wave == 1) { kk_mi = 1; kk_nj = 0; }
         if (wave == 2) { kk_mi = 1; kk_nj = 1; p_mj = 1; p_ni = 1; }
         if (wave == 3) { p_mj = 0; p_ni = 1; }
-        if (kk_mi >= 0) {
-            f32x16 acc = {0};
+        // Waves 0 and 2 run their two products side by side (the key operand is the same): one after the other, each waiting
+        // for its own accumulator, they were the longest phase of a chunk (fp32 12.7 k of 40 k clocks, 16-bit 5.4 k of 29 k).
+        f32x16 kk = {0}, qk = {0};
+        if (kk_mi >= 0 && p_mj >= 0) {
+            const E* ar = Ks + (32 * kk_mi + lr) * K_LD;   // kk_nj = p_mj = p_ni = kk_mi
+            const E* br = Qs + (32 * kk_mi + lr) * K_LD;
+#pragma unroll
+            for (int s = 0; s < NKD; ++s) {
+                const Frag kf = EL::load(ar, s, g), qf = EL::load(br, s, g);
+                q_img[(p_ni * NKD + s) * 64 + lane] = qf;  // (these two also emit Q's fragments)
+                kk = EL::mma(kf, kf, kk);
+                qk = EL::mma(kf, qf, qk);
+            }
+        } else if (kk_mi >= 0) {
             const E* ar = Ks + (32 * kk_mi + lr) * K_LD;
             const E* br = Ks + (32 * kk_nj + lr) * K_LD;
 #pragma unroll
-            for (int s = 0; s < NKD; ++s) acc = EL::mma(EL::load(ar, s, g), EL::load(br, s, g), acc);
+            for (int s = 0; s < NKD; ++s) kk = EL::mma(EL::load(ar, s, g), EL::load(br, s, g), kk);
+        } else {
+            const E* ar = Ks + (32 * p_mj + lr) * K_LD;
+            const E* br = Qs + (32 * p_ni + lr) * K_LD;
+#pragma unroll
+            for (int s = 0; s < NKD; ++s) qk = EL::mma(EL::load(ar, s, g), EL::load(br, s, g), qk);
+        }
+        if (kk_mi >= 0) {
             const int j = 32 * kk_nj + lr;
             const float gj = gS[j];
 #pragma unroll
             for (int idx = 0; idx < 16; ++idx) {
                 const int i = 32 * kk_mi + acc_row(idx, g);
-                const float val = bS[i] * EL::exp_(fminf(gS[i] - gj, 0.f)) * acc[idx];
+                const float val = bS[i] * EL::exp_(fminf(gS[i] - gj, 0.f)) * kk[idx];
                 Lf[i * LF_LD + j] = (j < i) ? val : 0.f;
             }
         }
         if (p_mj >= 0) {
             // D[key j][query i]: the accumulators of lane (i, g) are row i of P at the key
             // positions that lane carries as an A operand, i.e. P's fragments (row tile p_ni).
-            f32x16 acc = {0};
-            const E* ar = Ks + (32 * p_mj + lr) * K_LD;   // rows: key token j
-            const E* br = Qs + (32 * p_ni + lr) * K_LD;   // rows: query token i
-            const bool write_q = (p_mj == p_ni);          // waves 0 and 2 also emit Q's fragments
-#pragma unroll
-            for (int s = 0; s < NKD; ++s) {
-                const Frag qf = EL::load(br, s, g);
-                if (write_q) q_img[(p_ni * NKD + s) * 64 + lane] = qf;
-                acc = EL::mma(EL::load(ar, s, g), qf, acc);
-            }
             const int i = 32 * p_ni + lr;
             const float gi = gS[i];
 #pragma unroll
             for (int idx = 0; idx < 16; ++idx) {
                 const int j = 32 * p_mj + acc_row(idx, g);
-                const float val = a.scale * EL::exp_(fminf(gi - gS[j], 0.f)) * acc[idx];
-                acc[idx] = (j <= i) ? val : 0.f;
+                const float val = a.scale * EL::exp_(fminf(gi - gS[j], 0.f)) * qk[idx];
+                qk[idx] = (j <= i) ? val : 0.f;
             }
 #pragma unroll
             for (int sub = 0; sub < SPT; ++sub)
-                p_img[(p_ni * U::NKC + p_mj * SPT + sub) * 64 + lane] = EL::from_acc(acc, sub);
+                p_img[(p_ni * U::NKC + p_mj * SPT + sub) * 64 + lane] = EL::from_acc(qk, sub);
         }
     }
     __syncthreads();  // L is complete; K, Q in LDS are dead
@@ -425,7 +434,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, const int wg, const
         for (int s = 0; s < NKC; ++s)
             if (s < ns) {
                 const Frag kf = EL::load(ar, s, g);
-                if (nt == 1) kt_img[(mt * NKC + s) * 64 + lane] = EL::scale(kf, decS, s, g);   // decayed to the chunk end
+                if ((nt == 1) == (s >= NKC / 2))   // K^T decayed to the chunk end; the two tiles that read it emit half each
+                    kt_img[(mt * NKC + s) * 64 + lane] = EL::scale(kf, decS, s, g);
                 acc = EL::mma(kf, EL::load_scaled((nt == 1 && s < NKC / 2) ? br10 : br, bgS, s, g), acc);
             }
 #pragma unroll
@@ -437,7 +447,9 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, const int wg, const
     {
         typedef typename EL::UtVec UtVec;
         UtVec* ut = reinterpret_cast<UtVec*>(unit + U::UT_OFF);
-        for (int p = wave; p < (DV / 32) * 2; p += 4) {
+        // (with four tiles, the waves that had W's short tiles above take the long ones here)
+        for (int p0 = wave; p0 < (DV / 32) * 2; p0 += 4) {
+            const int p = DV == 64 ? p0 ^ 2 : p0;
             const int sl = p % (DV / 32), rt = p / (DV / 32);
             f32x16 acc = {0};
             const float* ar = Lf + (32 * rt + lr) * LF_LD;
