@@ -85,9 +85,9 @@ int32_t attn_kv_spill(const attn_shape *shape, int32_t n_req, const int32_t *n_r
 /*
  * Suffix prefill of the attention layer for a packed batch of resumed requests: appends the
  * suffix's keys and values to each request's cache rows and computes the attention output of
- * every suffix token over positions 1 .. its own (two launches on `stream`; three when the call
- * is small enough for key walks of 1024 keys and more to be split over workgroups, after which a
- * merge pass writes o).  Results do not depend on the batch a request is packed with as long as
+ * every suffix token over positions 1 .. its own (an append and an attention launch on `stream`,
+ * behind the upload of the index arrays; one more, a merge pass that writes o, when the call is
+ * small enough for key walks of 1024 keys and more to be split over workgroups).  Results do not depend on the batch a request is packed with as long as
  * its walk is not split.  A call whose requests all have at most 16 (token, query head of a group)
  * rows behind 1024 keys or more (decoding) is walked by a kernel of its own, whole or split, with
  * the sums over the keys in another order than the 128-row kernel's.  attn_tune_split(0) keeps every walk whole; attn_tune_pack(0) keeps one

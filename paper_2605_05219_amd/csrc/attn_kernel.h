@@ -529,13 +529,13 @@ __global__ void __launch_bounds__(ATT_THREADS, narrow_wgs_per_cu(D)) attn_narrow
     }
     const int koff = i16 * row_bytes + kvh * D * 2 + 16 * g;
     auto load_values = [&](int j, char* st) {                // block j of this wave; past the last one the descriptor is empty
-        const int soff = __builtin_amdgcn_readfirstlane((k0 + (wave + 4 * j) * NAR_KEYS) * row_bytes);
+        const int soff = __builtin_amdgcn_readfirstlane(j < my ? (k0 + (wave + 4 * j) * NAR_KEYS) * row_bytes : 0);
         const int bytes = j < my ? slot_bytes : 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) load_to_lds<NT ? 2 : 0>(vslot, bytes, st + i * 1024, voff[i], soff);
     };
     auto load_keys = [&](int j, u32x4* kf) {
-        const int soff = __builtin_amdgcn_readfirstlane((k0 + (wave + 4 * j) * NAR_KEYS) * row_bytes);
+        const int soff = __builtin_amdgcn_readfirstlane(j < my ? (k0 + (wave + 4 * j) * NAR_KEYS) * row_bytes : 0);
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(kslot, 0, j < my ? slot_bytes : 0, 0x00020000);
 #pragma unroll
         for (int b = 0; b < 2; ++b)
