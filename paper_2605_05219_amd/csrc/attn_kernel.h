@@ -59,7 +59,6 @@ constexpr int ATT_BQ = 128;       // rows (query columns of the accumulators) pe
 __host__ __device__ constexpr int att_kt(int d) { return d == 256 ? 32 : 64; }
 constexpr int ATT_THREADS = 256;
 constexpr int APPEND_THREADS = 256;
-constexpr float RESCALE_LOG2 = 8.f;
 
 struct AttnArgs {
     const uint16_t* q;        // [T][H_q][D]
@@ -294,7 +293,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) O[rb][i] = 0.f;
-    float m = -INFINITY;     // reference of this lane's query: within 2^RESCALE_LOG2 of its running maximum (both half-waves agree)
+    float m = -INFINITY;     // running maximum of the raw logits of this lane's query (both half-waves agree)
     float l = 0.f;           // this half-wave's share of the normaliser
     const float c = a.scale_log2e;
 
@@ -361,11 +360,10 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[kvb][i]);
         mx = max_with_other_half(mx);
-        // The reference of the weights follows the running maximum only when that has grown by more than 2^RESCALE_LOG2: the
-        // weights are then at most that large (fp16 and the fp32 sums hold them with the same relative precision), and most
-        // tiles need no pass over O (64 multiplications a lane, before that in nearly every tile of a walk's first half:
-        // some query of 32 nearly always sees a new maximum).  A row's own decision: nothing depends on its neighbours.
-        const float m_new = (mx - m) * c > RESCALE_LOG2 ? mx : m;
+        // The weights' reference is the running maximum itself, so that a row's heaviest weight is exactly 1 and carries no
+        // rounding.  (A reference that follows the maximum only when that has grown by 2^8 spares most passes over O, 4 % of a
+        // large call at d = 128, 7 % at 256, but rounds the weight that counts most to fp16 like the others: errors 1.6 to 1.7 times as large on peaked rows.)
+        const float m_new = fmaxf(m, mx);
         // -inf only in a part of a split walk whose first tiles lie past this query's limit: nothing to weigh yet
         const float m_ref = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = __builtin_amdgcn_exp2f((m - m_ref) * c);

@@ -311,6 +311,45 @@ def test_peaked_and_flat_logits_stay_within_tolerance():
     assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max()     # no bf16 weight error at all in this case
 
 
+def running_maximum_rule(c, scale, tile):
+    """The outputs in fp64 but for one rounding: a walk in tiles of `tile` keys takes its weights against the running maximum
+    and rounds them to fp16, so the heaviest weight of a row is exactly 1.  (What the kernels compute, fp32 sums aside.)"""
+    out = np.zeros((c.T, c.H_q, c.d))
+    for r in range(len(c.start_pos)):
+        lo, hi, c0 = int(c.cu_seqlens[r]), int(c.cu_seqlens[r + 1]), int(c.start_pos[r])
+        q, k, v = f64(c.q[lo:hi]), f64(c.k_full[r]), f64(c.v_full[r])
+        visible = np.arange(len(k))[None, :] <= (c0 + np.arange(hi - lo))[:, None]
+        for h in range(c.H_q):
+            g = h // (c.H_q // c.H_kv)
+            S = np.where(visible, q[:, h] @ k[:, g].T * (scale * np.log2(np.e)), -np.inf)
+            m, num, den = np.full(hi - lo, -np.inf), 0.0, 0.0
+            for t in range(0, len(k), tile):
+                m_new = np.maximum(m, S[:, t:t + tile].max(axis=1))       # finite: key 0 is visible to every row
+                w = np.exp2(S[:, t:t + tile] - m_new[:, None]).astype(np.float16).astype(np.float64)
+                alpha = np.exp2(m - m_new)
+                num, den, m = num * alpha[:, None] + w @ v[t:t + tile, g], den * alpha + w.sum(axis=1), m_new
+            out[lo:hi, h] = num / den[:, None]
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("q_spread", [1.0, 2.0, 4.0])
+@pytest.mark.parametrize("lens,starts", [
+    ([96, 128], [900, 700]),                                # the 128-row kernel, whole walks
+    ([8, 7, 5, 8, 6, 8], [1024, 1100, 1500, 1040, 1300, 1900]),   # the few-rows kernel
+])
+def test_error_is_that_of_weights_rounded_against_the_maximum(lens, starts, q_spread):
+    """The error against fp64, as a 2-norm, is the one of rounding the weights to fp16 against the running maximum, and no
+    more: 5 % on top cover the fp32 sums (1e-6 against 5e-5 and more) and weights that fp32 logits push over a rounding boundary.
+    (Weights taken against any older reference, the heaviest one rounded as well, give 1.1, 1.6 and 1.7 times as much here.)
+    Walks in parts or by several waves have several exactly weighted maxima a row and err less."""
+    c = wl.attn_case(3900, 4, 2, 128, lens, starts, q_spread=q_spread)
+    got, _, _ = gpu_prefill(c)
+    ref = oracle_o(c, 128 ** -0.5)
+    rel = lambda x: np.linalg.norm(x - ref) / np.linalg.norm(ref)
+    assert rel(got) <= 1.05 * rel(running_maximum_rule(c, 128 ** -0.5, 64))
+
+
 @pytest.mark.gpu
 def test_split_key_walks_agree_with_whole_walks(monkeypatch):
     """A call with few workgroups splits its long key walks and merges the parts: the same result up to the
