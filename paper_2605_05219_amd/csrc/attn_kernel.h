@@ -106,7 +106,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 // One wave-wide 16-byte-per-lane buffer load to LDS: lane i's chunk lands at lds + 16 i.  The descriptor covers
-// `bytes` from `base`; a lane whose byte offset voff + soff lies past it writes zeros.
+// `bytes` from `base`; a lane whose byte offset voff + soff lies past it writes zeros.  soff itself is at most `bytes`.
 // CPOL 2: a non-temporal access.
 template <int CPOL = 0>
 __device__ __forceinline__ void load_to_lds(const void* base, int bytes, char* lds, int voff, int soff) {
@@ -253,7 +253,9 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     // ---- tile loader: wave w brings pieces [w*PPW, (w+1)*PPW) of the key and of the value tile, one 16-byte
     // chunk per lane and piece, by buffer loads to LDS.  The descriptors cover rows [0, kv_len) of the request's
     // slot: lanes of rows past kv_len (the ragged end of the last tile) write zeros, which the mask never weighs.
-    // A lane's offset inside a piece does not change from tile to tile; the tile and piece move in the scalar offset.
+    // A lane's offset inside a piece does not change from tile to tile; the tile and piece move in the scalar offset, which
+    // stops at the descriptor's end: a piece wholly past it (also all of a tile past the walk's last) has no byte in range
+    // however the hardware compares the sum.
     constexpr int PPW = SM::PIECES / 4;                    // pieces per wave and tensor
     constexpr int RPP = 64 / CPR;                          // rows per piece
     const int row_bytes = a.H_kv * D * 2;
@@ -273,7 +275,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             const int p = wave * PPW + i;
-            const int soff = (t * ATT_KT + p * RPP) * row_bytes;
+            const int soff = min((t * ATT_KT + p * RPP) * row_bytes, slot_bytes);
             load_to_lds(kslot, slot_bytes, sb + SM::K_OFF + p * 1024, koff[i], soff);
             load_to_lds(vslot, slot_bytes, sb + SM::V_OFF + p * 1024, voff[i], soff);
         }
@@ -318,8 +320,8 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
         const int kv0 = t * ATT_KT;
         // The next tile's loads are issued in between the matrix instructions of S^T (issuing one takes some
         // tens of cycles, which a matrix instruction in flight covers).  Past the unit's last tile the loads
-        // are issued all the same: they stay inside the slot, or are cut to zeros by the descriptor, and land
-        // in the stage nobody reads.
+        // are issued all the same: they stay inside the visible rows, or are cut to zeros by the descriptor, and
+        // land in the stage nobody reads.
         issue(t + 1, other);
 
         // ---- S^T = K Q^T, in 32-row tiles

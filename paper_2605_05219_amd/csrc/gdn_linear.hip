@@ -183,9 +183,9 @@ gdn_linear_kernel(LinearArgs a) {
 #pragma unroll
         for (int t = 0; t < TJ; ++t) wf[set][t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 32 * t * RB + pos));
     };
-    // Loads are issued for every stage slot, also past the last k step: there the descriptor is empty (no lane is in
-    // range, nothing is fetched), so that the number of loads in flight, and with it every wait below, is the same in
-    // every round and the loop body has no branch for the scheduler to stop at.
+    // Loads are issued for every stage slot, also past the last k step: there the descriptor is empty and the scalar offset
+    // zero (no lane is in range by definition, nothing is fetched), so that the number of loads in flight, and with it every
+    // wait below, is the same in every round and the loop body has no branch for the scheduler to stop at.
     auto mma_all = [&](int set) {
 #pragma unroll
         for (int tj = 0; tj < TJ; ++tj)
@@ -196,7 +196,7 @@ gdn_linear_kernel(LinearArgs a) {
 #pragma unroll
     for (int p = 0; p < STAGES; ++p) {
         const bool live = p < n_steps;
-        LinLoad<CFG>::all(smem, p, p * BK, wave, xb, live ? x_bytes : 0, wb, live ? w_bytes : 0, xoff, woff);
+        LinLoad<CFG>::all(smem, p, live ? p * BK : 0, wave, xb, live ? x_bytes : 0, wb, live ? w_bytes : 0, xoff, woff);
     }
     wait_vm<(STAGES - 1) * CFG::LPS>();
     __syncthreads();
@@ -242,7 +242,7 @@ gdn_linear_kernel(LinearArgs a) {
             // to LDS takes tens of cycles to issue, so one goes out behind every few matrix instructions, which covers it;
             // the fragments of the next stage's first k step are read in between as well.
             const bool live = step + STAGES < n_steps;
-            const int xbytes = live ? x_bytes : 0, wbytes = live ? w_bytes : 0;
+            const int xbytes = live ? x_bytes : 0, wbytes = live ? w_bytes : 0, k_ahead = live ? (step + STAGES) * BK : 0;
             const char* xs = smem + next_stage * CFG::STAGE_BYTES;
             const char* ws = xs + CFG::X_BYTES;
             const int pos = (g ^ sw) * 16;
@@ -260,7 +260,7 @@ gdn_linear_kernel(LinearArgs a) {
                 }
 #pragma unroll
                 for (int j = i * NL / SLOTS; j < (i + 1) * NL / SLOTS; ++j)
-                    LinLoad<CFG>::one(j, smem, stage, (step + STAGES) * BK, wave, xb, xbytes, wb, wbytes, xoff, woff);
+                    LinLoad<CFG>::one(j, smem, stage, k_ahead, wave, xb, xbytes, wb, wbytes, xoff, woff);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

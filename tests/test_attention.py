@@ -296,6 +296,18 @@ def test_seeded_random_shapes_match_the_oracle():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_walks_that_end_anywhere_in_a_key_tile(d):
+    """Tiles whose last pieces, or all pieces but the first, lie past the visible rows, and walks after whose last tile nothing
+    of the slot is left: what lies past a request's rows (NaN here) never reaches an output."""
+    lens = [1, 2, 1, 3, 1, 5, 1, 17]
+    starts = [0, 31, 62, 61, 64, 123, 127, 175]            # 1, 33, 63, 64, 65, 128, 128 and 192 rows
+    c = wl.attn_case(3150 + d, 4, 2, d, lens, starts)
+    got, _, _ = gpu_prefill(c)
+    check_o(got, oracle_o(c, d ** -0.5), "f32")
+
+
+@pytest.mark.gpu
 def test_peaked_and_flat_logits_stay_within_tolerance():
     """Widely spread logits (a few keys carry the weight; the running maximum moves often) and all-equal logits
     (every weight is exactly 1: the result is the running mean of the values to fp32 accuracy)."""

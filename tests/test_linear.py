@@ -175,6 +175,23 @@ def test_linear_against_the_definition(T, N, K, bias, out, shape):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("shape", [0, 1, 2, 3])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320])
+def test_stages_past_the_last_k_step_fetch_nothing(shape, K):
+    """Fewer k steps than a shape has stages (2 to 5), and just as many: the loads issued for the others are out of range by
+    definition, on operands that end with their allocations."""
+    T, N = 70, 68
+    x, w, b = draw(31 + K, T, N, K, True)
+    prev = LN.gdn_linear_tune(shape)
+    try:
+        y = run_gpu(x, w, b, "f32")
+    finally:
+        LN.gdn_linear_tune(prev)
+    ref = lo.linear(x, w, b)
+    assert (np.abs(y - ref) <= bound(x, w, b, ref, K, "f32")).all()
+
+
+@pytest.mark.gpu
 def test_output_may_be_a_column_slice_of_a_wider_buffer():
     T, N, K = 200, 256, 128
     x, w, b = draw(5, T, N, K, True)
