@@ -85,14 +85,24 @@ int32_t attn_kv_spill(const attn_shape *shape, int32_t n_req, const int32_t *n_r
 /*
  * Suffix prefill of the attention layer for a packed batch of resumed requests: appends the
  * suffix's keys and values to each request's cache rows and computes the attention output of
- * every suffix token over positions 1 .. its own (an append and an attention launch on `stream`,
- * behind the upload of the index arrays; one more, a merge pass that writes o, when the call is
- * small enough for key walks of 1024 keys and more to be split over workgroups).  Results do not depend on the batch a request is packed with as long as
- * its walk is not split.  A call whose requests all have at most 16 (token, query head of a group)
- * rows behind 1024 keys or more (decoding) is walked by a kernel of its own, whole or split, with
- * the sums over the keys in another order than the 128-row kernel's.  attn_tune_split(0) keeps every walk whole; attn_tune_pack(0) keeps one
- * query head per workgroup also where suffixes are short, and either keeps such calls on the 128-row kernel (otherwise the heads of a key/value group
- * then share a workgroup's rows; results are bitwise the same either way).
+ * every suffix token over positions 1 .. its own.
+ *
+ * Launches on `stream`, behind the upload of the index arrays: an append and an attention launch,
+ * and, when the call is small enough for key walks of 1024 keys and more to be split over
+ * workgroups, a merge pass that writes o.  Results do not depend on the batch a request is packed
+ * with as long as its walk is not split.
+ *
+ * Requests of at most 16 rows (tokens x query heads of a key/value group, the group size a divisor
+ * of 128) behind 1024 keys or more (decoding) have a kernel of their own, which appends their rows
+ * itself and sums over the keys in another order than the 128-row kernel.  It serves calls of such
+ * requests and, in a launch beside the 128-row kernel's, mixed calls in which that pays.  In other
+ * mixed calls the 128-row kernel walks these requests, always split; whole, they are walked by
+ * their own kernel only.
+ *
+ * attn_tune_split(0) keeps every walk whole, attn_tune_pack(0) keeps one query head per workgroup
+ * also where suffixes are short (otherwise the heads of a key/value group then share a workgroup's
+ * rows), and either keeps every request on the 128-row kernel; among that kernel's whole walks the
+ * results are bitwise the same whatever the knobs.
  *   q            device, bf16, [T][H_q][d] (T = cu_seqlens[n_req]);  k_new, v_new: [T][H_kv][d]
  *   out_gate     device, bf16, [T][H_q][d], or NULL (no gate)
  *   cu_seqlens   host, n_req + 1;  start_pos: host, n_req, the restored prefix length c >= 0
@@ -117,8 +127,10 @@ int32_t attn_suffix_prefill(const attn_shape *shape, const void *q, const void *
  * block: rows = 128 / *heads_per_row_group suffix tokens starting at token unit_tile * that many
  * of request unit_req (with *heads_per_row_group query heads of a key/value group per token: 1,
  * or H_q / H_kv in calls with short suffixes), key tiles [unit_t0, unit_t1) of *key_tile_rows rows
- * each; unit_part is the workspace slot of a part of a split walk, or -1 for a whole walk.  Units
- * come in launch order, most key tiles first.  The five arrays hold `capacity` entries;
+ * each; unit_part numbers the parts of split walks, or is -1 for a whole walk.  A request of the
+ * few-rows kernel (see attn_suffix_prefill) has one unit or part for each key/value head, whatever
+ * *heads_per_row_group says of the others.  Units come most key tiles first, the launch order of
+ * either kernel.  The five arrays hold `capacity` entries;
  * *n_units is set also when that is too few (GDN_ERR_COUNT).
  */
 int32_t attn_plan(const attn_shape *shape, int32_t n_req, const int32_t *cu_seqlens,
@@ -130,7 +142,8 @@ int32_t attn_plan(const attn_shape *shape, int32_t n_req, const int32_t *cu_seql
 /*
  * Tuning knobs (not steps of the method; for tests and experiments).  attn_tune_split(0) forbids
  * cutting long key walks into parts, attn_tune_pack(0) forbids packing the query heads of a
- * key/value group into one workgroup's rows; a non-zero argument restores the automatic choice.
+ * key/value group into one workgroup's rows, and either forbids the few-rows kernel; a non-zero
+ * argument restores the automatic choice.
  * Each returns its previous setting (1 = automatic).  Process-wide; read at every call.
  */
 int32_t attn_tune_split(int32_t allow);

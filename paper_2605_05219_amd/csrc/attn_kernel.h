@@ -59,6 +59,7 @@ constexpr int ATT_BQ = 128;       // rows (query columns of the accumulators) pe
 __host__ __device__ constexpr int att_kt(int d) { return d == 256 ? 32 : 64; }
 constexpr int ATT_THREADS = 256;
 constexpr int APPEND_THREADS = 256;
+constexpr int NAR_ROWS = 16;      // rows (tokens x query heads of a key/value group) of a few-rows request, at most
 
 struct AttnArgs {
     const uint16_t* q;        // [T][H_q][D]
@@ -67,16 +68,19 @@ struct AttnArgs {
     const uint16_t* v_cache;  // fp16 bits
     void* o;                  // [T][H_q][D], float or bf16
     const int32_t* cu;        // device: n_req + 1
-    const int32_t* start;     // device: n_req
+    const int32_t* start;     // device: n_req (read for the requests of the 128-row kernel)
     const int32_t* slot;      // device: n_req
     const int32_t* unit_req;  // device: n_units, heaviest first
     const int32_t* unit_tile; // device: index of the 128-token tile inside the request
     const int32_t* unit_t0;   // device: first key tile of the unit
     const int32_t* unit_t1;   // device: one past its last key tile
-    const int32_t* unit_part; // device: workspace slot of a partial result, or -1: the unit is a whole walk
+    const int32_t* unit_part; // device: workspace slot of a partial result, -2 - slot for one of a few-rows request, or -1: the unit is a whole walk
     const int32_t* unit_rec;  // device, few-rows kernel instead of the five arrays: NAR_REC ints per unit
-    float* part_o;            // [slot][H_q][ATT_BQ][D] unnormalised partial outputs
-    float* part_ml;           // [slot][H_q][ATT_BQ][2] running maximum (raw logits) and normaliser
+    // rows of partial results: [slot][head block][ATT_BQ] and behind them, from row few_row0, [slot][head block][NAR_ROWS] of the
+    // few-rows requests, by whichever kernel
+    float* part_o;            // [row][D] unnormalised partial outputs
+    float* part_ml;           // [row][2] running maximum (raw logits) and normaliser
+    int64_t few_row0;
     int64_t slot_stride;      // elements
     int32_t n_units;
     int32_t H_q, H_kv;
@@ -91,7 +95,7 @@ struct AppendArgs {
     uint16_t* k_cache;
     uint16_t* v_cache;        // fp16 bits
     const int32_t* cu;
-    const int32_t* start;
+    const int32_t* start;     // -1: the request's rows are appended by the few-rows kernel
     const int32_t* slot;
     int64_t slot_stride;
     int64_t n_chunks;         // T * row_chunks
@@ -172,6 +176,7 @@ __global__ void __launch_bounds__(APPEND_THREADS) attn_append_kernel(AppendArgs 
         if (a.cu[mid] <= t) lo = mid; else hi = mid;
     }
     const int r = lo;
+    if (a.start[r] < 0) return;
     const int64_t row = (int64_t)a.start[r] + (t - a.cu[r]);
     const int64_t dst = (int64_t)a.slot[r] * a.slot_stride + (row * a.row_chunks + c) * 8;
     const int64_t src = ((int64_t)t * a.row_chunks + c) * 8;
@@ -425,9 +430,10 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 
     wait_vmcnt<0>();                           // no load to LDS may be in flight when the workgroup's LDS is given back
     // ---- a part of a split walk leaves its unnormalised result in its workspace slot
-    if (part >= 0) {
+    if (part != -1) {
         if (valid) {
-            const int64_t prow = ((int64_t)part * (a.H_q / R) + hb) * ATT_BQ + wrow;
+            const int64_t prow = part >= 0 ? ((int64_t)part * (a.H_q / R) + hb) * ATT_BQ + wrow
+                                           : a.few_row0 + ((int64_t)(-2 - part) * (a.H_q / R) + hb) * NAR_ROWS + wrow;
             const float lt = sum_with_other_half(l);
             if (g == 0) *reinterpret_cast<f32x2*>(a.part_ml + prow * 2) = f32x2{m, lt};
 #pragma unroll
@@ -454,7 +460,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 }
 
 // ---------------------------------------------------------------- few rows: the decode shape
-// Calls whose requests have at most NAR_ROWS rows (tokens x query heads of a key/value group) behind at least
+// Requests of at most NAR_ROWS rows (tokens x query heads of a key/value group) whose walk has at least
 // 1024 keys: decoding, and suffixes of a few tokens.  Bound: HBM (every key and value is read once for 16 rows at
 // most), so nothing is spent on sharing a tile between waves: each of the four waves of a workgroup walks its own blocks of
 // 32 keys (every fourth one of the unit's range) without a barrier, the keys straight into registers as matrix operands, the
@@ -462,8 +468,8 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
 // ahead: 16 KiB in flight per wave at d = 128, 128 KiB per compute unit, where about 50 KiB cover the latency of the
 // memory at its full rate.  The 16 rows are the columns of 16x16x32 products, both contractions transposed as in
 // attn_suffix_kernel.  The four results are merged through LDS.  The kernel appends the suffix rows that lie in its own
-// range of keys itself, in front of the walk (nobody else reads them), so such a call has no append launch.
-constexpr int NAR_ROWS = 16;
+// range of keys itself, in front of the walk (nobody else reads them), so a call of such requests has no append launch.
+// A unit's arithmetic depends on its own record only: a whole walk gives the same bits whatever is in the call beside it.
 constexpr int NAR_KEYS = 32;      // keys per block
 constexpr int NAR_REC = 8;        // a unit's record: first token, tokens, start, slot, first key, one past the last, workspace slot or -1
 __host__ __device__ constexpr int narrow_wgs_per_cu(int d) { return d == 64 ? 3 : d == 128 ? 2 : 1; }
@@ -686,7 +692,7 @@ __global__ void __launch_bounds__(ATT_THREADS, narrow_wgs_per_cu(D)) attn_narrow
             L += wt * ml[w][row][1];
         }
         if (part >= 0) {
-            const int64_t prow = ((int64_t)part * a.H_kv + kvh) * ATT_BQ + row;
+            const int64_t prow = a.few_row0 + ((int64_t)part * a.H_kv + kvh) * NAR_ROWS + row;
             if (dv == 0) *reinterpret_cast<f32x2*>(a.part_ml + prow * 2) = f32x2{M, L};
             *reinterpret_cast<f32x4*>(a.part_o + prow * D + dv) = acc;
         } else {
@@ -696,43 +702,54 @@ __global__ void __launch_bounds__(ATT_THREADS, narrow_wgs_per_cu(D)) attn_narrow
     }
 }
 
+// The split pieces of one kind of request.
+struct CombineSet {
+    const int32_t* piece_req;   // device: n_pieces
+    const int32_t* piece_tile;
+    const int32_t* piece_base;  // first workspace slot of the piece
+    const int32_t* piece_parts; // its number of parts (consecutive slots)
+    int64_t row0;               // first row of the set's partial results
+    int32_t slot_rows;          // rows per (slot, head block)
+    int32_t pack;               // as in AttnArgs
+    int32_t subs;               // workgroups per (piece, head block): enough threads for the rows of the fullest piece
+    int32_t blocks;             // workgroups of the set
+};
+
 struct CombineArgs {
     const float* part_o;
     const float* part_ml;
     const uint16_t* gate;     // or nullptr
     void* o;
     const int32_t* cu;
-    const int32_t* piece_req;   // device: n_pieces split pieces
-    const int32_t* piece_tile;
-    const int32_t* piece_base;  // first workspace slot of the piece
-    const int32_t* piece_parts; // its number of parts (consecutive slots)
+    CombineSet set[2];        // the other requests' pieces, the few-rows requests'
     int32_t H_q;
-    int32_t pack;               // as in AttnArgs
-    int32_t subs;               // workgroups per (piece, head): enough threads for the rows of the fullest piece
     float scale_log2e;
 };
 
-// Merges the parts of one split piece for one query head: o = sum_p w_p O_p / sum_p w_p l_p with
+// Merges the parts of one split piece for one head block: o = sum_p w_p O_p / sum_p w_p l_p with
 // w_p = 2^((m_p - max_p m_p) * scale * log2 e); a part that saw no key has m_p = -inf, weight 0 and O_p = 0.
-// One thread per (row, four value columns), `subs` workgroups per (piece, head); the loads of all
+// One thread per (row, four value columns), `subs` workgroups per (piece, head block); the loads of all
 // parts are independent of each other, so the pass costs a few memory round trips, not one per part.
 template <int D, typename OT>
 __global__ void __launch_bounds__(ATT_THREADS) attn_combine_kernel(CombineArgs a) {
     constexpr int CH = D / 4;                  // threads per row
-    const int ph = blockIdx.x / a.subs, sub = blockIdx.x % a.subs;
-    const int R = a.pack, HB = a.H_q / R, TPW = ATT_BQ / R;
+    const bool second = (int)blockIdx.x >= a.set[0].blocks;
+    const CombineSet s = second ? a.set[1] : a.set[0];
+    const int block = second ? (int)blockIdx.x - a.set[0].blocks : (int)blockIdx.x;
+    const int ph = block / s.subs, sub = block % s.subs;
+    const int R = s.pack, HB = a.H_q / R, TPW = ATT_BQ / R;
     const int piece = ph / HB, hb = ph % HB;
-    const int r = a.piece_req[piece];
-    const int q0 = a.piece_tile[piece] * TPW;
+    const int r = s.piece_req[piece];
+    const int q0 = s.piece_tile[piece] * TPW;
     const int tok0 = a.cu[r];
     const int rows = min(TPW, a.cu[r + 1] - tok0 - q0) * R;
-    const int base = a.piece_base[piece], P = a.piece_parts[piece];
+    const int base = s.piece_base[piece], P = s.piece_parts[piece];
     {
         const int idx = sub * ATT_THREADS + threadIdx.x;
         const int row = idx / CH, ch = idx - row * CH;
         if (row >= rows) return;
-        const int64_t prow0 = ((int64_t)base * HB + hb) * ATT_BQ + row;
-        const int64_t pstep = (int64_t)HB * ATT_BQ;                   // rows between consecutive parts
+        const int64_t prow0 = s.row0 + ((int64_t)base * HB + hb) * s.slot_rows + row;
+        const int64_t pstep = (int64_t)HB * s.slot_rows;              // rows between consecutive parts
         const int tl = row / R, hq = hb * R + (row - tl * R);
         float M = -INFINITY;
 #pragma unroll 4

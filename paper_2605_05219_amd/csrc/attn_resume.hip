@@ -53,18 +53,22 @@ int32_t check_slots(const int32_t* ids, int32_t n, int32_t n_slots, bool skip_em
 
 // Splitting the key walk: calls with fewer than SPLIT_BELOW workgroups cut the walks of their pieces
 // into parts of at least SPLIT_MIN_KEYS keys (whole tiles), aiming at SPLIT_BELOW workgroups in all; the
-// partial results of at most SPLIT_MAX_WGS (part, head) pairs live in the workspace.
+// partial results of at most SPLIT_MAX_WGS (part, head) pairs live in the workspace.  (A few-rows request's has NAR_ROWS rows
+// there instead of ATT_BQ.)
 constexpr int SPLIT_BELOW = 512;       // two workgroups per compute unit
 constexpr int SPLIT_MIN_KEYS = 512;
 constexpr int SPLIT_MAX_WGS = 768;
-// The few-rows kernel's walks are cut so that its workgroups fit the chip in one round, two per compute unit (64 one-token
-// requests behind 4 to 10 thousand keys, d = 128: at most 256 / 384 / 512 / 640 / 768 / 1024 workgroups 104 / 109 / 91 / 98 / 90 /
-// 107 us; four such requests 24 / 24 / 20 / 20 / 20 / 20 us).
+// The few-rows kernel's walks are cut into at most NARROW_WGS workgroups in all: two per compute unit, one round, at d = 64 and
+// 128 (64 one-token requests behind 4 to 10 thousand keys, d = 128: at most 256 / 384 / 512 / 640 / 768 / 1024 workgroups 104 / 109 /
+// 91 / 98 / 90 / 107 us; four such requests 24 / 24 / 20 / 20 / 20 / 20 us).  At d = 256 one workgroup fills a compute unit's LDS and
+// they run in two rounds; other limits were measured at d = 128 only.
 constexpr int NARROW_WGS = 512;
 
-// ints of the uploaded index arrays: cu (n_req+1), start, slot (n_req each), five or eight per unit, four per split piece
+// ints of the uploaded index arrays: cu (n_req+1), start, slot (n_req each), five per unit of the 128-row kernel, eight per unit
+// of the few-rows kernel, four per split piece
 // (with packed rows a piece is 128 / G tokens, G the heads per key/value head: at most G times as many pieces)
-constexpr int UNIT_INTS = NAR_REC;
+constexpr int WIDE_INTS = 5, UNIT_INTS = NAR_REC;
+static_assert(WIDE_INTS <= UNIT_INTS && NARROW_WGS <= SPLIT_MAX_WGS, "plan_ints and the partial results hold either kernel's units");
 inline int64_t max_items(int32_t n_req, int64_t T, int G) { return T * G / ATT_BQ + n_req; }
 inline int64_t max_units(int32_t n_req, int64_t T, int G) { return max_items(n_req, T, G) + SPLIT_MAX_WGS; }
 inline int64_t plan_ints(int32_t n_req, int64_t T, int G) {
@@ -107,8 +111,8 @@ hipError_t launch_narrow_d(int d, const AttnArgs& a, const AppendArgs& ap, unsig
 }
 
 template <typename OT>
-hipError_t launch_combine_d(int d, const CombineArgs& a, unsigned pairs /* (piece, head) */, hipStream_t stream) {
-    const dim3 grid(pairs * (unsigned)a.subs), block(ATT_THREADS);
+hipError_t launch_combine_d(int d, const CombineArgs& a, hipStream_t stream) {
+    const dim3 grid((unsigned)(a.set[0].blocks + a.set[1].blocks)), block(ATT_THREADS);
     switch (d) {
         case 64: hipLaunchKernelGGL((attn_combine_kernel<64, OT>), grid, block, 0, stream, a); break;
         case 128: hipLaunchKernelGGL((attn_combine_kernel<128, OT>), grid, block, 0, stream, a); break;
@@ -120,102 +124,146 @@ hipError_t launch_combine_d(int d, const CombineArgs& a, unsigned pairs /* (piec
 // The work of one attn_suffix_prefill call (host, integer): how the rows of a workgroup are made up, the pieces
 // (row tiles of a request), the cut of long key walks into parts, and the units (whole walks or parts) in launch order.
 std::atomic<int32_t> g_allow_split{1}, g_allow_pack{1};   // attn_tune_split / attn_tune_pack
-struct Unit { int32_t req, tile, t0, t1, part; };
+struct Unit { int32_t req, tile, t0, t1, part; bool few; };      // part: slot among those of its kind of request, or -1
+struct Piece { int32_t req, tile, n_tiles, parts, base; };       // base: first slot
 struct UnitPlan {
-    int pack = 1;                     // query heads per token in a workgroup's rows: 1, or H_q / H_kv
-    bool narrow = false;              // the few-rows kernel
-    int max_rows = 0;                 // rows of the fullest piece
-    std::vector<Unit> units;          // those with the most key tiles first
-    std::vector<int32_t> piece_req, piece_tile, piece_base, piece_parts;   // the split pieces and their workspace slots
+    int pack = 1;                     // 128-row kernel: query heads per token in a workgroup's rows: 1, or H_q / H_kv
+    bool apart = false;               // the few-rows requests are walked by the few-rows kernel
+    std::vector<char> few;            // per request
+    std::vector<Unit> units;          // of both kernels, those with the most key tiles first
+    // of the other requests, of the few-rows requests
+    int32_t longest[2] = {0, 0};      // longest suffix
+    int64_t n_units[2] = {0, 0};
+    std::vector<Piece> split[2];      // the split pieces and their workspace slots
+    int32_t n_slots[2] = {0, 0};
 };
+
+// The requests the few-rows kernel is for: at most 16 rows, and a walk long enough for the split below (shorter walks stay
+// whole and on the 128-row kernel, where a row's result does not depend on the suffix around it either).  Measured, whole call,
+// 64 one-token requests of 8 heads per key/value head behind 4 to 10 thousand keys, 128-row kernel against this one: d = 64 57
+// against 52 us, d = 128 131 against 91 (465 MB read: 73 us at the rate of a plain copy), d = 256 235 against 168; d = 128, four of
+// them 34 against 22, one 31 against 20.
+inline bool few_rows(int32_t len, int32_t start, int G) {
+    return len > 0 && ATT_BQ % G == 0 && (int64_t)len * G <= NAR_ROWS && start + len >= 2 * SPLIT_MIN_KEYS;
+}
+
+// Rows of a workgroup of the 128-row kernel: 128 tokens of one query head (1), or, where that would leave at least a fifth of all
+// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).
+int pick_pack(const attn_shape& s, int32_t n_req, const int32_t* len, const std::vector<char>& elsewhere) {
+    const int G = s.H_q / s.H_kv;
+    if (G == 1 || ATT_BQ % G != 0 || g_allow_pack.load() == 0) return 1;
+    int64_t rows_plain = 0, rows_packed = 0;
+    for (int32_t r = 0; r < n_req; ++r) {
+        if (elsewhere[r]) continue;
+        rows_plain += (int64_t)((len[r] + ATT_BQ - 1) / ATT_BQ) * s.H_q;
+        rows_packed += (int64_t)((len[r] + ATT_BQ / G - 1) / (ATT_BQ / G)) * s.H_kv;
+    }
+    return rows_packed * 5 <= rows_plain * 4 ? G : 1;
+}
+
+// Which kernel walks the few-rows requests.  What is in a call beside such a request must not change the bits of its whole walk,
+// so it is walked whole by the few-rows kernel only.  A call of nothing else takes that kernel.  A mixed call either takes both
+// kernels, one launch behind the other, or stays one launch of the 128-row kernel, which then cuts these walks into two parts at
+// least.  One launch is better where the call is small enough for split walks anyway (d = 128, both against one launch: 1 decode
+// row and 64 tokens 33 against 24 us, 32 decode rows and 32 short contexts 42 against 33), and where the other requests fill the
+// chip by themselves, so that the decode rows' reads hide under their products (64 decode rows and 8 suffixes of 200 to 1000
+// tokens 356 against 293, 32 and 32 886 against 791); between them, both (63 decode rows and 512 tokens behind 7680 keys 127 against
+// 139 us, 32 and four of 512 tokens 88 against 104, 128 decode rows and 128 short contexts 92 against 103).
+void pick_kernels(const attn_shape& s, int32_t n_req, const int32_t* len, const int32_t* start_pos, UnitPlan& out) {
+    const int G = s.H_q / s.H_kv;
+    const bool allowed = g_allow_pack.load() != 0 && g_allow_split.load() != 0;
+    int64_t n_few = 0, n_live = 0;
+    out.few.assign(n_req, 0);
+    for (int32_t r = 0; r < n_req; ++r) {
+        out.few[r] = allowed && few_rows(len[r], start_pos[r], G);
+        out.longest[out.few[r]] = std::max(out.longest[out.few[r]], len[r]);
+        n_few += out.few[r];
+        n_live += len[r] > 0;
+    }
+    out.pack = pick_pack(s, n_req, len, std::vector<char>(n_req, 0));
+    if (n_few == 0) return;
+    const int TPW = ATT_BQ / out.pack, HB = s.H_q / out.pack;
+    int64_t others = 0;
+    for (int32_t r = 0; r < n_req; ++r)
+        if (!out.few[r]) others += (len[r] + TPW - 1) / TPW;
+    const bool one_launch = n_few < n_live && ((others + n_few) * HB < SPLIT_BELOW || others * HB >= SPLIT_BELOW);
+    const bool room = 2 * n_few * HB * NAR_ROWS <= SPLIT_MAX_WGS * ATT_BQ && 2 * n_few * WIDE_INTS <= UNIT_INTS * SPLIT_MAX_WGS;   // two parts each
+    out.apart = !(one_launch && room);
+    if (out.apart) out.pack = pick_pack(s, n_req, len, out.few);
+}
 
 void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const int32_t* start_pos, UnitPlan& out) {
     const attn_shape* s = &sh;
-    // ---- rows of a workgroup: 128 tokens of one query head, or, where that would leave at least a fifth of all
-    // rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group
     const int KT = att_kt(s->d);
-    const int G = s->H_q / s->H_kv;
-    int pack = 1;
-    if (G > 1 && ATT_BQ % G == 0) {
-        int64_t rows_plain = 0, rows_packed = 0;
-        for (int32_t r = 0; r < n_req; ++r) {
-            rows_plain += (int64_t)((len[r] + ATT_BQ - 1) / ATT_BQ) * s->H_q;
-            rows_packed += (int64_t)((len[r] + ATT_BQ / G - 1) / (ATT_BQ / G)) * s->H_kv;
-        }
-        if (rows_packed * 5 <= rows_plain * 4 && g_allow_pack.load() != 0) pack = G;
-    }
-    // ---- the few-rows kernel: every request has at most 16 rows, and a walk long enough for the split below (shorter walks
-    // stay whole and on the 128-row kernel, where a row's result does not depend on the batch or on the suffix around it).
-    // Measured, whole call, one-token requests, 128-row kernel against this one: 64 of 8 heads per key/value head behind 4 to 10
-    // thousand keys 130 against 91 us (465 MB read: 73 us at the rate of a plain copy), d = 64 127 against 87, d = 256 119
-    // against 81, four of them 32 against 20.
-    bool narrow = ATT_BQ % G == 0 && g_allow_pack.load() != 0 && g_allow_split.load() != 0;
-    int32_t longest = 0;
+    pick_kernels(sh, n_req, len, start_pos, out);
+    const int pack = out.pack;
+    const int HB[2] = {s->H_q / pack, out.apart ? s->H_kv : s->H_q / pack};   // head blocks (workgroups) per unit
+    // ---- pieces: one per workgroup of suffix tokens of a request (one in all of a few-rows request)
+    std::vector<Piece> pieces[2];
+    int64_t wide_items = 0, wide_tiles = 0;       // of the 128-row kernel's walks
     for (int32_t r = 0; r < n_req; ++r) {
-        if (len[r] == 0) continue;
-        longest = std::max(longest, len[r]);
-        if ((int64_t)len[r] * G > NAR_ROWS || start_pos[r] + len[r] < 2 * SPLIT_MIN_KEYS) narrow = false;
-    }
-    if (longest == 0) narrow = false;
-    if (narrow) pack = G;
-    const int TPW = ATT_BQ / pack;        // tokens per workgroup
-    const int HB = s->H_q / pack;         // head blocks (workgroups) per unit
-    out.narrow = narrow;
-    out.max_rows = (int)std::min<int64_t>(longest, TPW) * pack;
-    // ---- pieces: one per TPW suffix tokens of a request
-    struct Piece { int32_t req, tile, n_tiles, parts; };
-    std::vector<Piece> pieces;
-    int64_t total_tiles = 0;
-    for (int32_t r = 0; r < n_req; ++r)
+        const int k = out.few[r], TPW = k ? NAR_ROWS : ATT_BQ / pack;
         for (int32_t t = 0; t * TPW < len[r]; ++t) {
             const int32_t kv = start_pos[r] + std::min((t + 1) * TPW, len[r]);
-            pieces.push_back({r, t, (kv + KT - 1) / KT, 1});
-            total_tiles += pieces.back().n_tiles;
+            pieces[k].push_back({r, t, (kv + KT - 1) / KT, 1, 0});
+            if (k && out.apart) continue;
+            ++wide_items;
+            wide_tiles += pieces[k].back().n_tiles;
         }
-    const int64_t n_items = (int64_t)pieces.size();
+    }
     // ---- too few workgroups for the chip: cut long key walks into parts
-    int64_t split_wgs = 0;
-    if (narrow) {
+    int64_t parts[2] = {0, 0};                    // of split walks
+    auto cut = [&](int k, auto&& parts_of) {
+        parts[k] = 0;
+        for (Piece& p : pieces[k]) {
+            p.parts = (int32_t)parts_of((int64_t)p.n_tiles);
+            if (p.parts > 1) parts[k] += p.parts;
+        }
+    };
+    if (out.apart) {
         auto count = [&](int64_t tp) {
             int64_t n = 0;
-            for (const Piece& p : pieces) n += (p.n_tiles + tp - 1) / tp;
-            return n * HB;
+            for (const Piece& p : pieces[1]) n += (p.n_tiles + tp - 1) / tp;
+            return n * HB[1];
         };
         int64_t lo = SPLIT_MIN_KEYS / KT, hi = lo;
-        for (const Piece& p : pieces) hi = std::max<int64_t>(hi, p.n_tiles);
+        for (const Piece& p : pieces[1]) hi = std::max<int64_t>(hi, p.n_tiles);
         while (lo < hi) {
             const int64_t mid = (lo + hi) / 2;
             if (count(mid) <= NARROW_WGS) hi = mid; else lo = mid + 1;
         }
-        for (Piece& p : pieces) p.parts = (int32_t)((p.n_tiles + lo - 1) / lo);      // (more requests than slots: lo is the longest walk)
-    } else if (n_items * HB < SPLIT_BELOW && g_allow_split.load() != 0) {
-        int64_t tp = std::max<int64_t>(SPLIT_MIN_KEYS / KT, (total_tiles * HB + SPLIT_BELOW - 1) / SPLIT_BELOW);
+        cut(1, [&](int64_t n) { return (n + lo - 1) / lo; });    // (more requests than workgroups: lo is the longest walk)
+    } else {
+        cut(1, [](int64_t) { return 2; });
+    }
+    if (wide_items * HB[0] < SPLIT_BELOW && g_allow_split.load() != 0) {
+        int64_t tp = std::max<int64_t>(SPLIT_MIN_KEYS / KT, (wide_tiles * HB[0] + SPLIT_BELOW - 1) / SPLIT_BELOW);
         for (;; tp *= 2) {
-            split_wgs = 0;
-            for (Piece& p : pieces) {
-                p.parts = p.n_tiles >= 2 * tp ? (int32_t)((p.n_tiles + tp - 1) / tp) : 1;
-                if (p.parts > 1) split_wgs += (int64_t)p.parts * HB;
-            }
-            if (split_wgs <= SPLIT_MAX_WGS) break;
+            cut(0, [&](int64_t n) { return n >= 2 * tp ? (n + tp - 1) / tp : 1; });
+            if (!out.apart) cut(1, [&](int64_t n) { return n >= 2 * tp ? (n + tp - 1) / tp : 2; });
+            // all partial results fit their part of the workspace, and all unit indexes theirs (plan_ints; with one key/value
+            // head and few heads to a group the second can be the tighter one)
+            if (parts[0] * HB[0] * ATT_BQ + parts[1] * HB[1] * NAR_ROWS <= (int64_t)SPLIT_MAX_WGS * ATT_BQ &&
+                WIDE_INTS * parts[0] + (out.apart ? NAR_REC : WIDE_INTS) * parts[1] <= (int64_t)UNIT_INTS * SPLIT_MAX_WGS)
+                break;
         }
     }
     // ---- units: a whole walk or one part of it; those with the most key tiles first
-    std::vector<Unit>& units = out.units;
-    std::vector<int32_t>&piece_req = out.piece_req, &piece_tile = out.piece_tile, &piece_base = out.piece_base,
-                        &piece_parts = out.piece_parts;
-    int32_t next_slot = 0;
-    for (const Piece& p : pieces) {
-        if (p.parts == 1) {
-            units.push_back({p.req, p.tile, 0, p.n_tiles, -1});
-            continue;
+    for (int k = 0; k < 2; ++k) {
+        for (Piece& p : pieces[k]) {
+            if (p.parts == 1) {
+                out.units.push_back({p.req, p.tile, 0, p.n_tiles, -1, k == 1});
+                continue;
+            }
+            p.base = out.n_slots[k];
+            out.split[k].push_back(p);
+            const int32_t per = (p.n_tiles + p.parts - 1) / p.parts;
+            for (int32_t j = 0; j < p.parts; ++j)
+                out.units.push_back({p.req, p.tile, j * per, std::min((j + 1) * per, p.n_tiles), out.n_slots[k]++, k == 1});
         }
-        piece_req.push_back(p.req); piece_tile.push_back(p.tile); piece_base.push_back(next_slot); piece_parts.push_back(p.parts);
-        const int32_t per = (p.n_tiles + p.parts - 1) / p.parts;
-        for (int32_t j = 0; j < p.parts; ++j)
-            units.push_back({p.req, p.tile, j * per, std::min((j + 1) * per, p.n_tiles), next_slot++});
+        out.n_units[k] = (int64_t)out.units.size() - (k ? out.n_units[0] : 0);
     }
-    std::stable_sort(units.begin(), units.end(), [](const Unit& x, const Unit& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
-    out.pack = pack;
+    std::stable_sort(out.units.begin(), out.units.end(), [](const Unit& x, const Unit& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
 }
 
 }  // namespace
@@ -316,7 +364,7 @@ int32_t attn_plan(const attn_shape* s, int32_t n_req, const int32_t* cu_seqlens,
     UnitPlan plan;
     build_units(*s, n_req, len.data(), start_pos, plan);
     *n_units = (int32_t)plan.units.size();
-    *heads_per_row_group = plan.pack;
+    *heads_per_row_group = plan.apart && plan.n_units[0] == 0 ? s->H_q / s->H_kv : plan.pack;
     if ((int64_t)plan.units.size() > capacity) return GDN_ERR_COUNT;
     if (!plan.units.empty() && (!unit_req || !unit_tile || !unit_t0 || !unit_t1 || !unit_part)) return GDN_ERR_NULL;
     for (size_t i = 0; i < plan.units.size(); ++i) {
@@ -324,7 +372,7 @@ int32_t attn_plan(const attn_shape* s, int32_t n_req, const int32_t* cu_seqlens,
         unit_tile[i] = plan.units[i].tile;
         unit_t0[i] = plan.units[i].t0;
         unit_t1[i] = plan.units[i].t1;
-        unit_part[i] = plan.units[i].part;
+        unit_part[i] = plan.units[i].part < 0 ? -1 : plan.units[i].part + (plan.units[i].few ? plan.n_slots[0] : 0);
     }
     return GDN_OK;
 }
@@ -343,12 +391,10 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     if (!cu_seqlens || !start_pos || !seq_slot) return GDN_ERR_NULL;
     if (cu_seqlens[0] != 0) return GDN_ERR_SEQLENS;
     std::vector<int32_t> len(n_req);
-    int64_t kv_rows = 0;
     for (int32_t r = 0; r < n_req; ++r) {
         if (cu_seqlens[r + 1] < cu_seqlens[r]) return GDN_ERR_SEQLENS;
         len[r] = cu_seqlens[r + 1] - cu_seqlens[r];
         if (start_pos[r] < 0 || (int64_t)start_pos[r] + len[r] > cap) return GDN_ERR_START;
-        if (len[r] > 0) kv_rows += start_pos[r] + len[r];
     }
     rc = check_slots(seq_slot, n_req, n_slots, true, len.data());
     if (rc != GDN_OK) return rc;
@@ -364,55 +410,56 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     build_units(*s, n_req, len.data(), start_pos, plan);
     const int G = s->H_q / s->H_kv;
     const int pack = plan.pack, HB = s->H_q / pack;
-    const std::vector<Unit>& units = plan.units;
-    const std::vector<int32_t>&piece_req = plan.piece_req, &piece_tile = plan.piece_tile, &piece_base = plan.piece_base,
-                              &piece_parts = plan.piece_parts;
-    const int64_t n_units = (int64_t)units.size();
-    const int64_t n_pieces = (int64_t)piece_req.size();
+    const int64_t n_narrow = plan.apart ? plan.n_units[1] : 0, n_wide = (int64_t)plan.units.size() - n_narrow;
     const bool xcd_split = 8 % s->H_kv == 0;
     int64_t blocks;
     if (xcd_split) {
         const int X = 8 / s->H_kv;
-        blocks = 8 * ((n_units * (G / pack) + X - 1) / X);
+        blocks = 8 * ((n_wide * (G / pack) + X - 1) / X);
     } else {
-        blocks = n_units * HB;
+        blocks = n_wide * HB;
     }
-    if (blocks > INT32_MAX) return GDN_ERR_COUNT;
+    if (blocks > INT32_MAX || n_narrow * s->H_kv > INT32_MAX) return GDN_ERR_COUNT;
 
     // the uploaded image is packed to what this call uses (the workspace is sized for the most a call can need):
     // a copy of a few hundred bytes takes the runtime's short path, one of 16 KiB and more does not
-    const int64_t MU = n_units, MI = n_pieces;
-    const int64_t unit_ints = plan.narrow ? NAR_REC * MU : 5 * MU;
-    const int64_t unit_at = plan.narrow ? (3 * (int64_t)n_req + 1 + NAR_REC - 1) / NAR_REC * NAR_REC : 3 * (int64_t)n_req + 1;   // records: aligned
-    std::vector<int32_t> img((size_t)(unit_at + unit_ints + 4 * MI), 0);
+    const int64_t rec_at = n_narrow > 0 ? (3 * (int64_t)n_req + 1 + NAR_REC - 1) / NAR_REC * NAR_REC : 3 * (int64_t)n_req + 1;   // records: aligned
+    const int64_t unit_at = rec_at + NAR_REC * n_narrow;
+    const int64_t piece_at[2] = {unit_at + WIDE_INTS * n_wide, unit_at + WIDE_INTS * n_wide + 4 * (int64_t)plan.split[0].size()};
+    std::vector<int32_t> img((size_t)(piece_at[1] + 4 * (int64_t)plan.split[1].size()), 0);
     int32_t* p_cu = img.data();
     int32_t* p_start = p_cu + n_req + 1;
     int32_t* p_slot = p_start + n_req;
-    int32_t* p_unit = p_cu + unit_at;          // five arrays of n_units, or records
-    int32_t* p_piece = p_unit + unit_ints;     // four arrays of n_pieces
+    int32_t* p_rec = p_cu + rec_at;            // records of the few-rows kernel's units
+    int32_t* p_unit = p_cu + unit_at;          // five arrays of n_wide
     std::memcpy(p_cu, cu_seqlens, sizeof(int32_t) * (n_req + 1));
-    std::memcpy(p_start, start_pos, sizeof(int32_t) * n_req);
+    for (int32_t r = 0; r < n_req; ++r) p_start[r] = plan.apart && plan.few[r] ? -1 : start_pos[r];
     std::memcpy(p_slot, seq_slot, sizeof(int32_t) * n_req);
     const int KT = att_kt(s->d);
-    for (int64_t i = 0; i < n_units; ++i) {
-        const Unit& u = units[i];
-        if (plan.narrow) {
+    for (const Unit& u : plan.units) {
+        if (u.few && plan.apart) {
             const int32_t kv = start_pos[u.req] + len[u.req];
             const int32_t rec[NAR_REC] = {cu_seqlens[u.req], len[u.req], start_pos[u.req], seq_slot[u.req], u.t0 * KT, std::min(u.t1 * KT, kv), u.part, 0};
-            std::memcpy(p_unit + NAR_REC * i, rec, sizeof rec);
+            std::memcpy(p_rec, rec, sizeof rec);
+            p_rec += NAR_REC;
             continue;
         }
-        p_unit[i] = u.req;
-        p_unit[MU + i] = u.tile;
-        p_unit[2 * MU + i] = u.t0;
-        p_unit[3 * MU + i] = u.t1;
-        p_unit[4 * MU + i] = u.part;
+        p_unit[0] = u.req;
+        p_unit[n_wide] = u.tile;
+        p_unit[2 * n_wide] = u.t0;
+        p_unit[3 * n_wide] = u.t1;
+        p_unit[4 * n_wide] = u.few && u.part >= 0 ? -2 - u.part : u.part;
+        ++p_unit;
     }
-    for (int64_t i = 0; i < n_pieces; ++i) {
-        p_piece[i] = piece_req[i];
-        p_piece[MI + i] = piece_tile[i];
-        p_piece[2 * MI + i] = piece_base[i];
-        p_piece[3 * MI + i] = piece_parts[i];
+    for (int k = 0; k < 2; ++k) {
+        const int64_t n = (int64_t)plan.split[k].size();
+        int32_t* p_piece = p_cu + piece_at[k];     // four arrays of n
+        for (int64_t i = 0; i < n; ++i) {
+            p_piece[i] = plan.split[k][i].req;
+            p_piece[n + i] = plan.split[k][i].tile;
+            p_piece[2 * n + i] = plan.split[k][i].base;
+            p_piece[3 * n + i] = plan.split[k][i].parts;
+        }
     }
     rc = gdn::upload_plan(img.data(), img.size() * sizeof(int32_t), workspace, stream);
     if (rc != GDN_OK) return rc;
@@ -433,7 +480,7 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     hipError_t e = hipSuccess;
     const int64_t ablocks = (ap.n_chunks + APPEND_THREADS - 1) / APPEND_THREADS;
     if (ablocks > INT32_MAX) return GDN_ERR_COUNT;
-    if (!plan.narrow) {                        // (the few-rows kernel appends its own rows)
+    if (n_wide > 0) {                          // (the few-rows kernel appends its own rows)
         hipLaunchKernelGGL(attn_append_kernel, dim3((unsigned)ablocks), dim3(APPEND_THREADS), 0, stream, ap);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_err(e);
@@ -448,33 +495,40 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     a.cu = ap.cu;
     a.start = ap.start;
     a.slot = ap.slot;
-    a.unit_rec = d + unit_at;
+    a.unit_rec = d + rec_at;
     a.unit_req = d + unit_at;
-    a.unit_tile = a.unit_req + MU;
-    a.unit_t0 = a.unit_req + 2 * MU;
-    a.unit_t1 = a.unit_req + 3 * MU;
-    a.unit_part = a.unit_req + 4 * MU;
+    a.unit_tile = a.unit_req + n_wide;
+    a.unit_t0 = a.unit_req + 2 * n_wide;
+    a.unit_t1 = a.unit_req + 3 * n_wide;
+    a.unit_part = a.unit_req + 4 * n_wide;
     a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan_bytes(n_req, T, G));
     a.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan_bytes(n_req, T, G) + part_ml_bytes());
+    a.few_row0 = (int64_t)plan.n_slots[0] * HB * ATT_BQ;
     a.slot_stride = slot_stride;
-    a.n_units = (int32_t)n_units;
+    a.n_units = (int32_t)n_wide;
     a.H_q = s->H_q;
     a.H_kv = s->H_kv;
     a.xcd_split = xcd_split ? 1 : 0;
-    a.pack = pack;
     a.scale_log2e = s->scale * 1.4426950408889634f;
-    if (plan.narrow) {
-        // non-temporal reads where a call reads more keys and values than the memory-side cache would hold for the next one
+    if (n_narrow > 0) {
+        // non-temporal reads where the launch reads more keys and values than the memory-side cache would hold for the next one
         // (465 MB 91 against 99 us with ordinary reads; 16 requests, 92 MB read again and again, 32 against 28)
-        const unsigned nb = (unsigned)(n_units * HB);
+        int64_t kv_rows = 0;
+        for (int32_t r = 0; r < n_req; ++r)
+            if (plan.few[r]) kv_rows += start_pos[r] + len[r];
+        const unsigned nb = (unsigned)(n_narrow * s->H_kv);
         const bool nt = kv_rows * s->H_kv * s->d * 4 > ((int64_t)128 << 20);
+        a.pack = G;
         e = s->o_dtype == GDN_F32 ? (nt ? launch_narrow_d<float, true>(s->d, a, ap, nb, stream) : launch_narrow_d<float, false>(s->d, a, ap, nb, stream))
                                   : (nt ? launch_narrow_d<uint16_t, true>(s->d, a, ap, nb, stream) : launch_narrow_d<uint16_t, false>(s->d, a, ap, nb, stream));
+        if (e != hipSuccess) return hip_err(e);
     }
-    else
+    if (n_wide > 0) {
+        a.pack = pack;
         e = s->o_dtype == GDN_F32 ? launch_attn_d<float>(s->d, a, (unsigned)blocks, stream)
                                   : launch_attn_d<uint16_t>(s->d, a, (unsigned)blocks, stream);
-    if (e != hipSuccess || n_pieces == 0) return hip_err(e);
+        if (e != hipSuccess) return hip_err(e);
+    }
 
     CombineArgs ca;
     ca.part_o = a.part_o;
@@ -482,16 +536,23 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     ca.gate = a.gate;
     ca.o = o;
     ca.cu = a.cu;
-    ca.piece_req = d + unit_at + unit_ints;
-    ca.piece_tile = ca.piece_req + MI;
-    ca.piece_base = ca.piece_req + 2 * MI;
-    ca.piece_parts = ca.piece_req + 3 * MI;
+    for (int k = 0; k < 2; ++k) {
+        CombineSet& c = ca.set[k];
+        const int64_t n = (int64_t)plan.split[k].size();
+        c.piece_req = d + piece_at[k];
+        c.piece_tile = c.piece_req + n;
+        c.piece_base = c.piece_req + 2 * n;
+        c.piece_parts = c.piece_req + 3 * n;
+        c.row0 = k ? a.few_row0 : 0;
+        c.slot_rows = k ? NAR_ROWS : ATT_BQ;
+        c.pack = k && plan.apart ? G : pack;
+        c.subs = (std::min(plan.longest[k], ATT_BQ / c.pack) * c.pack * (s->d / 4) + ATT_THREADS - 1) / ATT_THREADS;
+        c.blocks = (int32_t)(n * (s->H_q / c.pack) * c.subs);
+    }
+    if (ca.set[0].blocks + ca.set[1].blocks == 0) return GDN_OK;
     ca.H_q = s->H_q;
-    ca.pack = pack;
-    ca.subs = (plan.max_rows * (s->d / 4) + ATT_THREADS - 1) / ATT_THREADS;
     ca.scale_log2e = a.scale_log2e;
-    e = s->o_dtype == GDN_F32 ? launch_combine_d<float>(s->d, ca, (unsigned)(n_pieces * HB), stream)
-                              : launch_combine_d<uint16_t>(s->d, ca, (unsigned)(n_pieces * HB), stream);
+    e = s->o_dtype == GDN_F32 ? launch_combine_d<float>(s->d, ca, stream) : launch_combine_d<uint16_t>(s->d, ca, stream);
     return hip_err(e);
 }
 

@@ -186,6 +186,56 @@ def test_work_list_covers_every_tile_once_and_packs_and_splits_as_documented(mon
     assert ei.value.code == -11
 
 
+def _few_rows(H_q, H_kv, n, start):
+    """The documented rule: at most 16 (token, head of a group) rows behind 1024 keys or more, the group size a divisor of 128."""
+    G = H_q // H_kv
+    return n > 0 and 128 % G == 0 and n * G <= 16 and start + n >= 1024
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_mixed_calls_walk_decode_rows_whole_only_as_calls_of_their_own_do(seed):
+    """Decode rows, short-context rows and prefill chunks in one call: every key tile is walked once, and either every decode
+    row's walk is split (one launch of the 128-row kernel) or the decode rows' walks are those of a call of their own."""
+    rng = np.random.default_rng(seed)
+    H_q, H_kv = [(16, 2), (8, 8), (4, 1), (1, 1), (32, 4), (12, 4)][seed % 6]
+    d = int(rng.choice([64, 128, 256]))
+    G, KT = H_q // H_kv, 32 if d == 256 else 64
+    n = int(rng.integers(2, [90, 12][seed % 2]))
+    lens, starts = [], []
+    for _ in range(n):
+        kind = rng.integers(4)
+        lens.append(int(rng.integers(1, max(1, 16 // G) + 1)) if kind < 2 else int(rng.integers(0, 20)) if kind == 2 else int(rng.integers(17, 900)))
+        starts.append(int(rng.integers(1024, 12000)) if kind < 2 else int(rng.integers(0, 1500)))
+    lens[0], starts[0], lens[1], starts[1] = 1, 5000, 300, 7000
+    few = [_few_rows(H_q, H_kv, a, b) for a, b in zip(lens, starts)]
+
+    def plan(rows):
+        units, pack, kt = AT.attn_plan(AT.make_attn_shape(H_q, H_kv, d), np.concatenate([[0], np.cumsum([lens[r] for r in rows])]),
+                                       [starts[r] for r in rows])
+        assert kt == KT
+        return [(rows[u[0]], *map(int, u[1:])) for u in units], pack
+
+    units, pack = plan(list(range(n)))
+    alone, _ = plan([r for r in range(n) if few[r]])
+    cut = lambda us: sorted(u[:4] for u in us if few[u[0]])
+    apart = cut(alone) == cut(units)                       # the few-rows kernel's own launch
+    assert apart or all(u[4] >= 0 for u in units if few[u[0]])
+    walked = {}
+    for r, tile, t0, t1, part in units:
+        walked.setdefault((r, tile), []).append((t0, t1))
+    for (r, tile), spans in walked.items():
+        spans.sort()
+        rows = min(lens[r], (tile + 1) * (16 if few[r] else 128 // pack))
+        assert spans[0][0] == 0 and spans[-1][1] == -(-(starts[r] + rows) // KT)
+        assert all(a[1] == b[0] for a, b in zip(spans, spans[1:]))
+    assert set(walked) == {(r, t) for r in range(n) for t in range(-(-lens[r] // (16 if few[r] else 128 // pack)))}
+    slots = sorted(u[4] for u in units if u[4] >= 0)
+    assert slots == list(range(len(slots)))
+    parts = [sum(1 for u in units if u[4] >= 0 and few[u[0]] == k) for k in (False, True)]
+    assert parts[0] * (H_q // pack) * 128 + parts[1] * (H_kv if apart else H_q // pack) * 16 <= 768 * 128
+    assert 5 * parts[0] + (8 if apart else 5) * parts[1] <= 8 * 768
+
+
 # ----------------------------------------------------------------------------- GPU parity
 def f64(a):
     return wl.to_f32(a).astype(np.float64)
@@ -411,6 +461,43 @@ def test_few_rows_behind_long_prefixes(H_q, H_kv, d, lens, starts):
         check_o(got, oracle_o(c, d ** -0.5, True), "f32")
         bf, _, _ = gpu_prefill(c, "bf16")
         check_o(bf, oracle_o(c, d ** -0.5), "bf16")
+
+
+def _first_requests(c, n):
+    """The call of the first n requests of c alone (same pools)."""
+    T = int(c.cu_seqlens[n])
+    return wl.AttnCase(c.H_q, c.H_kv, c.d, c.q[:T], c.gate[:T], c.k_full[:n], c.v_full[:n], c.cu_seqlens[:n + 1], c.start_pos[:n],
+                       c.seq_slot[:n], c.n_slots, c.cap)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H_q,H_kv,d,n_decode", [(16, 8, 64, 66), (8, 4, 128, 130)])   # over 512 workgroups of decode rows: whole walks
+def test_whole_walks_do_not_depend_on_the_batch(H_q, H_kv, d, n_decode):
+    """Decode rows alone, and with a short-context row, a prefill chunk and an empty request beside them: the same bits."""
+    rng = np.random.default_rng(n_decode)
+    lens, starts = [1 + r % 4 for r in range(n_decode)], [int(x) for x in rng.integers(1023, 1200, n_decode)]
+    mixed = wl.attn_case(3850, H_q, H_kv, d, lens + [1, 0, 200], starts + [300, 3, 700])
+    alone = _first_requests(mixed, n_decode)
+    units, _, _ = AT.attn_plan(AT.make_attn_shape(H_q, H_kv, d), alone.cu_seqlens, alone.start_pos)
+    assert len(units) == n_decode and (units[:, 4] == -1).all()
+    got, want = gpu_prefill(mixed, gate=True)[0], gpu_prefill(alone, gate=True)[0]
+    assert np.array_equal(got[:alone.T], want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("o_dtype,gate", [("f32", False), ("bf16", True)])
+@pytest.mark.parametrize("H_q,H_kv,d", [(16, 2, 128), (4, 4, 64), (8, 2, 256), (6, 3, 64)])
+def test_decode_rows_beside_short_contexts_and_prefill_chunks(H_q, H_kv, d, o_dtype, gate):
+    """Both kernels in one call: decode rows behind long prefixes (split walks), one at 300 keys, one at the rule's edge of 1024,
+    a prefill chunk (whole or split), an empty request; outputs and every cache row."""
+    lens, starts = [1, 1, 150, 2, 1, 0, 1, 17], [2500, 300, 1300, 1022, 1022, 9, 4100, 1023]
+    c = wl.attn_case(3860 + d, H_q, H_kv, d, lens, starts, spare_slots=2)
+    got, k_after, v_after = gpu_prefill(c, o_dtype, gate)
+    check_o(got, oracle_o(c, d ** -0.5, gate), o_dtype)
+    k_want, v_want = pools_with_prefix(c)
+    for r, s in enumerate(c.seq_slot):
+        k_want[s, :len(c.k_full[r])], v_want[s, :len(c.v_full[r])] = c.k_full[r], v_bits(c.v_full[r])
+    assert np.array_equal(k_after, k_want) and np.array_equal(v_after, v_want)
 
 
 @pytest.mark.gpu
