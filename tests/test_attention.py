@@ -537,14 +537,32 @@ def test_resuming_at_c_reproduces_the_full_prefill_bit_for_bit():
         assert np.array_equal(k_res, k_full) and np.array_equal(v_res, v_full)
 
 
+BY_VALUE_WORDS = 2 * 896      # index images up to this many 32-bit words travel in kernel arguments, larger ones through the staging ring
+
+
+def image_words(c):
+    """Words of a call's index image if every request is on the 128-row kernel and nothing is split."""
+    units, _, _ = AT.attn_plan(AT.make_attn_shape(c.H_q, c.H_kv, c.d), c.cu_seqlens, c.start_pos)
+    assert (units[:, 4] == -1).all()
+    return 3 * len(c.start_pos) + 1 + 5 * len(units)
+
+
 @pytest.mark.gpu
-def test_calls_interleaved_on_two_side_streams_equal_the_default_stream_result():
-    """Two requests' calls (each with its own caches, output and workspace) enqueued alternately on two side streams,
-    several times over, give bit for bit what the same calls give on the default stream: the index arrays of the calls
-    travel through a shared ring of staging buffers and must not mix."""
+@pytest.mark.parametrize("images", ["in kernel arguments", "through the staging ring"])
+def test_calls_interleaved_on_two_side_streams_equal_the_default_stream_result(images):
+    """Calls (each with its own caches, output and workspace) enqueued in turn on two side streams, several times over, give bit
+    for bit what the same calls give on the default stream: the index arrays of the calls travel in kernel arguments, or, where
+    they are larger, through a shared ring of eight staging buffers, and must not mix.  (Three calls of different images
+    in turn, so that a buffer's next image is another one.)"""
     import torch
     from tests.harness import to_device
-    cases = [wl.attn_case(3700, 8, 2, 128, [150, 3], [700, 2100]), wl.attn_case(3701, 8, 2, 128, [64], [1500])]
+    if images == "in kernel arguments":
+        cases = [wl.attn_case(3700, 8, 2, 128, [150, 3], [700, 2100]), wl.attn_case(3701, 8, 2, 128, [64], [1500])]
+    else:
+        rng = np.random.default_rng(3702)
+        cases = [wl.attn_case(3703 + i, 2, 1, 64, [int(x) for x in rng.integers(1, 5, n)], [int(x) for x in rng.integers(0, 60, n)])
+                 for i, n in enumerate((300, 340, 260))]
+        assert all(image_words(c) > BY_VALUE_WORDS for c in cases)
     want = [gpu_prefill(c, gate=True)[0] for c in cases]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     sets = []
@@ -557,8 +575,8 @@ def test_calls_interleaved_on_two_side_streams_equal_the_default_stream_result()
                          ws=torch.empty(AT.attn_workspace_bytes(sh, len(c.start_pos), c.T), dtype=torch.uint8, device="cuda")))
     torch.cuda.synchronize()
     for rep in range(6):
-        for s_, st in zip(sets, streams):
-            c = s_["c"]
+        for i, s_ in enumerate(sets):
+            c, st = s_["c"], streams[i % 2]
             AT.attn_suffix_prefill(s_["sh"], s_["q"], s_["kn"], s_["vn"], s_["g"], c.cu_seqlens, c.start_pos, s_["k"], s_["v"],
                                    c.seq_slot, s_["o"], s_["ws"], stream=st)
     torch.cuda.synchronize()

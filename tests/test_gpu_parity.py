@@ -310,6 +310,71 @@ def test_run_to_run_bitwise_determinism():
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
+BY_VALUE_WORDS = 2 * 896      # plan images up to this many 32-bit words travel in kernel arguments, larger ones through the staging ring
+
+
+def plan_words(call):
+    """Words of a call's plan image: three per chunk, four per request and two."""
+    from paper_2605_05219_amd import binding as B
+    chunks = B.gdn_plan_chunks(call.cu_seqlens, call.start_pos, call.emit_cu, call.emit_pos)[0]
+    return 3 * len(chunks) + 4 * call.n_req + 2
+
+
+def many_chunks_call(seed, n_req, chunks):
+    """A small-headed call of n_req requests with `chunks` chunks in all: most chunks are one token with an emission of its own,
+    so a wrong word of the plan image shows in a token's output or in a slot."""
+    rng = np.random.default_rng(seed)
+    lens = [chunks // n_req + (r < chunks % n_req) for r in range(n_req)]
+    starts = [int(x) for x in rng.integers(0, 500, n_req)]
+    n_slots = n_req + chunks
+    ids = rng.permutation(n_slots)
+    emits = [[starts[r] + i + 1 for i in range(lens[r])] for r in range(n_req)]
+    at = np.concatenate([[0], np.cumsum(lens)])
+    slots = [[int(x) for x in ids[n_req + at[r]:n_req + at[r + 1]]] for r in range(n_req)]
+    per = [wl.token_streams(rng, 1, n, 1, 1, 64, 64, "f32", "slow") for n in lens]
+    pool = (rng.standard_normal((n_slots, 1, 1, 64, 64)) * 0.1).astype(np.float32)
+    return wl.pack_call(1, 1, 1, 64, 64, "f32", per, starts, [int(x) for x in ids[:n_req]], emits, slots, n_slots), pool
+
+
+@pytest.mark.parametrize("words", [895, 896, 897, 1791, 1792, 1793])
+def test_plan_images_around_the_piece_and_the_by_value_limit(words):
+    """896 words travel in the arguments of one launch, two such pieces at most; one word more goes through the staging ring."""
+    n_req = next(r for r in (1, 2, 3) if (words - 2 - 4 * r) % 3 == 0)
+    call, pool = many_chunks_call(words, n_req, (words - 2 - 4 * n_req) // 3)
+    assert plan_words(call) == words
+    check_call(call, pool, TOL["f32"])
+
+
+def test_more_large_plan_images_in_flight_than_the_staging_ring_has_buffers():
+    """Two streams, three calls with different large images in turn, 24 in all without a host wait between them: every call's
+    plan reaches it whole (a buffer is rewritten only when its upload has left it).  A long copy in front of each stream keeps the
+    uploads waiting while the host runs ahead."""
+    import torch
+    from tests.harness import GpuCall
+    cases = [many_chunks_call(4000 + i, n_req, 700 + 31 * i) for i, n_req in enumerate((5, 9, 3))]
+    assert all(plan_words(c) > BY_VALUE_WORDS for c, _ in cases)
+    want = [run_call_gpu(c, pool) for c, pool in cases]
+    # (each repetition has tensors and a workspace of its own: outputs of all of them are looked at)
+    calls = [[GpuCall(c, pool) for c, pool in cases] for _ in range(8)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    big = [torch.zeros(1 << 28, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    torch.cuda.synchronize()
+    for i, st in enumerate(streams):
+        with torch.cuda.stream(st):
+            for _ in range(20):
+                big[2 * i].copy_(big[2 * i + 1])
+    n = 0
+    for rep in calls:
+        for g in rep:
+            g.run(streams[n % 2])
+            n += 1
+    torch.cuda.synchronize()
+    for rep in calls:
+        for g, (c, _), (o, pool) in zip(rep, cases, want):
+            assert np.array_equal(g.o[:, :c.total_tokens].float().cpu().numpy(), o)
+            assert np.array_equal(g.pool.cpu().numpy(), pool)
+
+
 def test_calls_on_a_side_stream_and_interleaved_streams_are_bitwise_the_default_stream_result():
     """The library enqueues on the caller's stream only: a call on a side stream, and two calls with their own
     workspaces interleaved on two streams, give the default-stream result bit for bit."""
@@ -333,18 +398,23 @@ def test_calls_on_a_side_stream_and_interleaved_streams_are_bitwise_the_default_
         assert np.array_equal(g.pool.cpu().numpy(), ref_pool)
 
 
-def test_two_host_threads_calling_concurrently_get_the_single_thread_result():
+@pytest.mark.parametrize("images", ["in kernel arguments", "through the staging ring"])
+def test_two_host_threads_calling_concurrently_get_the_single_thread_result(images):
     """Two host threads, each with its own stream, tensors and workspace, call the library at the same time (ctypes
-    drops the interpreter lock during a call): the shared plan staging buffer and the one-time set-up are guarded, and
-    every call's result is the single-thread result bit for bit."""
+    drops the interpreter lock during a call): the shared ring of plan staging buffers (which small images do not use) and
+    the one-time set-up are guarded, and every call's result is the single-thread result bit for bit."""
     import threading
     import torch
     from tests.harness import GpuCall
-    scs = [wl.config2(orc.deepest_ckpt, seed=21 + i, n_req=3 + 2 * i, N=1024, M=4, tail=40) for i in range(2)]
-    pools = [fill_pool_from_oracle(sc)[0] for sc in scs]
-    refs = [run_call_gpu(sc.resume, pool) for sc, pool in zip(scs, pools)]
-    calls = [GpuCall(sc.resume, pool) for sc, pool in zip(scs, pools)]
-    streams = [torch.cuda.Stream() for _ in scs]
+    if images == "in kernel arguments":
+        cases = [(sc.resume, fill_pool_from_oracle(sc)[0])
+                 for sc in (wl.config2(orc.deepest_ckpt, seed=21 + i, n_req=3 + 2 * i, N=1024, M=4, tail=40) for i in range(2))]
+    else:
+        cases = [many_chunks_call(4100 + i, 4 + 3 * i, 650 + 40 * i) for i in range(2)]
+    assert all((plan_words(c) > BY_VALUE_WORDS) == (images != "in kernel arguments") for c, _ in cases)
+    refs = [run_call_gpu(c, pool) for c, pool in cases]
+    calls = [GpuCall(c, pool) for c, pool in cases]
+    streams = [torch.cuda.Stream() for _ in cases]
     torch.cuda.synchronize()
     errors = []
 
@@ -363,8 +433,8 @@ def test_two_host_threads_calling_concurrently_get_the_single_thread_result():
         t.join()
     assert not errors, errors
     torch.cuda.synchronize()
-    for i, sc in enumerate(scs):
-        T = sc.resume.total_tokens
+    for i, (c, _) in enumerate(cases):
+        T = c.total_tokens
         assert np.array_equal(calls[i].o[:, :T].float().cpu().numpy(), refs[i][0])
         assert np.array_equal(calls[i].pool.cpu().numpy(), refs[i][1])
 
