@@ -817,7 +817,7 @@ def side_measurements(args, torch, B, wl, dev, calls, pool, suffix, wall_cfg1_ms
             out["layer_group"] = {"layers": "3 GatedDeltaNet + 1 attention (16 query / 2 kv heads), d = 128, d_model 2048, projections included",
                                   "points": pts, "fit_ms": fit, "projection_flops_per_token": proj_flops_per_token,
                                   "note": "wall time of a whole hit per suffix length (8192 = a miss: nothing restored): in-projections of "
-                                          "the four layers (gdn_linear_split, one launch per layer, bf16), front ends of the three GatedDeltaNet layers, recurrence, "
+                                          "the four layers (gdn_linear_split, one call per layer, bf16), front ends of the three GatedDeltaNet layers, recurrence, "
                                           "back ends, their out-projections, attention and its out-projection; every layer reads the same "
                                           "hidden rows (the cost of a stacked group, not its data flow); host tier: checkpoint states "
                                           "(3 MiB) and the KV prefix come from pinned host memory inside the timed region; hbm tier: both "

@@ -42,7 +42,7 @@ int32_t gdn_linear(const void *x, int64_t ldx, const void *w, int64_t ldw, const
                    int64_t T, int32_t N, int32_t K, void *stream);
 
 /*
- * The same map with its outputs split by column range over several destinations, one launch: segment s holds
+ * The same map with its outputs split by column range over several destinations, in the launches of gdn_linear: segment s holds
  * outputs seg_cols[s] .. seg_cols[s + 1] - 1 and goes to seg_y[s] (T rows of that many elements at seg_ld[s]
  * elements).  This is the in-projection of a GatedDeltaNet layer as the layer's front end wants it: one weight
  * matrix [conv input | z | a | b], four separate tensors (include/gdn_layer.h); N = seg_cols[n_seg].
@@ -56,6 +56,13 @@ int32_t gdn_linear(const void *x, int64_t ldx, const void *w, int64_t ldw, const
 int32_t gdn_linear_split(const void *x, int64_t ldx, const void *w, int64_t ldw, const float *bias,
                          int32_t n_seg, const int32_t *seg_cols, void *const *seg_y, const int64_t *seg_ld,
                          int32_t out_dtype, int64_t T, int32_t K, void *stream);
+
+/*
+ * The launches gdn_linear and gdn_linear_split make for a problem (host only; for tests and for callers that want to see
+ * them): outputs 0 .. *cols - 1 in tile shape *shape and, where *cols < N, the others in a second launch in *rest_shape (shape
+ * numbers as for gdn_linear_tune).  T, N, K positive (else GDN_ERR_COUNT), K a multiple of 64 (else GDN_ERR_SHAPE).
+ */
+int32_t gdn_linear_plan(int64_t T, int32_t N, int32_t K, int32_t *shape, int32_t *cols, int32_t *rest_shape);
 
 /*
  * Tuning knob, not a method step: fixes the workgroup tile gdn_linear uses (0: 128 x 128; 1: 256 x 256 with four

@@ -544,6 +544,17 @@ extern "C" int32_t gdn_linear_split(const void* x, int64_t ldx, const void* w, i
     return linear_launch(a, out_dtype, (hipStream_t)stream_);
 }
 
+extern "C" int32_t gdn_linear_plan(int64_t T, int32_t N, int32_t K, int32_t* shape, int32_t* cols, int32_t* rest_shape) {
+    if (T <= 0 || N <= 0 || K <= 0) return GDN_ERR_COUNT;
+    if (K % 64 != 0) return GDN_ERR_SHAPE;
+    if (!shape || !cols || !rest_shape) return GDN_ERR_NULL;
+    const LinearPlan p = plan_linear(T, N, K);
+    *shape = p.shape;
+    *cols = p.cols;
+    *rest_shape = p.rest_shape;
+    return GDN_OK;
+}
+
 extern "C" int32_t gdn_linear_tune(int32_t shape) {
     return g_linear_shape.exchange(shape < 0 || shape > 3 ? -1 : shape);
 }

@@ -7,7 +7,7 @@ from .binding import GDN_BF16, GDN_F32, _check, _dp, _stream_ptr, lib
 
 _i32, _i64, _vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
 
-EXPORTS = ["gdn_linear", "gdn_linear_split", "gdn_linear_tune"]
+EXPORTS = ["gdn_linear", "gdn_linear_split", "gdn_linear_plan", "gdn_linear_tune"]
 
 _ready = False
 
@@ -20,6 +20,8 @@ def _lib():
         L.gdn_linear.argtypes = [_vp, _i64, _vp, _i64, _vp, _vp, _i64, _i32, _i64, _i32, _i32, _vp]
         L.gdn_linear_split.restype = _i32
         L.gdn_linear_split.argtypes = [_vp, _i64, _vp, _i64, _vp, _i32, _vp, _vp, _vp, _i32, _i64, _i32, _vp]
+        L.gdn_linear_plan.restype = _i32
+        L.gdn_linear_plan.argtypes = [_i64, _i32, _i32, _vp, _vp, _vp]
         L.gdn_linear_tune.restype = _i32
         L.gdn_linear_tune.argtypes = [_i32]
         _ready = True
@@ -56,8 +58,15 @@ def gdn_linear(x, w, bias, y, stream=None) -> None:
            "gdn_linear")
 
 
+def gdn_linear_plan(T: int, N: int, K: int):
+    """(tile shape, outputs it covers, tile shape of the other outputs) of a projection; host only."""
+    shape, cols, rest = _i32(0), _i32(0), _i32(0)
+    _check(_lib().gdn_linear_plan(int(T), int(N), int(K), ctypes.byref(shape), ctypes.byref(cols), ctypes.byref(rest)), "gdn_linear_plan")
+    return shape.value, cols.value, rest.value
+
+
 def gdn_linear_tune(shape: int) -> int:
-    """Fixes the workgroup tile (0, 1, 2) or returns the choice to the library (-1); returns the previous setting."""
+    """Fixes the workgroup tile (0, 1, 2, 3) or returns the choice to the library (-1); returns the previous setting."""
     return int(_lib().gdn_linear_tune(int(shape)))
 
 

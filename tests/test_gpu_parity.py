@@ -246,19 +246,30 @@ def test_fp32_recurrence_variants(L, H_qk, H_v, o_dtype, scale):
 
 
 def test_halved_slabs_of_a_long_call_are_bitwise_the_whole_ones():
-    """48 chains whose operand images exceed the memory-side cache's share: slabs of 32 rounds instead of 64."""
+    """48 chains whose operand images exceed the memory-side cache's share: slabs of 32 rounds instead of 64 (three recurrence
+    launches for the 65 rounds, counted, against two)."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(41)
     lens, starts = [4100, 3900, 4000], [0, 128, 64]
     per = [wl.token_streams(rng, 1, n, 16, 16, 128, 128, "bf16", "slow") for n in lens]
     pool = (rng.standard_normal((8, 1, 16, 128, 128)) * 0.1).astype(np.float32)
     call = wl.pack_call(1, 16, 16, 128, 128, "bf16", per, starts, [-1, 0, 1], [[2048, 4100], [4028], []], [[2, 3], [4], []], 8)
-    o_auto, pool_auto = run_call_gpu(call, pool)
+
+    def run_counted():
+        B.gdn_profile_enable(True)
+        try:
+            out = run_call_gpu(call, pool)
+            return out + (B.gdn_profile_collect()[4],)
+        finally:
+            B.gdn_profile_enable(False)
+
+    o_auto, pool_auto, n_auto = run_counted()
     prev = B.gdn_tune_slab_rounds(64)
     try:
-        o_64, pool_64 = run_call_gpu(call, pool)
+        o_64, pool_64, n_64 = run_counted()
     finally:
         B.gdn_tune_slab_rounds(prev)
+    assert (n_auto, n_64) == (3, 2)
     assert np.array_equal(o_auto, o_64) and np.array_equal(pool_auto, pool_64)
 
 

@@ -92,6 +92,26 @@ def test_tile_knob_round_trip():
     assert LN.gdn_linear_tune(prev) == -1
 
 
+def test_plan_covers_the_outputs_and_follows_the_knob():
+    rng = np.random.default_rng(9)
+    for _ in range(200):
+        T, N, K = int(np.exp(rng.uniform(0, 12))) , int(np.exp(rng.uniform(0, 9.5))), 64 * int(rng.integers(1, 65))
+        shape, cols, rest = LN.gdn_linear_plan(T, N, K)
+        assert shape in (0, 2, 3) and 0 < cols <= N
+        if cols < N:                           # whole tile columns of the large shape, the rest in a smaller one
+            assert shape == 2 and cols % 256 == 0 and rest in (0, 3)
+    for knob in (0, 1, 2, 3):
+        prev = LN.gdn_linear_tune(knob)
+        try:
+            assert LN.gdn_linear_plan(8192, 8224, 2048)[:2] == (knob, 8224)
+        finally:
+            LN.gdn_linear_tune(prev)
+    for T, N, K, code in [(0, 1, 64, -11), (1, -1, 64, -11), (1, 1, 0, -11), (1, 1, 100, -3)]:
+        with pytest.raises(B.GdnError) as ei:
+            LN.gdn_linear_plan(T, N, K)
+        assert ei.value.code == code
+
+
 def test_python_binding_rejects_mismatched_tensors():
     import torch
     x = torch.zeros((4, 64), dtype=torch.bfloat16)
@@ -233,17 +253,18 @@ def test_split_outputs_equal_the_whole_projection(shape, out):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("T,widths", [
-    (8192, [6144, 2048, 16, 16]),              # 33 columns of large tiles where 32 fill four rounds: the rest is two whole segments
-    (8100, [2048, 256, 256]),                  # eight columns of large tiles and a rest; a ragged last tile row
-    (8192, [2000, 304, 256]),                  # the cut (column 2048) inside the second segment
+@pytest.mark.parametrize("T,widths,cut", [
+    (8192, [6144, 2048, 16, 16], 8192),        # 33 columns of large tiles where 32 fill four rounds: the rest is two whole segments
+    (8100, [2048, 256, 256], 2048),            # eight columns of large tiles and a rest; a ragged last tile row
+    (8192, [2000, 304, 256], 2048),            # the cut inside the second segment
 ])
 @pytest.mark.parametrize("out", ["bf16", "f32"])
-def test_large_projection_cut_into_two_column_ranges(T, widths, out):
+def test_large_projection_cut_into_two_column_ranges(T, widths, cut, out):
     """Problems whose last round of large tiles would be nearly empty run as two launches; every shape computes the same
     sums in the same order, so whole and split outputs equal one launch of the 128 x 128 shape bit for bit."""
     import torch
     K, N = 2048, sum(widths)
+    assert LN.gdn_linear_plan(T, N, K)[:2] == (2, cut)
     g = torch.Generator(device="cuda"); g.manual_seed(T + N)
     x = torch.randn((T, K), device="cuda", generator=g).bfloat16()
     w = (torch.randn((N, K), device="cuda", generator=g) / K ** 0.5).bfloat16()
