@@ -59,7 +59,7 @@ typedef struct gdn_layer_shape {
 int64_t gdn_layer_workspace_bytes(int32_t n_req, int32_t n_emit);
 
 /*
- * Front end of the layer for a packed batch of resumed requests, one launch:
+ * Front end of the layer for a packed batch of resumed requests, one launch behind the upload of its index arrays:
  *   q, k, v     from x_qkv by the short convolution continued from each request's stored state,
  *               SiLU, and the per-head L2 normalisation of q and k;
  *   beta, gate  from b_pre, a_pre;

@@ -170,7 +170,11 @@ int32_t ckpt_scatter(float *pool, int64_t slot_stride, int32_t n_slots,
  *   workspace   device, 256-byte aligned, at least gdn_workspace_bytes(...) bytes; contents
  *               are scratch, nothing is carried between calls
  * Outputs: o within the stated tolerance of the token-by-token definition, emitted states
- * likewise, slot indexing exact.  Calls that share a workspace must be ordered on one stream.
+ * likewise, slot indexing exact.  The same call gives the same bits every time; which kernels serve
+ * a call depends on its shape, its types and how many chains (requests x layers x value heads) it
+ * has, and their sums have different orders, so a request's results may differ in rounding with
+ * what it is batched with (fp32 inputs: above and below half the compute units in chains).
+ * Calls that share a workspace must be ordered on one stream.
  */
 int32_t gdn_resume_prefill(const gdn_shape *shape,
                            const void *q, const void *k, const void *v,

@@ -129,7 +129,7 @@ gdn_linear_kernel(LinearArgs a) {
     // share their rows of x and of w in its L2.  (Row by row over the whole output, an XCD's 32 tiles touched nearly every row of w.)
     constexpr int GROUP_M = CFG::BM == 256 ? 4 : 8;
     const int seq = ((int)blockIdx.x & 7) * a.per_xcd + ((int)blockIdx.x >> 3);
-    if (seq >= a.tiles_m * a.tiles_n || ((int)blockIdx.x >> 3) >= a.per_xcd) return;
+    if (seq >= a.tiles_m * a.tiles_n) return;      // (the grid is 8 per_xcd)
     const int grp = seq / (GROUP_M * a.tiles_n), in_grp = seq % (GROUP_M * a.tiles_n);
     const int grp_rows = min(a.tiles_m - grp * GROUP_M, GROUP_M);
     const int tile_m = grp * GROUP_M + in_grp % grp_rows, tile_n = in_grp / grp_rows;
@@ -387,6 +387,8 @@ int chip_cus_linear() {
 // costs its latency (a workgroup alone walks k no faster) and more the fuller it is: the compute units share power and memory.
 // Fitted to T = 64 .. 8192, N = 32 .. 8224 (estimate against measured: 8192 x 8192 in shape 2 216 / 213, 8192 x 2560 91 / 93,
 // 4096 x 2560 43 / 43; in shape 0 8192 x 2560 87 / 84, 2048 x 8224 80 / 80, 512 x 8224 24 / 26; in shape 3 1024 x 2048 14.5 / 15.5).
+// All with the operands of the call before, in the caches: in a layer group's pass, each layer's weights cold, the small problems
+// take longer than the estimate says (512 x 8224 in shape 0 34 to 35 us, 512 x 2048 in shape 3 13, 512 x 2560 17).
 struct ShapeCost { int id, bm, bn, per_cu; double full, alone; bool square; };
 constexpr ShapeCost SHAPES[3] = {{3, 64, 64, 2, 14.5, 10.0, false}, {0, 128, 128, 2, 31.5, 16.0, false}, {2, 256, 256, 1, 54.0, 36.0, true}};
 double shape_cost(const ShapeCost& c, int64_t T, int64_t N) {
@@ -397,7 +399,8 @@ double shape_cost(const ShapeCost& c, int64_t T, int64_t N) {
 
 // Which tile shape a problem gets, and how many of its columns: a problem whose tiles leave a last round nearly empty may be cut
 // into columns that fill whole rounds of 256 x 256 tiles and a rest in a smaller shape, a launch of its own.  Measured in a layer
-// group's pass: 8192 x 8224 (33 tile columns where 32 fill four rounds) 284 us whole, 244 + 12 cut; 8192 x 2560 114 whole, 63 + 35 cut (alone: 2048 x 8224 90 / 68, 4096 x 8224 142 / 122).
+// group's pass: 8192 x 8224 (33 tile columns where 32 fill four rounds) 284 us whole, 240 + 12 cut; 8192 x 2560 114 whole, 62 + 35 cut
+// (alone: 2048 x 8224 90 / 68, 4096 x 8224 142 / 122).
 struct LinearPlan { int shape, rest_shape; int32_t cols; };   // outputs 0 .. cols - 1 in `shape`, the others in `rest_shape`
 LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
     const int forced = g_linear_shape.load();
