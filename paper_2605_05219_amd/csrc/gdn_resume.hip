@@ -810,20 +810,33 @@ struct WsLayout {
     int32_t R, n_bufs;
     int64_t plan, carry, slab, total;
 };
-// Latency variant with launches apart: a call whose operand images come to more than this cuts its slabs of 64 rounds in half.  The
-// preparation's stores and the recurrence's loads of a slab then stay in the 256 MiB memory-side cache (48 chains of 128 chunks
-// 437 against 349 us, 64 chains of up to 125 chunks 325 against 286); a call that fits it as a whole pays for every further
-// slab (48 chains of up to 86 chunks 149 against 153, 32 chunks 84 against 85; d = 64, 128 chains 140 against 152).
-constexpr int64_t SLAB_CACHE_BYTES = (int64_t)192 << 20;
-// n_chunks: chunks of the whole call; max_rounds: chunks of its longest request (or a bound).  for_call: the layout a call uses, in
-// place of the size that is enough for every call of these bounds.
-static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_rounds, int32_t n_req, bool for_call = false) {
+// Latency variant with launches apart: does a call cut its slabs of 64 rounds in half, so that the preparation's stores and the
+// recurrence's loads of a slab stay in the 256 MiB memory-side cache?  Only where the images of the first slab's chunks would not
+// stay there, and not when the whole call's do, for every further slab costs two launches; in a call of requests of very
+// different lengths these have few chunks to work on.  Measured, 64 rounds against 32, d = 128 (72.5 KiB a chunk): chains of 128
+// chunks each, 34 (150 MiB in a slab) 326 against 335 us, 36 (159) 329 / 330, 38 (168) 357 / 337, 48 (213) 475 / 372, 64 543 / 498;
+// chains of 32 to 128 chunks, 39 (145) 273 / 301, 43 (161) 304 / 330, 45 (169) 333 / 334, 46 (175) 340 / 321, 54 (204) 373 / 348; of 8
+// to 128, 46 (116) 256 / 272.  d = 64 (41 KiB a chunk): of 128 chunks, 66 (165) 363 / 338, 90 495 / 418, 112 561 / 491, 126 591 / 606; of
+// 32 to 128, 78 (168) 293 / 308, 90 (195) 341 / 331, 104 (225) 360 / 371, 124 (273) 399 / 432.
+constexpr int64_t MIB = (int64_t)1 << 20;
+static bool halve_slabs(const gdn_shape& s, int32_t rounds, int64_t n_chunks, const ChunkPlan& plan) {
+    const int64_t image = (int64_t)s.L * s.H_v * unit_bytes(s);      // of a chunk, all layers and heads
+    const int64_t n_req = (int64_t)plan.req_chunk_cu.size() - 1;
+    int64_t first = 0;
+    for (int64_t r = 0; r < n_req; ++r) first += std::min(rounds, plan.req_chunk_cu[r + 1] - plan.req_chunk_cu[r]);
+    if (rounds <= 32 || n_chunks * image <= 192 * MIB) return false;
+    const bool even = 20 * first >= 19 * n_req * rounds;             // nearly every request has chunks for the whole slab
+    return even ? first * image > 156 * MIB : s.d_k == 128 && first * image > 172 * MIB;
+}
+// n_chunks: chunks of the whole call; max_rounds: chunks of its longest request (or a bound).  plan: the layout the call with this
+// plan uses, in place of the size that is enough for every call of these bounds.
+static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_rounds, int32_t n_req, const ChunkPlan* plan = nullptr) {
     const int64_t units = (int64_t)s.L * s.H_v, n_chains = units * n_req, ub = unit_bytes(s);
     const int nw = pick_waves(n_chains, s.d_v / 32, s.in_dtype != GDN_F32);
     WsLayout w;
     w.R = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slab_rounds(n_chains, ub, nw, s.d_v / 32), max_rounds));
-    if (for_call && g_forced_rounds.load() == 0 && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && n_chunks * units * ub > SLAB_CACHE_BYTES)
-        w.R = std::min(w.R, 32);
+    if (plan && g_forced_rounds.load() == 0 && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && halve_slabs(s, w.R, n_chunks, *plan))
+        w.R = 32;
     w.plan = plan_bytes(n_chunks, n_req);
     w.carry = align_up(n_chains * s.d_v * s.d_k * (int64_t)sizeof(float), 256);
     w.slab = n_chains * w.R * ub;
@@ -923,7 +936,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     // The fused kernel needs the plan image only; the two-kernel path needs the carried states and a slab as well.
     // A workspace too small for the two-kernel path but large enough for the fused kernel gets the fused kernel
     // whatever the estimate says (gdn_workspace_bytes_fused is the size that asks for this).
-    WsLayout wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, true);
+    WsLayout wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
     int32_t n_staged = 0;
     if (src_on_host)
         for (int32_t r = 0; r < n_req; ++r) n_staged += src_slot[r] >= 0;

@@ -273,6 +273,22 @@ def test_halved_slabs_of_a_long_call_are_bitwise_the_whole_ones():
     assert np.array_equal(o_auto, o_64) and np.array_equal(pool_auto, pool_64)
 
 
+def test_slabs_of_ragged_calls_stay_whole():
+    """38 chains of 36 to 128 chunks, 198 MiB of images in all, 151 of them in the first slab of 64 rounds, where they stay in the
+    cache; few chains are left after it.  Two slabs, two recurrence launches."""
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(43)
+    lens = [8192] + [int(x) for x in np.exp(rng.uniform(np.log(2300), np.log(8192), 18))]
+    per = [wl.token_streams(rng, 1, n, 2, 2, 128, 128, "bf16", "slow") for n in lens]
+    call = wl.pack_call(1, 2, 2, 128, 128, "bf16", per, [0] * 19, [-1] * 19, [[]] * 19, [[]] * 19, 1)
+    B.gdn_profile_enable(True)
+    try:
+        run_call_gpu(call, np.zeros((1, 1, 2, 128, 128), np.float32))
+        assert B.gdn_profile_collect()[4] == 2
+    finally:
+        B.gdn_profile_enable(False)
+
+
 def test_bf16_output_and_scale():
     sc = wl.config1(orc.deepest_ckpt, seed=5, n_draws=2, N=1024, M=4, H=4, d=128)
     pool, _, _ = fill_pool_from_oracle(sc)
