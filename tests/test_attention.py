@@ -192,7 +192,7 @@ def _few_rows(H_q, H_kv, n, start):
     return n > 0 and 128 % G == 0 and n * G <= 16 and start + n >= 1024
 
 
-@pytest.mark.parametrize("seed", range(12))
+@pytest.mark.parametrize("seed", range(24))
 def test_mixed_calls_walk_decode_rows_whole_only_as_calls_of_their_own_do(seed):
     """Decode rows, short-context rows and prefill chunks in one call: every key tile is walked once, and either every decode
     row's walk is split (one launch of the 128-row kernel) or the decode rows' walks are those of a call of their own."""
@@ -200,7 +200,7 @@ def test_mixed_calls_walk_decode_rows_whole_only_as_calls_of_their_own_do(seed):
     H_q, H_kv = [(16, 2), (8, 8), (4, 1), (1, 1), (32, 4), (12, 4)][seed % 6]
     d = int(rng.choice([64, 128, 256]))
     G, KT = H_q // H_kv, 32 if d == 256 else 64
-    n = int(rng.integers(2, [90, 12][seed % 2]))
+    n = int(rng.integers(2, [90, 12][seed % 2])) if seed < 12 else int(rng.integers(150, 1000))   # many: no room for two parts each
     lens, starts = [], []
     for _ in range(n):
         kind = rng.integers(4)
