@@ -841,8 +841,8 @@ def side_measurements(args, torch, B, wl, dev, calls, pool, suffix, wall_cfg1_ms
 
 
 def phase_table(torch, B) -> int:
-    """The fused kernel's clocks per phase of one 64-token chunk, from the profiling build of the library (cycle stamps at
-    the phase boundaries of the 40th item of every eighth workgroup, one set per wave), on the configs[4] step."""
+    """The pipelined fused kernel's clocks per phase of one 64-token chunk, from the profiling build of the library (cycle stamps
+    at the phase boundaries of the 40th step of every fourth workgroup, one set per wave), on the configs[4] step."""
     import ctypes
     from paper_2605_05219_amd import build as BLD
     from paper_2605_05219_amd.device_call import config4_device
@@ -854,23 +854,24 @@ def phase_table(torch, B) -> int:
     for _ in range(3):
         step.run()
     torch.cuda.synchronize()
-    raw = np.zeros(64 * 4 * 16, dtype=np.uint64)
+    raw = np.zeros(64 * 8 * 16, dtype=np.uint64)
     rc = int(B.lib().gdn_phase_stamps(raw.ctypes.data_as(ctypes.c_void_p)))
     if rc != 0:
         print(f"gdn_phase_stamps: {rc}", file=sys.stderr)
         return 1
-    t = raw.reshape(64 * 4, 16).astype(np.int64)
-    t = t[(t[:, 0] > 0) & (t[:, 9] > t[:, 0])]
-    names = ["gates; stage K, Q, V, the next chunk's K loads in between", "the next chunk's gate loads", "barrier after staging",
-             "the next chunk's Q loads, diagonal gram block and its inverse", "the next chunk's V loads, L and P blocks",
-             "barrier after preparation", "substitution and outputs", "state update", "emission"]
-    d = np.diff(t[:, :10], axis=1)
-    print(json.dumps({"phase_table": {"workload": "configs[4] step, fused kernel, 40th item (a full 64-token chunk of a long chain) of every eighth workgroup",
-                                      "waves_sampled": int(d.shape[0]), "unit": "shader clocks per wave",
-                                      "mean": {n: float(x) for n, x in zip(names, d.mean(0))},
-                                      "min": {n: float(x) for n, x in zip(names, d.min(0))},
-                                      "max": {n: float(x) for n, x in zip(names, d.max(0))},
-                                      "total_mean": float(d.sum(1).mean())}}))
+    stamps = raw.reshape(64, 2, 4, 16).astype(np.int64)
+    roles = {"preparation waves": ["stage, fetch, prepare", "barrier"],
+             "recurrence waves": ["substitution and outputs", "V to LDS, the next chunk's V loads", "state update", "emission",
+                                  "a new chain's start state", "barrier"]}
+    table = {"workload": "configs[4] step, pipelined fused kernel, 40th step (a full 64-token chunk of a long chain) of every fourth workgroup",
+             "unit": "shader clocks per wave"}
+    for i, (role, names) in enumerate(roles.items()):
+        t = stamps[:, i].reshape(-1, 16)[:, :len(names) + 1]
+        d = np.diff(t[t.min(1) > 0], axis=1)
+        table[role] = {"waves_sampled": int(d.shape[0]), "mean": {n: float(x) for n, x in zip(names, d.mean(0))},
+                       "min": {n: float(x) for n, x in zip(names, d.min(0))}, "max": {n: float(x) for n, x in zip(names, d.max(0))},
+                       "total_mean": float(d.sum(1).mean())}
+    print(json.dumps({"phase_table": table}))
     return 0
 
 

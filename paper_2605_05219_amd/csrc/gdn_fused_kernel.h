@@ -1,4 +1,5 @@
-// Fused throughput kernel (bf16 inputs, d_k = d_v = D = 128 or 64): chunk preparation and recurrence of
+// Fused throughput kernel (bf16 inputs; pairs of value heads at d_k = d_v = D = 128, one head or pairs at 64; single heads at
+// D = 128, and calls bound by their longest chain at 64, run gdn_pipe_kernel.h): chunk preparation and recurrence of
 // one chain (request, layer, value head) in ONE workgroup, chunk after chunk, the chunk
 // operands never leaving the compute unit.  HBM sees q, k, v, the gates, o and the states,
 // nothing else.  A chain's chunks are serial, so the kernel only pays when chains are plentiful
@@ -151,21 +152,6 @@ __device__ __forceinline__ f32x4 inv16_tiles(const f32x4& d, const f32x4& dt, in
     const f32x4 p8t = mm16_rr(zero, p4, p4t);
     return mm16_rr(y, p8t, y);
 }
-
-// Profiling build only (-DGDN_PHASE_STAMPS, a library of its own: see build.py): cycle stamps at the phase boundaries of
-// the 40th item of every eighth workgroup (the kernel's steady state), one set per wave, read back by gdn_phase_stamps.  The product build has none.
-#ifdef GDN_PHASE_STAMPS
-__device__ unsigned long long g_phase_ts[64 * 4 * 16];
-#define GDN_PHASE(k_)                                                                                   \
-    do {                                                                                                \
-        if (gdn_item == 40 && (blockIdx.x & 7) == 0 && blockIdx.x < 512 && lane_ == 0 && hsel == 0)     \
-            g_phase_ts[((blockIdx.x >> 3) * 4 + wave) * 16 + (k_)] = __builtin_readcyclecounter();      \
-    } while (0)
-#define GDN_PHASE_ITEM() (++gdn_item)
-#else
-#define GDN_PHASE(k_) do {} while (0)
-#define GDN_PHASE_ITEM() ((void)0)
-#endif
 
 template <bool O_BF16, int D, int GV>
 __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2, (D == 128 || GV == 2) ? 2 : 3))) gdn_fused_kernel(FusedArgs a) {
@@ -320,8 +306,6 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
     bool first = true;
     bool state_pending = false;   // the start state of a new chain is still on its way
 
-    int gdn_item = 0;      // items done (used by the profiling build only)
-    (void)gdn_item;
     for (;;) {
         // The lane's coordinates are made opaque once per item: otherwise every address of the unrolled tile
         // accesses below is hoisted out of this loop and held in a register of its own for the whole kernel.
@@ -375,8 +359,6 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
             reserve_stale = false;
         }
         const Item nxt = next_item(cur);
-        GDN_PHASE_ITEM();
-        GDN_PHASE(0);
 
         // ---- gates, by wave 0: g_i = inclusive running sum of log a and what derives from it; identity beyond n.  Between
         //      blocks of 16 tokens the decay factors into a row and a column part, exp(g_i - g_j) = exp(g_i - g_end(c))
@@ -431,11 +413,8 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
             GDN_FETCH_K(r, tg, d0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        GDN_PHASE(1);
         GDN_FETCH_GATES(nxt, lane);
-        GDN_PHASE(2);
         __syncthreads();
-        GDN_PHASE(3);
 
         // operand over d_k columns 32 s + 8 g4 .. + 7 of row 16 blk + m of a tile
         GDN_FETCH_ALL(GDN_FETCH_Q, tg, d0);
@@ -464,8 +443,11 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = 4 * g4 + e;
-                d[e] = (m < i) ? bi[e] * EL::exp_(fminf(gi[e] - gj, 0.f)) * gr[e] : 0.f;     // D[i][m]
-                dt[e] = (i < m) ? bj * EL::exp_(fminf(gj - gi[e], 0.f)) * gr[e] : 0.f;       // D[m][i]
+                float x = bi[e] * EL::exp_(fminf(gi[e] - gj, 0.f)) * gr[e];     // D[i][m]
+                float xt = bj * EL::exp_(fminf(gj - gi[e], 0.f)) * gr[e];       // D[m][i]
+                pin(x); pin(xt);       // computed in every lane: no branch around an exponential
+                d[e] = (m < i) ? x : 0.f;
+                dt[e] = (i < m) ? xt : 0.f;
             }
             const f32x4 y = inv16_tiles(d, dt, m, g4);
             // T_aa from the accumulator layout to its transpose through the wave's own LDS patch (a wave's LDS
@@ -480,7 +462,6 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
                 for (int e = 0; e < 4; ++e) { tb[e] = at[e] * bi[e]; tgm[e] = -tb[e] * gm[e]; }
                 *reinterpret_cast<half8*>(tbtg + (ab * 16 + m) * PLD + 8 * g4) = cat8(cvt4(tb), cvt4(tgm));
             }
-            GDN_PHASE(4);
             GDN_FETCH_ALL(GDN_FETCH_V, tg, d0);
             const float gq = gS[16 * ia + m];
             // key blocks c: left of the diagonal of block row ab, L_ac -> -(T_aa L_ac) stored by rows; up to query
@@ -520,7 +501,8 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
                         const f32x4 gk = *reinterpret_cast<const f32x4*>(gS + 16 * c + 4 * g4);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float val = a.scale * EL::exp_(fminf(gq - gk[e], 0.f)) * acc[e];
+                            float val = a.scale * EL::exp_(fminf(gq - gk[e], 0.f)) * acc[e];
+                            pin(val);
                             p[e] = (4 * g4 + e <= m) ? val : 0.f;
                         }
                     }
@@ -528,14 +510,12 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
                 }
             }
         }
-        GDN_PHASE(5);
         __syncthreads();
         if (state_pending) {   // a chain's first chunk: its start state (and, with it, the next chunk's rows) must have landed
             wait_vmcnt<0>();
             state_pending = false;
         }
 
-        GDN_PHASE(6);
         // ---- recurrence step of this chunk, d_v columns WC wave + 16 nt + m
         {
             half8 sf[SS][NT];        // the state as an operand over d_k: step s = state tiles 2 s, 2 s + 1
@@ -652,7 +632,6 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
                         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ot[nt]), ro, o_lane + ab * 16 * o_step + 64 * nt, 0, 0);
                 }
             }
-            GDN_PHASE(7);
             // state update: S^T = gam_C S^T + sum_j K^T[.][j] (dec_j U[j][.]), two token blocks per product
             const float gam_last = gamS[C - 1];
 #pragma unroll
@@ -668,7 +647,6 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
                     accS[mt][nt] = mma32(k1, ud[1][nt], accS[mt][nt]);
                 }
             }
-            GDN_PHASE(8);
             // checkpoint emission: exact state after the last token of this chunk
             const int eslot = cur.eslot;   // looked up one item ahead, with the chunk's other bookkeeping
             if (eslot >= 0) {
@@ -681,7 +659,6 @@ __global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2
             }
         }
 
-        GDN_PHASE(9);
         if (nxt.chain < 0) break;
         cur = nxt;
     }

@@ -1,0 +1,622 @@
+// Pipelined fused kernel (bf16 inputs, d_k = d_v = D = 128 or 64, one value head per workgroup): the arithmetic of
+// gdn_fused_kernel.h, result for result, with the preparation of a chain's next chunk on four waves of their own, beside the
+// four waves that run the recurrence of the present one.
+//
+// What bounds it, and why this split: in the fused kernel a chunk of a chain takes the sum of its two dependent halves, the
+// preparation (staging, diagonal inverse, L and P blocks) and the recurrence (four block rows of substitution, outputs,
+// update), 12 k clocks alone on a compute unit, 16 to 18 k with a second workgroup beside it.  Neither half keeps the matrix pipe
+// busy for a third of its time; they are chains of latencies.  Only the recurrence needs the state, so the preparation can run
+// ahead: a chain then advances at the pace of the slower half, 7.8 k clocks a chunk with a preparation and a recurrence wave on
+// every SIMD (preparation alone 6.2 k, recurrence alone 5.4 k).  One workgroup of eight waves per compute unit does as much work per
+// clock as two of the fused kernel's (32768 chains the same time), and a chain goes twice as fast.  Measured at D = 128, before (fused kernel, or for
+// the third the two-kernel path) and after: 1024 chains of up to 66 chunks, 15.3 k (chunk, chain) units 428 -> 299 us; 1024 chains of up to
+// 345 chunks, 100 k units 2280 -> 1860; 96 chains of 128 chunks 648 -> 455; 8192 chains, 230 k units 4120 -> 4110.  With all compute units busy
+// the clock is held at 1.8 to 1.95 GHz by the power limit (2.4 with half of them): the same 7.8 k clocks are 4.2 to 4.6 us or 3.3.
+//
+// Pipeline.  A workgroup's items are the chunks of one chain after the other (the chains come longest first and are drawn as
+// in the fused kernel).  In step t
+//     the recurrence waves work on item t - 3: substitution, outputs, state update, emission,
+//     the preparation waves prepare item t - 2 out of LDS, stage item t - 1 from registers to LDS (fp16) and fetch item t,
+// and one barrier ends the step.  K and Q are held for three items in turn, pair tiles for two, gate vectors for three.  V is the
+// recurrence waves' own: a wave fetches, converts and stages only its own columns, behind its last reads of the previous
+// chunk's, so V needs one buffer and no barrier.  Rows are fetched a whole step ahead of their staging: staged and at once fetched again
+// at the top of a step; a fetch half a step later costs 8 %, since the load then has half a step to arrive in (5 % in calls bound by volume).
+//
+// Preparation wave a owns block row a and the P blocks of query block 3 - a; its code is instantiated per wave, so that all
+// of it is one straight line in which the diagonal inverse's dependent products, the other blocks' products and the loads overlap.
+// Wave 1 also walks the list of items one step ahead and leaves what the others need to know of an item in LDS (eight words,
+// four items in turn): with every wave walking the list itself the plan's scalar loads and the registers they spilled cost 3 %.
+//
+// Tried without gain: raised priority of either kind of wave (preparation 0, recurrence 15 % slower); staging in the middle of the
+// preparation (10 %: LDS writes there keep the compiler from reading ahead); V staged behind the update instead of before it (6 %).
+//
+// LDS (PipeSmem<D>: 158 KB at D = 128, 97 KB at D = 64: one workgroup per compute unit): tiles, swizzle and pair tiles as in the fused kernel.
+#pragma once
+#include <type_traits>
+#include "gdn_fused_kernel.h"
+
+namespace gdn {
+
+// Profiling build only (-DGDN_PHASE_STAMPS, a library of its own: see build.py): cycle stamps at the phase boundaries of
+// the 40th step of every fourth workgroup, one set per wave, read back by gdn_phase_stamps.  The product build has none.
+#ifdef GDN_PHASE_STAMPS
+__device__ unsigned long long g_pipe_ts[64 * 8 * 16];
+#define GDN_STAMP(role_, k_)                                                                                        \
+    do {                                                                                                            \
+        if (gdn_step == 40 && (blockIdx.x & 3) == 0 && blockIdx.x < 256 && lane_ == 0)                              \
+            g_pipe_ts[((blockIdx.x >> 2) * 8 + 4 * (role_) + wave) * 16 + (k_)] = __builtin_readcyclecounter();     \
+    } while (0)
+#define GDN_STAMP_STEP() (++gdn_step)
+#else
+#define GDN_STAMP(role_, k_) do {} while (0)
+#define GDN_STAMP_STEP() ((void)0)
+#endif
+
+template <int D_>
+struct PipeSmem {
+    static constexpr int C = 64, D = D_;
+    static constexpr int TILE_BYTES = C * D * 2;             // one of K, Q, V
+    static constexpr int PAIR_LD = 40, TF_LD = 20;           // halfs / floats per row
+    static constexpr int PAIR_BYTES = 16 * PAIR_LD * 2;      // one 16 x (2 x 16) fp16 pair tile
+    static constexpr int ROWS_OFF = 0, ROWS_BYTES = 2 * TILE_BYTES;      // [K | Q] of a chunk, three in turn
+    static constexpr int V_OFF = ROWS_OFF + 3 * ROWS_BYTES;
+    static constexpr int PAIRS_OFF = V_OFF + TILE_BYTES;                 // the pair tiles of a chunk, two in turn
+    static constexpr int TBTG_OFF = 0;
+    static constexpr int M_OFF = TBTG_OFF + 4 * PAIR_BYTES;
+    static constexpr int P_OFF = M_OFF + 4 * PAIR_BYTES;
+    static constexpr int PAIRS_BYTES = P_OFF + 6 * PAIR_BYTES;
+    static constexpr int TF_OFF = PAIRS_OFF + 2 * PAIRS_BYTES;
+    static constexpr int SM_OFF = TF_OFF + 4 * 16 * TF_LD * 4;           // the gate vectors of a chunk, three in turn
+    static constexpr int SM_BYTES = 8 * C * 4;                           // g, b, gam, dec, s, 3 x r
+    static constexpr int ITEM_OFF = SM_OFF + 3 * SM_BYTES;               // four items in turn, eight words each
+    static constexpr int BYTES = ITEM_OFF + 4 * 32;
+    static_assert(BYTES <= 160 * 1024, "a compute unit's LDS");
+    static constexpr __host__ __device__ int m_pair(int a, int c) { return (a == 1 ? 0 : a == 2 ? 1 : 2) + (c >> 1); }
+    static constexpr __host__ __device__ int p_pair(int a, int c) { return (a == 0 ? 0 : a == 1 ? 1 : a == 2 ? 2 : 4) + (c >> 1); }
+};
+
+template <bool O_BF16, int D>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) gdn_pipe_kernel(FusedArgs a) {
+    typedef Elem<half_t> EL;
+    typedef EL::In In;
+    typedef EL::Raw8 Raw8;
+    typedef PipeSmem<D> SM;
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    constexpr int C = 64, DK = D, DV = D, PLD = SM::PAIR_LD;
+    constexpr int NT = D / 64;        // 16-column tiles of the state per wave (a wave owns D / 4 columns of d_v)
+    constexpr int SS = D / 32;        // steps of 32 over d_k (one 16-byte piece per lane and step)
+    constexpr int MT = D / 16;        // 16-wide tiles over d_k
+    constexpr int RBY = 2 * D;        // bytes of a K, Q or V tile row
+    constexpr int PCS = D / 8;        // 16-byte pieces per row
+    constexpr int ROWS = D / 32;      // rows of K and of Q a preparation thread stages (256 threads, 64 rows of PCS pieces)
+    constexpr int WC = D / 4;         // d_v columns per recurrence wave
+    constexpr int WP = WC / 8;        // 16-byte pieces of a recurrence wave's part of a V row; as many pieces per lane
+
+    const int tid = threadIdx.x & 255;
+    const int lane_ = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool prep = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) == 0;
+
+    extern __shared__ __align__(16) char smem[];
+    char* const Vt = smem + SM::V_OFF;
+    const int units = a.L * a.H_v;
+    const In* const qg = reinterpret_cast<const In*>(a.q);
+    const In* const kg = reinterpret_cast<const In*>(a.k);
+    const In* const vg = reinterpret_cast<const In*>(a.v);
+    const int qk_step = a.H_qk * DK * 2, v_step = a.H_v * DV * 2;      // bytes from token to token
+
+    for (int i = threadIdx.x; i < 2 * SM::PAIRS_BYTES / 16; i += 512)
+        reinterpret_cast<u32x4*>(smem + SM::PAIRS_OFF)[i] = u32x4{0u, 0u, 0u, 0u};
+
+    // What a wave needs to know of an item (a chunk of a chain): eight words, in LDS.  n = 0: none; src: the pool slot of a new
+    // chain's start state (-1: the zero state), or SAME_CHAIN.
+    struct Item { int n, hq, hv, row_lo, row_hi, state, eslot, src; };
+    int* const items = reinterpret_cast<int*>(smem + SM::ITEM_OFF);
+    auto read_item = [&](int t) -> Item {
+        const i32x4 x = *reinterpret_cast<const i32x4*>(items + 8 * (t & 3)), y = *reinterpret_cast<const i32x4*>(items + 8 * (t & 3) + 4);
+        Item it;
+        it.n = __builtin_amdgcn_readfirstlane(x[0]); it.hq = __builtin_amdgcn_readfirstlane(x[1]);
+        it.hv = __builtin_amdgcn_readfirstlane(x[2]); it.row_lo = __builtin_amdgcn_readfirstlane(x[3]);
+        it.row_hi = __builtin_amdgcn_readfirstlane(y[0]); it.state = __builtin_amdgcn_readfirstlane(y[1]);
+        it.eslot = __builtin_amdgcn_readfirstlane(y[2]); it.src = __builtin_amdgcn_readfirstlane(y[3]);
+        return it;
+    };
+    auto row_of = [](const Item& it) -> int64_t { return (int64_t)(uint32_t)it.row_lo | ((int64_t)it.row_hi << 32); };
+    constexpr int SAME_CHAIN = -2;
+    // the walk over the workgroup's items, by one wave (wave 1 of the preparation): the present chain and chunk
+    struct Walk { int c, c_end, l, hv, hq, src; };
+    Walk wk;
+    int reserve = 2 * (int)gridDim.x - 1 - (int)blockIdx.x;     // the chain to open next, or
+    bool draw_pending = false;                                  // on its way,
+    int drawn = 0;                                              // in lane 0
+    auto publish = [&](int t, bool live, bool fresh) {          // item t as the walk stands
+        int w[8] = {0, 0, 0, 0, 0, 0, -1, SAME_CHAIN};
+        if (live) {
+            const int64_t row = (int64_t)wk.l * a.T_alloc + plan_word(a.chunk_tok0, wk.c);
+            w[0] = plan_word(a.chunk_len, wk.c);
+            w[1] = wk.hq; w[2] = wk.hv;
+            w[3] = (int)(uint32_t)row; w[4] = (int)(row >> 32);
+            w[5] = wk.l * a.H_v + wk.hv;
+            w[6] = plan_word(a.chunk_emit_slot, wk.c);
+            if (fresh) w[7] = wk.src;
+        }
+        if (lane_ < 8) {
+            int x = w[0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) x = lane_ == i ? w[i] : x;
+            items[8 * (t & 3) + lane_] = x;
+        }
+    };
+    auto open_chain = [&](int chain) -> bool {
+        if (chain >= a.n_chains) return false;
+        const int r = plan_word(a.req_order, chain / units), lh = chain % units;
+        wk.l = lh / a.H_v;
+        wk.hv = lh % a.H_v;
+        wk.hq = wk.hv / (a.H_v / a.H_qk);
+        wk.c = plan_word(a.req_chunk_cu, r);
+        wk.c_end = plan_word(a.req_chunk_cu, r + 1);
+        wk.src = plan_word(a.req_src_slot, r);
+        return true;
+    };
+    bool live = true;
+    auto walk_on = [&](int t) {       // publishes item t, the one after the walk's present one
+        bool fresh = false;
+        if (live) {
+            if (wk.c + 1 < wk.c_end) {
+                ++wk.c;
+            } else {
+                if (draw_pending) reserve = 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn);
+                live = fresh = open_chain(reserve);
+                draw_pending = live;
+                if (live && lane_ == 0) {
+                    int z = 0;
+                    pin(z);     // not a wave-uniform address to the compiler, which would wait for the result at once
+                    drawn = __hip_atomic_fetch_add(a.next_chain + z, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        }
+        publish(t, live, fresh);
+    };
+    // A descriptor over the rows of an item's head in one tensor (no rows when there is no item).
+#define GDN_ROWS(name_, base_, it_, heads_, head_, step_)                                                                       \
+    const __amdgpu_buffer_rsrc_t name_ = __builtin_amdgcn_make_buffer_rsrc(                                                     \
+        const_cast<In*>((base_) + (row_of(it_) * (heads_) + (head_)) * D), 0, (it_).n > 0 ? ((it_).n - 1) * (step_) + D * 2 : 0, 0x00020000)
+
+    // Step t: the recurrence works on item t - 3, the preparation on item t - 2, staging on t - 1, the fetch on item t.
+    if (prep && wave == 1) {
+        if (lane_ < 32) items[lane_] = (lane_ & 7) == 7 ? SAME_CHAIN : (lane_ & 7) == 6 ? -1 : 0;    // none
+        live = open_chain((int)blockIdx.x);
+        publish(0, live, true);
+    }
+    __syncthreads();
+    int t = 0;                       // every wave leaves after the step in which the recurrence worked on the last item
+    int s0 = 0, s1 = 1, s2 = 2;      // K/Q and gate buffers of the three items held in LDS
+    int gdn_step = 0;
+    (void)gdn_step;
+    int p0 = 0;                      // pair tiles read by the recurrence; the preparation writes the other
+
+    if (prep) {
+        Raw8 kraw[ROWS], qraw[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) kraw[r] = qraw[r] = EL::zero_raw();
+        In graw = In();
+        int n1 = 0, n2 = 0;
+        for (;;) {
+            GDN_STAMP_STEP();
+            GDN_STAMP(0, 0);
+            int lane = lane_, tg = tid / PCS, d0 = (tid % PCS) * 8;
+            pin(lane); pin(tg); pin(d0);
+            const int m = lane & 15, g4 = lane >> 4;
+            const Item i3 = read_item(t);
+            char* const Kt2 = smem + SM::ROWS_OFF + s2 * SM::ROWS_BYTES;
+            float* const sm2 = reinterpret_cast<float*>(smem + SM::SM_OFF + s2 * SM::SM_BYTES);
+            const char* const Kt = smem + SM::ROWS_OFF + s1 * SM::ROWS_BYTES;
+            const char* const Qt = Kt + SM::TILE_BYTES;
+            const float* const gS = reinterpret_cast<const float*>(smem + SM::SM_OFF + s1 * SM::SM_BYTES);
+            const float* const bS = gS + C;
+            const float* const gamS = bS + C;
+            const float* const sS = gamS + 2 * C;
+            const float* const rS = sS + C;
+            float* const Tf = reinterpret_cast<float*>(smem + SM::TF_OFF) + wave * 16 * SM::TF_LD;
+            char* const pairs = smem + SM::PAIRS_OFF + (p0 ^ 1) * SM::PAIRS_BYTES;
+            half_t* const tbtg = reinterpret_cast<half_t*>(pairs + SM::TBTG_OFF);
+            half_t* const mimg = reinterpret_cast<half_t*>(pairs + SM::M_OFF);
+            half_t* const pimg = reinterpret_cast<half_t*>(pairs + SM::P_OFF);
+            int row_b[SS];
+#pragma unroll
+            for (int s = 0; s < SS; ++s) row_b[s] = m * RBY + 16 * ((4 * s + g4) ^ swz<D>(m));
+            auto row_frag = [&](const char* tile, int blk, int s) -> half8 {
+                return *reinterpret_cast<const half8*>(tile + row_b[s] + blk * 16 * RBY);
+            };
+            auto stage = [&](char* tile, const Raw8& raw, int r) {     // row ROWS tg + r, widened exactly to fp16
+                const int i = ROWS * tg + r;
+                float x[8];
+                EL::unpack(raw, x);
+                half8 h;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h[e] = (half_t)x[e];
+                *reinterpret_cast<half8*>(tile + i * RBY + (((d0 >> 3) ^ swz<D>(i)) << 4)) = h;
+            };
+            auto step = [&](auto ab_) {
+                constexpr int ab = decltype(ab_)::value, ia = 3 - ab;
+                GDN_ROWS(rk, kg, i3, a.H_qk, i3.hq, qk_step);
+                GDN_ROWS(rq, qg, i3, a.H_qk, i3.hq, qk_step);
+                auto fetch = [&](int r) {
+                    if (r < ROWS) kraw[r < ROWS ? r : 0] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rk, (ROWS * tg + r) * qk_step + d0 * 2, 0, 2));
+                    else qraw[r >= ROWS ? r - ROWS : 0] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rq, (ROWS * tg + r - ROWS) * qk_step + d0 * 2, 0, 2));
+                };
+                // a quarter of the staging of i2, and of the fetch of i3 into the registers that this frees
+                auto place = [&](int p) {
+#pragma unroll
+                    for (int r = p * ROWS / 4; r < (p + 1) * ROWS / 4; ++r) {
+                        stage(Kt2, kraw[r], r);
+                        stage(Kt2 + SM::TILE_BYTES, qraw[r], r);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int r = p * ROWS / 4; r < (p + 1) * ROWS / 4; ++r) { fetch(r); fetch(ROWS + r); }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                place(0); place(1); place(2); place(3);
+                half8 ka[SS], qf[SS];
+#pragma unroll
+                for (int s = 0; s < SS; ++s) {
+                    ka[s] = row_frag(Kt, ab, s);
+                    qf[s] = row_frag(Qt, ia, s);
+                }
+                // diagonal block, gates and betas (see gdn_fused_kernel.h for each of the steps)
+                const f32x4 gi = *reinterpret_cast<const f32x4*>(gS + 16 * ab + 4 * g4);
+                const f32x4 bi = *reinterpret_cast<const f32x4*>(bS + 16 * ab + 4 * g4);
+                const float gj = gS[16 * ab + m], bj = bS[16 * ab + m];
+                if (ab == 0) {
+                    const float la = lane < n2 ? fmaxf(EL::log_(EL::widen(graw)), -88.f) : 0.f;
+                    const float s = wave_running_sum(la);
+                    const int sbits = __builtin_bit_cast(int, s);
+                    const float e0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sbits, 15));
+                    const float e1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sbits, 31));
+                    const float e2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sbits, 47));
+                    const float g_last = wave_last_lane(s);
+                    const float eb = lane < 16 ? e0 : lane < 32 ? e1 : lane < 48 ? e2 : g_last;
+                    sm2[lane] = s;
+                    sm2[2 * C + lane] = EL::exp_(s);
+                    sm2[3 * C + lane] = EL::exp_(g_last - s);
+                    sm2[4 * C + lane] = EL::exp_(fminf(eb - s, 0.f));
+                    sm2[5 * C + lane] = EL::exp_(fminf(s - e0, 0.f));
+                    sm2[6 * C + lane] = EL::exp_(fminf(s - e1, 0.f));
+                    sm2[7 * C + lane] = EL::exp_(fminf(s - e2, 0.f));
+                } else if (ab == 1) {
+                    sm2[C + lane] = lane < n2 ? EL::widen(graw) : 0.f;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (ab < 2) {
+                    if (lane < i3.n)
+                        graw = (reinterpret_cast<const In*>(ab == 0 ? a.gate : a.beta) + (row_of(i3) * a.H_v + i3.hv))[lane * a.H_v];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                f32x4 gr = {0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < SS; ++s) gr = mma32(ka[s], ka[s], gr);
+                f32x4 d, dt, y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = 4 * g4 + e;
+                    float x = bi[e] * EL::exp_(fminf(gi[e] - gj, 0.f)) * gr[e];     // D[i][m]
+                    float xt = bj * EL::exp_(fminf(gj - gi[e], 0.f)) * gr[e];       // D[m][i]
+                    pin(x); pin(xt);       // in every lane: no branch around an exponential
+                    d[e] = m < i ? x : 0.f;
+                    dt[e] = i < m ? xt : 0.f;
+                    y[e] = (i == m ? 1.f : 0.f) - d[e];
+                }
+                // The diagonal inverse (the products of inv16_tiles), between them the other blocks' raw products
+                f32x4 acl[4], acp[4];
+                auto block = [&](int c) {
+                    half8 kc[SS];
+#pragma unroll
+                    for (int s = 0; s < SS; ++s) kc[s] = row_frag(Kt, c, s);
+                    if (c < ab) {
+                        acl[c] = f32x4{0, 0, 0, 0};
+#pragma unroll
+                        for (int s = 0; s < SS; ++s) acl[c] = mma32(ka[s], kc[s], acl[c]);   // rows i in block ab, lanes j in block c
+                    }
+                    if (c <= ia) {
+                        acp[c] = f32x4{0, 0, 0, 0};
+#pragma unroll
+                        for (int s = 0; s < SS; ++s) acp[c] = mma32(kc[s], qf[s], acp[c]);
+                    }
+                };
+                const f32x4 zero = {0, 0, 0, 0};
+                __builtin_amdgcn_sched_barrier(0);
+                const f32x4 p2 = mm16_rr(zero, dt, d), p2t = mm16_rr(zero, d, dt);
+                block(0);
+                __builtin_amdgcn_sched_barrier(0);
+                y = mm16_rr(y, p2t, y);
+                const f32x4 p4 = mm16_rr(zero, p2t, p2), p4t = mm16_rr(zero, p2, p2t);
+                block(1);
+                __builtin_amdgcn_sched_barrier(0);
+                y = mm16_rr(y, p4t, y);
+                const f32x4 p8t = mm16_rr(zero, p4, p4t);
+                if (ab > 2 || ia >= 2) block(2);
+                __builtin_amdgcn_sched_barrier(0);
+                y = mm16_rr(y, p8t, y);
+                if (ia >= 3) block(3);
+                const float gq = gS[16 * ia + m];
+#pragma unroll
+                for (int c = 0; c <= ia; ++c) {
+                    f32x4 p;
+                    if (c < ia) {
+                        const float pr = a.scale * rS[c * C + 16 * ia + m];
+                        const f32x4 sk = *reinterpret_cast<const f32x4*>(sS + 16 * c + 4 * g4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) p[e] = pr * (sk[e] * acp[c][e]);
+                    } else {
+                        const f32x4 gk = *reinterpret_cast<const f32x4*>(gS + 16 * c + 4 * g4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float val = a.scale * EL::exp_(fminf(gq - gk[e], 0.f)) * acp[c][e];
+                            pin(val);
+                            p[e] = (4 * g4 + e <= m) ? val : 0.f;
+                        }
+                    }
+                    *reinterpret_cast<half4*>(pimg + (SM::p_pair(ia, c) * 16 + m) * PLD + 8 * g4 + 4 * (c & 1)) = cvt4(p);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Tf[(4 * g4 + e) * SM::TF_LD + m] = y[e];
+                const f32x4 at = *reinterpret_cast<const f32x4*>(Tf + m * SM::TF_LD + 4 * g4);   // T[m][4 g4 + e]
+                {
+                    const f32x4 gm = *reinterpret_cast<const f32x4*>(gamS + 16 * ab + 4 * g4);
+                    f32x4 tb, tgm;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { tb[e] = at[e] * bi[e]; tgm[e] = -tb[e] * gm[e]; }
+                    *reinterpret_cast<half8*>(tbtg + (ab * 16 + m) * PLD + 8 * g4) = cat8(cvt4(tb), cvt4(tgm));
+                }
+#pragma unroll
+                for (int c = 0; c < ab; ++c) {
+                    const float sj = sS[16 * c + m];
+                    const f32x4 ri = *reinterpret_cast<const f32x4*>(rS + c * C + 16 * ab + 4 * g4);
+                    f32x4 lt;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) lt[e] = (bi[e] * ri[e]) * (sj * acl[c][e]);   // L_ac[4 g4 + e][m]
+                    const f32x4 mt_ = mm16_rr(zero, lt, at);     // (L^T T^T): element e of lane (m, g4) = (T L)[m][4 g4 + e]
+                    f32x4 neg;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) neg[e] = -mt_[e];
+                    *reinterpret_cast<half4*>(mimg + (SM::m_pair(ab, c) * 16 + m) * PLD + 8 * g4 + 4 * (c & 1)) = cvt4(neg);
+                }
+            };
+            // (items that are none are staged and prepared like any other: their rows read as zeros, their results go nowhere)
+            if (wave == 0) step(std::integral_constant<int, 0>());
+            else if (wave == 1) step(std::integral_constant<int, 1>());
+            else if (wave == 2) step(std::integral_constant<int, 2>());
+            else step(std::integral_constant<int, 3>());
+            GDN_STAMP(0, 1);
+            if (wave == 1) walk_on(t + 1);
+            __syncthreads();
+            GDN_STAMP(0, 2);
+            if (t >= 3 && n1 == 0) break;
+            n1 = n2; n2 = i3.n;
+            ++t;
+            const int x = s0; s0 = s1; s1 = s2; s2 = x;
+            p0 ^= 1;
+        }
+    } else {
+        Raw8 vraw[WP];
+        Item i0 = {0, 0, 0, 0, 0, 0, -1, SAME_CHAIN}, i1 = i0;
+#pragma unroll
+        for (int r = 0; r < WP; ++r) vraw[r] = EL::zero_raw();
+        f32x4 accS[MT][NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) accS[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (;;) {
+            GDN_STAMP_STEP();
+            GDN_STAMP(1, 0);
+            int lane = lane_;
+            pin(lane);
+            const int m = lane & 15, g4 = lane >> 4;
+            const Item i2 = read_item(t - 1);
+            const int vrow = lane / WP, vpc = WP * wave + lane % WP;     // row (+ 64 / WP r) and piece of V this lane moves
+
+            const int64_t head_off = (int64_t)i0.state * DV * DK;
+            half8 ud[2][NT];   // diag(dec) U, like uh
+            const char* const Kt = smem + SM::ROWS_OFF + s0 * SM::ROWS_BYTES;
+            const char* const Qt = Kt + SM::TILE_BYTES;
+            const float* const gamS = reinterpret_cast<const float*>(smem + SM::SM_OFF + s0 * SM::SM_BYTES) + 2 * C;
+            const float* const decS = gamS + C;
+            const int trow = 4 * g4 + (m >> 2);
+            {
+                const char* const pairs = smem + SM::PAIRS_OFF + p0 * SM::PAIRS_BYTES;
+                const half_t* const tbtg = reinterpret_cast<const half_t*>(pairs + SM::TBTG_OFF);
+                const half_t* const mimg = reinterpret_cast<const half_t*>(pairs + SM::M_OFF);
+                const half_t* const pimg = reinterpret_cast<const half_t*>(pairs + SM::P_OFF);
+                int row_b[SS];
+#pragma unroll
+                for (int s = 0; s < SS; ++s) row_b[s] = m * RBY + 16 * ((4 * s + g4) ^ swz<D>(m));
+                auto row_frag = [&](const char* tile, int blk, int s) -> half8 {
+                    return *reinterpret_cast<const half8*>(tile + row_b[s] + blk * 16 * RBY);
+                };
+                int tv[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    tv[nt] = trow * RBY + 16 * ((WP * wave + 2 * nt + ((m & 3) >> 1)) ^ swz<D>(trow)) + 8 * (m & 1);   // + tok0 * RBY
+                half8 sf[SS][NT];        // the state as an operand over d_k: step s = state tiles 2 s, 2 s + 1
+#pragma unroll
+                for (int s = 0; s < SS; ++s)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) sf[s][nt] = cat8(cvt4(accS[2 * s][nt]), cvt4(accS[2 * s + 1][nt]));
+                half8 uh[2][NT];
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) uh[p][nt][e] = (half_t)0.f;
+                const int64_t row0 = row_of(i0);
+                constexpr int OB = O_BF16 ? 2 : 4;
+                const int o_step = a.H_v * DV * OB;
+                const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+                    reinterpret_cast<char*>(a.o) + ((row0 * a.H_v + i0.hv) * DV) * OB, 0, i0.n > 0 ? (i0.n - 1) * o_step + DV * OB : 0, 0x00020000);
+                const int o_lane = m * o_step + (WC * wave + 4 * g4) * OB;
+                auto state_products = [&](int ab, f32x4 (&ks)[NT], f32x4 (&ot)[NT]) {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) { ks[nt] = f32x4{0, 0, 0, 0}; ot[nt] = f32x4{0, 0, 0, 0}; }
+#pragma unroll
+                    for (int s = 0; s < SS; ++s) {
+                        const half8 kfr = row_frag(Kt, ab, s);
+                        const half8 qfr = row_frag(Qt, ab, s);
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) {
+                            ks[nt] = mma32(kfr, sf[s][nt], ks[nt]);
+                            ot[nt] = mma32(sf[s][nt], qfr, ot[nt]);
+                        }
+                    }
+                };
+                f32x4 ks_n[NT], ot_n[NT];
+                state_products(0, ks_n, ot_n);
+#pragma unroll
+                for (int ab = 0; ab < 4; ++ab) {
+                    const int row = 16 * ab + m;
+                    f32x4 ks[NT], ot[NT];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) { ks[nt] = ks_n[nt]; ot[nt] = ot_n[nt]; }
+                    if (ab < 3) state_products(ab + 1, ks_n, ot_n);
+                    const half8 tf = *reinterpret_cast<const half8*>(tbtg + (ab * 16 + m) * PLD + 8 * g4);
+                    f32x4 u[NT];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const half4 vt = tr_read(Vt + tv[nt] + ab * 16 * RBY);
+                        const f32x4 zero = {0, 0, 0, 0};
+                        u[nt] = mma32(tf, cat8(vt, cvt4(ks[nt])), zero);
+                    }
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+                        if (2 * p < ab) {
+                            const half8 mf = *reinterpret_cast<const half8*>(mimg + (SM::m_pair(ab, 2 * p) * 16 + m) * PLD + 8 * g4);
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) u[nt] = mma32(mf, uh[p][nt], u[nt]);
+                        }
+                    const f32x4 dc = *reinterpret_cast<const f32x4*>(decS + 16 * ab + 4 * g4);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const half4 h = cvt4(u[nt]);
+                        f32x4 x;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[e] = u[nt][e] * dc[e];
+                        const half4 hd = cvt4(x);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            uh[ab >> 1][nt][4 * (ab & 1) + e] = h[e];
+                            ud[ab >> 1][nt][4 * (ab & 1) + e] = hd[e];
+                        }
+                    }
+                    const float gm = gamS[row] * a.scale;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) ot[nt][e] *= gm;
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+                        if (2 * p <= ab) {
+                            const half8 pf = *reinterpret_cast<const half8*>(pimg + (SM::p_pair(ab, 2 * p) * 16 + m) * PLD + 8 * g4);
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) ot[nt] = mma32(uh[p][nt], pf, ot[nt]);
+                        }
+                    if (O_BF16) {
+                        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+                            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, __builtin_convertvector(ot[nt], bf16x4)), ro,
+                                                                  o_lane + ab * 16 * o_step + 32 * nt, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ot[nt]), ro, o_lane + ab * 16 * o_step + 64 * nt, 0, 0);
+                    }
+                }
+            }
+            GDN_STAMP(1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            // ---- V of i1 into the wave's own columns of the tile, V of i2 from memory
+#pragma unroll
+            for (int r = 0; r < WP; ++r) {
+                const int i = (64 / WP) * r + vrow;
+                float vv[8];
+                EL::unpack(vraw[r], vv);
+                half8 vh;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) vh[e] = (half_t)vv[e];
+                *reinterpret_cast<half8*>(Vt + i * RBY + ((vpc ^ swz<D>(i)) << 4)) = vh;
+            }
+            {
+                GDN_ROWS(rv, vg, i2, a.H_v, i2.hv, v_step);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < WP; ++r)
+                    vraw[r] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rv, ((64 / WP) * r + vrow) * v_step + vpc * 16, 0, 2));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            GDN_STAMP(1, 2);
+            {     // state update
+                int tr_b[SS];
+#pragma unroll
+                for (int s = 0; s < SS; ++s) tr_b[s] = trow * RBY + 16 * ((4 * s + (m & 3)) ^ swz<D>(trow));   // + tok0 * RBY + 8 h
+                const float gam_last = gamS[C - 1];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const char* kt = Kt + tr_b[mt >> 1] + 8 * (mt & 1);
+                    const half8 k0 = cat8(tr_read(kt), tr_read(kt + 16 * RBY));
+                    const half8 k1 = cat8(tr_read(kt + 32 * RBY), tr_read(kt + 48 * RBY));
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) accS[mt][nt][e] *= gam_last;
+                        accS[mt][nt] = mma32(k0, ud[0][nt], accS[mt][nt]);
+                        accS[mt][nt] = mma32(k1, ud[1][nt], accS[mt][nt]);
+                    }
+                }
+            }
+            GDN_STAMP(1, 3);
+            if (i0.eslot >= 0) {     // checkpoint emission: exact state after the last token of this chunk
+                {
+                    float* dst = a.state_dst + i0.eslot * a.dst_slot_stride + head_off;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            *reinterpret_cast<f32x4*>(dst + (WC * wave + 16 * nt + m) * DK + 32 * (mt >> 1) + 8 * g4 + 4 * (mt & 1)) = accS[mt][nt];
+                }
+            }
+            GDN_STAMP(1, 4);
+            if (i1.src != SAME_CHAIN) {     // a new chain: its start state, from the pool slot or zero
+                const int slot = i1.src;
+                if (slot >= 0) {
+                    const float* src = a.state_src + slot * a.src_slot_stride + (int64_t)i1.state * DV * DK;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            accS[mt][nt] = *reinterpret_cast<const f32x4*>(src + (WC * wave + 16 * nt + m) * DK + 32 * (mt >> 1) + 8 * g4 + 4 * (mt & 1));
+                    wait_vmcnt<0>();     // here, so that no other path has to wait for loads at the top of a step
+                } else {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) accS[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            GDN_STAMP(1, 5);
+            __syncthreads();
+            GDN_STAMP(1, 6);
+            if (t >= 3 && i1.n == 0) break;
+            i0 = i1; i1 = i2;
+            ++t;
+            const int x = s0; s0 = s1; s1 = s2; s2 = x;
+            p0 ^= 1;
+        }
+    }
+}
+
+#undef GDN_ROWS
+
+}  // namespace gdn

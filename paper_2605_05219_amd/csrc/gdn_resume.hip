@@ -13,6 +13,7 @@
 #include "gdn_prep_kernel.h"
 #include "gdn_decode_kernel.h"
 #include "gdn_fused_kernel.h"
+#include "gdn_pipe_kernel.h"
 #include "gdn_probe_kernel.h"
 #include "gdn_recur_kernel.h"
 #include "gdn_resume.h"
@@ -434,32 +435,52 @@ hipError_t launch_fused_t(const FusedArgs& fa, int per_cu, hipStream_t stream) {
                        lds, stream, fa);
     return hipGetLastError();
 }
+// Pipelined fused kernel: see gdn_pipe_kernel.h.  Its LDS leaves room for one workgroup per compute unit.
+template <bool O_BF16, int D>
+hipError_t launch_pipe_t(const FusedArgs& fa, hipStream_t stream) {
+    typedef PipeSmem<D> SM;
+    static std::once_flag once;
+    static hipError_t once_err = hipSuccess;
+    static int cus = 1;
+    std::call_once(once, [] {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gdn_pipe_kernel<O_BF16, D>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, CU_LDS_BYTES);
+        int dev = 0, n_cu = 0;
+        if (e == hipSuccess) e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+        once_err = e;
+        if (e == hipSuccess) cus = std::max(1, n_cu);
+    });
+    if (once_err != hipSuccess) return once_err;
+    hipLaunchKernelGGL((gdn_pipe_kernel<O_BF16, D>), dim3((unsigned)std::min<int64_t>(fa.n_chains, cus)), dim3(512), SM::BYTES, stream, fa);
+    return hipGetLastError();
+}
+std::atomic<int32_t> g_forced_per_cu{-1};
 // gv = value heads per workgroup (1, or 2 when the heads of a pair share a query/key head); fa.n_chains counts groups of gv heads.
-hipError_t launch_fused(const FusedArgs& fa, int d, int gv, int per_cu, hipStream_t stream) {
+// piped: single heads on the pipelined kernel.  The fused kernel puts as many workgroups on a compute unit as fit;
+// gdn_tune_fused_per_cu forces a number (results are the same for any).
+hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, hipStream_t stream) {
+    const int per_cu = std::max(0, (int)g_forced_per_cu.load());
     if (gv == 2) {
         if (d == 64) return fa.o_bf16 ? launch_fused_t<true, 64, 2>(fa, per_cu, stream) : launch_fused_t<false, 64, 2>(fa, per_cu, stream);
         return fa.o_bf16 ? launch_fused_t<true, 128, 2>(fa, per_cu, stream) : launch_fused_t<false, 128, 2>(fa, per_cu, stream);
     }
-    if (d == 64) return fa.o_bf16 ? launch_fused_t<true, 64, 1>(fa, per_cu, stream) : launch_fused_t<false, 64, 1>(fa, per_cu, stream);
-    return fa.o_bf16 ? launch_fused_t<true, 128, 1>(fa, per_cu, stream) : launch_fused_t<false, 128, 1>(fa, per_cu, stream);
+    if (d == 64) {
+        if (piped) return fa.o_bf16 ? launch_pipe_t<true, 64>(fa, stream) : launch_pipe_t<false, 64>(fa, stream);
+        return fa.o_bf16 ? launch_fused_t<true, 64, 1>(fa, per_cu, stream) : launch_fused_t<false, 64, 1>(fa, per_cu, stream);
+    }
+    return fa.o_bf16 ? launch_pipe_t<true, 128>(fa, stream) : launch_pipe_t<false, 128>(fa, stream);
 }
 
-// How many fused workgroups share a compute unit (0: as many as fit).  A chunk of a chain takes less time when its
-// workgroup has the compute unit to itself (measured at d = 128: 5.5 us against 6.8 us with two), so a call bound by its
-// longest chain rather than by its volume runs better on fewer, faster workgroups.  Estimates: one per compute unit
-// max(longest chain x 5.5 us, units x 0.0257 us) (all 256 busy, a chunk takes 6.6 us), two max(longest chain x 6.8 us,
-// units x 0.0183 us).  Measured, one against two: 1024 chains of up to 66 chunks, 14.8 k units 0.431 against 0.449 ms; 384
-// chains of up to 128 chunks, 28 k units 0.72 against 0.79; 512 chains, 39 k units 0.92 against 0.87; 1024 chains of up to 345
-// chunks, 99.5 k units 2.56 against 2.31.  gdn_tune_fused_per_cu forces the number.
-std::atomic<int32_t> g_forced_per_cu{-1};
-inline int fused_wgs_per_cu(const gdn_shape& s, int gv, int64_t total_units, int32_t longest_chain_chunks) {
-    const int forced = g_forced_per_cu.load();
-    if (forced >= 1) return forced;
-    if (s.d_k != 128 || gv != 1) return 0;
-    const double cus = (double)chip_cus(), units = (double)total_units, longest = (double)longest_chain_chunks;   // (figures from 256 compute units)
-    const double t1 = std::max(longest * 5.5, units * 0.0257 * 256.0 / cus);
-    const double t2 = std::max(longest * 6.8, units * 0.0183 * 256.0 / cus);
-    return t1 < t2 ? 1 : 0;
+// Single heads at d = 64: three fused workgroups to a compute unit get more chunks done in a time than the pipelined kernel's one
+// workgroup, which takes a chain through twice as fast.  Measured, fused against pipelined (us): units / longest chain = 95
+// (12.3 k units, longest 128 chunks) 485 / 304, 267 (32.8 k, 123) 554 / 406, 549 (67.5 k, 123) 739 / 719, 870 (110 k, 126) 1112 / 1183, 4096 (16.4 k, 4)
+// 208 / 230.  gdn_tune_fused_per_cu, which has a meaning for the fused kernel only, forces that one.
+inline bool fused_piped(const gdn_shape& s, int gv, int64_t total_units, int32_t longest_chain_chunks) {
+    if (gv != 1) return false;
+    if (s.d_k == 128) return true;
+    if (g_forced_per_cu.load() >= 1) return false;
+    return total_units * 256 < (int64_t)700 * longest_chain_chunks * chip_cus();
 }
 
 // Grouped value heads (H_v a multiple of H_qk): two value heads of one query/key head can share a workgroup of eight waves,
@@ -472,40 +493,52 @@ inline int fused_wgs_per_cu(const gdn_shape& s, int gv, int64_t total_units, int
 // d = 64 a pair's 81 KB of LDS leave a compute unit one workgroup where three single-head ones fit, and pairs never won
 // (9.47 against 9.56 ms on 32768 chains, 1.39 against 1.17 on 4096): forced only.  (Since then the one-head kernel has gained
 // about 10 % and the pair kernel 5 % from changes to their loads and to the order of the chains: on the first of these calls
-// 16.7 against 17.4 ms; the threshold was raised accordingly, pairs from three times the longest chain's time in volume.)  gdn_tune_fused_pair forces the choice.
+// 16.7 against 17.4 ms.  Against the pipelined kernel, which single heads run now, single / pair in us, volume over longest chain at 0.0186 us a unit and
+// 4.6 a chunk: ratio 1.7 (53 k units, longest 126) 1025 / 1093, 1.65 (51 k, 126) 1001 / 1071, 3.4 (107 k, 126) 1978 / 1869, 3.5 (110 k, 126) 2043 / 1952,
+// 4.0 (63 k, 63) 1194 / 1142, 8.3 (16 k, 8) 353 / 338, 16 (66 k, 16) 1284 / 1220: pairs from a ratio of three on.)  gdn_tune_fused_pair forces the choice.
 std::atomic<int32_t> g_forced_pair{-1};
 inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t longest_chain_chunks) {
     if (s.H_qk <= 0 || s.H_v % s.H_qk != 0 || (s.H_v / s.H_qk) % 2 != 0) return 1;
     const int forced = g_forced_pair.load();
     if (forced >= 0) return forced != 0 ? 2 : 1;
     if (s.d_k != 128) return 1;
-    return 0.0197 * (double)total_units >= 3.0 * 8.2 * (double)longest_chain_chunks ? 2 : 1;
+    return 0.0186 * (double)total_units >= 3.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
 }
 
-// The fused kernel serialises a chain's preparation along the chain; it pays when chains are
-// plentiful and the longest chain does not outlast the whole two-kernel run.  Estimates from
-// figures measured on MI355X (bf16; one call of 4 to 64 requests of up to 8192 tokens, 16 heads,
-// and the large configurations).  d = 128: fused, per chunk of one chain 5.5 us with one workgroup
-// per compute unit (up to 256 chains) and 6.8 us with two, per (chunk, chain) unit of a large call
-// 0.0183 us; two-kernel path 0.056 us per unit plus about 0.15 ms.  Measured, fused against
-// two-kernel: 64 chains 0.60 against 0.40 ms, 96 chains 0.61 against 0.52, 128 chains 0.62 against
-// 0.63, 160 chains 0.70 against 0.85, 256 chains 0.70 against 1.14, 512 chains 0.87 against 2.04,
-// 1024 chains 1.49 against 4.17.  d = 64: 3.4 / 4.4 us per chunk, 0.0094 us per unit; two-kernel
-// path 0.036 us per unit plus about 0.1 ms (requests of up to 4096 tokens: 96 chains 0.21 against
-// 0.17 ms, 128 chains 0.21 against 0.22, 256 chains 0.25 against 0.39, 1024 chains 0.45 against
-// 1.48).  gdn_tune_fused forces the choice.
+// The fused kernels serialise a chain's preparation along the chain; they pay when chains are plentiful and the longest chain
+// does not outlast the two-kernel run.  Where the latency variant of the two-kernel path has a workgroup for every 32
+// columns of every chain (up to 64 chains at d = 128) it wins or ties (64 chains of 128 chunks 434 against 451 us, of 32 chunks 110
+// against 127).  Beyond, estimates in us, fitted to 65 to 256 chains, even and ragged, of 2 to 128 chunks.  Pipelined kernel:
+// 20 + max(0.0186 per unit, 3.35 to 4.6 per chunk of the longest chain, by how many compute units are busy on average, since
+// the clock goes down with them); two-kernel path at d = 128: 25 + 0.0245 per unit + 2.35 per chunk.  Measured, pipelined against two-kernel: 96 chains
+// of 128 chunks 455 / 648, of 32 chunks 128 / 186, of 2 chunks 26 / 29, ragged up to 86 chunks 313 / 346; 80 ragged chains 312 / 296; 128 ragged
+// chains 316 / 372; 256 chains of 128 chunks 618 / 1679.  d = 64: pipelined 13 + max(0.0107 per unit, 2.3 to 2.8 per chunk), two-kernel 15 + 0.0523 per unit for 49 to 64
+// chains (whose recurrence shares its launch with the preparation) and 15 + 0.0234 per unit + 0.74 per chunk beyond: 64 chains of 128 chunks 305 / 426,
+// of 8 chunks 30 / 31, 64 ragged chains 204 / 164, 96 chains of 128 chunks 304 / 393.  gdn_tune_fused forces the choice.
+//
+// Start states in host memory: the two-kernel path fetches them beside its first preparation launch, the fused kernels wait for a copy,
+// so such calls keep the line they had with the fused kernel alone (from 128 chains on, longest chain at 5.5 / 6.8 us a chunk, d = 64 3.4 / 4.4).
 std::atomic<int32_t> g_forced_fused{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
-inline bool choose_fused(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks) {
+inline bool choose_fused(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks, bool src_on_host) {
     if (!fused_applies(s)) return false;
     const int forced = g_forced_fused.load();
     if (forced >= 0) return forced != 0;
-    if (n_chains < 128) return false;
     const bool big = s.d_k == 128;
-    const double per_chunk = n_chains <= chip_cus() ? (big ? 5.5 : 3.4) : (big ? 6.8 : 4.4);   // us: one or two workgroups per compute unit
-    const double t_two = (big ? 0.056 : 0.036) * (double)total_units + (big ? 150.0 : 100.0);
-    const double t_fused = std::max((big ? 0.0183 : 0.0094) * (double)total_units, per_chunk * (double)longest_chain_chunks);
-    return t_fused < t_two;
+    const double units = (double)total_units, longest = (double)longest_chain_chunks, cus = (double)chip_cus();
+    if (src_on_host) {
+        if (n_chains < 128) return false;
+        const double per_chunk = n_chains <= chip_cus() ? (big ? 5.5 : 3.4) : (big ? 6.8 : 4.4);
+        return std::max((big ? 0.0183 : 0.0094) * units, per_chunk * longest) < (big ? 0.056 : 0.036) * units + (big ? 150.0 : 100.0);
+    }
+    if (n_chains * 16 <= chip_cus() * (big ? 4 : 3)) return false;
+    const double busy = units / std::max(longest, 1.0) / cus;          // mean share of the compute units with a chain
+    const double slow = std::min(1.0, std::max(0.0, 2.0 * busy - 1.0));
+    const double per_chunk = big ? 3.35 + 1.25 * slow : 2.3 + 0.5 * slow;
+    const double t_pipe = (big ? 20.0 : 13.0) + std::max((big ? 0.0186 : 0.0107) * units * 256.0 / cus, per_chunk * longest);
+    const double t_two = big ? 25.0 + 0.0245 * units + 2.35 * longest
+                             : n_chains * 4 <= chip_cus() ? 15.0 + 0.0523 * units : 15.0 + 0.0234 * units + 0.74 * longest;
+    return t_pipe < t_two;
 }
 
 // Which recurrence variant a call gets: 1 = latency variant (few chains), else the number of
@@ -662,11 +695,11 @@ extern "C" {
 int32_t gdn_version(void) { return 100; }
 
 #ifdef GDN_PHASE_STAMPS
-// Profiling build only: the cycle stamps the fused kernel left (64 workgroups x 4 waves x 16 stamps), after a device
+// Profiling build only: the cycle stamps the fused kernel left (64 workgroups x 8 waves x 16 stamps), after a device
 // synchronisation.  Not declared in the public header: the product library does not export it.
 extern "C" int32_t gdn_phase_stamps(unsigned long long* out) {
     hipError_t e = hipDeviceSynchronize();
-    if (e == hipSuccess) e = hipMemcpyFromSymbol(out, HIP_SYMBOL(gdn::g_phase_ts), sizeof(unsigned long long) * 64 * 4 * 16);
+    if (e == hipSuccess) e = hipMemcpyFromSymbol(out, HIP_SYMBOL(gdn::g_pipe_ts), sizeof(unsigned long long) * 64 * 8 * 16);
     return e == hipSuccess ? GDN_OK : GDN_ERR_HIP - (int32_t)e;
 }
 #endif
@@ -941,7 +974,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     if (src_on_host)
         for (int32_t r = 0; r < n_req; ++r) n_staged += src_slot[r] >= 0;
     const int64_t staged_bytes = src_on_host ? (int64_t)n_staged * slot_elems * (int64_t)sizeof(float) : 0;
-    bool use_fused = choose_fused(s, (int64_t)n_req * s.L * s.H_v, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req);
+    bool use_fused = choose_fused(s, (int64_t)n_req * s.L * s.H_v, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req, src_on_host);
     if (!use_fused && fused_applies(s) && g_forced_fused.load() != 0 &&
         workspace_bytes < align_up(wl.total, 256) + staged_bytes)
         use_fused = true;
@@ -1083,8 +1116,8 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         fa.scale = s.scale;
         fa.o_bf16 = s.o_dtype == GDN_BF16;
         ProfChain prof(stream);
-        const int per_cu = fused_wgs_per_cu(s, gv, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req);
-        const hipError_t e = launch_fused(fa, s.d_k, gv, per_cu, stream);
+        const bool piped = fused_piped(s, gv, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req);
+        const hipError_t e = launch_fused(fa, s.d_k, gv, piped, stream);
         if (e != hipSuccess) return hip_err(e);
         prof.mark(1);
         std::lock_guard<std::mutex> lock(g_prof.mu);

@@ -919,6 +919,69 @@ def test_fused_chains_drawn_from_the_counter_match_the_oracle_for_any_workgroup_
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d,o_dtype", [(128, "f32"), (128, "bf16"), (64, "f32"), (64, "bf16")])
+def test_pipelined_kernel_hands_short_chains_over(d, o_dtype):
+    """More chains than twice the compute units, most of one or two chunks: the pipeline holds chunks of up to four chains at once,
+    with and without a start state, chunks that end on 1, 15, 16, 17, 63 and 64 tokens, emissions in neighbouring steps and
+    the last chains drawn from the counter.  Against the oracle; d = 64 also bit for bit against the fused kernel
+    (gdn_tune_fused_per_cu forces it), which does the same arithmetic."""
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(7100 + d)
+    L, H = 1, 16
+    lens = [300, 0] + [int(x) for x in rng.choice([1, 15, 16, 17, 63, 64, 65, 79, 128], 34)]
+    starts = [int(x) for x in rng.choice([0, 64, 100], len(lens))]
+    nxt, emits, eslots = 3, [], []
+    for s0, ln in zip(starts, lens):
+        e = sorted(set(int(x) for x in rng.integers(s0 + 1, s0 + ln + 1, 2)) | {s0 + ln}) if ln > 0 and rng.random() < 0.7 else []
+        emits.append(e)
+        eslots.append(list(range(nxt, nxt + len(e))))
+        nxt += len(e)
+    per_req = [wl.token_streams(rng, L, ln, H, H, d, d, "bf16") for ln in lens]
+    src = [-1 if s0 == 0 else int(rng.integers(0, 3)) for s0 in starts]
+    call = wl.pack_call(L, H, H, d, d, "bf16", per_req, starts, src, emits, eslots, nxt + 1)
+    pool = rng.standard_normal((nxt + 1,) + call.slot_shape).astype(np.float32) * 0.1
+    prev = B.gdn_tune_fused(1)
+    prev_n = B.gdn_tune_fused_per_cu(-1)
+    try:
+        check_call(call, pool, TOL["bf16"], o_dtype=o_dtype)
+        if o_dtype == "f32":
+            o1, p1 = run_call_gpu(call, pool)
+            B.gdn_tune_fused_per_cu(8)
+            o2, p2 = run_call_gpu(call, pool)
+            assert np.array_equal(o1.view(np.uint32), o2.view(np.uint32))
+            assert np.array_equal(p1.view(np.uint32), p2.view(np.uint32))
+    finally:
+        B.gdn_tune_fused(prev)
+        B.gdn_tune_fused_per_cu(prev_n)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,H,n_req,tokens,fused", [(128, 16, 4, 512, 0), (128, 13, 5, 512, 1), (128, 16, 5, 128, 1), (128, 16, 7, 700, 1),
+                                                    (64, 16, 3, 512, 0), (64, 7, 7, 1000, 1), (64, 16, 6, 1500, 1)])
+def test_automatic_choice_between_the_fused_and_the_two_kernel_path(d, H, n_req, tokens, fused):
+    """Either side of the smallest numbers of chains that run fused (65 at d = 128, 49 at 64, even requests): the automatic choice is
+    bit for bit the forced one, and meets the oracle."""
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(d + H * n_req)
+    lens = [tokens - int(x) for x in rng.integers(0, 30, n_req)]
+    per_req = [wl.token_streams(rng, 1, ln, H, H, d, d, "bf16") for ln in lens]
+    call = wl.pack_call(1, H, H, d, d, "bf16", per_req, [64] * n_req, [0] * n_req, [[64 + ln] for ln in lens], [[1 + r] for r in range(n_req)],
+                        n_req + 1)
+    pool = rng.standard_normal((n_req + 1,) + call.slot_shape).astype(np.float32) * 0.1
+    check_call(call, pool, TOL["bf16"])
+    o1, p1 = run_call_gpu(call, pool)
+    same = []
+    for mode in (0, 1):
+        prev = B.gdn_tune_fused(mode)
+        try:
+            o2, p2 = run_call_gpu(call, pool)
+        finally:
+            B.gdn_tune_fused(prev)
+        same.append(np.array_equal(o1.view(np.uint32), o2.view(np.uint32)) and np.array_equal(p1.view(np.uint32), p2.view(np.uint32)))
+    assert same == [fused == 0, fused == 1]
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("fused", [0, 1])
 def test_extreme_gates(fused, d):
