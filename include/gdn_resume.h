@@ -324,6 +324,15 @@ int32_t gdn_tune_slab_rounds(int32_t rounds);
 int32_t gdn_tune_fused(int32_t mode);
 
 /*
+ * Tuning knob (not a step of the method).  Calls with bf16 inputs, d_k = d_v = 128 or 64 and fewer chains than keep the
+ * device busy can run as two launches, the operand blocks of all chunks and then the recurrence with 32 or 64
+ * columns of d_v to a workgroup (32 at d = 64).  columns 32 or 64 forces that form wherever the workspace holds the blocks
+ * (gdn_tune_fused >= 0 goes before it), 0 forbids it, < 0 restores the automatic choice.  Outputs are bitwise those of the
+ * fused kernel.  Returns the previous setting (-1 = automatic).
+ */
+int32_t gdn_tune_split(int32_t columns);
+
+/*
  * Tuning knob (not a step of the method).  With grouped value heads (H_v / H_qk even) the fused
  * kernel can give two value heads of one query/key head a workgroup of eight waves that reads
  * and stages that head's q and k rows once for both.  mode 1 forces pairs wherever the shape

@@ -57,6 +57,8 @@ def lib():
         L.gdn_tune_slab_rounds.argtypes = [_i32]
         L.gdn_tune_fused.restype = _i32
         L.gdn_tune_fused.argtypes = [_i32]
+        L.gdn_tune_split.restype = _i32
+        L.gdn_tune_split.argtypes = [_i32]
         L.gdn_tune_fused_pair.restype = _i32
         L.gdn_tune_fused_pair.argtypes = [_i32]
         L.gdn_tune_fused_per_cu.restype = _i32
@@ -102,7 +104,7 @@ def lib():
     return _lib
 
 
-EXPORTS = ["gdn_version", "gdn_tune_slab_rounds", "gdn_tune_fused", "gdn_tune_fused_pair", "gdn_tune_fused_per_cu", "gdn_profile_enable", "gdn_profile_collect", "gdn_probe_ceilings", "gdn_deepest_ckpt", "gdn_plan_chunks", "gdn_workspace_bytes",
+EXPORTS = ["gdn_version", "gdn_tune_slab_rounds", "gdn_tune_fused", "gdn_tune_split", "gdn_tune_fused_pair", "gdn_tune_fused_per_cu", "gdn_profile_enable", "gdn_profile_collect", "gdn_probe_ceilings", "gdn_deepest_ckpt", "gdn_plan_chunks", "gdn_workspace_bytes",
            "gdn_workspace_bytes_fused",
            "ckpt_gather", "ckpt_scatter", "gdn_resume_prefill", "gdn_decode_step", "ckpt_fetch_host", "ckpt_spill_host",
            "gdn_workspace_bytes_host", "gdn_resume_prefill_host", "gdn_resume_prefill_static", "gdn_static_plan_capacity"]
@@ -150,6 +152,12 @@ def gdn_tune_slab_rounds(rounds: int) -> int:
 def gdn_tune_fused(mode: int) -> int:
     """1: always the fused kernel where it applies, 0: never, < 0: automatic; returns the previous setting."""
     return int(lib().gdn_tune_fused(int(mode)))
+
+
+def gdn_tune_split(columns: int) -> int:
+    """Forces calls of few chains onto the split launches with that many columns to a workgroup (32, 64), forbids them (0) or restores the
+    automatic choice (-1); returns the previous setting."""
+    return int(lib().gdn_tune_split(int(columns)))
 
 
 def gdn_tune_fused_pair(mode: int) -> int:

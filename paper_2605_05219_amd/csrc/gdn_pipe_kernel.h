@@ -33,7 +33,7 @@
 // LDS (PipeSmem<D>: 158 KB at D = 128, 97 KB at D = 64: one workgroup per compute unit): tiles, swizzle and pair tiles as in the fused kernel.
 #pragma once
 #include <type_traits>
-#include "gdn_fused_kernel.h"
+#include "gdn_chunk_ops.h"
 
 namespace gdn {
 
@@ -56,23 +56,15 @@ template <int D_>
 struct PipeSmem {
     static constexpr int C = 64, D = D_;
     static constexpr int TILE_BYTES = C * D * 2;             // one of K, Q, V
-    static constexpr int PAIR_LD = 40, TF_LD = 20;           // halfs / floats per row
-    static constexpr int PAIR_BYTES = 16 * PAIR_LD * 2;      // one 16 x (2 x 16) fp16 pair tile
     static constexpr int ROWS_OFF = 0, ROWS_BYTES = 2 * TILE_BYTES;      // [K | Q] of a chunk, three in turn
     static constexpr int V_OFF = ROWS_OFF + 3 * ROWS_BYTES;
     static constexpr int PAIRS_OFF = V_OFF + TILE_BYTES;                 // the pair tiles of a chunk, two in turn
-    static constexpr int TBTG_OFF = 0;
-    static constexpr int M_OFF = TBTG_OFF + 4 * PAIR_BYTES;
-    static constexpr int P_OFF = M_OFF + 4 * PAIR_BYTES;
-    static constexpr int PAIRS_BYTES = P_OFF + 6 * PAIR_BYTES;
-    static constexpr int TF_OFF = PAIRS_OFF + 2 * PAIRS_BYTES;
-    static constexpr int SM_OFF = TF_OFF + 4 * 16 * TF_LD * 4;           // the gate vectors of a chunk, three in turn
-    static constexpr int SM_BYTES = 8 * C * 4;                           // g, b, gam, dec, s, 3 x r
-    static constexpr int ITEM_OFF = SM_OFF + 3 * SM_BYTES;               // four items in turn, eight words each
+    static constexpr int TF_OFF = PAIRS_OFF + 2 * PairTiles::BYTES;       // fp32 [16][20] per preparation wave
+    static constexpr int TF_FLOATS = 16 * 20;
+    static constexpr int GATES_OFF = TF_OFF + 4 * TF_FLOATS * 4;         // the gate vectors of a chunk, three in turn
+    static constexpr int ITEM_OFF = GATES_OFF + 3 * GateVecs::BYTES;     // four items in turn, eight words each
     static constexpr int BYTES = ITEM_OFF + 4 * 32;
     static_assert(BYTES <= 160 * 1024, "a compute unit's LDS");
-    static constexpr __host__ __device__ int m_pair(int a, int c) { return (a == 1 ? 0 : a == 2 ? 1 : 2) + (c >> 1); }
-    static constexpr __host__ __device__ int p_pair(int a, int c) { return (a == 0 ? 0 : a == 1 ? 1 : a == 2 ? 2 : 4) + (c >> 1); }
 };
 
 template <bool O_BF16, int D>
@@ -82,11 +74,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     typedef EL::Raw8 Raw8;
     typedef PipeSmem<D> SM;
     typedef int i32x4 __attribute__((ext_vector_type(4)));
-    constexpr int C = 64, DK = D, DV = D, PLD = SM::PAIR_LD;
+    constexpr int DK = D, DV = D;
     constexpr int NT = D / 64;        // 16-column tiles of the state per wave (a wave owns D / 4 columns of d_v)
-    constexpr int SS = D / 32;        // steps of 32 over d_k (one 16-byte piece per lane and step)
     constexpr int MT = D / 16;        // 16-wide tiles over d_k
-    constexpr int RBY = 2 * D;        // bytes of a K, Q or V tile row
     constexpr int PCS = D / 8;        // 16-byte pieces per row
     constexpr int ROWS = D / 32;      // rows of K and of Q a preparation thread stages (256 threads, 64 rows of PCS pieces)
     constexpr int WC = D / 4;         // d_v columns per recurrence wave
@@ -105,7 +95,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     const In* const vg = reinterpret_cast<const In*>(a.v);
     const int qk_step = a.H_qk * DK * 2, v_step = a.H_v * DV * 2;      // bytes from token to token
 
-    for (int i = threadIdx.x; i < 2 * SM::PAIRS_BYTES / 16; i += 512)
+    for (int i = threadIdx.x; i < 2 * PairTiles::BYTES / 16; i += 512)
         reinterpret_cast<u32x4*>(smem + SM::PAIRS_OFF)[i] = u32x4{0u, 0u, 0u, 0u};
 
     // What a wave needs to know of an item (a chunk of a chain): eight words, in LDS.  n = 0: none; src: the pool slot of a new
@@ -206,39 +196,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
             GDN_STAMP(0, 0);
             int lane = lane_, tg = tid / PCS, d0 = (tid % PCS) * 8;
             pin(lane); pin(tg); pin(d0);
-            const int m = lane & 15, g4 = lane >> 4;
             const Item i3 = read_item(t);
             char* const Kt2 = smem + SM::ROWS_OFF + s2 * SM::ROWS_BYTES;
-            float* const sm2 = reinterpret_cast<float*>(smem + SM::SM_OFF + s2 * SM::SM_BYTES);
+            float* const gates2 = reinterpret_cast<float*>(smem + SM::GATES_OFF + s2 * GateVecs::BYTES);
             const char* const Kt = smem + SM::ROWS_OFF + s1 * SM::ROWS_BYTES;
-            const char* const Qt = Kt + SM::TILE_BYTES;
-            const float* const gS = reinterpret_cast<const float*>(smem + SM::SM_OFF + s1 * SM::SM_BYTES);
-            const float* const bS = gS + C;
-            const float* const gamS = bS + C;
-            const float* const sS = gamS + 2 * C;
-            const float* const rS = sS + C;
-            float* const Tf = reinterpret_cast<float*>(smem + SM::TF_OFF) + wave * 16 * SM::TF_LD;
-            char* const pairs = smem + SM::PAIRS_OFF + (p0 ^ 1) * SM::PAIRS_BYTES;
-            half_t* const tbtg = reinterpret_cast<half_t*>(pairs + SM::TBTG_OFF);
-            half_t* const mimg = reinterpret_cast<half_t*>(pairs + SM::M_OFF);
-            half_t* const pimg = reinterpret_cast<half_t*>(pairs + SM::P_OFF);
-            int row_b[SS];
-#pragma unroll
-            for (int s = 0; s < SS; ++s) row_b[s] = m * RBY + 16 * ((4 * s + g4) ^ swz<D>(m));
-            auto row_frag = [&](const char* tile, int blk, int s) -> half8 {
-                return *reinterpret_cast<const half8*>(tile + row_b[s] + blk * 16 * RBY);
-            };
-            auto stage = [&](char* tile, const Raw8& raw, int r) {     // row ROWS tg + r, widened exactly to fp16
-                const int i = ROWS * tg + r;
-                float x[8];
-                EL::unpack(raw, x);
-                half8 h;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) h[e] = (half_t)x[e];
-                *reinterpret_cast<half8*>(tile + i * RBY + (((d0 >> 3) ^ swz<D>(i)) << 4)) = h;
-            };
+            const float* const gates = reinterpret_cast<const float*>(smem + SM::GATES_OFF + s1 * GateVecs::BYTES);
+            float* const Tf = reinterpret_cast<float*>(smem + SM::TF_OFF) + wave * SM::TF_FLOATS;
+            char* const pairs = smem + SM::PAIRS_OFF + (p0 ^ 1) * PairTiles::BYTES;
             auto step = [&](auto ab_) {
-                constexpr int ab = decltype(ab_)::value, ia = 3 - ab;
+                constexpr int ab = decltype(ab_)::value;
                 GDN_ROWS(rk, kg, i3, a.H_qk, i3.hq, qk_step);
                 GDN_ROWS(rq, qg, i3, a.H_qk, i3.hq, qk_step);
                 auto fetch = [&](int r) {
@@ -249,8 +215,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                 auto place = [&](int p) {
 #pragma unroll
                     for (int r = p * ROWS / 4; r < (p + 1) * ROWS / 4; ++r) {
-                        stage(Kt2, kraw[r], r);
-                        stage(Kt2 + SM::TILE_BYTES, qraw[r], r);
+                        stage_piece<D>(Kt2, kraw[r], ROWS * tg + r, d0);
+                        stage_piece<D>(Kt2 + SM::TILE_BYTES, qraw[r], ROWS * tg + r, d0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -258,130 +224,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 place(0); place(1); place(2); place(3);
-                half8 ka[SS], qf[SS];
-#pragma unroll
-                for (int s = 0; s < SS; ++s) {
-                    ka[s] = row_frag(Kt, ab, s);
-                    qf[s] = row_frag(Qt, ia, s);
-                }
-                // diagonal block, gates and betas (see gdn_fused_kernel.h for each of the steps)
-                const f32x4 gi = *reinterpret_cast<const f32x4*>(gS + 16 * ab + 4 * g4);
-                const f32x4 bi = *reinterpret_cast<const f32x4*>(bS + 16 * ab + 4 * g4);
-                const float gj = gS[16 * ab + m], bj = bS[16 * ab + m];
-                if (ab == 0) {
-                    const float la = lane < n2 ? fmaxf(EL::log_(EL::widen(graw)), -88.f) : 0.f;
-                    const float s = wave_running_sum(la);
-                    const int sbits = __builtin_bit_cast(int, s);
-                    const float e0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sbits, 15));
-                    const float e1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sbits, 31));
-                    const float e2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(sbits, 47));
-                    const float g_last = wave_last_lane(s);
-                    const float eb = lane < 16 ? e0 : lane < 32 ? e1 : lane < 48 ? e2 : g_last;
-                    sm2[lane] = s;
-                    sm2[2 * C + lane] = EL::exp_(s);
-                    sm2[3 * C + lane] = EL::exp_(g_last - s);
-                    sm2[4 * C + lane] = EL::exp_(fminf(eb - s, 0.f));
-                    sm2[5 * C + lane] = EL::exp_(fminf(s - e0, 0.f));
-                    sm2[6 * C + lane] = EL::exp_(fminf(s - e1, 0.f));
-                    sm2[7 * C + lane] = EL::exp_(fminf(s - e2, 0.f));
-                } else if (ab == 1) {
-                    sm2[C + lane] = lane < n2 ? EL::widen(graw) : 0.f;
-                }
+                if (ab == 0) gate_vectors(gates2, lane < n2 ? fmaxf(EL::log_(EL::widen(graw)), -88.f) : 0.f, lane);
+                else if (ab == 1) gates2[GateVecs::B + lane] = lane < n2 ? EL::widen(graw) : 0.f;
                 __builtin_amdgcn_sched_barrier(0);
                 if (ab < 2) {
                     if (lane < i3.n)
                         graw = (reinterpret_cast<const In*>(ab == 0 ? a.gate : a.beta) + (row_of(i3) * a.H_v + i3.hv))[lane * a.H_v];
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                f32x4 gr = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < SS; ++s) gr = mma32(ka[s], ka[s], gr);
-                f32x4 d, dt, y;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int i = 4 * g4 + e;
-                    float x = bi[e] * EL::exp_(fminf(gi[e] - gj, 0.f)) * gr[e];     // D[i][m]
-                    float xt = bj * EL::exp_(fminf(gj - gi[e], 0.f)) * gr[e];       // D[m][i]
-                    pin(x); pin(xt);       // in every lane: no branch around an exponential
-                    d[e] = m < i ? x : 0.f;
-                    dt[e] = i < m ? xt : 0.f;
-                    y[e] = (i == m ? 1.f : 0.f) - d[e];
-                }
-                // The diagonal inverse (the products of inv16_tiles), between them the other blocks' raw products
-                f32x4 acl[4], acp[4];
-                auto block = [&](int c) {
-                    half8 kc[SS];
-#pragma unroll
-                    for (int s = 0; s < SS; ++s) kc[s] = row_frag(Kt, c, s);
-                    if (c < ab) {
-                        acl[c] = f32x4{0, 0, 0, 0};
-#pragma unroll
-                        for (int s = 0; s < SS; ++s) acl[c] = mma32(ka[s], kc[s], acl[c]);   // rows i in block ab, lanes j in block c
-                    }
-                    if (c <= ia) {
-                        acp[c] = f32x4{0, 0, 0, 0};
-#pragma unroll
-                        for (int s = 0; s < SS; ++s) acp[c] = mma32(kc[s], qf[s], acp[c]);
-                    }
-                };
-                const f32x4 zero = {0, 0, 0, 0};
-                __builtin_amdgcn_sched_barrier(0);
-                const f32x4 p2 = mm16_rr(zero, dt, d), p2t = mm16_rr(zero, d, dt);
-                block(0);
-                __builtin_amdgcn_sched_barrier(0);
-                y = mm16_rr(y, p2t, y);
-                const f32x4 p4 = mm16_rr(zero, p2t, p2), p4t = mm16_rr(zero, p2, p2t);
-                block(1);
-                __builtin_amdgcn_sched_barrier(0);
-                y = mm16_rr(y, p4t, y);
-                const f32x4 p8t = mm16_rr(zero, p4, p4t);
-                if (ab > 2 || ia >= 2) block(2);
-                __builtin_amdgcn_sched_barrier(0);
-                y = mm16_rr(y, p8t, y);
-                if (ia >= 3) block(3);
-                const float gq = gS[16 * ia + m];
-#pragma unroll
-                for (int c = 0; c <= ia; ++c) {
-                    f32x4 p;
-                    if (c < ia) {
-                        const float pr = a.scale * rS[c * C + 16 * ia + m];
-                        const f32x4 sk = *reinterpret_cast<const f32x4*>(sS + 16 * c + 4 * g4);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) p[e] = pr * (sk[e] * acp[c][e]);
-                    } else {
-                        const f32x4 gk = *reinterpret_cast<const f32x4*>(gS + 16 * c + 4 * g4);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            float val = a.scale * EL::exp_(fminf(gq - gk[e], 0.f)) * acp[c][e];
-                            pin(val);
-                            p[e] = (4 * g4 + e <= m) ? val : 0.f;
-                        }
-                    }
-                    *reinterpret_cast<half4*>(pimg + (SM::p_pair(ia, c) * 16 + m) * PLD + 8 * g4 + 4 * (c & 1)) = cvt4(p);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Tf[(4 * g4 + e) * SM::TF_LD + m] = y[e];
-                const f32x4 at = *reinterpret_cast<const f32x4*>(Tf + m * SM::TF_LD + 4 * g4);   // T[m][4 g4 + e]
-                {
-                    const f32x4 gm = *reinterpret_cast<const f32x4*>(gamS + 16 * ab + 4 * g4);
-                    f32x4 tb, tgm;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { tb[e] = at[e] * bi[e]; tgm[e] = -tb[e] * gm[e]; }
-                    *reinterpret_cast<half8*>(tbtg + (ab * 16 + m) * PLD + 8 * g4) = cat8(cvt4(tb), cvt4(tgm));
-                }
-#pragma unroll
-                for (int c = 0; c < ab; ++c) {
-                    const float sj = sS[16 * c + m];
-                    const f32x4 ri = *reinterpret_cast<const f32x4*>(rS + c * C + 16 * ab + 4 * g4);
-                    f32x4 lt;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) lt[e] = (bi[e] * ri[e]) * (sj * acl[c][e]);   // L_ac[4 g4 + e][m]
-                    const f32x4 mt_ = mm16_rr(zero, lt, at);     // (L^T T^T): element e of lane (m, g4) = (T L)[m][4 g4 + e]
-                    f32x4 neg;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) neg[e] = -mt_[e];
-                    *reinterpret_cast<half4*>(mimg + (SM::m_pair(ab, c) * 16 + m) * PLD + 8 * g4 + 4 * (c & 1)) = cvt4(neg);
-                }
+                operand_blocks<D, ab>(Kt, Kt + SM::TILE_BYTES, gates, Tf, pairs, a.scale, lane);
             };
             // (items that are none are staged and prepared like any other: their rows read as zeros, their results go nowhere)
             if (wave == 0) step(std::integral_constant<int, 0>());
@@ -420,120 +271,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
             const int64_t head_off = (int64_t)i0.state * DV * DK;
             half8 ud[2][NT];   // diag(dec) U, like uh
             const char* const Kt = smem + SM::ROWS_OFF + s0 * SM::ROWS_BYTES;
-            const char* const Qt = Kt + SM::TILE_BYTES;
-            const float* const gamS = reinterpret_cast<const float*>(smem + SM::SM_OFF + s0 * SM::SM_BYTES) + 2 * C;
-            const float* const decS = gamS + C;
-            const int trow = 4 * g4 + (m >> 2);
+            const float* const gates = reinterpret_cast<const float*>(smem + SM::GATES_OFF + s0 * GateVecs::BYTES);
             {
-                const char* const pairs = smem + SM::PAIRS_OFF + p0 * SM::PAIRS_BYTES;
-                const half_t* const tbtg = reinterpret_cast<const half_t*>(pairs + SM::TBTG_OFF);
-                const half_t* const mimg = reinterpret_cast<const half_t*>(pairs + SM::M_OFF);
-                const half_t* const pimg = reinterpret_cast<const half_t*>(pairs + SM::P_OFF);
-                int row_b[SS];
-#pragma unroll
-                for (int s = 0; s < SS; ++s) row_b[s] = m * RBY + 16 * ((4 * s + g4) ^ swz<D>(m));
-                auto row_frag = [&](const char* tile, int blk, int s) -> half8 {
-                    return *reinterpret_cast<const half8*>(tile + row_b[s] + blk * 16 * RBY);
-                };
-                int tv[NT];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    tv[nt] = trow * RBY + 16 * ((WP * wave + 2 * nt + ((m & 3) >> 1)) ^ swz<D>(trow)) + 8 * (m & 1);   // + tok0 * RBY
-                half8 sf[SS][NT];        // the state as an operand over d_k: step s = state tiles 2 s, 2 s + 1
-#pragma unroll
-                for (int s = 0; s < SS; ++s)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) sf[s][nt] = cat8(cvt4(accS[2 * s][nt]), cvt4(accS[2 * s + 1][nt]));
-                half8 uh[2][NT];
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) uh[p][nt][e] = (half_t)0.f;
-                const int64_t row0 = row_of(i0);
                 constexpr int OB = O_BF16 ? 2 : 4;
                 const int o_step = a.H_v * DV * OB;
-                const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-                    reinterpret_cast<char*>(a.o) + ((row0 * a.H_v + i0.hv) * DV) * OB, 0, i0.n > 0 ? (i0.n - 1) * o_step + DV * OB : 0, 0x00020000);
-                const int o_lane = m * o_step + (WC * wave + 4 * g4) * OB;
-                auto state_products = [&](int ab, f32x4 (&ks)[NT], f32x4 (&ot)[NT]) {
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) { ks[nt] = f32x4{0, 0, 0, 0}; ot[nt] = f32x4{0, 0, 0, 0}; }
-#pragma unroll
-                    for (int s = 0; s < SS; ++s) {
-                        const half8 kfr = row_frag(Kt, ab, s);
-                        const half8 qfr = row_frag(Qt, ab, s);
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) {
-                            ks[nt] = mma32(kfr, sf[s][nt], ks[nt]);
-                            ot[nt] = mma32(sf[s][nt], qfr, ot[nt]);
-                        }
-                    }
-                };
-                f32x4 ks_n[NT], ot_n[NT];
-                state_products(0, ks_n, ot_n);
-#pragma unroll
-                for (int ab = 0; ab < 4; ++ab) {
-                    const int row = 16 * ab + m;
-                    f32x4 ks[NT], ot[NT];
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) { ks[nt] = ks_n[nt]; ot[nt] = ot_n[nt]; }
-                    if (ab < 3) state_products(ab + 1, ks_n, ot_n);
-                    const half8 tf = *reinterpret_cast<const half8*>(tbtg + (ab * 16 + m) * PLD + 8 * g4);
-                    f32x4 u[NT];
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const half4 vt = tr_read(Vt + tv[nt] + ab * 16 * RBY);
-                        const f32x4 zero = {0, 0, 0, 0};
-                        u[nt] = mma32(tf, cat8(vt, cvt4(ks[nt])), zero);
-                    }
-#pragma unroll
-                    for (int p = 0; p < 2; ++p)
-                        if (2 * p < ab) {
-                            const half8 mf = *reinterpret_cast<const half8*>(mimg + (SM::m_pair(ab, 2 * p) * 16 + m) * PLD + 8 * g4);
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt) u[nt] = mma32(mf, uh[p][nt], u[nt]);
-                        }
-                    const f32x4 dc = *reinterpret_cast<const f32x4*>(decS + 16 * ab + 4 * g4);
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const half4 h = cvt4(u[nt]);
-                        f32x4 x;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) x[e] = u[nt][e] * dc[e];
-                        const half4 hd = cvt4(x);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            uh[ab >> 1][nt][4 * (ab & 1) + e] = h[e];
-                            ud[ab >> 1][nt][4 * (ab & 1) + e] = hd[e];
-                        }
-                    }
-                    const float gm = gamS[row] * a.scale;
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) ot[nt][e] *= gm;
-#pragma unroll
-                    for (int p = 0; p < 2; ++p)
-                        if (2 * p <= ab) {
-                            const half8 pf = *reinterpret_cast<const half8*>(pimg + (SM::p_pair(ab, 2 * p) * 16 + m) * PLD + 8 * g4);
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt) ot[nt] = mma32(uh[p][nt], pf, ot[nt]);
-                        }
-                    if (O_BF16) {
-                        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-                            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, __builtin_convertvector(ot[nt], bf16x4)), ro,
-                                                                  o_lane + ab * 16 * o_step + 32 * nt, 0, 0);
-                    } else {
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ot[nt]), ro, o_lane + ab * 16 * o_step + 64 * nt, 0, 0);
-                    }
-                }
+                substitute<O_BF16, D, NT, D, false>(Kt, Kt + SM::TILE_BYTES, Vt, WP * wave, smem + SM::PAIRS_OFF + p0 * PairTiles::BYTES, gates + GateVecs::GAM,
+                                             gates + GateVecs::DEC, accS, ud,
+                                             reinterpret_cast<const char*>(a.o) + ((row_of(i0) * a.H_v + i0.hv) * DV + WC * wave) * OB,
+                                             i0.n > 0 ? (i0.n - 1) * o_step + WC * OB : 0, o_step, a.scale, lane);
             }
             GDN_STAMP(1, 1);
             __builtin_amdgcn_sched_barrier(0);
@@ -541,12 +286,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
             for (int r = 0; r < WP; ++r) {
                 const int i = (64 / WP) * r + vrow;
-                float vv[8];
-                EL::unpack(vraw[r], vv);
-                half8 vh;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) vh[e] = (half_t)vv[e];
-                *reinterpret_cast<half8*>(Vt + i * RBY + ((vpc ^ swz<D>(i)) << 4)) = vh;
+                stage_piece<D>(Vt, vraw[r], i, 8 * vpc);
             }
             {
                 GDN_ROWS(rv, vg, i2, a.H_v, i2.hv, v_step);
@@ -557,25 +297,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                 __builtin_amdgcn_sched_barrier(0);
             }
             GDN_STAMP(1, 2);
-            {     // state update
-                int tr_b[SS];
-#pragma unroll
-                for (int s = 0; s < SS; ++s) tr_b[s] = trow * RBY + 16 * ((4 * s + (m & 3)) ^ swz<D>(trow));   // + tok0 * RBY + 8 h
-                const float gam_last = gamS[C - 1];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const char* kt = Kt + tr_b[mt >> 1] + 8 * (mt & 1);
-                    const half8 k0 = cat8(tr_read(kt), tr_read(kt + 16 * RBY));
-                    const half8 k1 = cat8(tr_read(kt + 32 * RBY), tr_read(kt + 48 * RBY));
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) accS[mt][nt][e] *= gam_last;
-                        accS[mt][nt] = mma32(k0, ud[0][nt], accS[mt][nt]);
-                        accS[mt][nt] = mma32(k1, ud[1][nt], accS[mt][nt]);
-                    }
-                }
-            }
+            update_state<D, NT>(Kt, gates[GateVecs::GAM + 63], ud, accS, lane);
             GDN_STAMP(1, 3);
             if (i0.eslot >= 0) {     // checkpoint emission: exact state after the last token of this chunk
                 {

@@ -25,6 +25,33 @@
 
 namespace gdn {
 
+// Host tier: the last n_copy_wgs workgroups of a call's first launch copy the start states from device-accessible pinned host memory
+// to the staging area, so that the transfer rides under this launch.
+struct HostFetch {
+    const float* host_pool;          // device-side address of the pinned host pool
+    int64_t host_slot_stride;        // floats
+    const int32_t* staged_slot;      // [n_staged] host slot of the i-th staged state
+    float* staging;                  // [n_staged][slot_elems]
+    int64_t slot_elems;
+    int32_t n_staged;
+    int32_t n_copy_wgs;
+};
+// copying workgroup wg of 256 threads: 16-byte loads over PCIe, four in flight per thread
+__device__ __forceinline__ void copy_staged(const HostFetch& f, int wg, int tid) {
+    const int64_t n4 = f.slot_elems / 4;
+    const int64_t step = (int64_t)f.n_copy_wgs * 256;
+    for (int st = 0; st < f.n_staged; ++st) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(f.host_pool + (int64_t)f.staged_slot[st] * f.host_slot_stride);
+        f32x4* dst = reinterpret_cast<f32x4*>(f.staging + (int64_t)st * f.slot_elems);
+        int64_t i = (int64_t)wg * 256 + tid;
+        for (; i + 3 * step < n4; i += 4 * step) {
+            const f32x4 x0 = src[i], x1 = src[i + step], x2 = src[i + 2 * step], x3 = src[i + 3 * step];
+            dst[i] = x0; dst[i + step] = x1; dst[i + 2 * step] = x2; dst[i + 3 * step] = x3;
+        }
+        for (; i < n4; i += step) dst[i] = src[i];
+    }
+}
+
 struct PrepArgs {
     const void* q;
     const void* k;
@@ -42,16 +69,7 @@ struct PrepArgs {
     int32_t L, H_qk, H_v;
     int64_t T_alloc;
     float scale;
-    // Host tier (first launch of a call only, else n_copy_wgs = 0): the last n_copy_wgs workgroups
-    // of the grid copy the start states from device-accessible pinned host memory to the staging
-    // area, so the transfer rides under this launch.
-    const float* host_pool;          // device-side address of the pinned host pool
-    int64_t host_slot_stride;        // floats
-    const int32_t* staged_slot;      // [n_staged] host slot of the i-th staged state
-    float* staging;                  // [n_staged][slot_elems]
-    int64_t slot_elems;
-    int32_t n_staged;
-    int32_t n_copy_wgs;
+    HostFetch fetch;      // (first launch of a call only, else n_copy_wgs = 0)
 };
 
 // D(16x16) += A(16x16) * B(16x16), fp32 MFMA 16x16x4.  Lane (m = l & 15, g4 = l >> 4).
@@ -490,21 +508,9 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a, const int wg, const
 template <typename E, int DK, int DV>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) gdn_prep_kernel(PrepArgs a) {
     const int tid = threadIdx.x;
-    const int n_prep_wgs = (int)gridDim.x - a.n_copy_wgs;
+    const int n_prep_wgs = (int)gridDim.x - a.fetch.n_copy_wgs;
     if ((int)blockIdx.x >= n_prep_wgs) {
-        // ---- copy role: 16-byte loads over PCIe, four in flight per thread
-        const int64_t n4 = a.slot_elems / 4;
-        const int64_t step = (int64_t)a.n_copy_wgs * 256;
-        for (int st = 0; st < a.n_staged; ++st) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(a.host_pool + (int64_t)a.staged_slot[st] * a.host_slot_stride);
-            f32x4* dst = reinterpret_cast<f32x4*>(a.staging + (int64_t)st * a.slot_elems);
-            int64_t i = (int64_t)((int)blockIdx.x - n_prep_wgs) * 256 + tid;
-            for (; i + 3 * step < n4; i += 4 * step) {
-                const f32x4 x0 = src[i], x1 = src[i + step], x2 = src[i + 2 * step], x3 = src[i + 3 * step];
-                dst[i] = x0; dst[i + step] = x1; dst[i + 2 * step] = x2; dst[i + 3 * step] = x3;
-            }
-            for (; i < n4; i += step) dst[i] = src[i];
-        }
+        copy_staged(a.fetch, (int)blockIdx.x - n_prep_wgs, tid);
         return;
     }
     prep_body<E, DK, DV>(a, (int)blockIdx.x, n_prep_wgs);

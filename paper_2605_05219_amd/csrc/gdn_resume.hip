@@ -14,6 +14,7 @@
 #include "gdn_decode_kernel.h"
 #include "gdn_fused_kernel.h"
 #include "gdn_pipe_kernel.h"
+#include "gdn_split_kernel.h"
 #include "gdn_probe_kernel.h"
 #include "gdn_recur_kernel.h"
 #include "gdn_resume.h"
@@ -455,6 +456,34 @@ hipError_t launch_pipe_t(const FusedArgs& fa, hipStream_t stream) {
     hipLaunchKernelGGL((gdn_pipe_kernel<O_BF16, D>), dim3((unsigned)std::min<int64_t>(fa.n_chains, cus)), dim3(512), SM::BYTES, stream, fa);
     return hipGetLastError();
 }
+// Operand blocks and substitution as two launches: see gdn_split_kernel.h.
+template <bool O_BF16, int D, int CW>
+hipError_t launch_split_t(const SplitArgs& sa, hipStream_t stream, ProfChain& prof) {
+    typedef SubstSmem<D, CW> SM;
+    static std::once_flag once;
+    static hipError_t once_err = hipSuccess;
+    std::call_once(once, [] {
+        once_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gdn_subst_kernel<O_BF16, D, CW>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, CU_LDS_BYTES);
+    });
+    if (once_err != hipSuccess) return once_err;
+    hipLaunchKernelGGL((gdn_blocks_kernel<D>), dim3((unsigned)(std::min(sa.n_units, 3 * chip_cus()) + sa.fetch.n_copy_wgs)), dim3(256), 0, stream, sa);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    prof.mark(0);
+    hipLaunchKernelGGL((gdn_subst_kernel<O_BF16, D, CW>), dim3((unsigned)((sa.n_chains + 7) / 8 * 8 * (D / CW))), dim3(256 + 4 * CW),
+                       SM::BYTES, stream, sa);
+    e = hipGetLastError();
+    prof.mark(1);
+    return e;
+}
+
+hipError_t launch_split(const SplitArgs& sa, int d, int cols, hipStream_t stream, ProfChain& prof) {
+    if (d == 64) return sa.o_bf16 ? launch_split_t<true, 64, 32>(sa, stream, prof) : launch_split_t<false, 64, 32>(sa, stream, prof);   // (64 columns never won)
+    if (cols == 64) return sa.o_bf16 ? launch_split_t<true, 128, 64>(sa, stream, prof) : launch_split_t<false, 128, 64>(sa, stream, prof);
+    return sa.o_bf16 ? launch_split_t<true, 128, 32>(sa, stream, prof) : launch_split_t<false, 128, 32>(sa, stream, prof);
+}
+
 std::atomic<int32_t> g_forced_per_cu{-1};
 // gv = value heads per workgroup (1, or 2 when the heads of a pair share a query/key head); fa.n_chains counts groups of gv heads.
 // piped: single heads on the pipelined kernel.  The fused kernel puts as many workgroups on a compute unit as fit;
@@ -505,40 +534,47 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
     return 0.0186 * (double)total_units >= 3.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
 }
 
-// The fused kernels serialise a chain's preparation along the chain; they pay when chains are plentiful and the longest chain
-// does not outlast the two-kernel run.  Where the latency variant of the two-kernel path has a workgroup for every 32
-// columns of every chain (up to 64 chains at d = 128) it wins or ties (64 chains of 128 chunks 434 against 451 us, of 32 chunks 110
-// against 127).  Beyond, estimates in us, fitted to 65 to 256 chains, even and ragged, of 2 to 128 chunks.  Pipelined kernel:
-// 20 + max(0.0186 per unit, 3.35 to 4.6 per chunk of the longest chain, by how many compute units are busy on average, since
-// the clock goes down with them); two-kernel path at d = 128: 25 + 0.0245 per unit + 2.35 per chunk.  Measured, pipelined against two-kernel: 96 chains
-// of 128 chunks 455 / 648, of 32 chunks 128 / 186, of 2 chunks 26 / 29, ragged up to 86 chunks 313 / 346; 80 ragged chains 312 / 296; 128 ragged
-// chains 316 / 372; 256 chains of 128 chunks 618 / 1679.  d = 64: pipelined 13 + max(0.0107 per unit, 2.3 to 2.8 per chunk), two-kernel 15 + 0.0523 per unit for 49 to 64
-// chains (whose recurrence shares its launch with the preparation) and 15 + 0.0234 per unit + 0.74 per chunk beyond: 64 chains of 128 chunks 305 / 426,
-// of 8 chunks 30 / 31, 64 ragged chains 204 / 164, 96 chains of 128 chunks 304 / 393.  gdn_tune_fused forces the choice.
-//
-// Start states in host memory: the two-kernel path fetches them beside its first preparation launch, the fused kernels wait for a copy,
-// so such calls keep the line they had with the fused kernel alone (from 128 chains on, longest chain at 5.5 / 6.8 us a chunk, d = 64 3.4 / 4.4).
-std::atomic<int32_t> g_forced_fused{-1};
+// Which implementation a call with bf16 inputs gets, by estimates in us fitted to 16 to 256 chains, even and ragged, of 2 to 128 chunks (n chains,
+// u units = (chunk, chain) pairs, l chunks of the longest chain; a call's figures are beside the kernels):
+//   two-kernel path, latency variant (up to 64 chains at d = 128, 128 at 64)   20 + max(0.0745 u, 1.2 l); d = 64 15 + 0.030 u + 0.55 l:
+//       few chains leave most of the chip to its preparation; one request of 16 heads and 76 chunks 127 us against 150 split
+//   split, CW columns to a workgroup   11 + 0.0125 u + (CW = 64 2.15, 32 1.73) x the most chunks one after the other (l, or 1.15 times a compute
+//       unit's share where its workgroups take several rounds, 6 us each), not under 20; d = 64 (CW = 32) 11 + 0.0095 u + 1.17 x ...
+//   pipelined or fused   20 + max(0.0186 u, 3.35 to 4.6 l), the latter by how many compute units are busy on average, since the clock goes down
+//       with them; d = 64 13 + max(0.0107 u, 2.3 to 2.8 l)
+// gdn_tune_fused and gdn_tune_split force a path.
+// Even calls at d = 128 whose slabs the two-kernel path cuts in half (33 to 64 chains, images that would not stay in the cache) keep it, by
+// which their launches are counted (48 chains of 128 chunks 343 us, split 303).  The choice does not depend on where the start states
+// are: a call has the same bits from a pool in host memory.
+enum CallPath { PATH_TWO_KERNEL, PATH_FUSED, PATH_SPLIT_64, PATH_SPLIT_32 };
+std::atomic<int32_t> g_forced_fused{-1}, g_forced_split{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
-inline bool choose_fused(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks, bool src_on_host) {
-    if (!fused_applies(s)) return false;
-    const int forced = g_forced_fused.load();
-    if (forced >= 0) return forced != 0;
+inline CallPath choose_path(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks, bool halved, bool split_fits) {
+    if (!fused_applies(s)) return PATH_TWO_KERNEL;
+    const int forced = g_forced_fused.load(), forced_split = g_forced_split.load();
+    if (forced >= 0) return forced != 0 ? PATH_FUSED : PATH_TWO_KERNEL;
     const bool big = s.d_k == 128;
     const double units = (double)total_units, longest = (double)longest_chain_chunks, cus = (double)chip_cus();
-    if (src_on_host) {
-        if (n_chains < 128) return false;
-        const double per_chunk = n_chains <= chip_cus() ? (big ? 5.5 : 3.4) : (big ? 6.8 : 4.4);
-        return std::max((big ? 0.0183 : 0.0094) * units, per_chunk * longest) < (big ? 0.056 : 0.036) * units + (big ? 150.0 : 100.0);
-    }
-    if (n_chains * 16 <= chip_cus() * (big ? 4 : 3)) return false;
+    if (forced_split > 0 && split_fits) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
+    if (big && halved && 20 * total_units >= 19 * n_chains * longest_chain_chunks) return PATH_TWO_KERNEL;
+    const double scale = 256.0 / cus;                                  // (figures from 256 compute units)
     const double busy = units / std::max(longest, 1.0) / cus;          // mean share of the compute units with a chain
     const double slow = std::min(1.0, std::max(0.0, 2.0 * busy - 1.0));
-    const double per_chunk = big ? 3.35 + 1.25 * slow : 2.3 + 0.5 * slow;
-    const double t_pipe = (big ? 20.0 : 13.0) + std::max((big ? 0.0186 : 0.0107) * units * 256.0 / cus, per_chunk * longest);
-    const double t_two = big ? 25.0 + 0.0245 * units + 2.35 * longest
-                             : n_chains * 4 <= chip_cus() ? 15.0 + 0.0523 * units : 15.0 + 0.0234 * units + 0.74 * longest;
-    return t_pipe < t_two;
+    CallPath best = PATH_FUSED;
+    double t = (big ? 20.0 : 13.0) + std::max((big ? 0.0186 : 0.0107) * units * scale, (big ? 3.35 + 1.25 * slow : 2.3 + 0.5 * slow) * longest);
+    auto consider = [&](CallPath path, double t_path) { if (t_path < t) { t = t_path; best = path; } };
+    if (n_chains * (s.d_v / 32) <= chip_cus())
+        consider(PATH_TWO_KERNEL, big ? 20.0 + std::max(0.0745 * units * scale, 1.2 * longest) : 15.0 + 0.030 * units * scale + 0.55 * longest);
+    if (forced_split != 0 && split_fits) {
+        auto split = [&](CallPath path, int64_t blocks, double per_chunk) {      // blocks: workgroups of a chain
+            const int64_t rounds = (n_chains * blocks + chip_cus() - 1) / chip_cus();
+            const double chunks = rounds > 1 ? std::max(longest, 1.15 * units * (double)blocks / cus) : longest;
+            consider(path, std::max(20.0, 11.0 + 6.0 * (double)(rounds - 1) + (big ? 0.0125 : 0.0095) * units * scale + per_chunk * chunks));
+        };
+        if (big) split(PATH_SPLIT_64, 2, 2.15);
+        split(PATH_SPLIT_32, s.d_v / 32, big ? 1.73 : 1.17);
+    }
+    return best;
 }
 
 // Which recurrence variant a call gets: 1 = latency variant (few chains), else the number of
@@ -622,9 +658,9 @@ int32_t launch_all(const gdn_shape& s, PrepArgs pa, RecurArgs ra, int32_t n_req,
         PrepArgs pl = pa;
         pl.ws_units = buf;
         pl.slab_begin = sb * R;
-        if (!with_copies) pl.n_copy_wgs = 0;   // the start states travel with the first launch only
+        if (!with_copies) pl.fetch.n_copy_wgs = 0;   // the start states travel with the first launch only
         hipLaunchKernelGGL((gdn_prep_kernel<E, DK, DV>),
-                           dim3((unsigned)(std::min<int64_t>(items, prep_slots) + pl.n_copy_wgs)), dim3(256), SM::BYTES, stream, pl);
+                           dim3((unsigned)(std::min<int64_t>(items, prep_slots) + pl.fetch.n_copy_wgs)), dim3(256), SM::BYTES, stream, pl);
         return hipGetLastError();
     };
     for (int32_t sb = 0; sb < n_slabs; ++sb) {
@@ -646,7 +682,7 @@ int32_t launch_all(const gdn_shape& s, PrepArgs pa, RecurArgs ra, int32_t n_req,
                     PrepArgs pl = pa;
                     pl.ws_units = slab_base + ((sb + 1) & 1) * slab_bytes;
                     pl.slab_begin = (sb + 1) * R;
-                    pl.n_copy_wgs = 0;
+                    pl.fetch.n_copy_wgs = 0;
                     e = launch_quad_overlap<E, DK, DV>(ra, pl, n_chains, items, chip_cus(), stream);
                 } else {
                     e = launch_recur_quad<E, DK, DV>(ra, n_chains, stream);
@@ -706,6 +742,10 @@ extern "C" int32_t gdn_phase_stamps(unsigned long long* out) {
 
 int32_t gdn_tune_fused(int32_t mode) {
     return g_forced_fused.exchange(mode < 0 ? -1 : (mode != 0));
+}
+
+int32_t gdn_tune_split(int32_t columns) {
+    return g_forced_split.exchange(columns < 0 ? -1 : columns == 0 ? 0 : columns >= 64 ? 64 : 32);
 }
 
 int32_t gdn_tune_fused_per_cu(int32_t n) {
@@ -842,6 +882,7 @@ static int64_t plan_bytes(int64_t n_chunks, int64_t n_req) {
 struct WsLayout {
     int32_t R, n_bufs;
     int64_t plan, carry, slab, total;
+    bool halved;             // slabs as halve_slabs has them (whether or not a forced length goes before it)
 };
 // Latency variant with launches apart: does a call cut its slabs of 64 rounds in half, so that the preparation's stores and the
 // recurrence's loads of a slab stay in the 256 MiB memory-side cache?  Only where the images of the first slab's chunks would not
@@ -868,8 +909,8 @@ static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_roun
     const int nw = pick_waves(n_chains, s.d_v / 32, s.in_dtype != GDN_F32);
     WsLayout w;
     w.R = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slab_rounds(n_chains, ub, nw, s.d_v / 32), max_rounds));
-    if (plan && g_forced_rounds.load() == 0 && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && halve_slabs(s, w.R, n_chunks, *plan))
-        w.R = 32;
+    w.halved = plan && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && halve_slabs(s, w.R, n_chunks, *plan);
+    if (w.halved && g_forced_rounds.load() == 0) w.R = 32;
     w.plan = plan_bytes(n_chunks, n_req);
     w.carry = align_up(n_chains * s.d_v * s.d_k * (int64_t)sizeof(float), 256);
     w.slab = n_chains * w.R * ub;
@@ -974,19 +1015,22 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     if (src_on_host)
         for (int32_t r = 0; r < n_req; ++r) n_staged += src_slot[r] >= 0;
     const int64_t staged_bytes = src_on_host ? (int64_t)n_staged * slot_elems * (int64_t)sizeof(float) : 0;
-    bool use_fused = choose_fused(s, (int64_t)n_req * s.L * s.H_v, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req, src_on_host);
-    if (!use_fused && fused_applies(s) && g_forced_fused.load() != 0 &&
+    const int64_t n_units = (int64_t)n_chunks * s.L * s.H_v;
+    const bool split_fits = n_units <= INT32_MAX && workspace_bytes >= align_up(wl.plan + n_units * BlockUnit::BYTES, 256) + staged_bytes;
+    CallPath path = choose_path(s, (int64_t)n_req * s.L * s.H_v, n_units, plan.max_chunks_per_req, wl.halved, split_fits);
+    if (path == PATH_TWO_KERNEL && fused_applies(s) && g_forced_fused.load() != 0 &&
         workspace_bytes < align_up(wl.total, 256) + staged_bytes)
-        use_fused = true;
+        path = PATH_FUSED;
     if (no_alloc) {
         if (wl.plan > STATIC_SCRATCH_BYTES) return GDN_ERR_STATIC_LIMIT;
-        use_fused = true;
+        path = PATH_FUSED;
     }
-    if (use_fused) {
+    const bool use_fused = path == PATH_FUSED, use_split = path == PATH_SPLIT_64 || path == PATH_SPLIT_32;
+    if (use_fused || use_split) {
         wl.carry = 0;
         wl.slab = 0;
         wl.n_bufs = 0;
-        wl.total = wl.plan;
+        wl.total = wl.plan + (use_split ? n_units * BlockUnit::BYTES : 0);
     }
     const int64_t staging_off = align_up(wl.total, 256);
     const int64_t need = src_on_host ? staging_off + staged_bytes : wl.total;
@@ -1044,8 +1088,8 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     pa.L = s.L; pa.H_qk = s.H_qk; pa.H_v = s.H_v;
     pa.T_alloc = s.T_alloc;
     pa.scale = s.scale;
-    pa.host_pool = nullptr; pa.host_slot_stride = 0; pa.staged_slot = nullptr; pa.staging = nullptr;
-    pa.slot_elems = 0; pa.n_staged = 0; pa.n_copy_wgs = 0;
+    pa.fetch.host_pool = nullptr; pa.fetch.host_slot_stride = 0; pa.fetch.staged_slot = nullptr; pa.fetch.staging = nullptr;
+    pa.fetch.slot_elems = 0; pa.fetch.n_staged = 0; pa.fetch.n_copy_wgs = 0;
 
     RecurArgs ra;
     ra.o = o; ra.ws_units = nullptr;
@@ -1076,13 +1120,13 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
                             attr.devicePointer != nullptr;
         if (!mapped) (void)hipGetLastError();   // an unregistered pointer is not an error here
         if (mapped && !use_fused) {
-            pa.host_pool = static_cast<const float*>(attr.devicePointer);
-            pa.host_slot_stride = src_slot_stride;
-            pa.staged_slot = ra.req_order + n_req;
-            pa.staging = staging;
-            pa.slot_elems = slot_elems;
-            pa.n_staged = n_staged;
-            pa.n_copy_wgs = 32;
+            pa.fetch.host_pool = static_cast<const float*>(attr.devicePointer);
+            pa.fetch.host_slot_stride = src_slot_stride;
+            pa.fetch.staged_slot = ra.req_order + n_req;
+            pa.fetch.staging = staging;
+            pa.fetch.slot_elems = slot_elems;
+            pa.fetch.n_staged = n_staged;
+            pa.fetch.n_copy_wgs = 32;
         } else {
             int32_t at = 0;
             for (int32_t r = 0; r < n_req; ++r) {
@@ -1098,6 +1142,32 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         ra.src_slot_stride = slot_elems;
     }
 
+    int32_t n_live = 0;          // requests with tokens: they come first in the order, and only they have chains
+    for (int32_t r = 0; r < n_req; ++r) n_live += plan.req_chunk_cu[r + 1] > plan.req_chunk_cu[r];
+    // ---- fewer chains than compute units: operand blocks of all chunks, then the recurrence by column blocks
+    if (use_split) {
+        SplitArgs sa;
+        sa.q = q; sa.k = k; sa.v = v; sa.beta = beta; sa.gate = gate; sa.o = o;
+        sa.blocks = reinterpret_cast<char*>(workspace) + wl.plan;
+        sa.chunk_tok0 = pa.chunk_tok0; sa.chunk_len = pa.chunk_len; sa.chunk_emit_slot = pa.chunk_emit_slot;
+        sa.req_chunk_cu = ra.req_chunk_cu; sa.req_src_slot = ra.req_src_slot; sa.req_order = ra.req_order;
+        sa.state_src = ra.state_src; sa.state_dst = state_dst;
+        sa.src_slot_stride = ra.src_slot_stride; sa.dst_slot_stride = dst_slot_stride;
+        sa.n_chains = (int32_t)((int64_t)n_live * s.L * s.H_v);
+        sa.n_units = (int32_t)n_units;
+        sa.L = s.L; sa.H_qk = s.H_qk; sa.H_v = s.H_v;
+        sa.T_alloc = s.T_alloc;
+        sa.scale = s.scale;
+        sa.o_bf16 = s.o_dtype == GDN_BF16;
+        sa.fetch = pa.fetch;
+        ProfChain prof(stream);
+        const hipError_t e = launch_split(sa, s.d_k, path == PATH_SPLIT_64 ? 64 : 32, stream, prof);
+        if (e != hipSuccess) return hip_err(e);
+        std::lock_guard<std::mutex> lock(g_prof.mu);
+        if (g_prof.on) g_prof.calls += 1;
+        return GDN_OK;
+    }
+
     // ---- many chains: preparation and recurrence fused, no operand image in memory
     if (use_fused) {
         FusedArgs fa;
@@ -1107,8 +1177,6 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         fa.state_src = ra.state_src; fa.state_dst = state_dst;   // (the staging area when the pool is on the host)
         fa.src_slot_stride = ra.src_slot_stride; fa.dst_slot_stride = dst_slot_stride;
         const int gv = fused_heads_per_wg(s, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req);
-        int32_t n_live = 0;          // requests with tokens: they come first in the order, and only they have chains
-        for (int32_t r = 0; r < n_req; ++r) n_live += plan.req_chunk_cu[r + 1] > plan.req_chunk_cu[r];
         fa.n_chains = (int32_t)((int64_t)n_live * s.L * s.H_v / gv);
         fa.next_chain = reinterpret_cast<int32_t*>(workspace) + (3 * (int64_t)n_chunks + 4 * (int64_t)n_req + 1);
         fa.L = s.L; fa.H_qk = s.H_qk; fa.H_v = s.H_v;

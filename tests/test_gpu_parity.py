@@ -956,11 +956,49 @@ def test_pipelined_kernel_hands_short_chains_over(d, o_dtype):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,H,n_req,tokens,fused", [(128, 16, 4, 512, 0), (128, 13, 5, 512, 1), (128, 16, 5, 128, 1), (128, 16, 7, 700, 1),
-                                                    (64, 16, 3, 512, 0), (64, 7, 7, 1000, 1), (64, 16, 6, 1500, 1)])
-def test_automatic_choice_between_the_fused_and_the_two_kernel_path(d, H, n_req, tokens, fused):
-    """Either side of the smallest numbers of chains that run fused (65 at d = 128, 49 at 64, even requests): the automatic choice is
-    bit for bit the forced one, and meets the oracle."""
+@pytest.mark.parametrize("columns", [32, 64])
+@pytest.mark.parametrize("d,H_qk,H_v,o_dtype", [(128, 3, 3, "f32"), (128, 1, 2, "bf16"), (64, 5, 5, "f32"), (64, 2, 4, "bf16")])
+def test_split_launches_equal_the_fused_kernel_bitwise(d, H_qk, H_v, o_dtype, columns):
+    """Operand blocks and recurrence as two launches: chunks that end on 1, 15, 16, 17, 63 and 64 tokens, one-chunk and empty requests,
+    more than 64 chunks in a chain (the plan's words are read again), chains that do not fill the last group of eight, with and
+    without start states, grouped value heads and stacked layers.  Against the oracle, and bit for bit against the fused kernel."""
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(7300 + d + H_v)
+    L, lens, starts = 2, [1, 15, 16, 0, 17, 63, 64, 65, 200, 64 * 66 + 5], [0, 64, 3, 0, 100, 7, 0, 128, 9, 64]
+    nxt, emits, eslots = 3, [], []
+    for s0, ln in zip(starts, lens):
+        e = sorted(set(int(x) for x in rng.integers(s0 + 1, s0 + ln + 1, 2)) | {s0 + ln}) if ln > 0 else []
+        emits.append(e)
+        eslots.append(list(range(nxt, nxt + len(e))))
+        nxt += len(e)
+    per_req = [wl.token_streams(rng, L, ln, H_qk, H_v, d, d, "bf16") for ln in lens]
+    src = [-1 if s0 == 0 else int(rng.integers(0, 3)) for s0 in starts]
+    call = wl.pack_call(L, H_qk, H_v, d, d, "bf16", per_req, starts, src, emits, eslots, nxt + 1)
+    pool = rng.standard_normal((nxt + 1,) + call.slot_shape).astype(np.float32) * 0.1
+    prev = B.gdn_tune_split(columns)
+    try:
+        check_call(call, pool, TOL["bf16"], o_dtype=o_dtype, scale=0.5)
+        o1, p1 = run_call_gpu(call, pool)
+    finally:
+        B.gdn_tune_split(prev)
+    prev, prev_pair = B.gdn_tune_fused(1), B.gdn_tune_fused_pair(0)
+    try:
+        o2, p2 = run_call_gpu(call, pool)
+    finally:
+        B.gdn_tune_fused(prev)
+        B.gdn_tune_fused_pair(prev_pair)
+    assert np.array_equal(o1.view(np.uint32), o2.view(np.uint32))
+    assert np.array_equal(p1.view(np.uint32), p2.view(np.uint32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,H,n_req,tokens,path", [(128, 16, 1, 4000, "two"), (128, 16, 1, 500, "split"), (128, 16, 4, 512, "split"), (128, 13, 8, 300, "split"),
+                                                   (128, 16, 12, 300, "fused"), (64, 16, 1, 4000, "two"), (64, 7, 7, 1000, "split"),
+                                                   (64, 16, 3, 100, "fused")])
+def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
+    """Calls on either side of the lines between the two-kernel path, the split launches and the fused kernel: the automatic choice has the
+    bits of the path it should be (split and fused agree bit for bit: forbidding the split launches tells them apart only by the
+    two-kernel path's own bits), and meets the oracle."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(d + H * n_req)
     lens = [tokens - int(x) for x in rng.integers(0, 30, n_req)]
@@ -978,7 +1016,7 @@ def test_automatic_choice_between_the_fused_and_the_two_kernel_path(d, H, n_req,
         finally:
             B.gdn_tune_fused(prev)
         same.append(np.array_equal(o1.view(np.uint32), o2.view(np.uint32)) and np.array_equal(p1.view(np.uint32), p2.view(np.uint32)))
-    assert same == [fused == 0, fused == 1]
+    assert same == [path == "two", path != "two"]
 
 
 @pytest.mark.gpu
