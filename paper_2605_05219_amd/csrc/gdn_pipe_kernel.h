@@ -22,6 +22,9 @@
 // chunk's, so V needs one buffer and no barrier.  Rows are fetched a whole step ahead of their staging: staged and at once fetched again
 // at the top of a step; a fetch half a step later costs 8 %, since the load then has half a step to arrive in (5 % in calls bound by volume).
 //
+// Rows come by ordinary loads (the fused kernel's are non-temporal): value heads that share a query/key head find each other's rows in
+// the L2, 1024 chains of up to 345 chunks with two value heads to a query/key head 1895 -> 1832 us, 8192 chains without the same.
+//
 // Preparation wave a owns block row a and the P blocks of query block 3 - a; its code is instantiated per wave, so that all
 // of it is one straight line in which the diagonal inverse's dependent products, the other blocks' products and the loads overlap.
 // Wave 1 also walks the list of items one step ahead and leaves what the others need to know of an item in LDS (eight words,
@@ -208,8 +211,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                 GDN_ROWS(rk, kg, i3, a.H_qk, i3.hq, qk_step);
                 GDN_ROWS(rq, qg, i3, a.H_qk, i3.hq, qk_step);
                 auto fetch = [&](int r) {
-                    if (r < ROWS) kraw[r < ROWS ? r : 0] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rk, (ROWS * tg + r) * qk_step + d0 * 2, 0, 2));
-                    else qraw[r >= ROWS ? r - ROWS : 0] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rq, (ROWS * tg + r - ROWS) * qk_step + d0 * 2, 0, 2));
+                    if (r < ROWS) kraw[r < ROWS ? r : 0] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rk, (ROWS * tg + r) * qk_step + d0 * 2, 0, 0));
+                    else qraw[r >= ROWS ? r - ROWS : 0] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rq, (ROWS * tg + r - ROWS) * qk_step + d0 * 2, 0, 0));
                 };
                 // a quarter of the staging of i2, and of the fetch of i3 into the registers that this frees
                 auto place = [&](int p) {
@@ -293,7 +296,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int r = 0; r < WP; ++r)
-                    vraw[r] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rv, ((64 / WP) * r + vrow) * v_step + vpc * 16, 0, 2));
+                    vraw[r] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rv, ((64 / WP) * r + vrow) * v_step + vpc * 16, 0, 0));
                 __builtin_amdgcn_sched_barrier(0);
             }
             GDN_STAMP(1, 2);
