@@ -59,11 +59,11 @@ __device__ __forceinline__ half8 row_operand(const char* tile, int blk, int s, i
 }
 
 // One preparation wave's operand blocks: block row ab of L and the P blocks of query block 3 - ab, straight-line code in
-// which the diagonal inverse's dependent products and the other blocks' products overlap.  Tf: fp32 [16][20] of the wave's own.
+// which the diagonal inverse's dependent products and the other blocks' products overlap.  Tf: fp32 [16][16] of the wave's own (read in order).
 template <int D, int ab>
 __device__ __forceinline__ void operand_blocks(const char* Kt, const char* Qt, const float* gates, float* Tf, char* pairs, float scale, int lane) {
     typedef Elem<half_t> EL;
-    constexpr int SS = D / 32, ia = 3 - ab, TF_LD = 20, LD = PairTiles::LD;
+    constexpr int SS = D / 32, ia = 3 - ab, TF_LD = 16, LD = PairTiles::LD;
     const int m = lane & 15, g4 = lane >> 4;
     const float* const gS = gates + GateVecs::G;
     const float* const bS = gates + GateVecs::B;

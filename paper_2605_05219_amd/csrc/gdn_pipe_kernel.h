@@ -62,8 +62,8 @@ struct PipeSmem {
     static constexpr int ROWS_OFF = 0, ROWS_BYTES = 2 * TILE_BYTES;      // [K | Q] of a chunk, three in turn
     static constexpr int V_OFF = ROWS_OFF + 3 * ROWS_BYTES;
     static constexpr int PAIRS_OFF = V_OFF + TILE_BYTES;                 // the pair tiles of a chunk, two in turn
-    static constexpr int TF_OFF = PAIRS_OFF + 2 * PairTiles::BYTES;       // fp32 [16][20] per preparation wave
-    static constexpr int TF_FLOATS = 16 * 20;
+    static constexpr int TF_OFF = PAIRS_OFF + 2 * PairTiles::BYTES;       // fp32 [16][16] per preparation wave
+    static constexpr int TF_FLOATS = 16 * 16;
     static constexpr int GATES_OFF = TF_OFF + 4 * TF_FLOATS * 4;         // the gate vectors of a chunk, three in turn
     static constexpr int ITEM_OFF = GATES_OFF + 3 * GateVecs::BYTES;     // four items in turn, eight words each
     static constexpr int BYTES = ITEM_OFF + 4 * 32;

@@ -5,15 +5,16 @@
 // What bounds the calls this is for is their longest chain.  The pipelined fused kernel takes a chain through at 3.3 us a chunk, the pace of its
 // preparation waves, on one compute unit, while others stand idle; the two-kernel path's preparation forms the full inverse and an image of 72 KB a
 // unit, 27 ns a unit with the whole chip, and its latency variant shares the chip with it (1.2 us a chunk for 16 chains, 2.4 for
-// 32, 3.4 for 64).  Here a unit's blocks are 14.5 KB (pair tiles, gam, dec) at 10 to 12 ns, and a chunk takes the recurrence waves alone: 1.7 us with 32
+// 32, 3.4 for 64).  Here a unit's blocks are 14.5 KB (pair tiles, gam, dec) at 10 ns (47 KB read and written: 4.7 TB/s), and a chunk takes the recurrence waves alone: 1.7 us with 32
 // columns to a workgroup, 2.1 with 64 (clocks: substitution and outputs 2750, update 830, barrier 150; a recurrence wave has 16
 // columns, the four helper waves, which bring and stage K, Q, V and the blocks, wait half of the time).  Measured at D = 128, two-kernel / pipelined / CW = 64 /
 // CW = 32, us: 48 chains of 128 chunks 344 / 446 / 340 / 303, of 8 chunks 35 / 46 / 33 / 29; 64 chains of 128 441 / 450 / 377 / 348, of 32 111 / 126 / 96 / 86; 96 ragged
-// chains of up to 86 chunks 340 / 308 / 228 / 199; 96 of 32 chunks 186 / 127 / 110 / 148, of 2 chunks 29 / 26 / 21 / 24; 128 of 128 838 / 455 / 538 / 668.  D = 64: 64 of
+// chains of up to 86 chunks 340 / 308 / 220 / 192; 96 of 32 chunks 186 / 127 / 110 / 148, of 2 chunks 29 / 26 / 21 / 24; 128 of 128 838 / 455 / 538 / 668.  D = 64: 64 of
 // 32 95 / 85 / 67 / 61, 128 ragged 234 / 206 / 166 / 146.
 //
 // Tried without gain: LDS operands read where they are used instead of one to two block rows ahead (the same); fetches one step ahead
-// instead of two (1.85 us a chunk); one unit to a preparation workgroup (16 ns a unit).
+// instead of two (1.85 us a chunk); one unit to a preparation workgroup (16 ns a unit), 1 KB more of LDS to one, which leaves room for two instead of
+// three (12 ns).
 #pragma once
 #include <type_traits>
 #include "gdn_chunk_ops.h"
@@ -55,9 +56,9 @@ struct SplitArgs {
 template <int D>
 struct BlocksSmem {
     static constexpr int TILE_BYTES = 64 * D * 2;
-    static constexpr int K_OFF = 0, Q_OFF = TILE_BYTES, PAIRS_OFF = 2 * TILE_BYTES, TF_OFF = PAIRS_OFF + PairTiles::BYTES, TF_FLOATS = 16 * 20;
+    static constexpr int K_OFF = 0, Q_OFF = TILE_BYTES, PAIRS_OFF = 2 * TILE_BYTES, TF_OFF = PAIRS_OFF + PairTiles::BYTES, TF_FLOATS = 16 * 16;
     static constexpr int GATES_OFF = TF_OFF + 4 * TF_FLOATS * 4, BYTES = GATES_OFF + GateVecs::BYTES;
-    static_assert(3 * BYTES <= 160 * 1024, "three workgroups per compute unit");
+    static_assert(3 * ((BYTES + 1279) / 1280 * 1280) <= 160 * 1024, "three workgroups per compute unit (LDS is given out in 1280 bytes)");
 };
 
 template <int D>
