@@ -129,6 +129,13 @@ __device__ __forceinline__ void operand_blocks(const char* Kt, const char* Qt, c
     __builtin_amdgcn_sched_barrier(0);
     y = mm16_rr(y, p8t, y);
     if (ia >= 3) block(3);
+    // a pair tile is written whole, 16 bytes a lane in order (its two blocks one by one, 8 bytes at a stride of 16, are two-way conflicts:
+    // 1024 chains of up to 345 chunks 1819 -> 1794 us, 8192 chains 4159 -> 4135)
+    auto put = [&](half_t* img, int tile, const half4& lo, const half4& hi) {
+        *reinterpret_cast<half8*>(img + (tile * 16 + m) * LD + 8 * g4) = cat8(lo, hi);
+    };
+    const half4 none = {(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
+    half4 even = none;
     const float gq = gS[16 * ia + m];
 #pragma unroll
     for (int c = 0; c <= ia; ++c) {
@@ -147,7 +154,10 @@ __device__ __forceinline__ void operand_blocks(const char* Kt, const char* Qt, c
                 p[e] = (4 * g4 + e <= m) ? val : 0.f;
             }
         }
-        *reinterpret_cast<half4*>(pimg + (PairTiles::p_pair(ia, c) * 16 + m) * LD + 8 * g4 + 4 * (c & 1)) = cvt4(p);
+        const half4 h = cvt4(p);
+        if (c & 1) put(pimg, PairTiles::p_pair(ia, c), even, h);
+        else if (c == ia) put(pimg, PairTiles::p_pair(ia, c), h, none);
+        else even = h;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) Tf[(4 * g4 + e) * TF_LD + m] = y[e];
@@ -170,7 +180,10 @@ __device__ __forceinline__ void operand_blocks(const char* Kt, const char* Qt, c
         f32x4 neg;
 #pragma unroll
         for (int e = 0; e < 4; ++e) neg[e] = -mt_[e];
-        *reinterpret_cast<half4*>(mimg + (PairTiles::m_pair(ab, c) * 16 + m) * LD + 8 * g4 + 4 * (c & 1)) = cvt4(neg);
+        const half4 h = cvt4(neg);
+        if (c & 1) put(mimg, PairTiles::m_pair(ab, c), even, h);
+        else if (c == ab - 1) put(mimg, PairTiles::m_pair(ab, c), h, none);
+        else even = h;
     }
 }
 

@@ -98,9 +98,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     const In* const vg = reinterpret_cast<const In*>(a.v);
     const int qk_step = a.H_qk * DK * 2, v_step = a.H_v * DV * 2;      // bytes from token to token
 
-    for (int i = threadIdx.x; i < 2 * PairTiles::BYTES / 16; i += 512)
-        reinterpret_cast<u32x4*>(smem + SM::PAIRS_OFF)[i] = u32x4{0u, 0u, 0u, 0u};
-
     // What a wave needs to know of an item (a chunk of a chain): eight words, in LDS.  n = 0: none; src: the pool slot of a new
     // chain's start state (-1: the zero state), or SAME_CHAIN.
     struct Item { int n, hq, hv, row_lo, row_hi, state, eslot, src; };

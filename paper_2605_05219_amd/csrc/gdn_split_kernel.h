@@ -80,7 +80,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
     const int tg = tid / PCS, d0 = (tid % PCS) * 8;
     float* const gates = reinterpret_cast<float*>(smem + SM::GATES_OFF);
     float* const Tf = reinterpret_cast<float*>(smem + SM::TF_OFF) + wave * SM::TF_FLOATS;
-    for (int i = tid; i < PairTiles::BYTES / 16; i += 256) reinterpret_cast<u32x4*>(smem + SM::PAIRS_OFF)[i] = u32x4{0u, 0u, 0u, 0u};
     // a unit's rows and gates, fetched while the one before it is worked on
     Raw8 kraw[ROWS], qraw[ROWS];
     In graw = In();
