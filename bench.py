@@ -11,7 +11,7 @@ batch (host planning, plan upload, one fused launch: 32768 chains).  Inputs are 
 device with a fixed seed and are resident in HBM before the timed region.
 
 Prints ONE JSON line.  `value` = suffix tokens per second through the whole 8-layer group.
-`roofline` is that of the dominant kernel (gdn_fused_kernel, one launch per step) from HIP events
+`roofline` is that of the dominant kernel (gdn_pipe_kernel, one launch per step) from HIP events
 the library records on the launch stream: algorithmic HBM bytes over the launch duration against
 8 TB/s (the binding roof: 140 flop per byte against a ridge of 312), with the matrix-core view
 beside it.  configs[1] (batch 1, latency bound) is reported as the side object `latency`.
@@ -129,7 +129,7 @@ def bench_config4(args, torch, B, dev):
         tfl = alg_flops / (launch_ms * 1e-3) / 1e12
         traffic = measured_traffic("fused_kernel_config4_hbm_traffic.txt", "traffic_bytes_per_launch")
         out["roofline"] = {
-            "bound": "hbm", "kernel": "gdn_fused_kernel (one launch per step)",
+            "bound": "hbm", "kernel": "gdn_pipe_kernel (one launch per step)",
             "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
             # HBM bytes per launch measured with rocprofv3 --pmc (FETCH_SIZE + WRITE_SIZE, scaled by a copy of known size),
             # read from the committed summary of the same command; None when that file is absent
