@@ -119,6 +119,24 @@ int64_t gdn_workspace_bytes_fused(const gdn_shape *shape, int32_t n_req, int64_t
                                   int32_t n_emit);
 
 /*
+ * Which kernels a gdn_resume_prefill call runs, by the code that chooses them (the knobs below included).  Host only, nothing is
+ * enqueued.  Arguments as for gdn_resume_prefill; n_host_states: 0, or for gdn_resume_prefill_host the number of requests with
+ * a start state, and the pool is taken to be pinned.  Returns one of the values below (NONE: no tokens), GDN_ERR_WORKSPACE when
+ * the call would be refused for its workspace, or the error of the index arrays.
+ */
+enum {
+    GDN_PATH_NONE = 0,
+    GDN_PATH_TWO_KERNEL = 1,    /* operand images, then the recurrence, slab by slab */
+    GDN_PATH_SPLIT_32 = 2,      /* operand blocks of all chunks, then the recurrence, 32 columns of d_v to a workgroup; */
+    GDN_PATH_SPLIT_64 = 3,      /* the same with 64 */
+    GDN_PATH_PIPELINED = 4,     /* one launch: preparation and recurrence of a chain in one workgroup, beside each other, */
+    GDN_PATH_FUSED = 5,         /* after each other, */
+    GDN_PATH_FUSED_PAIRS = 6    /* or for two value heads of a query/key head.  2 to 6 agree bit for bit */
+};
+int32_t gdn_resume_path(const gdn_shape *shape, int32_t n_req, const int32_t *cu_seqlens, const int32_t *start_pos,
+                        const int32_t *emit_cu, const int32_t *emit_pos, int32_t n_host_states, int64_t workspace_bytes);
+
+/*
  * Checkpoint load (Sec. 6, overhead decomposition, item (i): loading the stored checkpoint),
  * here from a pool in HBM:  dst[i] = pool[slot_ids[i]] for i < n, zeros when slot_ids[i] == -1.
  *   pool      device, fp32, n_slots slots at slot_stride floats

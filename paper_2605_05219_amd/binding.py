@@ -73,6 +73,8 @@ def lib():
         L.gdn_deepest_ckpt.argtypes = [_vp, _i32, _i32]
         L.gdn_plan_chunks.restype = _i32
         L.gdn_plan_chunks.argtypes = [_i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i32]
+        L.gdn_resume_path.restype = _i32
+        L.gdn_resume_path.argtypes = [ctypes.POINTER(gdn_shape), _i32, _vp, _vp, _vp, _vp, _i32, _i64]
         L.gdn_workspace_bytes.restype = _i64
         L.gdn_workspace_bytes.argtypes = [ctypes.POINTER(gdn_shape), _i32, _i64, _i32]
         L.gdn_workspace_bytes_fused.restype = _i64
@@ -104,7 +106,7 @@ def lib():
     return _lib
 
 
-EXPORTS = ["gdn_version", "gdn_tune_slab_rounds", "gdn_tune_fused", "gdn_tune_split", "gdn_tune_fused_pair", "gdn_tune_fused_per_cu", "gdn_profile_enable", "gdn_profile_collect", "gdn_probe_ceilings", "gdn_deepest_ckpt", "gdn_plan_chunks", "gdn_workspace_bytes",
+EXPORTS = ["gdn_version", "gdn_tune_slab_rounds", "gdn_tune_fused", "gdn_tune_split", "gdn_tune_fused_pair", "gdn_tune_fused_per_cu", "gdn_profile_enable", "gdn_profile_collect", "gdn_probe_ceilings", "gdn_deepest_ckpt", "gdn_plan_chunks", "gdn_workspace_bytes", "gdn_resume_path",
            "gdn_workspace_bytes_fused",
            "ckpt_gather", "ckpt_scatter", "gdn_resume_prefill", "gdn_decode_step", "ckpt_fetch_host", "ckpt_spill_host",
            "gdn_workspace_bytes_host", "gdn_resume_prefill_host", "gdn_resume_prefill_static", "gdn_static_plan_capacity"]
@@ -221,6 +223,16 @@ def gdn_workspace_bytes_fused(shape: gdn_shape, n_req: int, total_tokens: int, n
     """The plan-only workspace that makes a call run the fused kernel (see include/gdn_resume.h)."""
     return _check(lib().gdn_workspace_bytes_fused(ctypes.byref(shape), int(n_req), int(total_tokens), int(n_emit)),
                   "gdn_workspace_bytes_fused")
+
+
+PATHS = ["none", "two-kernel", "split 32", "split 64", "pipelined", "fused", "fused pairs"]
+
+
+def gdn_resume_path(shape: gdn_shape, cu_seqlens, start_pos, emit_cu, emit_pos, workspace_bytes: int, n_host_states: int = 0) -> str:
+    """The kernels a gdn_resume_prefill call with these arguments runs: one of PATHS (host only)."""
+    cu, sp, ecu, epos = _h32(cu_seqlens), _h32(start_pos), _h32(emit_cu), _h32(emit_pos)
+    return PATHS[_check(lib().gdn_resume_path(ctypes.byref(shape), int(sp.size), _hp(cu), _hp(sp), _hp(ecu), _hp(epos),
+                                              int(n_host_states), int(workspace_bytes)), "gdn_resume_path")]
 
 
 # ----------------------------------------------------------------------------- device entry points

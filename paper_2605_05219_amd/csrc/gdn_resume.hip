@@ -542,21 +542,18 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
 //       unit's share where its workgroups take several rounds, 6 us each), not under 20; d = 64 (CW = 32) 11 + 0.0095 u + 1.17 x ...
 //   pipelined or fused   20 + max(0.0186 u, 3.35 to 4.6 l), the latter by how many compute units are busy on average, since the clock goes down
 //       with them; d = 64 13 + max(0.0107 u, 2.3 to 2.8 l)
-// gdn_tune_fused and gdn_tune_split force a path.
-// Even calls at d = 128 whose slabs the two-kernel path cuts in half (33 to 64 chains, images that would not stay in the cache) keep it, by
-// which their launches are counted (48 chains of 128 chunks 343 us, split 303).  The choice does not depend on where the start states
+// gdn_tune_fused and gdn_tune_split force a path.  The choice does not depend on where the start states
 // are: a call has the same bits from a pool in host memory.
 enum CallPath { PATH_TWO_KERNEL, PATH_FUSED, PATH_SPLIT_64, PATH_SPLIT_32 };
 std::atomic<int32_t> g_forced_fused{-1}, g_forced_split{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
-inline CallPath choose_path(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks, bool halved, bool split_fits) {
+inline CallPath choose_path(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks, bool split_fits) {
     if (!fused_applies(s)) return PATH_TWO_KERNEL;
     const int forced = g_forced_fused.load(), forced_split = g_forced_split.load();
     if (forced >= 0) return forced != 0 ? PATH_FUSED : PATH_TWO_KERNEL;
     const bool big = s.d_k == 128;
     const double units = (double)total_units, longest = (double)longest_chain_chunks, cus = (double)chip_cus();
     if (forced_split > 0 && split_fits) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
-    if (big && halved && 20 * total_units >= 19 * n_chains * longest_chain_chunks) return PATH_TWO_KERNEL;
     const double scale = 256.0 / cus;                                  // (figures from 256 compute units)
     const double busy = units / std::max(longest, 1.0) / cus;          // mean share of the compute units with a chain
     const double slow = std::min(1.0, std::max(0.0, 2.0 * busy - 1.0));
@@ -882,7 +879,6 @@ static int64_t plan_bytes(int64_t n_chunks, int64_t n_req) {
 struct WsLayout {
     int32_t R, n_bufs;
     int64_t plan, carry, slab, total;
-    bool halved;             // slabs as halve_slabs has them (whether or not a forced length goes before it)
 };
 // Latency variant with launches apart: does a call cut its slabs of 64 rounds in half, so that the preparation's stores and the
 // recurrence's loads of a slab stay in the 256 MiB memory-side cache?  Only where the images of the first slab's chunks would not
@@ -909,14 +905,67 @@ static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_roun
     const int nw = pick_waves(n_chains, s.d_v / 32, s.in_dtype != GDN_F32);
     WsLayout w;
     w.R = (int32_t)std::max<int64_t>(1, std::min<int64_t>(slab_rounds(n_chains, ub, nw, s.d_v / 32), max_rounds));
-    w.halved = plan && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && halve_slabs(s, w.R, n_chunks, *plan);
-    if (w.halved && g_forced_rounds.load() == 0) w.R = 32;
+    if (plan && g_forced_rounds.load() == 0 && nw == 1 && !latency_shared(n_chains, s.d_v / 32) && halve_slabs(s, w.R, n_chunks, *plan))
+        w.R = 32;
     w.plan = plan_bytes(n_chunks, n_req);
     w.carry = align_up(n_chains * s.d_v * s.d_k * (int64_t)sizeof(float), 256);
     w.slab = n_chains * w.R * ub;
     w.n_bufs = (nw == 1 && latency_shared(n_chains, s.d_v / 32)) ? 2 : 1;   // two buffers: the next slab is prepared while this one is consumed
     w.total = w.plan + w.carry + w.n_bufs * w.slab;
     return w;
+}
+
+// The implementation a call runs and what it takes of the workspace: [wl.total | staged host states].
+struct Route {
+    CallPath path;
+    WsLayout wl;
+    int64_t n_units, staging_off, need;
+    void take(CallPath p, int64_t staged_bytes) {
+        path = p;
+        if (p != PATH_TWO_KERNEL) {
+            wl.carry = wl.slab = wl.n_bufs = 0;
+            wl.total = wl.plan + (p == PATH_FUSED ? 0 : n_units * BlockUnit::BYTES);
+        }
+        staging_off = align_up(wl.total, 256);
+        need = staged_bytes > 0 ? staging_off + staged_bytes : wl.total;
+    }
+};
+// The fused kernel needs the plan image only; the two-kernel path needs the carried states and a slab as well.
+// A workspace too small for the two-kernel path but large enough for the fused kernel gets the fused kernel
+// whatever the estimate says (gdn_workspace_bytes_fused is the size that asks for this).
+static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan, int64_t workspace_bytes, int64_t staged_bytes) {
+    Route r;
+    const int32_t n_chunks = (int32_t)plan.chunk_tok0.size();
+    r.wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
+    r.n_units = (int64_t)n_chunks * s.L * s.H_v;
+    const bool split_fits = r.n_units <= INT32_MAX && workspace_bytes >= align_up(r.wl.plan + r.n_units * BlockUnit::BYTES, 256) + staged_bytes;
+    CallPath path = choose_path(s, (int64_t)n_req * s.L * s.H_v, r.n_units, plan.max_chunks_per_req, split_fits);
+    if (path == PATH_TWO_KERNEL && fused_applies(s) && g_forced_fused.load() != 0 && workspace_bytes < align_up(r.wl.total, 256) + staged_bytes)
+        path = PATH_FUSED;
+    r.take(path, staged_bytes);
+    return r;
+}
+
+int32_t gdn_resume_path(const gdn_shape* shape, int32_t n_req, const int32_t* cu_seqlens, const int32_t* start_pos, const int32_t* emit_cu,
+                        const int32_t* emit_pos, int32_t n_host_states, int64_t workspace_bytes) {
+    int32_t rc = check_shape(shape);
+    if (rc != GDN_OK) return rc;
+    const gdn_shape& s = *shape;
+    if (n_host_states < 0 || n_host_states > n_req) return GDN_ERR_COUNT;
+    ChunkPlan plan;
+    rc = plan_chunks(n_req, cu_seqlens, start_pos, emit_cu, emit_pos, &plan);
+    if (rc != GDN_OK) return rc;
+    if (plan.chunk_tok0.empty()) return GDN_PATH_NONE;
+    const Route r = route_call(s, n_req, plan, workspace_bytes, (int64_t)n_host_states * s.L * s.H_v * s.d_v * s.d_k * (int64_t)sizeof(float));
+    if (workspace_bytes < r.need) return GDN_ERR_WORKSPACE;
+    switch (r.path) {
+        case PATH_TWO_KERNEL: return GDN_PATH_TWO_KERNEL;
+        case PATH_SPLIT_64: return GDN_PATH_SPLIT_64;
+        case PATH_SPLIT_32: return GDN_PATH_SPLIT_32;
+        default: break;
+    }
+    const int gv = fused_heads_per_wg(s, r.n_units, plan.max_chunks_per_req);
+    return gv == 2 ? GDN_PATH_FUSED_PAIRS : fused_piped(s, gv, r.n_units, plan.max_chunks_per_req) ? GDN_PATH_PIPELINED : GDN_PATH_FUSED;
 }
 
 int64_t gdn_workspace_bytes(const gdn_shape* shape, int32_t n_req, int64_t total_tokens, int32_t n_emit) {
@@ -1007,33 +1056,19 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     if (!q || !k || !v || !beta || !gate || !o) return GDN_ERR_NULL;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o)) return GDN_ERR_ALIGN;
 
-    // The fused kernel needs the plan image only; the two-kernel path needs the carried states and a slab as well.
-    // A workspace too small for the two-kernel path but large enough for the fused kernel gets the fused kernel
-    // whatever the estimate says (gdn_workspace_bytes_fused is the size that asks for this).
-    WsLayout wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
     int32_t n_staged = 0;
     if (src_on_host)
         for (int32_t r = 0; r < n_req; ++r) n_staged += src_slot[r] >= 0;
-    const int64_t staged_bytes = src_on_host ? (int64_t)n_staged * slot_elems * (int64_t)sizeof(float) : 0;
-    const int64_t n_units = (int64_t)n_chunks * s.L * s.H_v;
-    const bool split_fits = n_units <= INT32_MAX && workspace_bytes >= align_up(wl.plan + n_units * BlockUnit::BYTES, 256) + staged_bytes;
-    CallPath path = choose_path(s, (int64_t)n_req * s.L * s.H_v, n_units, plan.max_chunks_per_req, wl.halved, split_fits);
-    if (path == PATH_TWO_KERNEL && fused_applies(s) && g_forced_fused.load() != 0 &&
-        workspace_bytes < align_up(wl.total, 256) + staged_bytes)
-        path = PATH_FUSED;
+    const int64_t staged_bytes = (int64_t)n_staged * slot_elems * (int64_t)sizeof(float);
+    Route route = route_call(s, n_req, plan, workspace_bytes, staged_bytes);
     if (no_alloc) {
-        if (wl.plan > STATIC_SCRATCH_BYTES) return GDN_ERR_STATIC_LIMIT;
-        path = PATH_FUSED;
+        if (route.wl.plan > STATIC_SCRATCH_BYTES) return GDN_ERR_STATIC_LIMIT;
+        route.take(PATH_FUSED, staged_bytes);
     }
+    const WsLayout& wl = route.wl;
+    const CallPath path = route.path;
     const bool use_fused = path == PATH_FUSED, use_split = path == PATH_SPLIT_64 || path == PATH_SPLIT_32;
-    if (use_fused || use_split) {
-        wl.carry = 0;
-        wl.slab = 0;
-        wl.n_bufs = 0;
-        wl.total = wl.plan + (use_split ? n_units * BlockUnit::BYTES : 0);
-    }
-    const int64_t staging_off = align_up(wl.total, 256);
-    const int64_t need = src_on_host ? staging_off + staged_bytes : wl.total;
+    const int64_t staging_off = route.staging_off, need = route.need, n_units = route.n_units;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return GDN_ERR_WORKSPACE;
     if (workspace_bytes < need) return GDN_ERR_WORKSPACE;
 
@@ -1176,7 +1211,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         fa.req_chunk_cu = ra.req_chunk_cu; fa.req_src_slot = ra.req_src_slot; fa.req_order = ra.req_order;
         fa.state_src = ra.state_src; fa.state_dst = state_dst;   // (the staging area when the pool is on the host)
         fa.src_slot_stride = ra.src_slot_stride; fa.dst_slot_stride = dst_slot_stride;
-        const int gv = fused_heads_per_wg(s, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req);
+        const int gv = fused_heads_per_wg(s, n_units, plan.max_chunks_per_req);
         fa.n_chains = (int32_t)((int64_t)n_live * s.L * s.H_v / gv);
         fa.next_chain = reinterpret_cast<int32_t*>(workspace) + (3 * (int64_t)n_chunks + 4 * (int64_t)n_req + 1);
         fa.L = s.L; fa.H_qk = s.H_qk; fa.H_v = s.H_v;
@@ -1184,7 +1219,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         fa.scale = s.scale;
         fa.o_bf16 = s.o_dtype == GDN_BF16;
         ProfChain prof(stream);
-        const bool piped = fused_piped(s, gv, (int64_t)n_chunks * s.L * s.H_v, plan.max_chunks_per_req);
+        const bool piped = fused_piped(s, gv, n_units, plan.max_chunks_per_req);
         const hipError_t e = launch_fused(fa, s.d_k, gv, piped, stream);
         if (e != hipSuccess) return hip_err(e);
         prof.mark(1);

@@ -246,8 +246,9 @@ def test_fp32_recurrence_variants(L, H_qk, H_v, o_dtype, scale):
 
 
 def test_halved_slabs_of_a_long_call_are_bitwise_the_whole_ones():
-    """48 chains whose operand images exceed the memory-side cache's share: slabs of 32 rounds instead of 64 (three recurrence
-    launches for the 65 rounds, counted, against two)."""
+    """48 chains whose operand images exceed the memory-side cache's share: on the two-kernel path (forced: left to itself the library gives
+    this call to the split launches) slabs of 32 rounds instead of 64 (three recurrence launches for the 65 rounds, counted,
+    against two)."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(41)
     lens, starts = [4100, 3900, 4000], [0, 128, 64]
@@ -263,30 +264,34 @@ def test_halved_slabs_of_a_long_call_are_bitwise_the_whole_ones():
         finally:
             B.gdn_profile_enable(False)
 
-    o_auto, pool_auto, n_auto = run_counted()
-    prev = B.gdn_tune_slab_rounds(64)
+    prev_fused, prev = B.gdn_tune_fused(0), B.gdn_tune_slab_rounds(0)
     try:
+        o_auto, pool_auto, n_auto = run_counted()
+        B.gdn_tune_slab_rounds(64)
         o_64, pool_64, n_64 = run_counted()
     finally:
         B.gdn_tune_slab_rounds(prev)
+        B.gdn_tune_fused(prev_fused)
     assert (n_auto, n_64) == (3, 2)
     assert np.array_equal(o_auto, o_64) and np.array_equal(pool_auto, pool_64)
 
 
 def test_slabs_of_ragged_calls_stay_whole():
     """38 chains of 36 to 128 chunks, 198 MiB of images in all, 151 of them in the first slab of 64 rounds, where they stay in the
-    cache; few chains are left after it.  Two slabs, two recurrence launches."""
+    cache; few chains are left after it.  On the two-kernel path two slabs, two recurrence launches."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(43)
     lens = [8192] + [int(x) for x in np.exp(rng.uniform(np.log(2300), np.log(8192), 18))]
     per = [wl.token_streams(rng, 1, n, 2, 2, 128, 128, "bf16", "slow") for n in lens]
     call = wl.pack_call(1, 2, 2, 128, 128, "bf16", per, [0] * 19, [-1] * 19, [[]] * 19, [[]] * 19, 1)
+    prev = B.gdn_tune_fused(0)
     B.gdn_profile_enable(True)
     try:
         run_call_gpu(call, np.zeros((1, 1, 2, 128, 128), np.float32))
         assert B.gdn_profile_collect()[4] == 2
     finally:
         B.gdn_profile_enable(False)
+        B.gdn_tune_fused(prev)
 
 
 def test_bf16_output_and_scale():

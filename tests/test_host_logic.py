@@ -340,3 +340,15 @@ def test_bench_refuses_more_than_one_gpu_with_a_message():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     res = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert res.returncode == 2 and res.stdout == "" and "ONE GPU" in res.stderr
+
+
+def resume_path(lens, L, H, d, ws, host=0, dtype="bf16"):
+    """The path of a call of requests of these lengths (tokens), each from a stored state, with a workspace of ws bytes."""
+    shape = B.make_shape(L, H, H, d, d, dtype, "f32", sum(lens))
+    return B.gdn_resume_path(shape, np.concatenate([[0], np.cumsum(lens)]), [0] * len(lens), [0] * (len(lens) + 1), [], ws, host)
+
+
+def test_even_calls_with_halved_slabs_go_by_the_estimate():
+    """48 even chains of 128 chunks: no special case next to ragged calls of the same volume."""
+    assert resume_path([8192] * 3, 1, 16, 128, 1 << 32) == "split 32"
+    assert resume_path([8192, 8192, 7000], 1, 16, 128, 1 << 32) == "split 32"
