@@ -100,10 +100,11 @@ int32_t gdn_plan_chunks(int32_t n_req, const int32_t *cu_seqlens, const int32_t 
 /*
  * Upper bound, in bytes, of the workspace gdn_resume_prefill needs for a call with this
  * shape, n_req requests, total_tokens packed tokens and n_emit emissions.  Negative on error.
- * The per-chunk intermediates are produced and consumed slab by slab (a bounded number of
- * chunks of every request at a time), so beyond one slab the bound does not grow with the
- * sequence length: it holds the chunk plan, one carried state per (request, layer, head) and
- * one slab.
+ * It holds what any call within these bounds is given by the library's own choice: the chunk plan, and either one
+ * carried state per (request, layer, head) and one slab (the intermediates of a bounded number of chunks of every
+ * request, produced and consumed slab by slab: beyond one slab this does not grow with the sequence length), or, where the split
+ * launches may be chosen, the operand blocks of all chunks (14.5 KiB per chunk, layer and value head; calls whose
+ * blocks come to more than 1 GiB, or one chunk round of slabs and states where that is more, do not get the split launches).
  */
 int64_t gdn_workspace_bytes(const gdn_shape *shape, int32_t n_req, int64_t total_tokens,
                             int32_t n_emit);
@@ -111,8 +112,8 @@ int64_t gdn_workspace_bytes(const gdn_shape *shape, int32_t n_req, int64_t total
 /*
  * The smaller workspace that suffices when the call is served by the fused kernel (bf16 inputs,
  * d_k = d_v = 128 or 64: preparation and recurrence of a chain in one workgroup, see gdn_tune_fused):
- * the chunk plan only.  A call given at least this much but less than gdn_workspace_bytes runs
- * the fused kernel whatever the library's estimate says; for other shapes the value equals
+ * the chunk plan only.  A call given at least this much, but too little for the kernels that the library's
+ * estimate picks, runs the fused kernel instead; for other shapes the value equals
  * gdn_workspace_bytes.  Negative on error.
  */
 int64_t gdn_workspace_bytes_fused(const gdn_shape *shape, int32_t n_req, int64_t total_tokens,
@@ -189,9 +190,10 @@ int32_t ckpt_scatter(float *pool, int64_t slot_stride, int32_t n_slots,
  *               are scratch, nothing is carried between calls
  * Outputs: o within the stated tolerance of the token-by-token definition, emitted states
  * likewise, slot indexing exact.  The same call gives the same bits every time; which kernels serve
- * a call depends on its shape, its types and how many chains (requests x layers x value heads) it
- * has, and their sums have different orders, so a request's results may differ in rounding with
- * what it is batched with (fp32 inputs: above and below half the compute units in chains).
+ * a call depends on its shape, its types, how many chains (requests x layers x value heads) it
+ * has and how many chunks these have, and the sums of some have different orders (gdn_resume_path), so a request's results may differ in
+ * rounding with what it is batched with (fp32 inputs: above and below half the compute units in chains).  A workspace of
+ * gdn_workspace_bytes or more does not change the choice; a smaller one may (gdn_workspace_bytes_fused).
  * Calls that share a workspace must be ordered on one stream.
  */
 int32_t gdn_resume_prefill(const gdn_shape *shape,
@@ -344,9 +346,9 @@ int32_t gdn_tune_fused(int32_t mode);
 /*
  * Tuning knob (not a step of the method).  Calls with bf16 inputs, d_k = d_v = 128 or 64 and fewer chains than keep the
  * device busy can run as two launches, the operand blocks of all chunks and then the recurrence with 32 or 64
- * columns of d_v to a workgroup (32 at d = 64).  columns 32 or 64 forces that form wherever the workspace holds the blocks
- * (gdn_tune_fused >= 0 goes before it), 0 forbids it, < 0 restores the automatic choice.  Outputs are bitwise those of the
- * fused kernel.  Returns the previous setting (-1 = automatic).
+ * columns of d_v to a workgroup (32 at d = 64).  columns 32 or 64 forces that form wherever the workspace holds the blocks (query
+ * its size after setting it; with a smaller one the fused kernel runs; gdn_tune_fused >= 0 goes before it), 0 forbids it, < 0 restores the
+ * automatic choice.  Outputs are bitwise those of the fused kernel.  Returns the previous setting (-1 = automatic).
  */
 int32_t gdn_tune_split(int32_t columns);
 

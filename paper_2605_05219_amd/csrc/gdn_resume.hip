@@ -542,34 +542,57 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
 //       unit's share where its workgroups take several rounds, 6 us each), not under 20; d = 64 (CW = 32) 11 + 0.0095 u + 1.17 x ...
 //   pipelined or fused   20 + max(0.0186 u, 3.35 to 4.6 l), the latter by how many compute units are busy on average, since the clock goes down
 //       with them; d = 64 13 + max(0.0107 u, 2.3 to 2.8 l)
-// gdn_tune_fused and gdn_tune_split force a path.  The choice does not depend on where the start states
-// are: a call has the same bits from a pool in host memory.
+// gdn_tune_fused and gdn_tune_split force a path.  The choice goes by the shape and the plan alone, not by the slab length, the size of
+// the workspace or where the start states are: neither changes a call's bits (a workspace without room for what was chosen is the one exception, see route_call).
 enum CallPath { PATH_TWO_KERNEL, PATH_FUSED, PATH_SPLIT_64, PATH_SPLIT_32 };
 std::atomic<int32_t> g_forced_fused{-1}, g_forced_split{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
-inline CallPath choose_path(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks, bool split_fits) {
+inline double two_kernel_us(bool big, int64_t, double units, double longest) {
+    units *= 256.0 / (double)chip_cus();                               // (figures from 256 compute units)
+    return big ? 20.0 + std::max(0.0745 * units, 1.2 * longest) : 15.0 + 0.030 * units + 0.55 * longest;
+}
+inline double split_us(bool big, bool cw64, double units, double chunks, int64_t rounds) {
+    return 11.0 + 6.0 * (double)(rounds - 1) + (big ? 0.0125 : 0.0095) * units * 256.0 / (double)chip_cus() + (cw64 ? 2.15 : big ? 1.73 : 1.17) * chunks;
+}
+inline bool two_kernel_considered(const gdn_shape& s, int64_t n_chains) { return n_chains * (s.d_v / 32) <= chip_cus(); }
+// The operand blocks of a call that may run the split launches take at most this much of the workspace: 1 GiB (72 k units), the throughput variants' slab, or what
+// one round of the two-kernel path takes.
+inline int64_t split_budget(const gdn_shape& s, int64_t n_chains) {
+    return std::max((int64_t)1 << 30, n_chains * (s.d_v * s.d_k * (int64_t)sizeof(float) + unit_bytes(s)));
+}
+// The most units with which a call of at most max_units can get the split launches, but for their budget.  Where the two-kernel path is considered, few chains
+// get them only while they are short: for a given u the split launches are best against it when the chains are even, l = u / n (the difference falls as l grows),
+// and there the difference is convex in u and positive at 0: it changes its sign at most once below a u where it is negative.
+inline int64_t split_units_bound(const gdn_shape& s, int64_t n_chains, int64_t max_units) {
+    const bool big = s.d_k == 128;
+    const double n = (double)std::max<int64_t>(n_chains, 1);
+    auto may_win = [&](int64_t u) { return two_kernel_us(big, n_chains, (double)u, (double)u / n) > split_us(big, false, (double)u, (double)u / n, 1); };
+    if (!two_kernel_considered(s, n_chains) || may_win(max_units)) return max_units;
+    int64_t lo = 0, hi = max_units;
+    while (lo + 1 < hi) (may_win((lo + hi) / 2) ? lo : hi) = (lo + hi) / 2;
+    return hi;
+}
+inline CallPath choose_path(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks) {
     if (!fused_applies(s)) return PATH_TWO_KERNEL;
     const int forced = g_forced_fused.load(), forced_split = g_forced_split.load();
     if (forced >= 0) return forced != 0 ? PATH_FUSED : PATH_TWO_KERNEL;
+    if (forced_split > 0) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
     const bool big = s.d_k == 128;
     const double units = (double)total_units, longest = (double)longest_chain_chunks, cus = (double)chip_cus();
-    if (forced_split > 0 && split_fits) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
-    const double scale = 256.0 / cus;                                  // (figures from 256 compute units)
     const double busy = units / std::max(longest, 1.0) / cus;          // mean share of the compute units with a chain
     const double slow = std::min(1.0, std::max(0.0, 2.0 * busy - 1.0));
     CallPath best = PATH_FUSED;
-    double t = (big ? 20.0 : 13.0) + std::max((big ? 0.0186 : 0.0107) * units * scale, (big ? 3.35 + 1.25 * slow : 2.3 + 0.5 * slow) * longest);
+    double t = (big ? 20.0 : 13.0) + std::max((big ? 0.0186 : 0.0107) * units * 256.0 / cus, (big ? 3.35 + 1.25 * slow : 2.3 + 0.5 * slow) * longest);
     auto consider = [&](CallPath path, double t_path) { if (t_path < t) { t = t_path; best = path; } };
-    if (n_chains * (s.d_v / 32) <= chip_cus())
-        consider(PATH_TWO_KERNEL, big ? 20.0 + std::max(0.0745 * units * scale, 1.2 * longest) : 15.0 + 0.030 * units * scale + 0.55 * longest);
-    if (forced_split != 0 && split_fits) {
-        auto split = [&](CallPath path, int64_t blocks, double per_chunk) {      // blocks: workgroups of a chain
+    if (two_kernel_considered(s, n_chains)) consider(PATH_TWO_KERNEL, two_kernel_us(big, n_chains, units, longest));
+    if (forced_split != 0 && total_units <= INT32_MAX && total_units * BlockUnit::BYTES <= split_budget(s, n_chains)) {
+        auto split = [&](CallPath path, int64_t blocks, bool cw64) {      // blocks: workgroups of a chain
             const int64_t rounds = (n_chains * blocks + chip_cus() - 1) / chip_cus();
             const double chunks = rounds > 1 ? std::max(longest, 1.15 * units * (double)blocks / cus) : longest;
-            consider(path, std::max(20.0, 11.0 + 6.0 * (double)(rounds - 1) + (big ? 0.0125 : 0.0095) * units * scale + per_chunk * chunks));
+            consider(path, std::max(20.0, split_us(big, cw64, units, chunks, rounds)));
         };
-        if (big) split(PATH_SPLIT_64, 2, 2.15);
-        split(PATH_SPLIT_32, s.d_v / 32, big ? 1.73 : 1.17);
+        if (big) split(PATH_SPLIT_64, 2, true);
+        split(PATH_SPLIT_32, s.d_v / 32, false);
     }
     return best;
 }
@@ -930,20 +953,19 @@ struct Route {
         need = staged_bytes > 0 ? staging_off + staged_bytes : wl.total;
     }
 };
-// The fused kernel needs the plan image only; the two-kernel path needs the carried states and a slab as well.
-// A workspace too small for the two-kernel path but large enough for the fused kernel gets the fused kernel
-// whatever the estimate says (gdn_workspace_bytes_fused is the size that asks for this).
+// The fused kernel needs the plan image only, the split launches the operand blocks of all chunks as well, the two-kernel path the carried
+// states and a slab.  A workspace of at least gdn_workspace_bytes holds whichever is chosen.  A smaller one that holds the plan gets the fused kernel whatever
+// the estimate says (gdn_workspace_bytes_fused is the size that asks for this): the same bits in place of the split launches, others in place of the two-kernel path.
 static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan, int64_t workspace_bytes, int64_t staged_bytes) {
     Route r;
     const int32_t n_chunks = (int32_t)plan.chunk_tok0.size();
-    r.wl = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
+    const WsLayout full = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
     r.n_units = (int64_t)n_chunks * s.L * s.H_v;
-    const bool split_fits = r.n_units <= INT32_MAX && workspace_bytes >= align_up(r.wl.plan + r.n_units * BlockUnit::BYTES, 256) + staged_bytes;
-    CallPath path = choose_path(s, (int64_t)n_req * s.L * s.H_v, r.n_units, plan.max_chunks_per_req, split_fits);
-    if (path == PATH_TWO_KERNEL && fused_applies(s) && g_forced_fused.load() != 0 && workspace_bytes < align_up(r.wl.total, 256) + staged_bytes)
-        path = PATH_FUSED;
-    r.take(path, staged_bytes);
-    return r;
+    for (CallPath path = choose_path(s, (int64_t)n_req * s.L * s.H_v, r.n_units, plan.max_chunks_per_req);; path = PATH_FUSED) {
+        r.wl = full;
+        r.take(path, staged_bytes);
+        if (workspace_bytes >= r.need || path == PATH_FUSED || !fused_applies(s) || g_forced_fused.load() == 0) return r;
+    }
 }
 
 int32_t gdn_resume_path(const gdn_shape* shape, int32_t n_req, const int32_t* cu_seqlens, const int32_t* start_pos, const int32_t* emit_cu,
@@ -973,7 +995,12 @@ int64_t gdn_workspace_bytes(const gdn_shape* shape, int32_t n_req, int64_t total
     if (rc != GDN_OK) return rc;
     if (n_req < 0 || total_tokens < 0 || n_emit < 0) return GDN_ERR_COUNT;
     const int64_t max_chunks = total_tokens / GDN_CHUNK + n_req + n_emit + 1;
-    return ws_layout(*shape, max_chunks, max_chunks, n_req).total;
+    const gdn_shape& s = *shape;
+    const WsLayout w = ws_layout(s, max_chunks, max_chunks, n_req);
+    if (!fused_applies(s)) return w.total;
+    const int64_t heads = (int64_t)s.L * s.H_v, n_chains = heads * n_req, units = heads * max_chunks;
+    const int64_t blocks = g_forced_split.load() > 0 ? units : std::min(split_units_bound(s, n_chains, units), split_budget(s, n_chains) / BlockUnit::BYTES);
+    return std::max(w.total, w.plan + blocks * BlockUnit::BYTES);
 }
 
 int64_t gdn_workspace_bytes_fused(const gdn_shape* shape, int32_t n_req, int64_t total_tokens, int32_t n_emit) {

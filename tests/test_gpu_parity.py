@@ -199,6 +199,44 @@ def test_short_slabs_carry_the_state_bitwise(n_req, dtype, rounds):
     assert np.array_equal(pool_auto, pool_forced)
 
 
+@pytest.mark.parametrize("tokens,rounds", [([8192, 8192], (1, 8)), ([2048] * 4, (1, 4)), ([10600, 10600], ())])
+def test_neither_slab_length_nor_pool_place_nor_spare_workspace_changes_a_bit(tokens, rounds):
+    """Calls near the lines between the paths and sizes of the workspace: the automatic setting against forced slab lengths (workspace queried after
+    setting them), against a pinned host pool and against twice the workspace.  One request starts from the zero state, so that
+    the host pool's workspace has room to spare."""
+    import torch
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(len(tokens) + tokens[0])
+    H, d, n = 16, 128, len(tokens)
+    per = [wl.token_streams(rng, 1, t, H, H, d, d, "bf16", "slow") for t in tokens]
+    src_pool = (rng.standard_normal((2, 1, H, d, d)) * 0.4).astype(np.float32)
+    call = wl.pack_call(1, H, H, d, d, "bf16", per, [0] + [64] * (n - 1), [-1] + [1] * (n - 1), [[t + (64 if r else 0)] for r, t in enumerate(tokens)],
+                        [[r] for r in range(n)], n)
+
+    def run(place="device", spare=1):
+        dst = torch.zeros((n, 1, H, d, d), dtype=torch.float32, device="cuda")
+        g = GpuCall(call, torch.from_numpy(src_pool).cuda(), dst_pool=dst)
+        ws_bytes = B.gdn_workspace_bytes_host if place == "host" else B.gdn_workspace_bytes
+        ws = torch.empty(spare * ws_bytes(g.shape, n, call.total_tokens, n), dtype=torch.uint8, device="cuda")
+        pool = torch.from_numpy(src_pool).pin_memory() if place == "host" else torch.from_numpy(src_pool).cuda()
+        (B.gdn_resume_prefill_host if place == "host" else B.gdn_resume_prefill)(
+            g.shape, g.q, g.k, g.v, g.beta, g.gate, call.cu_seqlens, call.start_pos, pool, call.src_slot, call.emit_cu, call.emit_pos, dst,
+            call.emit_slot, g.o, ws)
+        torch.cuda.synchronize()
+        return g.o.view(torch.int32), dst.view(torch.int32)
+
+    want = run()
+    for got in [run("host"), run(spare=2)]:
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    for r in rounds:
+        prev = B.gdn_tune_slab_rounds(r)
+        try:
+            got = run()
+        finally:
+            B.gdn_tune_slab_rounds(prev)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), r
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("H_qk,H_v,L,o_dtype", [(2, 2, 1, "f32"), (2, 4, 2, "bf16")])
 def test_fused_and_two_kernel_paths_both_meet_the_oracle(mode, H_qk, H_v, L, o_dtype):

@@ -348,7 +348,56 @@ def resume_path(lens, L, H, d, ws, host=0, dtype="bf16"):
     return B.gdn_resume_path(shape, np.concatenate([[0], np.cumsum(lens)]), [0] * len(lens), [0] * (len(lens) + 1), [], ws, host)
 
 
+def path_calls():
+    """(lengths, layers, heads, d): even and ragged calls of 1 to 300 chains, short and long, some around the limits of the two-kernel
+    path's slabs."""
+    rng = np.random.default_rng(77)
+    calls = [([8192] * 2, 1, 16, 128), ([10600] * 2, 1, 16, 128), ([16384] * 2, 1, 16, 128), ([12000] * 2, 1, 16, 128), ([8192], 3, 16, 64),
+             ([6500] * 4, 1, 16, 64), ([8192] * 3, 1, 16, 128), ([2048] * 4, 1, 16, 128), ([4100, 3900, 4000], 1, 16, 128), ([131072] * 2, 1, 16, 128),
+             ([1048576], 2, 16, 128), ([65536] * 6, 1, 16, 128)]
+    for _ in range(400):
+        d, H, L = int(rng.choice([64, 128])), int(rng.choice([2, 8, 13, 16])), int(rng.choice([1, 1, 2, 3]))
+        n = int(rng.integers(1, 13))
+        hi = int(np.exp(rng.uniform(np.log(64), np.log(40000))))
+        lo = hi if rng.random() < 0.4 else int(np.exp(rng.uniform(0, np.log(hi))))
+        calls.append(([int(x) for x in np.exp(rng.uniform(np.log(lo), np.log(hi), n))], L, H, d))
+    return calls
+
+
+def queried(lens, L, H, d, host=False):
+    f = B.gdn_workspace_bytes_host if host else B.gdn_workspace_bytes
+    return f(B.make_shape(L, H, H, d, d, "bf16", "f32", sum(lens)), len(lens), sum(lens), 0)
+
+
 def test_even_calls_with_halved_slabs_go_by_the_estimate():
     """48 even chains of 128 chunks: no special case next to ragged calls of the same volume."""
     assert resume_path([8192] * 3, 1, 16, 128, 1 << 32) == "split 32"
     assert resume_path([8192, 8192, 7000], 1, 16, 128, 1 << 32) == "split 32"
+
+
+def test_a_larger_workspace_than_the_queried_one_changes_nothing():
+    for lens, L, H, d in path_calls():
+        ws = queried(lens, L, H, d)
+        assert resume_path(lens, L, H, d, ws) == resume_path(lens, L, H, d, 1 << 40), (lens, L, H, d, ws)
+
+
+def test_the_slab_length_does_not_change_the_arithmetic():
+    """With a forced slab length the call stays with the two-kernel path or with the others, which agree bit for bit, as it is."""
+    for lens, L, H, d in path_calls():
+        auto = resume_path(lens, L, H, d, queried(lens, L, H, d))
+        for rounds in (1, 4, 8, 64, 200):
+            prev = B.gdn_tune_slab_rounds(rounds)
+            try:
+                forced = resume_path(lens, L, H, d, queried(lens, L, H, d))
+            finally:
+                B.gdn_tune_slab_rounds(prev)
+            assert (forced == "two-kernel") == (auto == "two-kernel"), (lens, L, H, d, rounds, auto, forced)
+
+
+def test_host_and_device_pools_get_the_same_arithmetic():
+    """Start states from a host pool, all of them or some, with the workspace queried for either."""
+    for lens, L, H, d in path_calls():
+        dev = resume_path(lens, L, H, d, queried(lens, L, H, d))
+        for staged in {1, len(lens) // 2, len(lens)}:
+            host = resume_path(lens, L, H, d, queried(lens, L, H, d, host=True), staged)
+            assert (host == "two-kernel") == (dev == "two-kernel"), (lens, L, H, d, staged, dev, host)
