@@ -534,25 +534,32 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
     return 0.0186 * (double)total_units >= 3.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
 }
 
-// Which implementation a call with bf16 inputs gets, by estimates in us fitted to 16 to 256 chains, even and ragged, of 2 to 128 chunks (n chains,
-// u units = (chunk, chain) pairs, l chunks of the longest chain; a call's figures are beside the kernels):
-//   two-kernel path, latency variant (up to 64 chains at d = 128, 128 at 64)   20 + max(0.0745 u, 1.2 l); d = 64 15 + 0.030 u + 0.55 l:
-//       few chains leave most of the chip to its preparation; one request of 16 heads and 76 chunks 127 us against 150 split
+// Which implementation a call with bf16 inputs gets, by estimates in us fitted to 4 to 256 chains, even and ragged, of 1 to 1024 chunks (n chains,
+// u units = (chunk, chain) pairs, l chunks of the longest chain; more figures are beside the kernels):
+//   two-kernel path, latency variant (up to 64 chains at d = 128, 128 at 64), the longest chain or the preparation of all units:
+//       max(13 + 0.65 min(n, 16) + 1.2 l, 16 + 0.0715 u).  d = 64, up to 64 chains, where preparation and recurrence share the chip: 10 + 0.6 min(n, 25) + max(0.95 l,
+//       0.029 u x the compute units / those that the recurrence leaves), else 15 + 0.032 u + 0.7 l
 //   split, CW columns to a workgroup   11 + 0.0125 u + (CW = 64 2.15, 32 1.73) x the most chunks one after the other (l, or 1.15 times a compute
-//       unit's share where its workgroups take several rounds, 6 us each), not under 20; d = 64 (CW = 32) 11 + 0.0095 u + 1.17 x ...
+//       unit's share where its workgroups take several rounds, 6 us each), not under 20; d = 64 (CW = 32) 11 + 0.0095 u + 1.25 x ...
 //   pipelined or fused   20 + max(0.0186 u, 3.35 to 4.6 l), the latter by how many compute units are busy on average, since the clock goes down
 //       with them; d = 64 13 + max(0.0107 u, 2.3 to 2.8 l)
+// Measured, two-kernel / split: d = 128, 8 chains of 12 / 24 chunks 31 / 35, 42 / 53; 16 of 8 / 16 / 24 31 / 29, 43 / 42, 52 / 56; 24 of 16 / 32 44 / 45, 67 / 72; 32 of
+// 32 / 256 80 / 74, 606 / 502.  d = 64, 8 of 12 / 32 27 / 27, 39 / 49; 16 of 8 / 24 30 / 25, 43 / 42; 32 of 16 / 64 / 128 / 256 / 512 38 / 34, 99 / 98, 180 / 178, 354 / 395, 690 / 806;
+// 48 of 16 / 512 46 / 37, 1120 / 893; ragged chains of up to 1024, 32 (20.5 k units) 1075 / 1458, 64 (30 k) 1820 / 1555.
 // gdn_tune_fused and gdn_tune_split force a path.  The choice goes by the shape and the plan alone, not by the slab length, the size of
 // the workspace or where the start states are: neither changes a call's bits (a workspace without room for what was chosen is the one exception, see route_call).
 enum CallPath { PATH_TWO_KERNEL, PATH_FUSED, PATH_SPLIT_64, PATH_SPLIT_32 };
 std::atomic<int32_t> g_forced_fused{-1}, g_forced_split{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
-inline double two_kernel_us(bool big, int64_t, double units, double longest) {
-    units *= 256.0 / (double)chip_cus();                               // (figures from 256 compute units)
-    return big ? 20.0 + std::max(0.0745 * units, 1.2 * longest) : 15.0 + 0.030 * units + 0.55 * longest;
+inline double two_kernel_us(bool big, int64_t n_chains, double units, double longest) {
+    const double cus = (double)chip_cus(), n = (double)n_chains;
+    units *= 256.0 / cus;                                              // (figures from 256 compute units)
+    if (big) return std::max(13.0 + 0.65 * std::min(n, 16.0) + 1.2 * longest, 16.0 + 0.0715 * units);
+    if (4.0 * n > cus) return 15.0 + 0.032 * units + 0.7 * longest;
+    return 10.0 + 0.6 * std::min(n, 25.0) + std::max(0.95 * longest, 0.029 * units * cus / (cus - 2.0 * n));
 }
 inline double split_us(bool big, bool cw64, double units, double chunks, int64_t rounds) {
-    return 11.0 + 6.0 * (double)(rounds - 1) + (big ? 0.0125 : 0.0095) * units * 256.0 / (double)chip_cus() + (cw64 ? 2.15 : big ? 1.73 : 1.17) * chunks;
+    return 11.0 + 6.0 * (double)(rounds - 1) + (big ? 0.0125 : 0.0095) * units * 256.0 / (double)chip_cus() + (cw64 ? 2.15 : big ? 1.73 : 1.25) * chunks;
 }
 inline bool two_kernel_considered(const gdn_shape& s, int64_t n_chains) { return n_chains * (s.d_v / 32) <= chip_cus(); }
 // The operand blocks of a call that may run the split launches take at most this much of the workspace: 1 GiB (72 k units), the throughput variants' slab, or what

@@ -375,6 +375,13 @@ def test_even_calls_with_halved_slabs_go_by_the_estimate():
     assert resume_path([8192, 8192, 7000], 1, 16, 128, 1 << 32) == "split 32"
 
 
+@pytest.mark.parametrize("n_req,H,d,chunks,path", [(1, 8, 128, 12, "two-kernel"), (1, 8, 128, 24, "two-kernel"), (1, 16, 128, 8, "split 32"), (1, 16, 128, 24, "two-kernel"),
+                                                   (2, 16, 128, 256, "split 32"), (1, 8, 64, 32, "two-kernel"), (1, 16, 64, 8, "split 32"), (2, 16, 64, 16, "split 32"),
+                                                   (2, 16, 64, 256, "two-kernel"), (2, 16, 64, 512, "two-kernel"), (3, 16, 64, 512, "split 32")])
+def test_few_chains_get_the_path_that_was_measured_faster(n_req, H, d, chunks, path):
+    assert resume_path([64 * chunks] * n_req, 1, H, d, 1 << 32) == path
+
+
 def test_a_larger_workspace_than_the_queried_one_changes_nothing():
     for lens, L, H, d in path_calls():
         ws = queried(lens, L, H, d)
