@@ -3,8 +3,10 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <vector>
 
@@ -534,74 +536,114 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
     return 0.0186 * (double)total_units >= 3.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
 }
 
-// Which implementation a call with bf16 inputs gets, by estimates in us fitted to 4 to 256 chains, even and ragged, of 1 to 1024 chunks (n chains,
-// u units = (chunk, chain) pairs, l chunks of the longest chain; more figures are beside the kernels):
-//   two-kernel path, latency variant (up to 64 chains at d = 128, 128 at 64), the longest chain or the preparation of all units:
-//       max(13 + 0.65 min(n, 16) + 1.2 l, 16 + 0.0715 u).  d = 64, up to 64 chains, where preparation and recurrence share the chip: 10 + 0.6 min(n, 25) + max(0.95 l,
-//       0.029 u x the compute units / those that the recurrence leaves), else 15 + 0.032 u + 0.7 l
-//   split, CW columns to a workgroup   11 + 0.0125 u + (CW = 64 2.15, 32 1.73) x the most chunks one after the other (l, or 1.15 times a compute
-//       unit's share where its workgroups take several rounds, 6 us each), not under 20; d = 64 (CW = 32) 11 + 0.0095 u + 1.25 x ...
-//   pipelined or fused   20 + max(0.0186 u, 3.35 to 4.6 l), the latter by how many compute units are busy on average, since the clock goes down
-//       with them; d = 64 13 + max(0.0107 u, 2.3 to 2.8 l)
-// Measured, two-kernel / split: d = 128, 8 chains of 12 / 24 chunks 31 / 35, 42 / 53; 16 of 8 / 16 / 24 31 / 29, 43 / 42, 52 / 56; 24 of 16 / 32 44 / 45, 67 / 72; 32 of
-// 32 / 256 80 / 74, 606 / 502.  d = 64, 8 of 12 / 32 27 / 27, 39 / 49; 16 of 8 / 24 30 / 25, 43 / 42; 32 of 16 / 64 / 128 / 256 / 512 38 / 34, 99 / 98, 180 / 178, 354 / 395, 690 / 806;
-// 48 of 16 / 512 46 / 37, 1120 / 893; ragged chains of up to 1024, 32 (20.5 k units) 1075 / 1458, 64 (30 k) 1820 / 1555.
-// gdn_tune_fused and gdn_tune_split force a path.  The choice goes by the shape and the plan alone, not by the slab length, the size of
-// the workspace or where the start states are: neither changes a call's bits (a workspace without room for what was chosen is the one exception, see route_call).
+// Which implementation a call with bf16 inputs gets, by estimates in us (two_kernel_us, split_us, fused_us) fitted to 442 calls of 8 to 256 chains, even and
+// ragged, of 1 to 512 chunks; n chains, u units = (chunk, chain) pairs, l chunks of the longest chain.  The choice was the fastest of the four or within 5 % of it
+// in all but 17 of them, where it was within 11 %.  Measured, two-kernel / pipelined / CW = 64 / CW = 32:
+//   d = 128   8 chains of 64 chunks 91 / 227 / 139 / 117; 16 of 8 31 / 46 / 32 / 28, of 64 99 / 230 / 145 / 122; 32 of 32 79 / 126 / 86 / 74, of 256 608 / 865 / 574 / 495;
+//             64 ragged of up to 256 (7.3 k units) 604 / 858 / 577 / 489; 120 of 32 203 / 130 / 117 / 158; 128 of 64 412 / 236 / 250 / 325
+//   d = 64    8 of 32 46 / 89 / - / 49; 32 of 512 691 / 1200 / - / 864; 48 ragged of up to 64 (1.7 k units) 106 / 164 / - / 95; 120 of 32 122 / 93 / - / 81; 128 of 64 266 / 169 / - / 163
+// gdn_tune_fused and gdn_tune_split force a path.  The choice goes by the shape and the plan alone, not by the slab length or the size of
+// the workspace (without room for what was chosen a workspace gets the fused kernel, see route_call) or where the start states are.
 enum CallPath { PATH_TWO_KERNEL, PATH_FUSED, PATH_SPLIT_64, PATH_SPLIT_32 };
 std::atomic<int32_t> g_forced_fused{-1}, g_forced_split{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
-inline double two_kernel_us(bool big, int64_t n_chains, double units, double longest) {
-    const double cus = (double)chip_cus(), n = (double)n_chains;
-    units *= 256.0 / cus;                                              // (figures from 256 compute units)
-    if (big) return std::max(13.0 + 0.65 * std::min(n, 16.0) + 1.2 * longest, 16.0 + 0.0715 * units);
-    if (4.0 * n > cus) return 15.0 + 0.032 * units + 0.7 * longest;
-    return 10.0 + 0.6 * std::min(n, 25.0) + std::max(0.95 * longest, 0.029 * units * cus / (cus - 2.0 * n));
-}
-inline double split_us(bool big, bool cw64, double units, double chunks, int64_t rounds) {
-    return 11.0 + 6.0 * (double)(rounds - 1) + (big ? 0.0125 : 0.0095) * units * 256.0 / (double)chip_cus() + (cw64 ? 2.15 : big ? 1.73 : 1.25) * chunks;
-}
+// What the estimates know of a call.  lens: chunks of the requests that have any, longest first (only up to as many chains as the estimates look at one by one).
+struct CallSize {
+    int64_t n_chains, heads, units;
+    int32_t longest;
+    std::vector<int32_t> lens;
+};
+inline double clamp01(double x) { return std::min(1.0, std::max(0.0, x)); }
+inline double per_256(double units) { return units * 256.0 / (double)chip_cus(); }      // (the figures are from 256 compute units)
 inline bool two_kernel_considered(const gdn_shape& s, int64_t n_chains) { return n_chains * (s.d_v / 32) <= chip_cus(); }
+// Two-kernel path, latency variant.  start + per_chunk of the longest chain + per_unit of the preparation; while preparation and recurrence share the chip (up to
+// 32 chains at d = 128, 64 at d = 64), each chunk round takes the longer of the two, and the preparation has the compute units that the recurrence leaves.
+struct TwoKernelRates { double start, per_chunk, per_unit; bool shared; };
+inline TwoKernelRates two_kernel_rates(bool big, int64_t n_chains) {
+    const double n = (double)n_chains, cus = (double)chip_cus();
+    if (big) {
+        if (8.0 * n <= cus) return {14.0 + 0.55 * std::min(n, 16.0), 1.2, per_256(0.0735), true};
+        return {18.0, 1.25, per_256(0.0275), false};
+    }
+    if (4.0 * n <= cus) return {10.0 + 0.6 * std::min(n, 25.0), 1.0, per_256(0.0275) * cus / (cus - 2.0 * n), true};
+    return {18.7, 0.98, per_256(0.0191), false};
+}
+inline double two_kernel_us(bool big, const CallSize& c) {
+    const TwoKernelRates t = two_kernel_rates(big, c.n_chains);
+    double us = t.start;
+    if (!t.shared) {
+        us += t.per_chunk * c.longest + t.per_unit * (double)c.units;
+    } else {
+        for (size_t k = 0; k < c.lens.size(); ++k) {      // the rounds in which requests 0 to k have a chunk
+            const int32_t rounds = c.lens[k] - (k + 1 < c.lens.size() ? c.lens[k + 1] : 0);
+            us += rounds * std::max(t.per_chunk, t.per_unit * (double)((int64_t)(k + 1) * c.heads));
+        }
+    }
+    return std::max(24.5, us);       // (here and below: under this the launches bound a call)
+}
+// Split launches, cw columns to a workgroup: the blocks of all units, then the most chunks that a compute unit's workgroups take one after the
+// other: up to two workgroups each, the longest first, from the lengths.  At d = 64 the chunks slow down as the call's data outgrow the
+// memory-side cache (1.03 us each up to 6.4 k units, 1.44 from 12 k), at d = 128, with twice the time for a chunk's data, hardly.
+struct SplitRates { double start, per_chunk, per_unit; };
+inline SplitRates split_rates(bool big, int cw) {
+    if (!big) return {13.8, 1.03, per_256(0.0089)};
+    return cw == 64 ? SplitRates{16.2, 1.84, per_256(0.0108)} : SplitRates{15.3, 1.50, per_256(0.0114)};
+}
+inline double split_us(bool big, int cw, const CallSize& c) {
+    const SplitRates t = split_rates(big, cw);
+    const int64_t cus = chip_cus(), blocks = (big ? 128 : 64) / cw, wgs = c.n_chains * blocks;
+    double chunks = c.longest, grown;
+    if (wgs > 2 * cus) {
+        chunks = std::max(chunks, 1.15 * (double)(c.units * blocks) / (double)cus);
+    } else {
+        auto chunks_of = [&](int64_t wg) { return (size_t)(wg / (c.heads * blocks)) < c.lens.size() ? c.lens[wg / (c.heads * blocks)] : 0; };
+        for (int64_t i = 0; cus + i < wgs; ++i) chunks = std::max(chunks, (double)(chunks_of(cus + i) + chunks_of(cus - 1 - i)));
+    }
+    if (!big) grown = 0.41 * clamp01(((double)c.units - 6400.0) / 5600.0);
+    else grown = cw == 64 ? 0.09 * clamp01(((double)c.units - 4800.0) / 2400.0) : c.units > 6200 ? 0.045 : 0.0;
+    return std::max(24.5, t.start + t.per_unit * (double)c.units + (t.per_chunk + grown) * chunks + (big && wgs > cus ? 4.5 : 0.0));
+}
+// Pipelined or fused: a chain's chunks by how many compute units are busy on average, since the clock goes down with them.
+inline double fused_us(bool big, const CallSize& c) {
+    const double slow = clamp01(2.0 * (double)c.units / std::max((double)c.longest, 1.0) / (double)chip_cus() - 1.0);
+    return std::max(22.0, (big ? 20.5 : 14.0) + std::max(per_256(big ? 0.0186 : 0.0107) * (double)c.units, (big ? 3.3 + 1.2 * slow : 2.33 + 0.4 * slow) * c.longest));
+}
 // The operand blocks of a call that may run the split launches take at most this much of the workspace: 1 GiB (72 k units), the throughput variants' slab, or what
 // one round of the two-kernel path takes.
 inline int64_t split_budget(const gdn_shape& s, int64_t n_chains) {
     return std::max((int64_t)1 << 30, n_chains * (s.d_v * s.d_k * (int64_t)sizeof(float) + unit_bytes(s)));
 }
 // The most units with which a call of at most max_units can get the split launches, but for their budget.  Where the two-kernel path is considered, few chains
-// get them only while they are short: for a given u the split launches are best against it when the chains are even, l = u / n (the difference falls as l grows),
-// and there the difference is convex in u and positive at 0: it changes its sign at most once below a u where it is negative.
+// get them only while they are short: with k the slope of the chord of max(per_chunk, per_unit x) over 0 to n chains, two_kernel_us is at most
+// start + per_chunk l + k u (the launches' floor is the same), split_us at least start + per_chunk l + per_unit u, and l is at least u / n.
 inline int64_t split_units_bound(const gdn_shape& s, int64_t n_chains, int64_t max_units) {
+    if (!two_kernel_considered(s, n_chains)) return max_units;
     const bool big = s.d_k == 128;
     const double n = (double)std::max<int64_t>(n_chains, 1);
-    auto may_win = [&](int64_t u) { return two_kernel_us(big, n_chains, (double)u, (double)u / n) > split_us(big, false, (double)u, (double)u / n, 1); };
-    if (!two_kernel_considered(s, n_chains) || may_win(max_units)) return max_units;
-    int64_t lo = 0, hi = max_units;
-    while (lo + 1 < hi) (may_win((lo + hi) / 2) ? lo : hi) = (lo + hi) / 2;
-    return hi;
+    const TwoKernelRates two = two_kernel_rates(big, n_chains);
+    const SplitRates split = split_rates(big, 32);       // (64 columns: a later start and more for a chunk; for a unit the 32 columns' is not the smaller)
+    const double k = two.shared ? std::max(0.0, two.per_unit - two.per_chunk / n) : two.per_unit;
+    const double gain = (two.per_chunk - split.per_chunk) / n + k - std::min(split.per_unit, split_rates(big, 64).per_unit);      // of a unit more, at most
+    if (gain >= 0.0) return max_units;
+    return (int64_t)std::min((double)max_units, std::max(0.0, (two.start - split.start) / -gain));
 }
-inline CallPath choose_path(const gdn_shape& s, int64_t n_chains, int64_t total_units, int32_t longest_chain_chunks) {
+inline CallPath choose_path(const gdn_shape& s, const CallSize& c) {
     if (!fused_applies(s)) return PATH_TWO_KERNEL;
     const int forced = g_forced_fused.load(), forced_split = g_forced_split.load();
     if (forced >= 0) return forced != 0 ? PATH_FUSED : PATH_TWO_KERNEL;
     if (forced_split > 0) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
     const bool big = s.d_k == 128;
-    const double units = (double)total_units, longest = (double)longest_chain_chunks, cus = (double)chip_cus();
-    const double busy = units / std::max(longest, 1.0) / cus;          // mean share of the compute units with a chain
-    const double slow = std::min(1.0, std::max(0.0, 2.0 * busy - 1.0));
-    CallPath best = PATH_FUSED;
-    double t = (big ? 20.0 : 13.0) + std::max((big ? 0.0186 : 0.0107) * units * 256.0 / cus, (big ? 3.35 + 1.25 * slow : 2.3 + 0.5 * slow) * longest);
-    auto consider = [&](CallPath path, double t_path) { if (t_path < t) { t = t_path; best = path; } };
-    if (two_kernel_considered(s, n_chains)) consider(PATH_TWO_KERNEL, two_kernel_us(big, n_chains, units, longest));
-    if (forced_split != 0 && total_units <= INT32_MAX && total_units * BlockUnit::BYTES <= split_budget(s, n_chains)) {
-        auto split = [&](CallPath path, int64_t blocks, bool cw64) {      // blocks: workgroups of a chain
-            const int64_t rounds = (n_chains * blocks + chip_cus() - 1) / chip_cus();
-            const double chunks = rounds > 1 ? std::max(longest, 1.15 * units * (double)blocks / cus) : longest;
-            consider(path, std::max(20.0, split_us(big, cw64, units, chunks, rounds)));
-        };
-        if (big) split(PATH_SPLIT_64, 2, true);
-        split(PATH_SPLIT_32, s.d_v / 32, false);
+    CallPath split = PATH_FUSED;
+    double t_split = HUGE_VAL;
+    const double t_fused = fused_us(big, c);
+    if (forced_split != 0 && c.units <= INT32_MAX && c.units * BlockUnit::BYTES <= split_budget(s, c.n_chains)) {
+        split = PATH_SPLIT_32;
+        t_split = split_us(big, 32, c);
+        const double t_64 = big ? split_us(big, 64, c) : HUGE_VAL;
+        if (t_64 < t_split) { split = PATH_SPLIT_64; t_split = t_64; }
     }
-    return best;
+    if (two_kernel_considered(s, c.n_chains) && two_kernel_us(big, c) < std::min(t_split, t_fused)) return PATH_TWO_KERNEL;
+    return t_split < t_fused ? split : PATH_FUSED;
 }
 
 // Which recurrence variant a call gets: 1 = latency variant (few chains), else the number of
@@ -967,8 +1009,17 @@ static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan
     Route r;
     const int32_t n_chunks = (int32_t)plan.chunk_tok0.size();
     const WsLayout full = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
-    r.n_units = (int64_t)n_chunks * s.L * s.H_v;
-    for (CallPath path = choose_path(s, (int64_t)n_req * s.L * s.H_v, r.n_units, plan.max_chunks_per_req);; path = PATH_FUSED) {
+    CallSize c;
+    c.heads = (int64_t)s.L * s.H_v;
+    c.n_chains = n_req * c.heads;
+    c.units = r.n_units = n_chunks * c.heads;
+    c.longest = plan.max_chunks_per_req;
+    if (c.n_chains <= 2 * chip_cus()) {
+        for (int32_t i = 0; i < n_req; ++i)
+            if (plan.req_chunk_cu[i + 1] > plan.req_chunk_cu[i]) c.lens.push_back(plan.req_chunk_cu[i + 1] - plan.req_chunk_cu[i]);
+        std::sort(c.lens.begin(), c.lens.end(), std::greater<int32_t>());
+    }
+    for (CallPath path = choose_path(s, c);; path = PATH_FUSED) {
         r.wl = full;
         r.take(path, staged_bytes);
         if (workspace_bytes >= r.need || path == PATH_FUSED || !fused_applies(s) || g_forced_fused.load() == 0) return r;

@@ -377,9 +377,16 @@ def test_even_calls_with_halved_slabs_go_by_the_estimate():
 
 @pytest.mark.parametrize("n_req,H,d,chunks,path", [(1, 8, 128, 12, "two-kernel"), (1, 8, 128, 24, "two-kernel"), (1, 16, 128, 8, "split 32"), (1, 16, 128, 24, "two-kernel"),
                                                    (2, 16, 128, 256, "split 32"), (1, 8, 64, 32, "two-kernel"), (1, 16, 64, 8, "split 32"), (2, 16, 64, 16, "split 32"),
-                                                   (2, 16, 64, 256, "two-kernel"), (2, 16, 64, 512, "two-kernel"), (3, 16, 64, 512, "split 32")])
+                                                   (2, 16, 64, 256, "two-kernel"), (2, 16, 64, 512, "two-kernel"), (3, 16, 64, 512, "split 32"), (15, 8, 64, 32, "split 32"), (8, 16, 64, 32, "split 32"),
+                                                   (15, 8, 128, 32, "split 64"), (14, 16, 128, 32, "pipelined")])
 def test_few_chains_get_the_path_that_was_measured_faster(n_req, H, d, chunks, path):
     assert resume_path([64 * chunks] * n_req, 1, H, d, 1 << 32) == path
+
+
+def test_ragged_calls_get_the_path_that_was_measured_faster():
+    """64 chains of 37 to 256 chunks (two-kernel path 604 us, split 489) and 256 of 2 to 32 at d = 64 (pipelined 89, split 74)."""
+    assert resume_path([64 * c for c in (256, 120, 44, 37)], 1, 16, 128, 1 << 32) == "split 32"
+    assert resume_path([64 * c for c in (32, 31, 28, 22, 20, 16, 15, 11, 8, 7, 5, 4, 3, 3, 2, 2)], 1, 16, 64, 1 << 32) == "split 32"
 
 
 def test_a_larger_workspace_than_the_queried_one_changes_nothing():
