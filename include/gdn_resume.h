@@ -100,7 +100,7 @@ int32_t gdn_plan_chunks(int32_t n_req, const int32_t *cu_seqlens, const int32_t 
 /*
  * Upper bound, in bytes, of the workspace gdn_resume_prefill needs for a call with this
  * shape, n_req requests, total_tokens packed tokens and n_emit emissions.  Negative on error.
- * It holds what any call within these bounds is given by the library's own choice: the chunk plan, and either one
+ * It holds what any call of n_req requests with no more tokens and emissions is given by the library's own choice: the chunk plan, and either one
  * carried state per (request, layer, head) and one slab (the intermediates of a bounded number of chunks of every
  * request, produced and consumed slab by slab: beyond one slab this does not grow with the sequence length), or, where the split
  * launches may be chosen, the operand blocks of all chunks (14.5 KiB per chunk, layer and value head; calls whose
@@ -248,9 +248,11 @@ int64_t gdn_static_plan_capacity(void);
  * gdn_resume_prefill_host: gdn_resume_prefill with the start states read from a pinned HOST
  * pool (host_state_src, host pointer; src_slot indexes it; -1 = zero state as before).  The
  * states are brought to a staging area behind the workspace proper: when the pool is pinned
- * memory the device can address, by workgroups appended to the first preparation launch (the
- * transfer rides under that launch; only the recurrence needs the states), otherwise by
- * copies on `stream` ahead of the first launch.  The workspace must hold
+ * memory the device can address, by workgroups of the first of several launches (the
+ * transfer rides under that launch; only the recurrence needs the states), otherwise, and where the
+ * call is one launch (gdn_resume_path: PIPELINED, FUSED, FUSED_PAIRS), by
+ * copies on `stream` ahead of it; the choice between the split launches and these counts the copies in.
+ * The workspace must hold
  * gdn_workspace_bytes_host(...) bytes.  Outputs are bitwise those of gdn_resume_prefill on a
  * device copy of the pool.
  */

@@ -25,7 +25,7 @@
 
 namespace gdn {
 
-// Host tier: the last n_copy_wgs workgroups of a call's first launch copy the start states from device-accessible pinned host memory
+// Host tier: n_copy_wgs workgroups of a call's first launch, the first or the last of its grid, copy the start states from device-accessible pinned host memory
 // to the staging area, so that the transfer rides under this launch.
 struct HostFetch {
     const float* host_pool;          // device-side address of the pinned host pool

@@ -469,7 +469,8 @@ hipError_t launch_split_t(const SplitArgs& sa, hipStream_t stream, ProfChain& pr
                                        hipFuncAttributeMaxDynamicSharedMemorySize, CU_LDS_BYTES);
     });
     if (once_err != hipSuccess) return once_err;
-    hipLaunchKernelGGL((gdn_blocks_kernel<D>), dim3((unsigned)(std::min(sa.n_units, 3 * chip_cus()) + sa.fetch.n_copy_wgs)), dim3(256), 0, stream, sa);
+    // three workgroups to a compute unit, the copying ones among them: a working one that had to wait for a place would take its whole share of the units after the others
+    hipLaunchKernelGGL((gdn_blocks_kernel<D>), dim3((unsigned)std::min(sa.n_units + sa.fetch.n_copy_wgs, 3 * chip_cus())), dim3(256), 0, stream, sa);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     prof.mark(0);
@@ -543,7 +544,8 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
 //             64 ragged of up to 256 (7.3 k units) 604 / 858 / 577 / 489; 120 of 32 203 / 130 / 117 / 158; 128 of 64 412 / 236 / 250 / 325
 //   d = 64    8 of 32 46 / 89 / - / 49; 32 of 512 691 / 1200 / - / 864; 48 ragged of up to 64 (1.7 k units) 106 / 164 / - / 95; 120 of 32 122 / 93 / - / 81; 128 of 64 266 / 169 / - / 163
 // gdn_tune_fused and gdn_tune_split force a path.  The choice goes by the shape and the plan alone, not by the slab length or the size of
-// the workspace (without room for what was chosen a workspace gets the fused kernel, see route_call) or where the start states are.
+// the workspace (without room for what was chosen a workspace gets the fused kernel, see route_call).  Start states in pinned host memory change it between the
+// split launches and the fused kernel only (host_states > 0): these have the same bits, so a call has them wherever its pool is.
 enum CallPath { PATH_TWO_KERNEL, PATH_FUSED, PATH_SPLIT_64, PATH_SPLIT_32 };
 std::atomic<int32_t> g_forced_fused{-1}, g_forced_split{-1};
 inline bool fused_applies(const gdn_shape& s) { return s.in_dtype == GDN_BF16 && s.d_k == s.d_v && (s.d_k == 128 || s.d_k == 64); }
@@ -627,15 +629,16 @@ inline int64_t split_units_bound(const gdn_shape& s, int64_t n_chains, int64_t m
     if (gain >= 0.0) return max_units;
     return (int64_t)std::min((double)max_units, std::max(0.0, (two.start - split.start) / -gain));
 }
-inline CallPath choose_path(const gdn_shape& s, const CallSize& c) {
+// host_states: start states in pinned host memory, of state_bytes each.  The fused kernel has them copied one by one in front of it (8 us and 20 us a MiB each), the
+// split launches fetch them beside the blocks (17.5 us a MiB in all, over the blocks' time).
+inline CallPath choose_path(const gdn_shape& s, const CallSize& c, int32_t host_states, int64_t state_bytes) {
     if (!fused_applies(s)) return PATH_TWO_KERNEL;
     const int forced = g_forced_fused.load(), forced_split = g_forced_split.load();
     if (forced >= 0) return forced != 0 ? PATH_FUSED : PATH_TWO_KERNEL;
     if (forced_split > 0) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
     const bool big = s.d_k == 128;
     CallPath split = PATH_FUSED;
-    double t_split = HUGE_VAL;
-    const double t_fused = fused_us(big, c);
+    double t_split = HUGE_VAL, t_fused = fused_us(big, c);
     if (forced_split != 0 && c.units <= INT32_MAX && c.units * BlockUnit::BYTES <= split_budget(s, c.n_chains)) {
         split = PATH_SPLIT_32;
         t_split = split_us(big, 32, c);
@@ -643,6 +646,11 @@ inline CallPath choose_path(const gdn_shape& s, const CallSize& c) {
         if (t_64 < t_split) { split = PATH_SPLIT_64; t_split = t_64; }
     }
     if (two_kernel_considered(s, c.n_chains) && two_kernel_us(big, c) < std::min(t_split, t_fused)) return PATH_TWO_KERNEL;
+    if (host_states > 0) {
+        const double mib = (double)state_bytes / (double)(1 << 20);
+        t_fused += host_states * (8.0 + 20.0 * mib);
+        t_split += std::max(0.0, host_states * 17.5 * mib - split_rates(big, 32).per_unit * (double)c.units);
+    }
     return t_split < t_fused ? split : PATH_FUSED;
 }
 
@@ -1005,8 +1013,10 @@ struct Route {
 // The fused kernel needs the plan image only, the split launches the operand blocks of all chunks as well, the two-kernel path the carried
 // states and a slab.  A workspace of at least gdn_workspace_bytes holds whichever is chosen.  A smaller one that holds the plan gets the fused kernel whatever
 // the estimate says (gdn_workspace_bytes_fused is the size that asks for this): the same bits in place of the split launches, others in place of the two-kernel path.
-static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan, int64_t workspace_bytes, int64_t staged_bytes) {
+// staged_states: start states that come from host memory; pinned: from device-accessible host memory.
+static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan, int64_t workspace_bytes, int32_t staged_states, bool pinned) {
     Route r;
+    const int64_t state_bytes = (int64_t)s.L * s.H_v * s.d_v * s.d_k * (int64_t)sizeof(float), staged_bytes = staged_states * state_bytes;
     const int32_t n_chunks = (int32_t)plan.chunk_tok0.size();
     const WsLayout full = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
     CallSize c;
@@ -1019,7 +1029,7 @@ static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan
             if (plan.req_chunk_cu[i + 1] > plan.req_chunk_cu[i]) c.lens.push_back(plan.req_chunk_cu[i + 1] - plan.req_chunk_cu[i]);
         std::sort(c.lens.begin(), c.lens.end(), std::greater<int32_t>());
     }
-    for (CallPath path = choose_path(s, c);; path = PATH_FUSED) {
+    for (CallPath path = choose_path(s, c, pinned ? staged_states : 0, state_bytes);; path = PATH_FUSED) {
         r.wl = full;
         r.take(path, staged_bytes);
         if (workspace_bytes >= r.need || path == PATH_FUSED || !fused_applies(s) || g_forced_fused.load() == 0) return r;
@@ -1036,7 +1046,7 @@ int32_t gdn_resume_path(const gdn_shape* shape, int32_t n_req, const int32_t* cu
     rc = plan_chunks(n_req, cu_seqlens, start_pos, emit_cu, emit_pos, &plan);
     if (rc != GDN_OK) return rc;
     if (plan.chunk_tok0.empty()) return GDN_PATH_NONE;
-    const Route r = route_call(s, n_req, plan, workspace_bytes, (int64_t)n_host_states * s.L * s.H_v * s.d_v * s.d_k * (int64_t)sizeof(float));
+    const Route r = route_call(s, n_req, plan, workspace_bytes, n_host_states, true);
     if (workspace_bytes < r.need) return GDN_ERR_WORKSPACE;
     switch (r.path) {
         case PATH_TWO_KERNEL: return GDN_PATH_TWO_KERNEL;
@@ -1144,11 +1154,18 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     int32_t n_staged = 0;
     if (src_on_host)
         for (int32_t r = 0; r < n_req; ++r) n_staged += src_slot[r] >= 0;
-    const int64_t staged_bytes = (int64_t)n_staged * slot_elems * (int64_t)sizeof(float);
-    Route route = route_call(s, n_req, plan, workspace_bytes, staged_bytes);
+    // is the pool device-accessible pinned memory?  (An unregistered pointer is not an error here.)
+    const float* pinned_pool = nullptr;
+    if (n_staged > 0) {
+        hipPointerAttribute_t attr;
+        std::memset(&attr, 0, sizeof attr);
+        if (hipPointerGetAttributes(&attr, state_src) != hipSuccess) (void)hipGetLastError();
+        else if (attr.type == hipMemoryTypeHost) pinned_pool = static_cast<const float*>(attr.devicePointer);
+    }
+    Route route = route_call(s, n_req, plan, workspace_bytes, n_staged, pinned_pool != nullptr);
     if (no_alloc) {
         if (route.wl.plan > STATIC_SCRATCH_BYTES) return GDN_ERR_STATIC_LIMIT;
-        route.take(PATH_FUSED, staged_bytes);
+        route.take(PATH_FUSED, 0);      // (this entry has no host pool)
     }
     const WsLayout& wl = route.wl;
     const CallPath path = route.path;
@@ -1234,13 +1251,8 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     //      of a 1 MiB state they hide.)
     if (src_on_host && n_staged > 0) {
         float* staging = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + staging_off);
-        hipPointerAttribute_t attr;
-        std::memset(&attr, 0, sizeof attr);
-        const bool mapped = hipPointerGetAttributes(&attr, state_src) == hipSuccess && attr.type == hipMemoryTypeHost &&
-                            attr.devicePointer != nullptr;
-        if (!mapped) (void)hipGetLastError();   // an unregistered pointer is not an error here
-        if (mapped && !use_fused) {
-            pa.fetch.host_pool = static_cast<const float*>(attr.devicePointer);
+        if (pinned_pool && !use_fused) {
+            pa.fetch.host_pool = pinned_pool;
             pa.fetch.host_slot_stride = src_slot_stride;
             pa.fetch.staged_slot = ra.req_order + n_req;
             pa.fetch.staging = staging;

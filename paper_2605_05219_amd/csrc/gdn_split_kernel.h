@@ -70,9 +70,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
     constexpr int PCS = D / 8, ROWS = D / 32;
     __shared__ __align__(16) char smem[SM::BYTES];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int n_work = (int)gridDim.x - a.fetch.n_copy_wgs;
-    if ((int)blockIdx.x >= n_work) {
-        copy_staged(a.fetch, (int)blockIdx.x - n_work, tid);
+    const int n_work = (int)gridDim.x - a.fetch.n_copy_wgs, wg = (int)blockIdx.x - a.fetch.n_copy_wgs;
+    if (wg < 0) {         // first in the grid: the copies begin with the launch
+        copy_staged(a.fetch, (int)blockIdx.x, tid);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
         if (wave < 2 && lane < n)                                                                                               \
             graw = (reinterpret_cast<const In*>(wave == 0 ? a.gate : a.beta) + (row_ * a.H_v + hv_))[lane * a.H_v];             \
     } while (0)
-    int u = blockIdx.x;
+    int u = wg;
     if (u >= a.n_units) return;
     GDN_FETCH_UNIT(u);
     for (;;) {

@@ -199,7 +199,7 @@ def test_short_slabs_carry_the_state_bitwise(n_req, dtype, rounds):
     assert np.array_equal(pool_auto, pool_forced)
 
 
-@pytest.mark.parametrize("tokens,rounds", [([8192, 8192], (1, 8)), ([2048] * 4, (1, 4)), ([10600, 10600], ())])
+@pytest.mark.parametrize("tokens,rounds", [([8192, 8192], (1, 8)), ([2048] * 4, (1, 4)), ([10600, 10600], ()), ([128] * 7, (1,))])
 def test_neither_slab_length_nor_pool_place_nor_spare_workspace_changes_a_bit(tokens, rounds):
     """Calls near the lines between the paths and sizes of the workspace: the automatic setting against forced slab lengths (workspace queried after
     setting them), against a pinned host pool and against twice the workspace.  One request starts from the zero state, so that

@@ -408,6 +408,14 @@ def test_the_slab_length_does_not_change_the_arithmetic():
             assert (forced == "two-kernel") == (auto == "two-kernel"), (lens, L, H, d, rounds, auto, forced)
 
 
+def test_short_calls_from_a_host_pool_get_the_launches_that_fetch_beside_their_work():
+    """Copies in front of the fused kernel cost more than the second launch: 15 requests of 2 chunks, 8 heads of 64, 199 us against 49."""
+    for n, H, d, chunks in [(3, 16, 64, 2), (15, 8, 64, 2), (7, 16, 128, 128), (15, 8, 64, 128)]:
+        lens = [64 * chunks] * n
+        assert resume_path(lens, 1, H, d, queried(lens, 1, H, d)) in ("pipelined", "split 64")
+        assert resume_path(lens, 1, H, d, queried(lens, 1, H, d, host=True), n).startswith("split")
+
+
 def test_host_and_device_pools_get_the_same_arithmetic():
     """Start states from a host pool, all of them or some, with the workspace queried for either."""
     for lens, L, H, d in path_calls():
