@@ -349,21 +349,6 @@ hipError_t launch_recur_f32(const RecurArgs& ra, int64_t n_chains, hipStream_t s
     return hipGetLastError();
 }
 
-template <typename E, int DK, int DV, int NSW>
-hipError_t launch_recur_ring(const RecurArgs& ra, int64_t n_chains, hipStream_t stream) {
-    constexpr int smem = RingSmem<E, DK, DV, NSW>::BYTES;
-    constexpr int SG = (DV / 32) / NSW;
-    // once per process, also when several host threads make their first call together
-    static std::once_flag once;
-    static hipError_t once_err = hipSuccess;
-    std::call_once(once, [] { once_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gdn_recur_ring_kernel<E, DK, DV, NSW>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem); });
-    if (once_err != hipSuccess) return once_err;
-    hipLaunchKernelGGL((gdn_recur_ring_kernel<E, DK, DV, NSW>), dim3((unsigned)(n_chains * SG)), dim3(64 * (NSW + 1)), smem, stream,
-                       ra);
-    return hipGetLastError();
-}
-
 template <typename E, int DK, int DV>
 hipError_t launch_recur_quad(const RecurArgs& ra, int64_t n_chains, hipStream_t stream) {
     constexpr int smem = QuadSmem<E, DK, DV>::BYTES;
@@ -766,17 +751,7 @@ int32_t launch_all(const gdn_shape& s, PrepArgs pa, RecurArgs ra, int32_t n_req,
                 }
             }
         }
-        // Throughput variants.  While two slices per workgroup still give at most one workgroup per compute
-        // unit (65 to 128 chains at four slices), the ring variant: no register staging, the next chunk lands
-        // in LDS while this one is worked on (measured: 96 chains 0.51 against 0.58 ms, 128 chains 0.57 against
-        // 0.64 ms).
         bool launched = false;
-        if constexpr (sizeof(typename Elem<E>::Frag) == 16 && NS == 4) {
-            if (nw >= 2 && n_chains * 2 <= chip_cus()) {
-                e = launch_recur_ring<E, DK, DV, 2>(ra, n_chains, stream);
-                launched = true;
-            }
-        }
         // fp32 operands, two workgroups per chain and at most one per compute unit: the 16-column variant (measured, a
         // whole call, the throughput variant against this one: 2 chains of 4 chunks 62 against 40 us, 64 chains of up to 32
         // chunks 337 against 203, 128 chains 405 against 274; 144 chains, more workgroups than compute units, keep 417)
