@@ -53,6 +53,25 @@ def worst_state_err(state, state_ref):
     return float((diff / np.where(den > 0, den, 1.0)).max())
 
 
+def call_path(call, o_dtype="f32"):
+    """The kernels the library runs this call on, with the workspace it asks for (gdn_resume_path)."""
+    from paper_2605_05219_amd import binding as B
+    shape = B.make_shape(call.L, call.H_qk, call.H_v, call.d_k, call.d_v, call.dtype, o_dtype, call.total_tokens)
+    ws = B.gdn_workspace_bytes(shape, call.n_req, call.total_tokens, int(call.emit_pos.size))
+    return B.gdn_resume_path(shape, call.cu_seqlens, call.start_pos, call.emit_cu, call.emit_pos, ws)
+
+
+def run_call_counted(call, pool, o_dtype="f32"):
+    """run_call_gpu, and the launches of preparation and of recurrence (or fused) kernels that it took."""
+    from paper_2605_05219_amd import binding as B
+    B.gdn_profile_enable(True)
+    try:
+        out = run_call_gpu(call, pool, o_dtype)
+        return out + tuple(B.gdn_profile_collect()[3:5])
+    finally:
+        B.gdn_profile_enable(False)
+
+
 def run_call_oracle(call, pool):
     from oracle import gdn_oracle as orc
     s = call.streams

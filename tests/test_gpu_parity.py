@@ -10,7 +10,7 @@ import pytest
 
 from oracle import gdn_oracle as orc
 from paper_2605_05219_amd import workloads as wl
-from tests.harness import GpuCall, max_norm_err, run_call_gpu, run_call_oracle, worst_head_err, worst_state_err
+from tests.harness import GpuCall, call_path, max_norm_err, run_call_counted, run_call_gpu, run_call_oracle, worst_head_err, worst_state_err
 
 pytestmark = pytest.mark.gpu
 
@@ -148,18 +148,20 @@ def test_destination_may_be_own_source_slot():
     check_call(call, pool, TOL["bf16"])
 
 
-@pytest.mark.parametrize("n_req,fused", [(2, -1), (3, -1), (4, -1), (6, -1), (12, 0), (12, -1), (16, 0), (16, -1), (32, 0), (32, -1)])
-def test_batch_sizes_cover_every_launch_shape(n_req, fused):
-    """16 heads x n_req requests: 32 chains run the latency variant with the next slab's preparation sharing the
-    recurrence's launch, 48 and 64 chains the latency variant with separate launches (the recurrence takes most of the chip),
-    96 chains two value-head slices per workgroup fed through an LDS ring; with the fused kernel forbidden 192 and 256 chains
-    run the register-staged kernel with two slices per workgroup and 512 chains the one with four; left to itself the library
-    gives these three sizes (short chains) to the fused kernel."""
+@pytest.mark.parametrize("n_req,fused,path", [(2, 0, "two-kernel"), (3, 0, "two-kernel"), (4, 0, "two-kernel"), (6, 0, "two-kernel"), (2, -1, "split 32"),
+                                              (3, -1, "split 32"), (4, -1, "split 32"), (6, -1, "split 64"), (12, 0, "two-kernel"), (12, -1, "split 32"),
+                                              (16, 0, "two-kernel"), (16, -1, "pipelined"), (32, 0, "two-kernel"), (32, -1, "pipelined")])
+def test_batch_sizes_cover_every_launch_shape(n_req, fused, path):
+    """16 heads x n_req requests.  On the two-kernel path (forced) 32 chains run the latency variant with the next slab's preparation
+    sharing the recurrence's launch, 48 and 64 chains the latency variant with separate launches (the recurrence takes most of the chip),
+    96 to 256 chains the register-staged kernel with two value-head slices per workgroup and 512 chains the one with four; left to
+    itself the library gives these short chains to the split launches and the pipelined kernel."""
     from paper_2605_05219_amd import binding as B
     sc = wl.config2(orc.deepest_ckpt, seed=2000 + n_req, n_req=n_req, N=1024, M=4, tail=70)
     pool, _, _ = fill_pool_from_oracle(sc)
     prev = B.gdn_tune_fused(fused)
     try:
+        assert call_path(sc.resume) == path
         check_call(sc.resume, pool, TOL["bf16"])
     finally:
         B.gdn_tune_fused(prev)
@@ -168,8 +170,8 @@ def test_batch_sizes_cover_every_launch_shape(n_req, fused):
 @pytest.mark.parametrize("n_req,dtype", [(1, "bf16"), (4, "bf16"), (6, "bf16"), (32, "bf16"), (3, "f32")])
 @pytest.mark.parametrize("rounds", [1, 3])
 def test_short_slabs_carry_the_state_bitwise(n_req, dtype, rounds):
-    """Slabs of 1 or 3 chunk rounds: every recurrence variant hands its state from slab to slab
-    through the workspace; outputs and emitted states equal the automatic setting's bit for bit
+    """Slabs of 1 or 3 chunk rounds on the two-kernel path (16, 64, 96 and 512 chains, fp32): every recurrence variant hands its
+    state from slab to slab through the workspace, a launch per slab; outputs and emitted states equal the automatic setting's bit for bit
     (and so meet the oracle tolerance, checked on the forced run)."""
     from paper_2605_05219_amd import binding as B
     d = 128 if dtype == "bf16" else 64
@@ -188,13 +190,17 @@ def test_short_slabs_carry_the_state_bitwise(n_req, dtype, rounds):
     for e in emits:
         slots.append(list(range(nxt, nxt + len(e)))); nxt += len(e)
     call = wl.pack_call(1, H, H, d, d, dtype, per, starts, src, emits, slots, n_slots)
-    o_auto, pool_auto = run_call_gpu(call, pool)
-    prev = B.gdn_tune_slab_rounds(rounds)
+    longest = int(np.diff(B.gdn_plan_chunks(call.cu_seqlens, call.start_pos, call.emit_cu, call.emit_pos)[3]).max())
+    prev_fused, prev = B.gdn_tune_fused(0), B.gdn_tune_slab_rounds(0)
     try:
-        o_forced, pool_forced = run_call_gpu(call, pool)
+        o_auto, pool_auto, _, n_auto = run_call_counted(call, pool)
+        B.gdn_tune_slab_rounds(rounds)
+        o_forced, pool_forced, _, n_forced = run_call_counted(call, pool)
         check_call(call, pool, TOL[dtype])
     finally:
         B.gdn_tune_slab_rounds(prev)
+        B.gdn_tune_fused(prev_fused)
+    assert (n_auto, n_forced) == (1, -(-longest // rounds))
     assert np.array_equal(o_auto, o_forced)
     assert np.array_equal(pool_auto, pool_forced)
 
@@ -927,10 +933,10 @@ def test_head_pairs_in_one_workgroup_equal_single_heads_bitwise(d, H_qk, H_v):
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [128, 64])
 def test_fused_chains_drawn_from_the_counter_match_the_oracle_for_any_workgroup_count(d):
-    """640 short chains (20 requests, some empty, x 2 layers x 16 heads) on the fused kernel with one workgroup per compute
-    unit: the first two rounds of chains are dealt by workgroup number, the rest are drawn from the counter in memory while
-    the kernel runs.  Checked against the oracle, and bit for bit against the same call with as many workgroups per compute
-    unit as fit (another grid, another assignment of chains to workgroups)."""
+    """640 short chains (20 requests, some empty, x 2 layers x 16 heads) on the fused (d = 64) or pipelined (d = 128) kernel with one
+    workgroup per compute unit: the first two rounds of chains are dealt by workgroup number, the rest are drawn from the counter in memory while
+    the kernel runs.  Checked against the oracle, and bit for bit against another assignment of chains to workgroups: the same call with as many workgroups
+    per compute unit as fit, or, where one is all that fits, on the split launches, whose grid has the chains in order."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(6400 + d)
     L, H, n_req = 2, 16, 20
@@ -950,13 +956,19 @@ def test_fused_chains_drawn_from_the_counter_match_the_oracle_for_any_workgroup_
     prev = B.gdn_tune_fused(1)
     prev_n = B.gdn_tune_fused_per_cu(1)
     try:
+        assert call_path(call) == ("pipelined" if d == 128 else "fused")
         check_call(call, pool, TOL["bf16"])
         o1, p1 = run_call_gpu(call, pool)
         B.gdn_tune_fused_per_cu(8)
+        if d == 128:
+            B.gdn_tune_fused(-1)
+            B.gdn_tune_split(64)
+            assert call_path(call) == "split 64"
         o2, p2 = run_call_gpu(call, pool)
     finally:
         B.gdn_tune_fused(prev)
         B.gdn_tune_fused_per_cu(prev_n)
+        B.gdn_tune_split(-1)
     assert np.array_equal(o1.view(np.uint32), o2.view(np.uint32))
     assert np.array_equal(p1.view(np.uint32), p2.view(np.uint32))
 
@@ -999,8 +1011,8 @@ def test_pipelined_kernel_hands_short_chains_over(d, o_dtype):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("columns", [32, 64])
-@pytest.mark.parametrize("d,H_qk,H_v,o_dtype", [(128, 3, 3, "f32"), (128, 1, 2, "bf16"), (64, 5, 5, "f32"), (64, 2, 4, "bf16")])
+@pytest.mark.parametrize("d,H_qk,H_v,o_dtype,columns", [(128, 3, 3, "f32", 32), (128, 3, 3, "f32", 64), (128, 1, 2, "bf16", 32), (128, 1, 2, "bf16", 64),
+                                                        (64, 5, 5, "f32", 32), (64, 2, 4, "bf16", 32)])
 def test_split_launches_equal_the_fused_kernel_bitwise(d, H_qk, H_v, o_dtype, columns):
     """Operand blocks and recurrence as two launches: chunks that end on 1, 15, 16, 17, 63 and 64 tokens, one-chunk and empty requests,
     more than 64 chunks in a chain (the plan's words are read again), chains that do not fill the last group of eight, with and
@@ -1020,13 +1032,16 @@ def test_split_launches_equal_the_fused_kernel_bitwise(d, H_qk, H_v, o_dtype, co
     pool = rng.standard_normal((nxt + 1,) + call.slot_shape).astype(np.float32) * 0.1
     prev = B.gdn_tune_split(columns)
     try:
+        assert call_path(call, o_dtype) == f"split {columns}"
         check_call(call, pool, TOL["bf16"], o_dtype=o_dtype, scale=0.5)
-        o1, p1 = run_call_gpu(call, pool)
+        o1, p1, n_blocks, n_recur = run_call_counted(call, pool)
     finally:
         B.gdn_tune_split(prev)
+    assert (n_blocks, n_recur) == (1, 1)
     prev, prev_pair = B.gdn_tune_fused(1), B.gdn_tune_fused_pair(0)
     try:
-        o2, p2 = run_call_gpu(call, pool)
+        o2, p2, n_blocks, n_recur = run_call_counted(call, pool)
+        assert (n_blocks, n_recur) == (0, 1)
     finally:
         B.gdn_tune_fused(prev)
         B.gdn_tune_fused_pair(prev_pair)
@@ -1035,13 +1050,12 @@ def test_split_launches_equal_the_fused_kernel_bitwise(d, H_qk, H_v, o_dtype, co
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,H,n_req,tokens,path", [(128, 16, 1, 4000, "two"), (128, 16, 1, 500, "split"), (128, 16, 4, 512, "split"), (128, 13, 8, 300, "split"),
-                                                   (128, 16, 12, 300, "fused"), (64, 16, 1, 4000, "two"), (64, 7, 7, 1000, "split"),
-                                                   (64, 16, 3, 100, "fused")])
+@pytest.mark.parametrize("d,H,n_req,tokens,path", [(128, 16, 1, 4000, "two-kernel"), (128, 16, 1, 500, "split 32"), (128, 16, 4, 512, "split 32"),
+                                                   (128, 13, 8, 300, "split 64"), (128, 16, 12, 300, "pipelined"), (64, 16, 1, 4000, "two-kernel"),
+                                                   (64, 7, 7, 1000, "split 32"), (64, 16, 3, 100, "pipelined")])
 def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
-    """Calls on either side of the lines between the two-kernel path, the split launches and the fused kernel: the automatic choice has the
-    bits of the path it should be (split and fused agree bit for bit: forbidding the split launches tells them apart only by the
-    two-kernel path's own bits), and meets the oracle."""
+    """Calls on either side of the lines between the two-kernel path, the split launches and the pipelined kernel: the automatic choice has the
+    bits of the path it should be (split and pipelined agree bit for bit and differ in their launches, which are counted), and meets the oracle."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(d + H * n_req)
     lens = [tokens - int(x) for x in rng.integers(0, 30, n_req)]
@@ -1049,8 +1063,10 @@ def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
     call = wl.pack_call(1, H, H, d, d, "bf16", per_req, [64] * n_req, [0] * n_req, [[64 + ln] for ln in lens], [[1 + r] for r in range(n_req)],
                         n_req + 1)
     pool = rng.standard_normal((n_req + 1,) + call.slot_shape).astype(np.float32) * 0.1
+    assert call_path(call) == path
     check_call(call, pool, TOL["bf16"])
-    o1, p1 = run_call_gpu(call, pool)
+    o1, p1, n_prep, n_recur = run_call_counted(call, pool)
+    assert path == "two-kernel" or (n_prep, n_recur) == (0 if path == "pipelined" else 1, 1)
     same = []
     for mode in (0, 1):
         prev = B.gdn_tune_fused(mode)
@@ -1059,7 +1075,7 @@ def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
         finally:
             B.gdn_tune_fused(prev)
         same.append(np.array_equal(o1.view(np.uint32), o2.view(np.uint32)) and np.array_equal(p1.view(np.uint32), p2.view(np.uint32)))
-    assert same == [path == "two", path != "two"]
+    assert same == [path == "two-kernel", path != "two-kernel"]
 
 
 @pytest.mark.gpu
