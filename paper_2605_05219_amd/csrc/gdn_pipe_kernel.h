@@ -33,7 +33,8 @@
 // Tried without gain: raised priority of either kind of wave (preparation 0, recurrence 15 % slower); staging in the middle of the
 // preparation (10 %: LDS writes there keep the compiler from reading ahead); V staged behind the update instead of before it (6 %).
 //
-// LDS (PipeSmem<D>: 158 KB at D = 128, 97 KB at D = 64: one workgroup per compute unit): tiles, swizzle and pair tiles as in the fused kernel.
+// LDS (PipeSmem<D>: 150 KB at D = 128, 94 KB at D = 64: one workgroup per compute unit): tiles and swizzle as in the fused kernel, pair tiles unpadded
+// (PairTiles).
 #pragma once
 #include <type_traits>
 #include "gdn_chunk_ops.h"

@@ -152,7 +152,8 @@ __global__ void __launch_bounds__(256 + 4 * CW) __attribute__((amdgpu_waves_per_
     typedef EL::Raw8 Raw8;
     typedef SubstSmem<D, CW> SM;
     constexpr int DK = D, DV = D, MT = D / 16, PCS = D / 8, ROWS = D / 32, NCB = D / CW;
-    constexpr int VP = CW / 32 > 0 ? CW / 32 : 1;     // 16-byte pieces of V per helper thread (CW = 16: half of the threads have one)
+    static_assert(CW == 32 || CW == 64, "whole pieces of V for every helper thread");
+    constexpr int VP = CW / 32;                       // 16-byte pieces of V per helper thread
     constexpr int UP = SM::UNIT_BYTES / 16 / 256;     // pieces of a unit per helper thread
     const int chain = (int)(blockIdx.x / (8 * NCB)) * 8 + (int)(blockIdx.x & 7), col0 = CW * (int)((blockIdx.x >> 3) % NCB);
     if (chain >= a.n_chains) return;
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(256 + 4 * CW) __attribute__((amdgpu_waves_per_
 #pragma unroll
             for (int i = 0; i < VP; ++i) {
                 const int vrow = vr + i * (256 / (CW / 8));
-                if (vrow < 64) stage_piece<SM::VD>(Vt, vraw[set][i], vrow, 8 * vc);
+                stage_piece<SM::VD>(Vt, vraw[set][i], vrow, 8 * vc);
                 __builtin_amdgcn_sched_barrier(0);
                 vraw[set][i] = __builtin_bit_cast(Raw8, __builtin_amdgcn_raw_buffer_load_b128(rv, vrow * v_step + col0 * 2 + vc * 16, 0, 2));
                 __builtin_amdgcn_sched_barrier(0);
