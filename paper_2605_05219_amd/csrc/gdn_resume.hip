@@ -490,9 +490,10 @@ hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, hipStrea
 }
 
 // Single heads at d = 64: three fused workgroups to a compute unit get more chunks done in a time than the pipelined kernel's one
-// workgroup, which takes a chain through twice as fast.  Measured, fused against pipelined (us): units / longest chain = 95
-// (12.3 k units, longest 128 chunks) 485 / 304, 267 (32.8 k, 123) 554 / 406, 549 (67.5 k, 123) 739 / 719, 870 (110 k, 126) 1112 / 1183, 4096 (16.4 k, 4)
-// 208 / 230.  gdn_tune_fused_per_cu, which has a meaning for the fused kernel only, forces that one.
+// workgroup, which takes a chain through twice as fast.  Measured, fused against pipelined (us): units / longest chain = 50
+// (2.8 k units, longest 56 chunks) 206 / 138, 319 (33.8 k, 106) 457 / 357, 512 (64.5 k, 126) 644 / 636, 580 (65.5 k, 113) 651 / 644, 640 (20.5 k, 32) 222 / 232, 768 (24.6 k, 32)
+// 240 / 251, 896 (28.7 k, 32) 342 / 309 (896 chains are two rounds of 768 workgroups), 1180 (90.9 k, 77) 846 / 889, 1843 (232 k, 126) 2064 / 2256, 4096 (131 k, 32) 1280 / 1286.
+// gdn_tune_fused_per_cu, which has a meaning for the fused kernel only, forces that one.
 inline bool fused_piped(const gdn_shape& s, int gv, int64_t total_units, int32_t longest_chain_chunks) {
     if (gv != 1) return false;
     if (s.d_k == 128) return true;
@@ -502,17 +503,14 @@ inline bool fused_piped(const gdn_shape& s, int gv, int64_t total_units, int32_t
 
 // Grouped value heads (H_v a multiple of H_qk): two value heads of one query/key head can share a workgroup of eight waves,
 // which then reads and stages that head's q and k rows once for both (a fifth of a call's bytes with fp32 outputs).  It
-// needs an even group size.  The eight waves move in step, where two workgroups of four on a compute unit overlap each
-// other's phases, so a chunk of a chain takes longer (8.2 against 7.7 us at d = 128) and only calls bound by their
-// volume gain.  Measured at d = 128, 8 query/key heads under 16 value heads, pairs against single heads: 32768 chains of
-// up to 126 chunks 16.3 against 18.2 ms; 8192 chains 4.25 against 4.74; 4096 chains 2.29 against 2.32; 2048 chains 1.36
-// either way; 2048 chains of up to 32 chunks 0.47 against 0.44; 1024 chains of up to 320 chunks 2.66 against 2.50.  At
-// d = 64 a pair's 81 KB of LDS leave a compute unit one workgroup where three single-head ones fit, and pairs never won
-// (9.47 against 9.56 ms on 32768 chains, 1.39 against 1.17 on 4096): forced only.  (Since then the one-head kernel has gained
-// about 10 % and the pair kernel 5 % from changes to their loads and to the order of the chains: on the first of these calls
-// 16.7 against 17.4 ms.  Against the pipelined kernel, which single heads run now, single / pair in us, volume over longest chain at 0.0186 us a unit and
-// 4.6 a chunk: ratio 1.7 (53 k units, longest 126) 1025 / 1093, 1.65 (51 k, 126) 1001 / 1071, 3.4 (107 k, 126) 1978 / 1869, 3.5 (110 k, 126) 2043 / 1952,
-// 4.0 (63 k, 63) 1194 / 1142, 8.3 (16 k, 8) 353 / 338, 16 (66 k, 16) 1284 / 1220: pairs from a ratio of three on.)  gdn_tune_fused_pair forces the choice.
+// needs an even group size.  The eight waves move in step through preparation and recurrence, so a chain takes longer than on the pipelined kernel that runs
+// single heads, and calls bound by their longest chain lose: at d = 128, 8 query/key heads under 16 value heads, fp32 / bf16 outputs, single against pairs in us, volume
+// over longest chain at 0.0186 us a unit and 4.6 a chunk: ratio 0.8 (11 k units, longest 56) 247 / 236 against 431 / 413, 1.4 (14 k, 42) 270 / 258 against 359 / 350, 2.6 (72 k,
+// 113) 1196 / 1142 against 1205 / 1135.  From there on the two are equal within 2 %, the pairs' fewer bytes worth a little with short chains or bf16 outputs, the single heads' pace with long
+// ones: 4.0 (94 k, 95) 1556 / 1483 against 1564 / 1484, 4.0 (281 k, 287) 4589 / 4452 against 4692 / 4430, 7.6 (206 k, 110) 3406 / 3249 against 3394 / 3207, 17 (66 k, 16) 1135 / 1084
+// against 1137 / 1091, 28 (866 k, 126) 14254 / 13531 against 14258 / 13530, 61 (121 k, 8) 2433 / 2324 against 2381 / 2256.  Pairs from a ratio of three on: a fifth less traffic
+// at the same time.  At d = 64 a pair's 81 KB of LDS leave a compute unit one workgroup where three single-head ones fit, and pairs never
+// won (9.47 against 9.56 ms on 32768 chains, 1.39 against 1.17 on 4096): forced only.  gdn_tune_fused_pair forces the choice.
 std::atomic<int32_t> g_forced_pair{-1};
 inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t longest_chain_chunks) {
     if (s.H_qk <= 0 || s.H_v % s.H_qk != 0 || (s.H_v / s.H_qk) % 2 != 0) return 1;
