@@ -367,8 +367,7 @@ int32_t gdn_tune_fused_pair(int32_t mode);
 /*
  * Tuning knob (not a step of the method).  How many workgroups of the fused kernel may share a
  * compute unit: n >= 1 forces that number (more than fit means as many as fit; it also keeps single heads
- * at d = 64 from the pipelined form of the kernel, which has a compute unit to itself, as single heads at d = 128 always
- * have), n < 1 restores the automatic choice.  Outputs are
+ * from the pipelined form of the kernel, which has a compute unit to itself), n < 1 restores the automatic choice.  Outputs are
  * bitwise the same for every setting.  Returns the previous setting (-1 = automatic).
  */
 int32_t gdn_tune_fused_per_cu(int32_t n);

@@ -1,9 +1,9 @@
-// Fused throughput kernel (bf16 inputs; pairs of value heads at d_k = d_v = D = 128, one head or pairs at 64; single heads at
-// D = 128, and calls bound by their longest chain at 64, run gdn_pipe_kernel.h): chunk preparation and recurrence of
+// Fused throughput kernel (bf16 inputs, d_k = d_v = D = 128 or 64; pairs of value heads, and single heads where gdn_pipe_kernel.h
+// is not the better one: short chains, and at D = 64 volume): chunk preparation and recurrence of
 // one chain (request, layer, value head) in ONE workgroup, chunk after chunk, the chunk
 // operands never leaving the compute unit.  HBM sees q, k, v, the gates, o and the states,
 // nothing else.  A chain's chunks are serial, so the kernel only pays when chains are plentiful
-// and none is so long that it outlasts the rest (the host decides).  The grid is persistent (one workgroup of a pair, up to three of one
+// and none is so long that it outlasts the rest (the host decides).  The grid is persistent (one workgroup of a pair, two or three of one
 // head per compute unit); the chains come longest first and are taken in turn by whichever workgroup is free (see the items).
 //
 // Per 64-token chunk, with g the running sum of log a, gam = exp(g), L_ij = b_i exp(g_i - g_j)(k_i.k_j)
@@ -33,7 +33,7 @@
 // V tile, pair tiles, gate vectors and state, and its arithmetic is that of the one-head kernel instruction for instruction.
 // The barriers span all eight waves.
 //
-// LDS (FusedSmem<D, GV>: one head 49 KB, three workgroups per compute unit; a pair 113 KB at D = 128, 81 KB at D = 64, one):
+// LDS (FusedSmem<D, GV>: 73 KB at D = 128, two workgroups per compute unit; 49 KB at D = 64, three; a pair 113 KB / 81 KB, one):
 //   K, Q, V  fp16 [64][D], rows unpadded, the 16-byte pieces of a row XOR-swizzled with the row number (swz):
 //            row reads (lane = token, one piece: the A/B operand of a product over d_k) are free of bank
 //            conflicts, transposing reads (ds_read_b64_tr_b16: lane = column, four tokens: K^T for the state
@@ -95,8 +95,8 @@ struct FusedSmem {
     static constexpr int RESERVE_OFF = HEAD_OFF + GV * HEAD_BYTES;   // one word: the chain the workgroup opens after the next one
     static constexpr int BYTES = RESERVE_OFF + 16;
     static_assert(HEAD_OFF % 16 == 0 && HEAD_BYTES % 16 == 0 && M_OFF % 16 == 0 && P_OFF % 16 == 0 && TF_OFF % 16 == 0 && SM_OFF % 16 == 0, "alignment");
-    static_assert(GV == 2 || (GV == 1 && D == 64), "a pair, or one head at D = 64");
-    static_assert(GV == 2 ? BYTES <= 160 * 1024 : 3 * BYTES <= 160 * 1024, "a pair has a compute unit to itself; three single-head workgroups share one");
+    static_assert(GV == 1 || GV == 2, "one head or a pair");
+    static_assert((GV == 2 ? 1 : D == 128 ? 2 : 3) * BYTES <= 160 * 1024, "a pair has a compute unit to itself; two or three single-head workgroups share one");
     // pair tile index of block (a, c) of M (c < a) and of P (c <= a)
     static constexpr __host__ __device__ int m_pair(int a, int c) { return (a == 1 ? 0 : a == 2 ? 1 : 2) + (c >> 1); }
     static constexpr __host__ __device__ int p_pair(int a, int c) { return (a == 0 ? 0 : a == 1 ? 1 : a == 2 ? 2 : 4) + (c >> 1); }
@@ -154,7 +154,7 @@ __device__ __forceinline__ f32x4 inv16_tiles(const f32x4& d, const f32x4& dt, in
 }
 
 template <bool O_BF16, int D, int GV>
-__global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2, GV == 2 ? 2 : 3))) gdn_fused_kernel(FusedArgs a) {
+__global__ void __launch_bounds__(256 * GV) __attribute__((amdgpu_waves_per_eu(2, (D == 128 || GV == 2) ? 2 : 3))) gdn_fused_kernel(FusedArgs a) {
     typedef Elem<half_t> EL;
     typedef EL::In In;
     typedef EL::Raw8 Raw8;

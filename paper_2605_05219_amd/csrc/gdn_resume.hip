@@ -474,10 +474,10 @@ hipError_t launch_split(const SplitArgs& sa, int d, int cols, hipStream_t stream
 
 std::atomic<int32_t> g_forced_per_cu{-1};
 // gv = value heads per workgroup (1, or 2 when the heads of a pair share a query/key head); fa.n_chains counts groups of gv heads.
-// piped: single heads on the pipelined kernel.  The fused kernel puts as many workgroups on a compute unit as fit;
-// gdn_tune_fused_per_cu forces a number (results are the same for any).
-hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, hipStream_t stream) {
-    const int per_cu = std::max(0, (int)g_forced_per_cu.load());
+// piped: single heads on the pipelined kernel.  The fused kernel puts as many workgroups on a compute unit as fit, or one; gdn_tune_fused_per_cu
+// forces a number (results are the same for any).
+hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, bool one_per_cu, hipStream_t stream) {
+    const int forced = g_forced_per_cu.load(), per_cu = forced >= 1 ? forced : one_per_cu ? 1 : 0;
     if (gv == 2) {
         if (d == 64) return fa.o_bf16 ? launch_fused_t<true, 64, 2>(fa, per_cu, stream) : launch_fused_t<false, 64, 2>(fa, per_cu, stream);
         return fa.o_bf16 ? launch_fused_t<true, 128, 2>(fa, per_cu, stream) : launch_fused_t<false, 128, 2>(fa, per_cu, stream);
@@ -486,19 +486,8 @@ hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, hipStrea
         if (piped) return fa.o_bf16 ? launch_pipe_t<true, 64>(fa, stream) : launch_pipe_t<false, 64>(fa, stream);
         return fa.o_bf16 ? launch_fused_t<true, 64, 1>(fa, per_cu, stream) : launch_fused_t<false, 64, 1>(fa, per_cu, stream);
     }
-    return fa.o_bf16 ? launch_pipe_t<true, 128>(fa, stream) : launch_pipe_t<false, 128>(fa, stream);
-}
-
-// Single heads at d = 64: three fused workgroups to a compute unit get more chunks done in a time than the pipelined kernel's one
-// workgroup, which takes a chain through twice as fast.  Measured, fused against pipelined (us): units / longest chain = 50
-// (2.8 k units, longest 56 chunks) 206 / 138, 319 (33.8 k, 106) 457 / 357, 512 (64.5 k, 126) 644 / 636, 580 (65.5 k, 113) 651 / 644, 640 (20.5 k, 32) 222 / 232, 768 (24.6 k, 32)
-// 240 / 251, 896 (28.7 k, 32) 342 / 309 (896 chains are two rounds of 768 workgroups), 1180 (90.9 k, 77) 846 / 889, 1843 (232 k, 126) 2064 / 2256, 4096 (131 k, 32) 1280 / 1286.
-// gdn_tune_fused_per_cu, which has a meaning for the fused kernel only, forces that one.
-inline bool fused_piped(const gdn_shape& s, int gv, int64_t total_units, int32_t longest_chain_chunks) {
-    if (gv != 1) return false;
-    if (s.d_k == 128) return true;
-    if (g_forced_per_cu.load() >= 1) return false;
-    return total_units * 256 < (int64_t)700 * longest_chain_chunks * chip_cus();
+    if (piped) return fa.o_bf16 ? launch_pipe_t<true, 128>(fa, stream) : launch_pipe_t<false, 128>(fa, stream);
+    return fa.o_bf16 ? launch_fused_t<true, 128, 1>(fa, per_cu, stream) : launch_fused_t<false, 128, 1>(fa, per_cu, stream);
 }
 
 // Grouped value heads (H_v a multiple of H_qk): two value heads of one query/key head can share a workgroup of eight waves,
@@ -520,7 +509,7 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
     return 0.0186 * (double)total_units >= 3.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
 }
 
-// Which implementation a call with bf16 inputs gets, by estimates in us (two_kernel_us, split_us, fused_us) fitted to 442 calls of 8 to 256 chains, even and
+// Which implementation a call with bf16 inputs gets, by estimates in us (two_kernel_us, split_us, pipelined_us, fused_us) fitted to 442 calls of 8 to 256 chains, even and
 // ragged, of 1 to 512 chunks; n chains, u units = (chunk, chain) pairs, l chunks of the longest chain.  The choice was the fastest of the four or within 5 % of it
 // in all but 17 of them, where it was within 11 %.  Measured, two-kernel / pipelined / CW = 64 / CW = 32:
 //   d = 128   8 chains of 64 chunks 91 / 227 / 139 / 117; 16 of 8 31 / 46 / 32 / 28, of 64 99 / 230 / 145 / 122; 32 of 32 79 / 126 / 86 / 74, of 256 608 / 865 / 574 / 495;
@@ -566,6 +555,20 @@ inline double two_kernel_us(bool big, const CallSize& c) {
     }
     return std::max(24.5, us);       // (here and below: under this the launches bound a call)
 }
+// The most chunks that a compute unit's workgroups take one after the other, with `blocks` of them to a chain: up to two each, the longest first, by the lengths.
+inline double most_chunks(const CallSize& c, int64_t blocks, double spread) {
+    const int64_t cus = chip_cus(), wgs = c.n_chains * blocks;
+    double chunks = c.longest;
+    if (wgs > 2 * cus) return std::max(chunks, spread * (double)(c.units * blocks) / (double)cus);
+    const int64_t group = c.heads * blocks;      // workgroups of a request: of one length
+    for (int64_t i = 0; cus + i < wgs;) {
+        const int64_t late = (cus + i) / group, early = (cus - 1 - i) / group;
+        if (late >= (int64_t)c.lens.size()) break;      // (requests without chunks)
+        chunks = std::max(chunks, (double)(c.lens[late] + c.lens[early]));
+        i = std::min((late + 1) * group - cus, cus - early * group);
+    }
+    return chunks;
+}
 // Split launches, cw columns to a workgroup: the blocks of all units, then the most chunks that a compute unit's workgroups take one after the
 // other: up to two workgroups each, the longest first, from the lengths.  At d = 64 the chunks slow down as the call's data outgrow the
 // memory-side cache (1.03 us each up to 6.4 k units, 1.44 from 12 k), at d = 128, with twice the time for a chunk's data, hardly.
@@ -588,10 +591,39 @@ inline double split_us(bool big, int cw, const CallSize& c) {
     else grown = cw == 64 ? 0.09 * clamp01(((double)c.units - 4800.0) / 2400.0) : c.units > 6200 ? 0.045 : 0.0;
     return std::max(24.5, t.start + t.per_unit * (double)c.units + (t.per_chunk + grown) * chunks + (big && wgs > cus ? 4.5 : 0.0));
 }
-// Pipelined or fused: a chain's chunks by how many compute units are busy on average, since the clock goes down with them.
+// Pipelined: a chain's chunks by how many compute units are busy on average, since the clock goes down with them, and the steps in which the pipeline fills.
+inline double pipelined_us(bool big, const CallSize& c) {
+    const double busy = (double)c.units / std::max((double)c.longest, 1.0) / (double)chip_cus();
+    if (big) return std::max(22.0, 20.5 + std::max(per_256(0.0186) * (double)c.units, (3.3 + 1.2 * clamp01(2.0 * busy - 1.0)) * c.longest));
+    return std::max(20.0, 15.0 + (2.36 + 0.3 * clamp01(0.5 * (busy - 1.0))) * most_chunks(c, 1, 1.05));
+}
+// Fused, one head to a workgroup.  d = 128: one or two workgroups to a compute unit?  A chunk takes less time with one, and a call bound by its longest chain is the better for it.  Measured,
+// one / two: 288 ragged chains of up to 4 chunks (592 units) 33 / 37, 432 (816) 40 / 42, 288 even ones 58 / 47, 512 of up to 4 (1232) 45 / 42.
+inline bool fused_one_per_cu(const CallSize& c) {
+    return std::max(5.5 * c.longest, per_256(0.0257) * (double)c.units) < std::max(6.8 * c.longest, per_256(0.0183) * (double)c.units);
+}
+// The longest chain's chunks, slower beside those of the chains that share its compute unit: the lengths say which, or in large calls the mean number of them.
 inline double fused_us(bool big, const CallSize& c) {
-    const double slow = clamp01(2.0 * (double)c.units / std::max((double)c.longest, 1.0) / (double)chip_cus() - 1.0);
-    return std::max(22.0, (big ? 20.5 : 14.0) + std::max(per_256(big ? 0.0186 : 0.0107) * (double)c.units, (big ? 3.3 + 1.2 * slow : 2.33 + 0.4 * slow) * c.longest));
+    const double busy = (double)c.units / std::max((double)c.longest, 1.0) / (double)chip_cus();
+    const int64_t second = chip_cus() / c.heads;         // the request whose chains come second on a compute unit
+    double us;
+    if (c.lens.empty()) us = (big ? std::max(5.5, 1.5 + 4.2 * busy) : std::max(3.55, 2.2 + 1.65 * busy)) * c.longest;
+    else us = (big ? 5.5 : 3.55) * c.longest + (second < (int64_t)c.lens.size() ? (big ? 4.2 : 1.7) * c.lens[second] : 0.0);
+    if (big) return std::max(20.0, 9.0 + (fused_one_per_cu(c) ? std::min(us, 5.5 * most_chunks(c, 1, 1.1)) : us));
+    return std::max(19.0, 7.0 + std::max(us, per_256(0.0102) * (double)c.units));
+}
+// Single heads on the pipelined kernel?  It takes a chain through 1.5 times as fast as the fused kernel with a compute unit to itself, but its first three steps only fill
+// the pipeline, and the fused kernel's workgroups, two to a compute unit at d = 128, three at 64, overlap each other's phases.  Measured, fused / pipelined (us):
+//   d = 128, chains x chunks   192 x 1 21 / 25, x 2 23 / 28, x 4 34 / 35, x 6 45 / 42, x 8 55 / 48; 288 x 1 23 / 31, x 4 47 / 52; 512 x 1 27 / 36, x 4 54 / 59, x 16 158 / 158; 1600 x 1 66 / 78, x 4 163 / 161,
+//       3200 x 1 145 / 140, x 4 307 / 290; ragged 768 of up to 8 (2.3 k units) 70 / 65, 1024 (3.3 k) 88 / 91, 1600 (5.5 k) 136 / 141, 1600 of up to 16 (8.3 k) 189 / 183, of up to 128 (39 k) 896 / 691
+//   d = 64   192 x 4 23 / 25, x 8 38 / 33, x 16 66 / 52; 288 x 2 20 / 25, x 8 48 / 53, x 16 89 / 92; 512 x 8 53 / 57, x 126 644 / 636; 1600 x 4 80 / 97, x 16 276 / 293; ragged 1024 of up to 16 (4.4 k) 76 / 64,
+//       1600 of up to 16 (8.7 k) 98 / 108, of up to 64 (24 k) 293 / 259, 3200 of up to 32 (27 k) 255 / 296; 8192 of up to 126 (232 k) 2064 / 2256
+// gdn_tune_fused_per_cu, which has a meaning for the fused kernel only, forces that one.
+inline bool fused_piped(const gdn_shape& s, int gv, const CallSize& c) {
+    if (gv != 1 || g_forced_per_cu.load() >= 1) return false;
+    if (s.d_k != 128) return pipelined_us(false, c) < fused_us(false, c);
+    const bool short_on_average = 2 * c.units <= 9 * c.n_chains && per_256(0.0186) * (double)c.units >= 1.5 * 4.6 * c.longest;
+    return c.n_chains > 8 * chip_cus() || (c.longest > 4 && !short_on_average);
 }
 // The operand blocks of a call that may run the split launches take at most this much of the workspace: 1 GiB (72 k units), the throughput variants' slab, or what
 // one round of the two-kernel path takes.
@@ -621,7 +653,7 @@ inline CallPath choose_path(const gdn_shape& s, const CallSize& c, int32_t host_
     if (forced_split > 0) return forced_split == 64 ? PATH_SPLIT_64 : PATH_SPLIT_32;
     const bool big = s.d_k == 128;
     CallPath split = PATH_FUSED;
-    double t_split = HUGE_VAL, t_fused = fused_us(big, c);
+    double t_split = HUGE_VAL, t_fused = fused_piped(s, 1, c) ? pipelined_us(big, c) : fused_us(big, c);
     if (forced_split != 0 && c.units <= INT32_MAX && c.units * BlockUnit::BYTES <= split_budget(s, c.n_chains)) {
         split = PATH_SPLIT_32;
         t_split = split_us(big, 32, c);
@@ -971,13 +1003,14 @@ static WsLayout ws_layout(const gdn_shape& s, int64_t n_chunks, int64_t max_roun
 // The implementation a call runs and what it takes of the workspace: [wl.total | staged host states].
 struct Route {
     CallPath path;
+    CallSize size;
     WsLayout wl;
-    int64_t n_units, staging_off, need;
+    int64_t staging_off, need;
     void take(CallPath p, int64_t staged_bytes) {
         path = p;
         if (p != PATH_TWO_KERNEL) {
             wl.carry = wl.slab = wl.n_bufs = 0;
-            wl.total = wl.plan + (p == PATH_FUSED ? 0 : n_units * BlockUnit::BYTES);
+            wl.total = wl.plan + (p == PATH_FUSED ? 0 : size.units * BlockUnit::BYTES);
         }
         staging_off = align_up(wl.total, 256);
         need = staged_bytes > 0 ? staging_off + staged_bytes : wl.total;
@@ -992,12 +1025,13 @@ static Route route_call(const gdn_shape& s, int32_t n_req, const ChunkPlan& plan
     const int64_t state_bytes = (int64_t)s.L * s.H_v * s.d_v * s.d_k * (int64_t)sizeof(float), staged_bytes = staged_states * state_bytes;
     const int32_t n_chunks = (int32_t)plan.chunk_tok0.size();
     const WsLayout full = ws_layout(s, n_chunks, plan.max_chunks_per_req, n_req, &plan);
-    CallSize c;
+    CallSize& c = r.size;
     c.heads = (int64_t)s.L * s.H_v;
     c.n_chains = n_req * c.heads;
-    c.units = r.n_units = n_chunks * c.heads;
+    c.units = n_chunks * c.heads;
     c.longest = plan.max_chunks_per_req;
     if (c.n_chains <= 2 * chip_cus()) {
+        c.lens.reserve(n_req);
         for (int32_t i = 0; i < n_req; ++i)
             if (plan.req_chunk_cu[i + 1] > plan.req_chunk_cu[i]) c.lens.push_back(plan.req_chunk_cu[i + 1] - plan.req_chunk_cu[i]);
         std::sort(c.lens.begin(), c.lens.end(), std::greater<int32_t>());
@@ -1027,8 +1061,8 @@ int32_t gdn_resume_path(const gdn_shape* shape, int32_t n_req, const int32_t* cu
         case PATH_SPLIT_32: return GDN_PATH_SPLIT_32;
         default: break;
     }
-    const int gv = fused_heads_per_wg(s, r.n_units, plan.max_chunks_per_req);
-    return gv == 2 ? GDN_PATH_FUSED_PAIRS : fused_piped(s, gv, r.n_units, plan.max_chunks_per_req) ? GDN_PATH_PIPELINED : GDN_PATH_FUSED;
+    const int gv = fused_heads_per_wg(s, r.size.units, r.size.longest);
+    return gv == 2 ? GDN_PATH_FUSED_PAIRS : fused_piped(s, gv, r.size) ? GDN_PATH_PIPELINED : GDN_PATH_FUSED;
 }
 
 int64_t gdn_workspace_bytes(const gdn_shape* shape, int32_t n_req, int64_t total_tokens, int32_t n_emit) {
@@ -1143,7 +1177,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
     const WsLayout& wl = route.wl;
     const CallPath path = route.path;
     const bool use_fused = path == PATH_FUSED, use_split = path == PATH_SPLIT_64 || path == PATH_SPLIT_32;
-    const int64_t staging_off = route.staging_off, need = route.need, n_units = route.n_units;
+    const int64_t staging_off = route.staging_off, need = route.need, n_units = route.size.units;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return GDN_ERR_WORKSPACE;
     if (workspace_bytes < need) return GDN_ERR_WORKSPACE;
 
@@ -1289,8 +1323,9 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         fa.scale = s.scale;
         fa.o_bf16 = s.o_dtype == GDN_BF16;
         ProfChain prof(stream);
-        const bool piped = fused_piped(s, gv, n_units, plan.max_chunks_per_req);
-        const hipError_t e = launch_fused(fa, s.d_k, gv, piped, stream);
+        const bool piped = fused_piped(s, gv, route.size);
+        const bool one_per_cu = s.d_k == 128 && gv == 1 && fused_one_per_cu(route.size);
+        const hipError_t e = launch_fused(fa, s.d_k, gv, piped, one_per_cu, stream);
         if (e != hipSuccess) return hip_err(e);
         prof.mark(1);
         std::lock_guard<std::mutex> lock(g_prof.mu);

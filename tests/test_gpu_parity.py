@@ -933,10 +933,10 @@ def test_head_pairs_in_one_workgroup_equal_single_heads_bitwise(d, H_qk, H_v):
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [128, 64])
 def test_fused_chains_drawn_from_the_counter_match_the_oracle_for_any_workgroup_count(d):
-    """640 short chains (20 requests, some empty, x 2 layers x 16 heads) on the fused (d = 64) or pipelined (d = 128) kernel with one
-    workgroup per compute unit: the first two rounds of chains are dealt by workgroup number, the rest are drawn from the counter in memory while
-    the kernel runs.  Checked against the oracle, and bit for bit against another assignment of chains to workgroups: the same call with as many workgroups
-    per compute unit as fit, or, where one is all that fits, on the split launches, whose grid has the chains in order."""
+    """640 short chains (20 requests, some empty, x 2 layers x 16 heads) on the fused kernel with one workgroup per compute
+    unit: the first two rounds of chains are dealt by workgroup number, the rest are drawn from the counter in memory while
+    the kernel runs.  Checked against the oracle, and bit for bit against the same call with as many workgroups per compute
+    unit as fit (another grid, another assignment of chains to workgroups)."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(6400 + d)
     L, H, n_req = 2, 16, 20
@@ -956,19 +956,13 @@ def test_fused_chains_drawn_from_the_counter_match_the_oracle_for_any_workgroup_
     prev = B.gdn_tune_fused(1)
     prev_n = B.gdn_tune_fused_per_cu(1)
     try:
-        assert call_path(call) == ("pipelined" if d == 128 else "fused")
         check_call(call, pool, TOL["bf16"])
         o1, p1 = run_call_gpu(call, pool)
         B.gdn_tune_fused_per_cu(8)
-        if d == 128:
-            B.gdn_tune_fused(-1)
-            B.gdn_tune_split(64)
-            assert call_path(call) == "split 64"
         o2, p2 = run_call_gpu(call, pool)
     finally:
         B.gdn_tune_fused(prev)
         B.gdn_tune_fused_per_cu(prev_n)
-        B.gdn_tune_split(-1)
     assert np.array_equal(o1.view(np.uint32), o2.view(np.uint32))
     assert np.array_equal(p1.view(np.uint32), p2.view(np.uint32))
 
@@ -978,12 +972,12 @@ def test_fused_chains_drawn_from_the_counter_match_the_oracle_for_any_workgroup_
 def test_pipelined_kernel_hands_short_chains_over(d, o_dtype):
     """More chains than twice the compute units, most of one or two chunks: the pipeline holds chunks of up to four chains at once,
     with and without a start state, chunks that end on 1, 15, 16, 17, 63 and 64 tokens, emissions in neighbouring steps and
-    the last chains drawn from the counter.  Against the oracle; d = 64 also bit for bit against the fused kernel
-    (gdn_tune_fused_per_cu forces it), which does the same arithmetic."""
+    the last chains drawn from the counter; one longer chain, with which the call is the pipelined kernel's.  Against the oracle, and bit for bit
+    against the fused kernel (gdn_tune_fused_per_cu forces it), which does the same arithmetic."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(7100 + d)
     L, H = 1, 16
-    lens = [300, 0] + [int(x) for x in rng.choice([1, 15, 16, 17, 63, 64, 65, 79, 128], 34)]
+    lens = [900, 0] + [int(x) for x in rng.choice([1, 15, 16, 17, 63, 64, 65, 79, 128], 34)]
     starts = [int(x) for x in rng.choice([0, 64, 100], len(lens))]
     nxt, emits, eslots = 3, [], []
     for s0, ln in zip(starts, lens):
@@ -998,10 +992,12 @@ def test_pipelined_kernel_hands_short_chains_over(d, o_dtype):
     prev = B.gdn_tune_fused(1)
     prev_n = B.gdn_tune_fused_per_cu(-1)
     try:
+        assert call_path(call, o_dtype) == "pipelined"
         check_call(call, pool, TOL["bf16"], o_dtype=o_dtype)
         if o_dtype == "f32":
             o1, p1 = run_call_gpu(call, pool)
             B.gdn_tune_fused_per_cu(8)
+            assert call_path(call, o_dtype) == "fused"
             o2, p2 = run_call_gpu(call, pool)
             assert np.array_equal(o1.view(np.uint32), o2.view(np.uint32))
             assert np.array_equal(p1.view(np.uint32), p2.view(np.uint32))
@@ -1052,10 +1048,10 @@ def test_split_launches_equal_the_fused_kernel_bitwise(d, H_qk, H_v, o_dtype, co
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,H,n_req,tokens,path", [(128, 16, 1, 4000, "two-kernel"), (128, 16, 1, 500, "split 32"), (128, 16, 4, 512, "split 32"),
                                                    (128, 13, 8, 300, "split 64"), (128, 16, 12, 300, "pipelined"), (64, 16, 1, 4000, "two-kernel"),
-                                                   (64, 7, 7, 1000, "split 32"), (64, 16, 3, 100, "pipelined")])
+                                                   (64, 7, 7, 1000, "split 32"), (64, 16, 3, 100, "fused"), (128, 16, 12, 100, "fused")])
 def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
-    """Calls on either side of the lines between the two-kernel path, the split launches and the pipelined kernel: the automatic choice has the
-    bits of the path it should be (split and pipelined agree bit for bit and differ in their launches, which are counted), and meets the oracle."""
+    """Calls on either side of the lines between the two-kernel path, the split launches, the pipelined and the fused kernel: the automatic choice has the
+    bits of the path it should be (all but the first agree bit for bit; split differs in its launches, which are counted), and meets the oracle."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(d + H * n_req)
     lens = [tokens - int(x) for x in rng.integers(0, 30, n_req)]
@@ -1066,7 +1062,7 @@ def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
     assert call_path(call) == path
     check_call(call, pool, TOL["bf16"])
     o1, p1, n_prep, n_recur = run_call_counted(call, pool)
-    assert path == "two-kernel" or (n_prep, n_recur) == (0 if path == "pipelined" else 1, 1)
+    assert path == "two-kernel" or (n_prep, n_recur) == (path.startswith("split"), 1)
     same = []
     for mode in (0, 1):
         prev = B.gdn_tune_fused(mode)

@@ -383,6 +383,13 @@ def test_few_chains_get_the_path_that_was_measured_faster(n_req, H, d, chunks, p
     assert resume_path([64 * chunks] * n_req, 1, H, d, 1 << 32) == path
 
 
+@pytest.mark.parametrize("n_req,d,chunks,path", [(12, 128, 1, "fused"), (24, 128, 4, "fused"), (100, 128, 1, "fused"), (16, 128, 8, "pipelined"), (400, 128, 4, "pipelined"),
+                                                 (40, 128, 32, "pipelined"), (16, 64, 4, "fused"), (100, 64, 8, "fused"), (16, 64, 16, "pipelined"), (32, 64, 126, "pipelined"),
+                                                 (400, 64, 4, "fused")])
+def test_short_chains_get_the_fused_kernel_and_long_ones_the_pipelined(n_req, d, chunks, path):
+    assert resume_path([64 * chunks] * n_req, 1, 16, d, 1 << 32) == path
+
+
 def test_ragged_calls_get_the_path_that_was_measured_faster():
     """64 chains of 37 to 256 chunks (two-kernel path 604 us, split 489) and 256 of 2 to 32 at d = 64 (pipelined 89, split 74)."""
     assert resume_path([64 * c for c in (256, 120, 44, 37)], 1, 16, 128, 1 << 32) == "split 32"
@@ -412,7 +419,7 @@ def test_short_calls_from_a_host_pool_get_the_launches_that_fetch_beside_their_w
     """Copies in front of the fused kernel cost more than the second launch: 15 requests of 2 chunks, 8 heads of 64, 199 us against 49."""
     for n, H, d, chunks in [(3, 16, 64, 2), (15, 8, 64, 2), (7, 16, 128, 128), (15, 8, 64, 128)]:
         lens = [64 * chunks] * n
-        assert resume_path(lens, 1, H, d, queried(lens, 1, H, d)) in ("pipelined", "split 64")
+        assert resume_path(lens, 1, H, d, queried(lens, 1, H, d)) in ("fused", "pipelined", "split 64")
         assert resume_path(lens, 1, H, d, queried(lens, 1, H, d, host=True), n).startswith("split")
 
 
