@@ -510,8 +510,8 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
 }
 
 // Which implementation a call with bf16 inputs gets, by estimates in us (two_kernel_us, split_us, pipelined_us, fused_us) fitted to 442 calls of 8 to 256 chains, even and
-// ragged, of 1 to 512 chunks; n chains, u units = (chunk, chain) pairs, l chunks of the longest chain.  The choice was the fastest of the four or within 5 % of it
-// in all but 17 of them, where it was within 11 %.  Measured, two-kernel / pipelined / CW = 64 / CW = 32:
+// ragged, of 1 to 512 chunks; n chains, u units = (chunk, chain) pairs, l chunks of the longest chain.  The choice was the fastest or within 5 % of it
+// in all but 5 of them, and there within 12 %.  Measured, two-kernel / pipelined / CW = 64 / CW = 32:
 //   d = 128   8 chains of 64 chunks 91 / 227 / 139 / 117; 16 of 8 31 / 46 / 32 / 28, of 64 99 / 230 / 145 / 122; 32 of 32 79 / 126 / 86 / 74, of 256 608 / 865 / 574 / 495;
 //             64 ragged of up to 256 (7.3 k units) 604 / 858 / 577 / 489; 120 of 32 203 / 130 / 117 / 158; 128 of 64 412 / 236 / 250 / 325
 //   d = 64    8 of 32 46 / 89 / - / 49; 32 of 512 691 / 1200 / - / 864; 48 ragged of up to 64 (1.7 k units) 106 / 164 / - / 95; 120 of 32 122 / 93 / - / 81; 128 of 64 266 / 169 / - / 163
@@ -530,30 +530,36 @@ struct CallSize {
 inline double clamp01(double x) { return std::min(1.0, std::max(0.0, x)); }
 inline double per_256(double units) { return units * 256.0 / (double)chip_cus(); }      // (the figures are from 256 compute units)
 inline bool two_kernel_considered(const gdn_shape& s, int64_t n_chains) { return n_chains * (s.d_v / 32) <= chip_cus(); }
-// Two-kernel path, latency variant.  start + per_chunk of the longest chain + per_unit of the preparation; while preparation and recurrence share the chip (up to
-// 32 chains at d = 128, 64 at d = 64), each chunk round takes the longer of the two, and the preparation has the compute units that the recurrence leaves.
-struct TwoKernelRates { double start, per_chunk, per_unit; bool shared; };
+// Two-kernel path, latency variant.  start + per_chunk of the longest chain + beside of every unit (chains that run slow each other down) + the preparation.  While preparation and
+// recurrence share the chip (up to 32 chains at d = 128, 64 at d = 64) a unit of the first slab, which the whole chip prepares, costs `first`, and each chunk round behind it
+// takes the longer of the chain's chunk and per_unit of its units, prepared on the compute units that the recurrence leaves.  Apart, a unit costs `first` up to
+// first_units of them (their images stay in the caches), per_unit beyond.
+struct TwoKernelRates { double start, per_chunk, beside, first, per_unit, first_units; bool shared; };
 inline TwoKernelRates two_kernel_rates(bool big, int64_t n_chains) {
-    const double n = (double)n_chains, cus = (double)chip_cus();
+    const double n = (double)n_chains, cus = (double)chip_cus(), scale = 256.0 / cus;      // (the figures are from 256 compute units)
     if (big) {
-        if (8.0 * n <= cus) return {14.0 + 0.55 * std::min(n, 16.0), 1.2, per_256(0.0735), true};
-        return {18.0, 1.25, per_256(0.0275), false};
+        if (8.0 * n <= cus) return {14.3 + 0.43 * std::min(n, 16.0), 1.02 + 0.0144 * n, 0.0, 0.0, 0.073 * scale, 0.0, true};
+        return {14.9 + 0.112 * n, 1.48, 0.0, 0.0118 * scale, 0.0261 * scale, 1728.0, false};
     }
-    if (4.0 * n <= cus) return {10.0 + 0.6 * std::min(n, 25.0), 1.0, per_256(0.0275) * cus / (cus - 2.0 * n), true};
-    return {18.7, 0.98, per_256(0.0191), false};
+    if (4.0 * n <= cus) return {12.6 + 0.26 * std::min(n, 16.0), 0.865, 0.0098, 0.0074 * scale, 0.0277 * scale * cus / (cus - 2.0 * n), 0.0, true};
+    return {14.9 + 0.047 * n, 1.07, 0.0, 0.0137 * scale, 0.0226 * scale, 2486.0, false};
 }
-inline double two_kernel_us(bool big, const CallSize& c) {
-    const TwoKernelRates t = two_kernel_rates(big, c.n_chains);
-    double us = t.start;
+int32_t auto_slab_rounds(int64_t n_chains, int64_t unit_bytes, int nw, int ns);
+inline double two_kernel_us(const gdn_shape& s, const CallSize& c) {
+    const TwoKernelRates t = two_kernel_rates(s.d_k == 128, c.n_chains);
+    double us = t.start + t.per_chunk * c.longest + t.beside * (double)c.units;
     if (!t.shared) {
-        us += t.per_chunk * c.longest + t.per_unit * (double)c.units;
+        const double first = std::min((double)c.units, t.first_units);
+        us += t.first * first + t.per_unit * ((double)c.units - first);
     } else {
+        const int32_t slab = auto_slab_rounds(c.n_chains, unit_bytes(s), 1, s.d_v / 32);
         for (size_t k = 0; k < c.lens.size(); ++k) {      // the rounds in which requests 0 to k have a chunk
-            const int32_t rounds = c.lens[k] - (k + 1 < c.lens.size() ? c.lens[k + 1] : 0);
-            us += rounds * std::max(t.per_chunk, t.per_unit * (double)((int64_t)(k + 1) * c.heads));
+            const double units = (double)((int64_t)(k + 1) * c.heads);
+            const int32_t next = k + 1 < c.lens.size() ? c.lens[k + 1] : 0, beyond = std::max(c.lens[k], slab) - std::max(next, slab);
+            us += (c.lens[k] - next - beyond) * t.first * units + beyond * std::max(0.0, (t.per_unit - t.beside) * units - t.per_chunk);
         }
     }
-    return std::max(24.5, us);       // (here and below: under this the launches bound a call)
+    return std::max(23.5, us);       // (here and below: under this the launches bound a call)
 }
 // The most chunks that a compute unit's workgroups take one after the other, with `blocks` of them to a chain: up to two each, the longest first, by the lengths.
 inline double most_chunks(const CallSize& c, int64_t blocks, double spread) {
@@ -569,8 +575,7 @@ inline double most_chunks(const CallSize& c, int64_t blocks, double spread) {
     }
     return chunks;
 }
-// Split launches, cw columns to a workgroup: the blocks of all units, then the most chunks that a compute unit's workgroups take one after the
-// other: up to two workgroups each, the longest first, from the lengths.  At d = 64 the chunks slow down as the call's data outgrow the
+// Split launches, cw columns to a workgroup: the blocks of all units, then the chunks of the fullest compute unit.  At d = 64 the chunks slow down as the call's data outgrow the
 // memory-side cache (1.03 us each up to 6.4 k units, 1.44 from 12 k), at d = 128, with twice the time for a chunk's data, hardly.
 struct SplitRates { double start, per_chunk, per_unit; };
 inline SplitRates split_rates(bool big, int cw) {
@@ -579,17 +584,14 @@ inline SplitRates split_rates(bool big, int cw) {
 }
 inline double split_us(bool big, int cw, const CallSize& c) {
     const SplitRates t = split_rates(big, cw);
-    const int64_t cus = chip_cus(), blocks = (big ? 128 : 64) / cw, wgs = c.n_chains * blocks;
-    double chunks = c.longest, grown;
-    if (wgs > 2 * cus) {
-        chunks = std::max(chunks, 1.15 * (double)(c.units * blocks) / (double)cus);
-    } else {
-        auto chunks_of = [&](int64_t wg) { return (size_t)(wg / (c.heads * blocks)) < c.lens.size() ? c.lens[wg / (c.heads * blocks)] : 0; };
-        for (int64_t i = 0; cus + i < wgs; ++i) chunks = std::max(chunks, (double)(chunks_of(cus + i) + chunks_of(cus - 1 - i)));
-    }
+    const int64_t blocks = (big ? 128 : 64) / cw;
+    const double chunks = most_chunks(c, blocks, 1.15);
+    const int64_t rounds = (c.n_chains * blocks + chip_cus() - 1) / chip_cus();
+    const double later = chunks > c.longest ? (big ? 4.5 : 1.2) * (double)(rounds - 1) : 0.0;      // workgroups that start behind others
+    double grown;
     if (!big) grown = 0.41 * clamp01(((double)c.units - 6400.0) / 5600.0);
     else grown = cw == 64 ? 0.09 * clamp01(((double)c.units - 4800.0) / 2400.0) : c.units > 6200 ? 0.045 : 0.0;
-    return std::max(24.5, t.start + t.per_unit * (double)c.units + (t.per_chunk + grown) * chunks + (big && wgs > cus ? 4.5 : 0.0));
+    return std::max(23.5, t.start + t.per_unit * (double)c.units + (t.per_chunk + grown) * chunks + later);
 }
 // Pipelined: a chain's chunks by how many compute units are busy on average, since the clock goes down with them, and the steps in which the pipeline fills.
 inline double pipelined_us(bool big, const CallSize& c) {
@@ -631,15 +633,16 @@ inline int64_t split_budget(const gdn_shape& s, int64_t n_chains) {
     return std::max((int64_t)1 << 30, n_chains * (s.d_v * s.d_k * (int64_t)sizeof(float) + unit_bytes(s)));
 }
 // The most units with which a call of at most max_units can get the split launches, but for their budget.  Where the two-kernel path is considered, few chains
-// get them only while they are short: with k the slope of the chord of max(per_chunk, per_unit x) over 0 to n chains, two_kernel_us is at most
-// start + per_chunk l + k u (the launches' floor is the same), split_us at least start + per_chunk l + per_unit u, and l is at least u / n.
+// get them only while they are short: with k the most that a unit costs beside the longest chain's chunks (in shared launches the slope of the chord of
+// max(per_chunk, per_unit x) over 0 to n chains), two_kernel_us is at most start + per_chunk l + k u (the launches' floor is the same), split_us at least
+// start + per_chunk l + per_unit u, and l is at least u / n.
 inline int64_t split_units_bound(const gdn_shape& s, int64_t n_chains, int64_t max_units) {
     if (!two_kernel_considered(s, n_chains)) return max_units;
     const bool big = s.d_k == 128;
     const double n = (double)std::max<int64_t>(n_chains, 1);
     const TwoKernelRates two = two_kernel_rates(big, n_chains);
     const SplitRates split = split_rates(big, 32);       // (64 columns: a later start and more for a chunk; for a unit the 32 columns' is not the smaller)
-    const double k = two.shared ? std::max(0.0, two.per_unit - two.per_chunk / n) : two.per_unit;
+    const double k = two.beside + (two.shared ? std::max(two.first, two.per_unit - two.beside - two.per_chunk / n) : two.per_unit);
     const double gain = (two.per_chunk - split.per_chunk) / n + k - std::min(split.per_unit, split_rates(big, 64).per_unit);      // of a unit more, at most
     if (gain >= 0.0) return max_units;
     return (int64_t)std::min((double)max_units, std::max(0.0, (two.start - split.start) / -gain));
@@ -660,7 +663,8 @@ inline CallPath choose_path(const gdn_shape& s, const CallSize& c, int32_t host_
         const double t_64 = big ? split_us(big, 64, c) : HUGE_VAL;
         if (t_64 < t_split) { split = PATH_SPLIT_64; t_split = t_64; }
     }
-    if (two_kernel_considered(s, c.n_chains) && two_kernel_us(big, c) < std::min(t_split, t_fused)) return PATH_TWO_KERNEL;
+    // (what is within the estimates' error goes to the path whose workspace does not grow with the call)
+    if (two_kernel_considered(s, c.n_chains) && two_kernel_us(s, c) < 1.04 * std::min(t_split, t_fused)) return PATH_TWO_KERNEL;
     if (host_states > 0) {
         const double mib = (double)state_bytes / (double)(1 << 20);
         t_fused += host_states * (8.0 + 20.0 * mib);
@@ -696,9 +700,7 @@ inline bool latency_shared(int64_t n_chains, int ns) {
 // the 256 compute units); the throughput variants only bound the workspace.  gdn_tune_slab_rounds
 // overrides the choice.
 std::atomic<int32_t> g_forced_rounds{0};
-inline int32_t slab_rounds(int64_t n_chains, int64_t unit_bytes, int nw, int ns) {
-    const int32_t forced = g_forced_rounds.load();
-    if (forced > 0) return forced;
+int32_t auto_slab_rounds(int64_t n_chains, int64_t unit_bytes, int nw, int ns) {
     // Latency variant with launches apart (33 to 64 chains at four slices): every slab costs two launches
     // and a hand-over of the states, so slabs are long (measured at 64 chains: 0.56 ms with 8 rounds, 0.31 ms
     // with 64).
@@ -710,6 +712,10 @@ inline int32_t slab_rounds(int64_t n_chains, int64_t unit_bytes, int nw, int ns)
     const int64_t q = std::max<int64_t>(1, 512 / std::max<int64_t>(1, n_chains));
     r = std::max(q, r / q * q);
     return (int32_t)std::min<int64_t>(r, 1 << 16);
+}
+inline int32_t slab_rounds(int64_t n_chains, int64_t unit_bytes, int nw, int ns) {
+    const int32_t forced = g_forced_rounds.load();
+    return forced > 0 ? forced : auto_slab_rounds(n_chains, unit_bytes, nw, ns);
 }
 
 template <typename E, int DK, int DV>

@@ -149,7 +149,7 @@ def test_destination_may_be_own_source_slot():
 
 
 @pytest.mark.parametrize("n_req,fused,path", [(2, 0, "two-kernel"), (3, 0, "two-kernel"), (4, 0, "two-kernel"), (6, 0, "two-kernel"), (2, -1, "split 32"),
-                                              (3, -1, "split 32"), (4, -1, "split 32"), (6, -1, "split 64"), (12, 0, "two-kernel"), (12, -1, "split 32"),
+                                              (3, -1, "split 32"), (4, -1, "split 32"), (6, -1, "split 64"), (12, 0, "two-kernel"), (12, -1, "split 64"),
                                               (16, 0, "two-kernel"), (16, -1, "pipelined"), (32, 0, "two-kernel"), (32, -1, "pipelined")])
 def test_batch_sizes_cover_every_launch_shape(n_req, fused, path):
     """16 heads x n_req requests.  On the two-kernel path (forced) 32 chains run the latency variant with the next slab's preparation

@@ -391,7 +391,10 @@ def test_short_chains_get_the_fused_kernel_and_long_ones_the_pipelined(n_req, d,
 
 
 def test_ragged_calls_get_the_path_that_was_measured_faster():
-    """64 chains of 37 to 256 chunks (two-kernel path 604 us, split 489) and 256 of 2 to 32 at d = 64 (pipelined 89, split 74)."""
+    """64 chains of 37 to 256 chunks (two-kernel path 604 us, split 489), 256 of 2 to 32 at d = 64 (pipelined 89, split 74), 32 of 19 and 47 (two-kernel path 92, split 98), 48
+    of up to 125 at d = 64 (146 against 164)."""
+    assert resume_path([64 * 47, 64 * 19], 1, 16, 128, 1 << 32) == "two-kernel"
+    assert resume_path([64 * 125, 64 * 3, 64 * 2], 1, 16, 64, 1 << 32) == "two-kernel"
     assert resume_path([64 * c for c in (256, 120, 44, 37)], 1, 16, 128, 1 << 32) == "split 32"
     assert resume_path([64 * c for c in (32, 31, 28, 22, 20, 16, 15, 11, 8, 7, 5, 4, 3, 3, 2, 2)], 1, 16, 64, 1 << 32) == "split 32"
 
