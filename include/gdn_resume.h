@@ -359,7 +359,7 @@ int32_t gdn_tune_split(int32_t columns);
  * kernel can give two value heads of one query/key head a workgroup of eight waves that reads
  * and stages that head's q and k rows once for both.  mode 1 forces pairs wherever the shape
  * allows them, mode 0 forbids them, mode < 0 restores the automatic choice (pairs at d_k = 128
- * when the call is bound by its volume, not by its longest chain).  Outputs are bitwise the same either way:
+ * when the call's volume outweighs its longest chain by far).  Outputs are bitwise the same either way:
  * each head's arithmetic is unchanged.  Returns the previous setting (-1 = automatic).
  */
 int32_t gdn_tune_fused_pair(int32_t mode);

@@ -496,9 +496,10 @@ hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, bool one
 // single heads, and calls bound by their longest chain lose: at d = 128, 8 query/key heads under 16 value heads, fp32 / bf16 outputs, single against pairs in us, volume
 // over longest chain at 0.0186 us a unit and 4.6 a chunk: ratio 0.8 (11 k units, longest 56) 247 / 236 against 431 / 413, 1.4 (14 k, 42) 270 / 258 against 359 / 350, 2.6 (72 k,
 // 113) 1196 / 1142 against 1205 / 1135.  From there on the two are equal within 2 %, the pairs' fewer bytes worth a little with short chains or bf16 outputs, the single heads' pace with long
-// ones: 4.0 (94 k, 95) 1556 / 1483 against 1564 / 1484, 4.0 (281 k, 287) 4589 / 4452 against 4692 / 4430, 7.6 (206 k, 110) 3406 / 3249 against 3394 / 3207, 17 (66 k, 16) 1135 / 1084
-// against 1137 / 1091, 28 (866 k, 126) 14254 / 13531 against 14258 / 13530, 61 (121 k, 8) 2433 / 2324 against 2381 / 2256.  Pairs from a ratio of three on: a fifth less traffic
-// at the same time.  At d = 64 a pair's 81 KB of LDS leave a compute unit one workgroup where three single-head ones fit, and pairs never
+// ones: 4.0 (94 k, 95) 1556 / 1483 against 1564 / 1484, 4.0 (281 k, 287) 4589 / 4452 against 4692 / 4430, 7.6 (206 k, 110) 3406 / 3249 against 3394 / 3207, 28 (866 k, 126) 14254 / 13531
+// against 14258 / 13530, 61 (121 k, 8) 2433 / 2324 against 2381 / 2256.  Even chains lose more, since pairs make half as many, longer pieces to deal out: 1152 of 125 chunks (ratio
+// 4.7) 2468 against 3045, 1792 (7.3) 3588 against 4109, 2304 of 64 (9.3) 2391 against 2630, 3328 of 64 (13) 3448 against 3721, 4096 of 64 (17) 4220 against 4253.  Pairs from a ratio of
+// 16 on.  At d = 64 a pair's 81 KB of LDS leave a compute unit one workgroup where three single-head ones fit, and pairs never
 // won (9.47 against 9.56 ms on 32768 chains, 1.39 against 1.17 on 4096): forced only.  gdn_tune_fused_pair forces the choice.
 std::atomic<int32_t> g_forced_pair{-1};
 inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t longest_chain_chunks) {
@@ -506,7 +507,7 @@ inline int fused_heads_per_wg(const gdn_shape& s, int64_t total_units, int32_t l
     const int forced = g_forced_pair.load();
     if (forced >= 0) return forced != 0 ? 2 : 1;
     if (s.d_k != 128) return 1;
-    return 0.0186 * (double)total_units >= 3.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
+    return 0.0186 * (double)total_units >= 16.0 * 4.6 * (double)longest_chain_chunks ? 2 : 1;
 }
 
 // Which implementation a call with bf16 inputs gets, by estimates in us (two_kernel_us, split_us, pipelined_us, fused_us) fitted to 442 calls of 8 to 256 chains, even and

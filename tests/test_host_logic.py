@@ -390,6 +390,15 @@ def test_short_chains_get_the_fused_kernel_and_long_ones_the_pipelined(n_req, d,
     assert resume_path([64 * chunks] * n_req, 1, 16, d, 1 << 32) == path
 
 
+def test_pairs_of_value_heads_only_where_volume_outweighs_the_longest_chain_by_far():
+    """8 query/key heads under 16 value heads: 1152 even chains of 125 chunks 2.47 ms with single heads, 3.05 in pairs; 32768 chains of 8 2.43 and 2.38."""
+    def path(lens, L):
+        shape = B.make_shape(L, 8, 16, 128, 128, "bf16", "f32", sum(lens))
+        return B.gdn_resume_path(shape, np.concatenate([[0], np.cumsum(lens)]), [0] * len(lens), [0] * (len(lens) + 1), [], 1 << 34)
+    assert path([8000] * 24, 3) == "pipelined"
+    assert path([512] * 256, 8) == "fused pairs"
+
+
 def test_ragged_calls_get_the_path_that_was_measured_faster():
     """64 chains of 37 to 256 chunks (two-kernel path 604 us, split 489), 256 of 2 to 32 at d = 64 (pipelined 89, split 74), 32 of 19 and 47 (two-kernel path 92, split 98), 48
     of up to 125 at d = 64 (146 against 164)."""
