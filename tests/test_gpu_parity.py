@@ -861,12 +861,13 @@ def test_seeded_random_calls_match_the_oracle(many):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("pair", [0, 1])
-def test_seeded_random_calls_on_the_fused_kernel(pair):
+@pytest.mark.parametrize("pair,longest", [(0, 0), (1, 0), (0, 650)])
+def test_seeded_random_calls_on_the_fused_kernel(pair, longest):
     """The fused kernel forced onto small seeded calls it would not be chosen for: both head sizes, one value head (an
     output row is then exactly as long as the output descriptor's last row), grouped value heads (one head per workgroup,
     and two heads of a query/key head per workgroup where the group size is even), chunks of 1 to 64 tokens, requests of
-    length 0, several layers, emits anywhere, both output types."""
+    length 0, several layers, emits anywhere, both output types.  With one request of 650 tokens the single heads are the pipelined
+    kernel's."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(9090)
     shapes = [(1, 1, 1, 128), (1, 1, 2, 128), (2, 1, 1, 64), (1, 2, 4, 128), (3, 2, 2, 64), (1, 4, 4, 128), (2, 2, 8, 64),
@@ -878,6 +879,8 @@ def test_seeded_random_calls_on_the_fused_kernel(pair):
             L, H_qk, H_v, d = shapes[it % len(shapes)]
             n_req = int(rng.integers(1, 7))
             lens = [int(x) for x in rng.choice([0, 1, 2, 15, 16, 17, 63, 64, 65, 100, 129, 200], n_req)]
+            if longest:
+                lens[-1] = longest
             if sum(lens) == 0:
                 lens[0] = 3
             starts = [int(x) for x in rng.choice([0, 0, 64, 100, 512], n_req)]
@@ -891,6 +894,8 @@ def test_seeded_random_calls_on_the_fused_kernel(pair):
             src = [-1 if s0 == 0 else int(rng.integers(0, 3)) for s0 in starts]
             call = wl.pack_call(L, H_qk, H_v, d, d, "bf16", per_req, starts, src, emits, eslots, nxt + 1)
             pool = rng.standard_normal((nxt + 1,) + call.slot_shape).astype(np.float32) * 0.1
+            if longest:
+                assert call_path(call) == "pipelined"
             check_call(call, pool, TOL["bf16"], o_dtype="bf16" if it % 2 else "f32")
     finally:
         B.gdn_tune_fused(prev)
@@ -1076,14 +1081,14 @@ def test_automatic_choice_of_the_path(d, H, n_req, tokens, path):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("fused", [0, 1])
-def test_extreme_gates(fused, d):
+@pytest.mark.parametrize("fused,n,path", [(0, 200, "two-kernel"), (1, 200, "fused"), (1, 700, "pipelined")])
+def test_extreme_gates(fused, n, path, d):
     """Gates that forget within one token (a = 1e-30, below what the clamp of log a lets through unchanged), gates of
     exactly 1, and ordinary ones mixed token by token, with beta at 0 and 1 among them: the decay factors between blocks
     may underflow but must never turn into infinities or NaNs, and a forgotten state must really be gone."""
     from paper_2605_05219_amd import binding as B
     rng = np.random.default_rng(31337)
-    L, H, n = 1, 2, 200
+    L, H = 1, 2
     st = wl.token_streams(rng, L, n, H, H, d, d, "bf16")
     gate = wl.to_f32(st.gate).copy()
     beta = wl.to_f32(st.beta).copy()
@@ -1094,10 +1099,11 @@ def test_extreme_gates(fused, d):
     beta[rng.integers(0, 6, beta.shape) == 0] = 0.0
     beta[rng.integers(0, 6, beta.shape) == 0] = 1.0
     st = wl.Streams(st.q, st.k, st.v, wl.to_storage(beta, "bf16"), wl.to_storage(gate, "bf16"))
-    call = wl.pack_call(L, H, H, d, d, "bf16", [st], [64], [1], [[100, 264]], [[2, 3]], 5)
+    call = wl.pack_call(L, H, H, d, d, "bf16", [st], [64], [1], [[100, 64 + n]], [[2, 3]], 5)
     pool = (rng.standard_normal((5,) + call.slot_shape) * 0.5).astype(np.float32)
     prev = B.gdn_tune_fused(fused)
     try:
+        assert call_path(call) == path
         check_call(call, pool, TOL["bf16"])
     finally:
         B.gdn_tune_fused(prev)
