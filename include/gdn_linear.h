@@ -21,7 +21,7 @@
  *   K a multiple of 64; x, w 16-byte aligned with ldx, ldw multiples of 8; y 8-byte aligned (bf16)
  *   or 16-byte aligned (fp32) with ldy a multiple of 4.  T = 0 or N = 0 is legal and does nothing.
  * Arithmetic: bf16 products on the matrix cores, fp32 accumulation over k in the order of the
- * k index by blocks of 16; the bias is added in fp32; one rounding to out_dtype.
+ * k index by blocks of 32; the bias is added in fp32; one rounding to out_dtype.
  * Errors: GDN_ERR_NULL, GDN_ERR_ALIGN, GDN_ERR_SHAPE (K not a multiple of 64, a leading dimension
  * smaller than its row, an unknown out_dtype), GDN_ERR_COUNT (a negative size, or a leading dimension of 4 Mi
  * elements and more: a 256-row tile is addressed with 31-bit byte offsets).
@@ -60,13 +60,13 @@ int32_t gdn_linear_split(const void *x, int64_t ldx, const void *w, int64_t ldw,
 /*
  * The launches gdn_linear and gdn_linear_split make for a problem (host only; for tests and for callers that want to see
  * them): outputs 0 .. *cols - 1 in tile shape *shape and, where *cols < N, the others in a second launch in *rest_shape (shape
- * numbers as for gdn_linear_tune).  T, N, K positive (else GDN_ERR_COUNT), K a multiple of 64 (else GDN_ERR_SHAPE).
+ * numbers as for gdn_linear_tune; the two forms of shape 0, 4 and 5, are reported as 0).  T, N, K positive (else GDN_ERR_COUNT), K a multiple of 64 (else GDN_ERR_SHAPE).
  */
 int32_t gdn_linear_plan(int64_t T, int32_t N, int32_t K, int32_t *shape, int32_t *cols, int32_t *rest_shape);
 
 /*
  * Tuning knob, not a method step: fixes the workgroup tile gdn_linear uses (0: 128 x 128; 1: 256 x 256 with four
- * waves; 2: 256 x 256 with eight waves; 3: 64 x 64; anything else: chosen per call from T, N and K, the default, which
+ * waves; 2: 256 x 256 with eight waves; 3: 64 x 64; 4: 128 x 128 with more k steps in flight; 5: 4 with 160 outputs; anything else: chosen per call from T, N and K, the default, which
  * may also cut a large problem into two column ranges, a launch each).  Every shape computes the same
  * sums in the same order, so the results do not depend on it.  Process-wide; returns the previous setting (-1 = per
  * call).

@@ -1,19 +1,24 @@
 // gdn_linear: the layers' projections y = x w^T + bias on the bf16 matrix cores (see include/gdn_linear.h).
 //
 // One workgroup of four or eight waves makes a BM (tokens) x BN (outputs) tile, a wave its part of it as tiles of
-// v_mfma_f32_32x32x16_bf16.  Both operands are read along k, so a k step of BK needs a BM x BK tile of x and a
+// v_mfma_f32_16x16x32_bf16.  Both operands are read along k, so a k step of BK needs a BM x BK tile of x and a
 // BN x BK tile of w; they come from memory with 16-byte buffer loads straight to LDS (no registers) into a ring of
-// STAGES stages, STAGES - 1 k steps ahead of the matrix cores: one barrier per k step.  Four shapes are built:
-//   0: 128 x 128 x 64, 2 stages, four waves, two workgroups per compute unit   small problems (more, smaller workgroups)
-//   1: 256 x 256 x 32, 4 stages, four waves, one workgroup per compute unit: a wave holds 128 x 128 outputs in 256
-//      accumulator registers: half the operand bytes per flop, from memory and from LDS, three k steps of loads in flight
+// STAGES stages, STAGES - 1 k steps ahead of the matrix cores: one barrier per k step.  The shapes that are built:
+//   0: 128 x 128 x 64, 2 stages, four waves, two workgroups per compute unit   many small tiles: one workgroup's waits under the other's products
+//   1: 256 x 256 x 64, 2 stages, four waves, one workgroup per compute unit: a wave holds 128 x 128 outputs in 256
+//      accumulator registers: fewer operand bytes from LDS per flop, one wave per SIMD (kept for comparison: within 3 % of 2 either way)
 //   2: 256 x 256 x 64, 2 stages, eight waves of 128 tokens x 64 outputs, two per SIMD: while one wave of a SIMD is held up
-//      issuing its loads to LDS the other feeds the matrix pipe, and a barrier covers 64 of k (the default for large
-//      problems; 1 is kept for comparison)
-//   3: 64 x 64 x 64, 5 stages, four waves of one 32 x 32 tile, two workgroups per compute unit: problems whose 64 x 64 tiles fit
-//      the chip in one round, where a larger tile would walk k on too few compute units (512 x 2048 x 2048 11.7 us against 17 of
-//      shape 0; 64 x 64 x 128 in 4 stages with one workgroup per compute unit, the form before this one, 12.1, and with 257 to
-//      512 tiles, its second round, 21 against 14 us)
+//      issuing its loads to LDS the other feeds the matrix pipe, and a barrier covers 64 of k (the default for large problems)
+//   3: 64 x 64 x 64, 5 stages, four waves of 32 x 32 outputs, two workgroups per compute unit: problems whose 64 x 64 tiles fit
+//      the chip in one round, where a larger tile would walk k on too few compute units (512 x 2048 x 2048 9.9 us against 16 of
+//      shape 4 and 21 of shape 0)
+//   4: 128 x 128 x 64, 4 stages, eight waves, one workgroup per compute unit: problems of at most one round of such tiles are bound by
+//      the latency of a k step's loads (0.9 us where the weights come from memory), of which this shape has three in flight
+//      (384 x 8224 x 2048 23 us against 31 of shape 0)
+//   5: 128 x 160 x 64, 4 stages, four waves, one workgroup per compute unit: the same for problems that shape 4 just does not
+//      fit in one round (512 x 8224: 260 tiles of 128 outputs for 256 compute units, 208 of 160; 27 us against 36 of shape 4, 32 of shape 0)
+// The products are v_mfma_f32_16x16x32_bf16: half the accumulator traffic per flop of the 32 x 32 x 16 instruction, at the same rate on
+// paper; on a chip held by its power limit 8192 x 2048 x 2048 takes 51 us with it and 56 with the other, 512 x 2048 10.4 and 12.3.
 // A load to LDS writes a wave's 1 KiB contiguously (lane i at 16 i), so rows are unpadded (2 BK bytes) and bank
 // conflicts are avoided by choosing WHICH 16-byte piece of its row a lane fetches: piece p of row r is stored at
 // position p ^ swz(r), swz(r) = (r / rows per 256 bytes) % pieces per row, which makes the 16 lanes that read the
@@ -36,7 +41,6 @@ namespace linear {
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 
@@ -78,17 +82,19 @@ struct LinCfg {
     static constexpr int ROWS_PER_LOAD = 1024 / RB;    // rows a wave-wide load covers
     static constexpr int X_BYTES = BM * RB, W_BYTES = BN * RB, STAGE_BYTES = X_BYTES + W_BYTES;
     static constexpr int SMEM = STAGES * STAGE_BYTES;
-    static constexpr int TI = WM / 32, TJ = WN / 32;   // 32 x 32 tiles of a wave along tokens / outputs
+    static constexpr int TI = WM / 16, TJ = WN / 16;   // 16 x 16 tiles of a wave along tokens / outputs
     static constexpr int XL = BM / ROWS_PER_LOAD / NW, WL = BN / ROWS_PER_LOAD / NW;   // loads per wave and stage
     static constexpr int LPS = XL + WL;
     static constexpr int AHEAD = (STAGES - 2) * LPS;   // loads that may still be in flight when a stage is handed over
-    static_assert(PP * RL == 16 && (STAGES - 1) * LPS < 64 && SMEM <= 160 * 1024 && (BK / 16) % 2 == 0 &&
-                  ((TI * TJ) % LPS == 0 || LPS % (TI * TJ) == 0) && XL >= 1 && WL >= 1, "tile shape");
+    static_assert(PP * RL == 16 && (STAGES - 1) * LPS < 64 && SMEM * WGS_PER_CU <= 160 * 1024 && (BK / 32) % 2 == 0 &&
+                  XL * ROWS_PER_LOAD * NW == BM && WL * ROWS_PER_LOAD * NW == BN && TI * 16 == WM && TJ * 16 == WN, "tile shape");
 };
 typedef LinCfg<128, 128, 64, 2, 2, 2, 2> LinSmall;
-typedef LinCfg<256, 256, 32, 4, 1, 2, 2> LinBig;      // four waves, 128 x 128 outputs each
+typedef LinCfg<256, 256, 64, 2, 1, 2, 2> LinBig;      // four waves, 128 x 128 outputs each
 typedef LinCfg<256, 256, 64, 2, 1, 2, 4> LinBig8;     // eight waves, 128 tokens x 64 outputs each: two waves per SIMD
-typedef LinCfg<64, 64, 64, 5, 2, 2, 2> LinTiny;       // four waves of one 32 x 32 tile each, four k steps of 64 in flight
+typedef LinCfg<64, 64, 64, 5, 2, 2, 2> LinTiny;       // four waves of 32 x 32 outputs each, four k steps of 64 in flight
+typedef LinCfg<128, 128, 64, 4, 1, 2, 4> LinDeep;     // eight waves, 64 x 32 outputs each, three k steps of 64 in flight
+typedef LinCfg<128, 160, 64, 4, 1, 2, 2> LinWide;     // four waves, 64 x 80 outputs each, three k steps of 64 in flight
 
 // The loads of one wave for one stage: 1 KiB each, XL of its quarter of the x tile, then WL of the w tile.
 template <typename CFG>
@@ -123,12 +129,18 @@ gdn_linear_kernel(LinearArgs a) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / CFG::WAVES_N, wn = wave % CFG::WAVES_N;   // the wave's part: tokens WM wm .., outputs WN wn ..
-    const int lr = lane & 31, g = lane >> 5;
+    const int lr = lane & 15, g = lane >> 4;
     // ---- which tile.  Workgroups are dealt to the 8 XCDs (each with an L2 of its own) in turn: XCD x takes a consecutive run of the
     // tiles, which are numbered GROUP_M tile rows at a time, down the rows first, so that the tiles an XCD works on together
     // share their rows of x and of w in its L2.  (Row by row over the whole output, an XCD's 32 tiles touched nearly every row of w.)
     constexpr int GROUP_M = CFG::BM == 256 ? 4 : 8;
-    const int seq = ((int)blockIdx.x & 7) * a.per_xcd + ((int)blockIdx.x >> 3);
+    // Each XCD enters its run an eighth further on than the one before: XCDs that walk the same columns in step would all wait for the
+    // same cold rows of w on every k step; so a row comes from memory for one or two of them and from the memory-side cache for
+    // the others (8192 x 8192 x 2048 with cold weights 226 -> 209 us; 197 with warm ones either way).
+    const int xcd = (int)blockIdx.x & 7;
+    int in_run = ((int)blockIdx.x >> 3) + xcd * a.per_xcd / 8;
+    if (in_run >= a.per_xcd) in_run -= a.per_xcd;
+    const int seq = xcd * a.per_xcd + in_run;
     if (seq >= a.tiles_m * a.tiles_n) return;      // (the grid is 8 per_xcd)
     const int grp = seq / (GROUP_M * a.tiles_n), in_grp = seq % (GROUP_M * a.tiles_n);
     const int grp_rows = min(a.tiles_m - grp * GROUP_M, GROUP_M);
@@ -155,20 +167,20 @@ gdn_linear_kernel(LinearArgs a) {
         const int row = (BN / CFG::NW) * wave + RPL * j + ld_row;
         woff[j] = (int)(row * a.ldw * 2) + ((ld_pos ^ ((row / RL) % PP)) << 4);
     }
-    f32x16 acc[TJ][TI];          // [output tile][token tile]: lane = token, register 4 b + e = output 8 b + 4 g + e
+    f32x4 acc[TJ][TI];           // [output tile][token tile]: lane lr = token, register e = output 4 g + e
 #pragma unroll
     for (int i = 0; i < TJ; ++i)
 #pragma unroll
         for (int j = 0; j < TI; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
-    // fragment reads: row r of a tile, piece 2 kk + g, stored at (2 kk + g) ^ swz(r); tile origins are multiples of 16 rows
-    const int sw = (lr % 16) / RL;
+    // fragment reads: row r of a tile, piece 4 kk + g, stored at (4 kk + g) ^ swz(r); tile origins are multiples of 16 rows
+    const int sw = lr / RL;
     const int xrow = (CFG::WM * wm + lr) * RB, wrow = (CFG::WN * wn + lr) * RB;
     const int n_steps = a.K / BK;
-    constexpr int KK = BK / 16;              // matrix-instruction steps per stage (2 or 4)
-    // The stages are consumed through two fragment sets: while the matrix cores work on one k step of 16, the fragments of
+    constexpr int KK = BK / 32;              // matrix-instruction steps per stage (even)
+    // The stages are consumed through two fragment sets: while the matrix cores work on one k step of 32, the fragments of
     // the next are read from LDS, also across the stage boundary.  The hand-over of a stage therefore sits before the LAST
     // k step of the stage in front of it: wait for this wave's loads of the next stage, for its own fragment reads, then the
     // barrier; after it the next stage is readable by every wave and the current one (whose last fragments are in
@@ -177,11 +189,11 @@ gdn_linear_kernel(LinearArgs a) {
     auto read_frags = [&](int stage, int kk, int set) {
         const char* xs = smem + stage * CFG::STAGE_BYTES;
         const char* ws = xs + CFG::X_BYTES;
-        const int pos = ((2 * kk + g) ^ sw) * 16;
+        const int pos = ((4 * kk + g) ^ sw) * 16;
 #pragma unroll
-        for (int t = 0; t < TI; ++t) xf[set][t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 32 * t * RB + pos));
+        for (int t = 0; t < TI; ++t) xf[set][t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 16 * t * RB + pos));
 #pragma unroll
-        for (int t = 0; t < TJ; ++t) wf[set][t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 32 * t * RB + pos));
+        for (int t = 0; t < TJ; ++t) wf[set][t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 16 * t * RB + pos));
     };
     // Loads are issued for every stage slot, also past the last k step: there the descriptor is empty and the scalar offset
     // zero (no lane is in range by definition, nothing is fetched), so that the number of loads in flight, and with it every
@@ -191,7 +203,7 @@ gdn_linear_kernel(LinearArgs a) {
         for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti)
-                acc[tj][ti] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][tj], xf[set][ti], acc[tj][ti], 0, 0, 0);
+                acc[tj][ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[set][tj], xf[set][ti], acc[tj][ti], 0, 0, 0);
     };
 #pragma unroll
     for (int p = 0; p < STAGES; ++p) {
@@ -213,18 +225,18 @@ gdn_linear_kernel(LinearArgs a) {
             const int rs = (kk & 1) ^ 1, ms = kk & 1;
             const char* xs = smem + stage * CFG::STAGE_BYTES;
             const char* ws = xs + CFG::X_BYTES;
-            const int pos = ((2 * (kk + 1) + g) ^ sw) * 16;
+            const int pos = ((4 * (kk + 1) + g) ^ sw) * 16;
             constexpr int NM = TI * TJ, NR = TI + TJ;
             constexpr int SLOTS = NM < NR ? NM : NR;
 #pragma unroll
             for (int i = 0; i < SLOTS; ++i) {
 #pragma unroll
                 for (int q = i * NM / SLOTS; q < (i + 1) * NM / SLOTS; ++q)
-                    acc[q / TI][q % TI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ms][q / TI], xf[ms][q % TI], acc[q / TI][q % TI], 0, 0, 0);
+                    acc[q / TI][q % TI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ms][q / TI], xf[ms][q % TI], acc[q / TI][q % TI], 0, 0, 0);
 #pragma unroll
                 for (int r = i * NR / SLOTS; r < (i + 1) * NR / SLOTS; ++r) {
-                    if (r < TI) xf[rs][r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 32 * r * RB + pos));
-                    else wf[rs][r - TI] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 32 * (r - TI) * RB + pos));
+                    if (r < TI) xf[rs][r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 16 * r * RB + pos));
+                    else wf[rs][r - TI] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 16 * (r - TI) * RB + pos));
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -247,16 +259,16 @@ gdn_linear_kernel(LinearArgs a) {
             const char* ws = xs + CFG::X_BYTES;
             const int pos = (g ^ sw) * 16;
             constexpr int NM = TI * TJ, NL = CFG::LPS, NR = TI + TJ;
-            constexpr int SLOTS = NM < NL ? NM : NL;             // interleave slots
+            constexpr int SLOTS = NM < (NL > NR ? NL : NR) ? NM : (NL > NR ? NL : NR);   // interleave slots
 #pragma unroll
             for (int i = 0; i < SLOTS; ++i) {
 #pragma unroll
                 for (int q = i * NM / SLOTS; q < (i + 1) * NM / SLOTS; ++q)
-                    acc[q / TI][q % TI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[1][q / TI], xf[1][q % TI], acc[q / TI][q % TI], 0, 0, 0);
+                    acc[q / TI][q % TI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[1][q / TI], xf[1][q % TI], acc[q / TI][q % TI], 0, 0, 0);
 #pragma unroll
                 for (int r = i * NR / SLOTS; r < (i + 1) * NR / SLOTS; ++r) {
-                    if (r < TI) xf[0][r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 32 * r * RB + pos));
-                    else wf[0][r - TI] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 32 * (r - TI) * RB + pos));
+                    if (r < TI) xf[0][r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 16 * r * RB + pos));
+                    else wf[0][r - TI] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 16 * (r - TI) * RB + pos));
                 }
 #pragma unroll
                 for (int j = i * NL / SLOTS; j < (i + 1) * NL / SLOTS; ++j)
@@ -282,11 +294,11 @@ gdn_linear_kernel(LinearArgs a) {
     constexpr int ES = OUT_BF16 ? 2 : 4;
     constexpr int WN = CFG::WN, WM = CFG::WM;                      // the wave's outputs and tokens
     constexpr int REGION = CFG::SMEM / CFG::NW;                    // the wave's part of the ring
-    constexpr int PW = (WN * ES <= 256) ? WN : 256 / ES;           // outputs per pass: a row of at most 256 bytes
-    constexpr int RBY = PW * ES, PPR = RBY / 16;                   // row bytes, 16-byte pieces per row
+    constexpr int PW = WN * ES <= 256 ? WN : WN % (256 / ES) == 0 ? 256 / ES : 16;   // outputs per pass: a row of at most 256 bytes
+    constexpr int RBY = PW * ES <= 64 ? 64 : PW * ES <= 128 ? 128 : 256, PPR = RBY / 16;   // row bytes (a power of two), 16-byte pieces per row
     constexpr int RPI = 1024 / RBY;                                // rows a wave-wide 16-byte access covers
-    constexpr int TP = (WM * RBY <= REGION) ? WM : REGION / RBY;   // tokens per pass
-    static_assert(TP % 32 == 0 && TP >= 32 && WM % TP == 0 && WN % PW == 0 && PW % 32 == 0, "epilogue region");
+    constexpr int TP = (WM * RBY <= REGION) ? WM : REGION / RBY >= 64 ? 64 : 32;   // tokens per pass
+    static_assert(TP * RBY <= REGION && TP % RPI == 0 && WM % TP == 0 && WN % PW == 0 && PW % 16 == 0, "epilogue region");
     wait_vm<0>();
     __syncthreads();
     char* const reg = smem + wave * REGION;
@@ -297,33 +309,31 @@ gdn_linear_kernel(LinearArgs a) {
 #pragma unroll
         for (int t0 = 0; t0 < WM; t0 += TP) {
 #pragma unroll
-            for (int tj = c0 / 32; tj < (c0 + PW) / 32; ++tj)
+            for (int tj = c0 / 16; tj < (c0 + PW) / 16; ++tj) {
+                const int cl = 16 * tj + 4 * g;                    // first of the lane's four outputs, within the wave's part
+                f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+                if (a.bias) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int cl = 32 * tj + 8 * b + 4 * g;        // first of the lane's four outputs, within the wave's part
-                    f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-                    if (a.bias) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col0 + cl + e < a.N) bv[e] = a.bias[col0 + cl + e];
-                    }
-#pragma unroll
-                    for (int ti = t0 / 32; ti < (t0 + TP) / 32; ++ti) {
-                        const int row = 32 * ti + lr - t0;
-                        f32x4 v = {acc[tj][ti][4 * b] + bv[0], acc[tj][ti][4 * b + 1] + bv[1], acc[tj][ti][4 * b + 2] + bv[2], acc[tj][ti][4 * b + 3] + bv[3]};
-                        const int byte = (cl - c0) * ES;
-                        char* const dst = reg + row * RBY + (((byte >> 4) ^ (row % PPR)) << 4) + (byte & 15);
-                        if (OUT_BF16) *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v, bf16x4);
-                        else *reinterpret_cast<f32x4*>(dst) = v;
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (col0 + cl + e < a.N) bv[e] = a.bias[col0 + cl + e];
                 }
+#pragma unroll
+                for (int ti = t0 / 16; ti < (t0 + TP) / 16; ++ti) {
+                    const int row = 16 * ti + lr - t0;
+                    f32x4 v = {acc[tj][ti][0] + bv[0], acc[tj][ti][1] + bv[1], acc[tj][ti][2] + bv[2], acc[tj][ti][3] + bv[3]};
+                    const int byte = (cl - c0) * ES;
+                    char* const dst = reg + row * RBY + (((byte >> 4) ^ (row % PPR)) << 4) + (byte & 15);
+                    if (OUT_BF16) *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v, bf16x4);
+                    else *reinterpret_cast<f32x4*>(dst) = v;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < TP / RPI; ++i) {
                 const int row = RPI * i + lane / PPR, piece = lane % PPR;
                 const u32x4 val = *reinterpret_cast<const u32x4*>(reg + row * RBY + ((piece ^ (row % PPR)) << 4));
                 const int64_t tok = tok0 + t0 + row;
                 const int col = col0 + c0 + piece * (16 / ES);
-                if (tok < a.T && col < a.N) {
+                if (tok < a.T && col < a.N && (RBY == PW * ES || piece * 16 < PW * ES)) {
                     // the destination of this piece: the whole output, or the segment its first column lies in (segment
                     // boundaries are multiples of 8 columns, so a piece lies in one segment)
                     char* base = reinterpret_cast<char*>(a.y);
@@ -385,12 +395,16 @@ int chip_cus_linear() {
 
 // The estimated time of a problem in a tile shape, in us at K = 2048: full rounds of workgroups over the chip, and a last one that
 // costs its latency (a workgroup alone walks k no faster) and more the fuller it is: the compute units share power and memory.
-// Fitted to T = 64 .. 8192, N = 32 .. 8224 (estimate against measured: 8192 x 8192 in shape 2 216 / 213, 8192 x 2560 91 / 93,
-// 4096 x 2560 43 / 43; in shape 0 8192 x 2560 87 / 84, 2048 x 8224 80 / 80, 512 x 8224 24 / 26; in shape 3 1024 x 2048 14.5 / 15.5).
-// All with the operands of the call before, in the caches: in a layer group's pass, each layer's weights cold, the small problems
-// take longer than the estimate says (512 x 8224 in shape 0 34 to 35 us, 512 x 2048 in shape 3 13, 512 x 2560 17).
+// Fitted to T = 64 .. 8192, N = 2048 .. 8224, all shapes at each, the weights of the larger N not in the caches (a round then takes 4
+// to 7 us more, in every shape).  us, in shapes 3 / 0 / 4 / 5 / 2: 512 x 2048 9.9 / 21 / 16 / 20 / 39, 1400 x 2048 21 / 24 / 18 /
+// 21 / 40, 700 x 6144 38 / 32 / 34 / 25 / 50, 384 x 8224 31 / 31 / 23 / 27 / 50, 512 x 8224 40 / 32 / 36 / 27 / 51, 2048 x 6144
+// 78 / 58 / 63 / 67 / 51, 8192 x 2048 101 / 60 / 73 / 85 / 52, 8192 x 6144 299 / 181 / 217 / 219 / 154.
 struct ShapeCost { int id, bm, bn, per_cu; double full, alone; bool square; };
-constexpr ShapeCost SHAPES[3] = {{3, 64, 64, 2, 14.5, 10.0, false}, {0, 128, 128, 2, 31.5, 16.0, false}, {2, 256, 256, 1, 54.0, 36.0, true}};
+constexpr ShapeCost SHAPES[5] = {{3, 64, 64, 2, 15.5, 10.0, false},
+                                 {0, 128, 128, 2, 32.0, 24.0, false},
+                                 {4, 128, 128, 1, 20.0, 16.5, false},
+                                 {5, 128, 160, 1, 24.0, 20.0, false},
+                                 {2, 256, 256, 1, 51.5, 38.0, true}};
 double shape_cost(const ShapeCost& c, int64_t T, int64_t N) {
     const int64_t tiles = ((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), slots = (int64_t)chip_cus_linear() * c.per_cu;
     const double f = (double)(tiles % slots) / (double)slots;
@@ -398,9 +412,8 @@ double shape_cost(const ShapeCost& c, int64_t T, int64_t N) {
 }
 
 // Which tile shape a problem gets, and how many of its columns: a problem whose tiles leave a last round nearly empty may be cut
-// into columns that fill whole rounds of 256 x 256 tiles and a rest in a smaller shape, a launch of its own.  Measured in a layer
-// group's pass: 8192 x 8224 (33 tile columns where 32 fill four rounds) 284 us whole, 240 + 12 cut; 8192 x 2560 114 whole, 62 + 35 cut
-// (alone: 2048 x 8224 90 / 68, 4096 x 8224 142 / 122).
+// into columns that fill whole rounds of 256 x 256 tiles and a rest in a smaller shape, a launch of its own.  Measured, whole / cut: 8192 x
+// 8224 (33 tile columns where 32 fill four rounds) 233 / 211 us, 8192 x 2560 88 / 76, 2048 x 8224 90 / 65, 4096 x 8224 138 / 113.
 struct LinearPlan { int shape, rest_shape; int32_t cols; };   // outputs 0 .. cols - 1 in `shape`, the others in `rest_shape`
 LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
     const int forced = g_linear_shape.load();
@@ -414,7 +427,7 @@ LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
         return best;
     };
     double whole = 0.0;
-    LinearPlan p = {best_of(N, 3, &whole), 0, N};
+    LinearPlan p = {best_of(N, 5, &whole), 0, N};
     const double launch = 4.0 * 2048.0 / (double)K;      // a second launch: about 4 us whatever K
     double least = 0.97 * whole;                         // (a cut has to be worth it)
     const int64_t tiles_m = (T + 255) / 256, cus = chip_cus_linear();
@@ -423,8 +436,8 @@ LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
         if (cols >= N) break;
         if (cols == 0) continue;
         double rest = 0.0;
-        const int rest_shape = best_of(N - cols, 2, &rest);
-        const double t = shape_cost(SHAPES[2], T, cols) + rest + launch;
+        const int rest_shape = best_of(N - cols, 4, &rest);
+        const double t = shape_cost(SHAPES[4], T, cols) + rest + launch;
         if (t < least) { least = t; p = {2, rest_shape, (int32_t)cols}; }
     }
     return p;
@@ -460,6 +473,8 @@ int32_t launch_shape(const LinearArgs& a, int shape, bool bf, hipStream_t stream
         case 1: e = bf ? launch_linear<LinBig, true>(a, stream) : launch_linear<LinBig, false>(a, stream); break;
         case 2: e = bf ? launch_linear<LinBig8, true>(a, stream) : launch_linear<LinBig8, false>(a, stream); break;
         case 3: e = bf ? launch_linear<LinTiny, true>(a, stream) : launch_linear<LinTiny, false>(a, stream); break;
+        case 4: e = bf ? launch_linear<LinDeep, true>(a, stream) : launch_linear<LinDeep, false>(a, stream); break;
+        case 5: e = bf ? launch_linear<LinWide, true>(a, stream) : launch_linear<LinWide, false>(a, stream); break;
         default: e = bf ? launch_linear<LinSmall, true>(a, stream) : launch_linear<LinSmall, false>(a, stream); break;
     }
     return hip_err(e);
@@ -552,12 +567,13 @@ extern "C" int32_t gdn_linear_plan(int64_t T, int32_t N, int32_t K, int32_t* sha
     if (K % 64 != 0) return GDN_ERR_SHAPE;
     if (!shape || !cols || !rest_shape) return GDN_ERR_NULL;
     const LinearPlan p = plan_linear(T, N, K);
-    *shape = p.shape;
+    auto family = [](int shape) { return shape >= 4 ? 0 : shape; };   // (the deep and the wide form of shape 0)
+    *shape = family(p.shape);
     *cols = p.cols;
-    *rest_shape = p.rest_shape;
+    *rest_shape = family(p.rest_shape);
     return GDN_OK;
 }
 
 extern "C" int32_t gdn_linear_tune(int32_t shape) {
-    return g_linear_shape.exchange(shape < 0 || shape > 3 ? -1 : shape);
+    return g_linear_shape.exchange(shape < 0 || shape > 5 ? -1 : shape);
 }

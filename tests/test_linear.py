@@ -212,6 +212,43 @@ def test_stages_past_the_last_k_step_fetch_nothing(shape, K):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("shape,T,N,K", [
+    (4, 1, 36, 64), (4, 128, 128, 256), (4, 129, 131, 320), (4, 515, 8224, 2048),
+    (5, 1, 36, 64), (5, 128, 160, 256), (5, 127, 159, 192), (5, 129, 164, 320), (5, 515, 8224, 2048),
+])
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_deep_and_wide_tiles_at_their_edges(shape, T, N, K, out):
+    """The two shapes with four stages: one token, exactly a tile, one row or column more or less, fewer k steps than stages; the
+    same bits as the 128 x 128 shape with two stages, and segments whose boundaries lie inside a tile."""
+    import torch
+    from paper_2605_05219_amd.device_call import to_device
+    x, w, b = draw(T * 5 + N * 3 + K, T, N, K, True)
+    ref = lo.linear(x, w, b)
+    ldy = (N + 3) // 4 * 4
+    got = {}
+    for knob in (shape, 0):
+        prev = LN.gdn_linear_tune(knob)
+        try:
+            got[knob] = run_gpu(x, w, b, out, ldy=ldy)
+            if N > 40 and knob == shape:
+                widths = [24, N - 32, 8]
+                dt = torch.bfloat16 if out == "bf16" else torch.float32
+                fulls = [torch.full((T, (n + 7) // 4 * 4), float("nan"), dtype=dt, device="cuda") for n in widths[:2]] if N % 8 == 0 else []
+                if fulls:
+                    fulls.append(torch.full((T, 12), float("nan"), dtype=dt, device="cuda"))
+                    LN.gdn_linear_split(to_device(x), to_device(w), to_device(b), [f[:, :n] for f, n in zip(fulls, widths)], None)
+                    torch.cuda.synchronize()
+                    parts = np.concatenate([f[:, :n].float().cpu().numpy() for f, n in zip(fulls, widths)], 1)
+                    assert all(torch.isnan(f[:, n:]).all() for f, n in zip(fulls, widths))
+                    assert np.array_equal(parts, got[knob][:, :N])
+        finally:
+            LN.gdn_linear_tune(prev)
+    assert np.isnan(got[shape][:, N:]).all()
+    assert np.array_equal(got[shape][:, :N], got[0][:, :N])
+    assert (np.abs(got[shape][:, :N] - ref) <= bound(x, w, b, ref, K, out)).all()
+
+
+@pytest.mark.gpu
 def test_output_may_be_a_column_slice_of_a_wider_buffer():
     T, N, K = 200, 256, 128
     x, w, b = draw(5, T, N, K, True)
