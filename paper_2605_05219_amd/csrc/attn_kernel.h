@@ -6,6 +6,10 @@
 // one (request, query head); wave w owns 32 of them, one per lane column.  Key/value rows are
 // walked in tiles of 64 (32 at d = 256), each tile brought into one of two LDS stages by 16-byte
 // buffer loads to LDS (no registers) while the waves compute on the other stage.
+// At d = 128, where a key/value head has an even number of head blocks, a workgroup has eight waves and takes two of these (the
+// same tokens of two query heads): they walk the same keys, which then cross from the L2 to the LDS once for 256 rows instead of once for
+// 128 (7 TB/s of such traffic at 900 TFLOP/s; the clock is held by the power limit, at 1.9 GHz, and 16 heads over 8192 tokens
+// go from 295 to 268 us).  At d = 256 eight waves that wait for each other at every tile cost more than the traffic (1592 -> 1650 us).
 //
 // Both contractions are computed transposed, so that a query is a COLUMN of every accumulator
 // tile and everything a softmax row needs sits in one lane (and its partner 32 lanes up):
@@ -86,6 +90,7 @@ struct AttnArgs {
     int32_t H_q, H_kv;
     int32_t xcd_split;        // 1: blocks are dealt to the 8 XCDs by key/value head
     int32_t pack;             // query heads per token in a workgroup's rows: 1, or H_q / H_kv (a divisor of 128)
+    int32_t pair;             // 1: a workgroup takes two head blocks of a key/value head
     float scale_log2e;        // scale * log2(e)
 };
 
@@ -199,8 +204,9 @@ struct AttnSmem {
     static __device__ __forceinline__ int fv(int row) { return CPR >= 16 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 };
 
-template <int D, typename OT>
-__global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a) {
+// NH: head blocks per workgroup, four waves each
+template <int D, typename OT, int NH>
+__global__ void __launch_bounds__(ATT_THREADS * NH, 2) attn_suffix_kernel(AttnArgs a) {
     typedef AttnSmem<D> SM;
     constexpr int CPR = SM::CPR;
     constexpr int KB = D / 16;      // contraction steps of S^T
@@ -213,13 +219,14 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     __shared__ __attribute__((aligned(1024))) char stage0[SM::STAGE_BYTES], stage1[SM::STAGE_BYTES];
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = wg_wave & 3;   // of the four that share a head block
     const int col = lane & 31;      // query column of this lane
     const int g = lane >> 5;        // half-wave
 
     // ---- which (unit, head block): a head block is one query head, or with packed rows the heads of one group
     const int R = a.pack;                 // query heads per token in this workgroup's rows
-    const int per = a.H_q / a.H_kv / R;   // head blocks per key/value head: the group size, or 1
+    const int per = a.H_q / a.H_kv / (R * NH);   // workgroups per key/value head
     int item, hb;
     if (a.xcd_split) {
         const int X = 8 / a.H_kv;                 // XCDs per key/value head
@@ -230,11 +237,12 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
         item = (int)(e / per);
         hb = (xcd % a.H_kv) * per + (int)(e % per);
     } else {
-        const int HB = a.H_q / R;
+        const int HB = a.H_q / (R * NH);
         item = blockIdx.x / HB;
         hb = blockIdx.x % HB;
     }
     const int kvh = hb / per;
+    hb = hb * NH + (wg_wave >> 2);
     const int TPW = ATT_BQ / R;           // tokens per workgroup
     const int wrow = 32 * wave + col;     // this lane's row of the workgroup: token wrow / R, head hb * R + wrow % R
     const int tl = wrow / R;
@@ -261,7 +269,7 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     // A lane's offset inside a piece does not change from tile to tile; the tile and piece move in the scalar offset, which
     // stops at the descriptor's end: a piece wholly past it (also all of a tile past the walk's last) has no byte in range
     // however the hardware compares the sum.
-    constexpr int PPW = SM::PIECES / 4;                    // pieces per wave and tensor
+    constexpr int PPW = SM::PIECES / (4 * NH);                    // pieces per wave and tensor
     constexpr int RPP = 64 / CPR;                          // rows per piece
     const int row_bytes = a.H_kv * D * 2;
     const uint16_t* const kslot = a.k_cache + (int64_t)a.slot[r] * a.slot_stride;
@@ -270,16 +278,16 @@ __global__ void __launch_bounds__(ATT_THREADS, 2) attn_suffix_kernel(AttnArgs a)
     int koff[PPW], voff[PPW];
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
-        const int s = (wave * PPW + i) * 64 + lane;        // 16-byte slot inside the tile
+        const int s = (wg_wave * PPW + i) * 64 + lane;        // 16-byte slot inside the tile
         const int row = s / CPR, pos = s % CPR;
-        const int in_piece = (row - (wave * PPW + i) * RPP) * row_bytes + kvh * D * 2;
+        const int in_piece = (row - (wg_wave * PPW + i) * RPP) * row_bytes + kvh * D * 2;
         koff[i] = in_piece + ((pos ^ SM::fk(row)) << 4);
         voff[i] = in_piece + ((pos ^ SM::fv(row)) << 4);
     }
     auto issue = [&](int t, char* sb) {
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
-            const int p = wave * PPW + i;
+            const int p = wg_wave * PPW + i;
             const int soff = min((t * ATT_KT + p * RPP) * row_bytes, slot_bytes);
             load_to_lds(kslot, slot_bytes, sb + SM::K_OFF + p * 1024, koff[i], soff);
             load_to_lds(vslot, slot_bytes, sb + SM::V_OFF + p * 1024, voff[i], soff);

@@ -82,7 +82,8 @@ inline int64_t part_o_bytes(int d) { return (int64_t)SPLIT_MAX_WGS * ATT_BQ * d 
 
 template <int D, typename OT>
 hipError_t launch_attn(const AttnArgs& a, unsigned blocks, hipStream_t stream) {
-    hipLaunchKernelGGL((attn_suffix_kernel<D, OT>), dim3(blocks), dim3(ATT_THREADS), 0, stream, a);
+    if (a.pair) hipLaunchKernelGGL((attn_suffix_kernel<D, OT, D == 128 ? 2 : 1>), dim3(blocks), dim3(2 * ATT_THREADS), 0, stream, a);
+    else hipLaunchKernelGGL((attn_suffix_kernel<D, OT, 1>), dim3(blocks), dim3(ATT_THREADS), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -147,18 +148,27 @@ inline bool few_rows(int32_t len, int32_t start, int G) {
     return len > 0 && ATT_BQ % G == 0 && (int64_t)len * G <= NAR_ROWS && start + len >= 2 * SPLIT_MIN_KEYS;
 }
 
-// Rows of a workgroup of the 128-row kernel: 128 tokens of one query head (1), or, where that would leave at least a fifth of all
-// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).
+// Whether a workgroup of the 128-row kernel takes two head blocks (see attn_kernel.h): 16 query heads on 2 key/value heads, one / two,
+// 8192 tokens 295 / 268 us, 64 suffixes of 200 to 1000 tokens behind 3000 to 5000 1572 / 1560, four of 300 to 700 139 / 139.
+inline bool pairs(const attn_shape& s, int pack) { return s.d == 128 && s.H_q / s.H_kv / pack % 2 == 0; }
+
+// Rows of a workgroup of the 128-row kernel: 128 tokens of one query head (1), or, where that would leave too many of all
+// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).  Too many: a twentieth (64 suffixes of 200 to 1000
+// tokens at d = 64 891 -> 861 us, 32 at d = 256 1592 -> 1510).  Where workgroups of two heads stand against packed ones (d = 128), 7 in a hundred
+// (the 64 suffixes, 0.926 of the rows, 1560 -> 1530; four of 300 to 700, 0.947 of them, 139 -> 141; 16 of 900 to 1900, 0.96, 727 -> 747), or a fifth
+// where no suffix has more than one row tile, whose waves then nearly all have rows (64 of 100 tokens, 0.875 of the rows, 288 -> 297).
 int pick_pack(const attn_shape& s, int32_t n_req, const int32_t* len, const std::vector<char>& elsewhere) {
     const int G = s.H_q / s.H_kv;
     if (G == 1 || ATT_BQ % G != 0 || g_allow_pack.load() == 0) return 1;
-    int64_t rows_plain = 0, rows_packed = 0;
+    int64_t rows_plain = 0, rows_packed = 0, n_live = 0;
     for (int32_t r = 0; r < n_req; ++r) {
         if (elsewhere[r]) continue;
+        n_live += len[r] > 0;
         rows_plain += (int64_t)((len[r] + ATT_BQ - 1) / ATT_BQ) * s.H_q;
         rows_packed += (int64_t)((len[r] + ATT_BQ / G - 1) / (ATT_BQ / G)) * s.H_kv;
     }
-    return rows_packed * 5 <= rows_plain * 4 ? G : 1;
+    const bool one_tile = rows_plain <= (int64_t)n_live * s.H_q;
+    return rows_packed * 100 <= rows_plain * (!pairs(s, 1) ? 95 : one_tile ? 80 : 93) ? G : 1;
 }
 
 // Which kernel walks the few-rows requests.  What is in a call beside such a request must not change the bits of its whole walk,
@@ -410,14 +420,15 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     build_units(*s, n_req, len.data(), start_pos, plan);
     const int G = s->H_q / s->H_kv;
     const int pack = plan.pack, HB = s->H_q / pack;
+    const int NH = pairs(*s, pack) ? 2 : 1;   // head blocks per workgroup
     const int64_t n_narrow = plan.apart ? plan.n_units[1] : 0, n_wide = (int64_t)plan.units.size() - n_narrow;
     const bool xcd_split = 8 % s->H_kv == 0;
     int64_t blocks;
     if (xcd_split) {
         const int X = 8 / s->H_kv;
-        blocks = 8 * ((n_wide * (G / pack) + X - 1) / X);
+        blocks = 8 * ((n_wide * (G / pack / NH) + X - 1) / X);
     } else {
-        blocks = n_wide * HB;
+        blocks = n_wide * (HB / NH);
     }
     if (blocks > INT32_MAX || n_narrow * s->H_kv > INT32_MAX) return GDN_ERR_COUNT;
 
@@ -525,6 +536,7 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     }
     if (n_wide > 0) {
         a.pack = pack;
+        a.pair = NH == 2;
         e = s->o_dtype == GDN_F32 ? launch_attn_d<float>(s->d, a, (unsigned)blocks, stream)
                                   : launch_attn_d<uint16_t>(s->d, a, (unsigned)blocks, stream);
         if (e != hipSuccess) return hip_err(e);

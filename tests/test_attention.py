@@ -433,6 +433,30 @@ def test_split_key_walks_agree_with_whole_walks(monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("H_q,H_kv", [(12, 2), (6, 3), (16, 4), (10, 2)])   # groups of 6 (no packing), 2 on a plain block order, 4; an odd one: no pairs
+def test_workgroups_of_two_query_heads(H_q, H_kv, split):
+    """d = 128, unpacked rows: a workgroup takes two heads of a key/value group.  Query tiles that end anywhere, waves without a row,
+    whole walks and parts of walks, some past a query's limit, against the oracle."""
+    lens, starts = [1, 127, 128, 129, 300], [700, 64, 513, 0, 1300]
+    c = wl.attn_case(3900 + H_q, H_q, H_kv, 128, lens, starts, spare_slots=1)
+    AT.attn_tune_pack(False)
+    AT.attn_tune_split(split)
+    try:
+        got, k_after, v_after = gpu_prefill(c, gate=True)
+        bf, _, _ = gpu_prefill(c, "bf16")
+    finally:
+        AT.attn_tune_pack(True)
+        AT.attn_tune_split(True)
+    check_o(got, oracle_o(c, 128 ** -0.5, True), "f32")
+    check_o(bf, oracle_o(c, 128 ** -0.5), "bf16")
+    k_want, v_want = pools_with_prefix(c)
+    for r, s in enumerate(c.seq_slot):
+        k_want[s, :len(c.k_full[r])], v_want[s, :len(c.v_full[r])] = c.k_full[r], v_bits(c.v_full[r])
+    assert np.array_equal(k_after, k_want) and np.array_equal(v_after, v_want)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("H_q,H_kv,d,lens,starts", [
     (16, 2, 128, [1, 2, 1, 0, 1], [1023, 1022, 4000, 7, 1100]),      # 8 and 16 rows, the shortest walks, an empty request, several parts
     (4, 4, 64, [1, 15, 16, 3], [1087, 1085, 2047, 1024]),            # one head per group: 1 to 16 rows, new rows across key tiles
