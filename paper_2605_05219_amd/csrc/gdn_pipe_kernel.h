@@ -117,7 +117,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     // the walk over the workgroup's items, by one wave (wave 1 of the preparation): the present chain and chunk
     struct Walk { int c, c_end, l, hv, hq, src; };
     Walk wk;
-    int drawn = 0;                                              // in lane 0: the next chain less gridDim.x, drawn with the present one's last chunk
+    int reserve = 2 * (int)gridDim.x - 1 - (int)blockIdx.x;     // the chain to open next, or
+    bool draw_pending = false;                                  // on its way,
+    int drawn = 0;                                              // in lane 0
     auto publish = [&](int t, bool live, bool fresh) {          // item t as the walk stands
         int w[8] = {0, 0, 0, 0, 0, 0, -1, SAME_CHAIN};
         if (live) {
@@ -148,19 +150,21 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         return true;
     };
     bool live = true;
-    auto draw_behind_last = [&] {     // a step ahead of its use
-        if (live && wk.c + 1 == wk.c_end && lane_ == 0) {
-            int z = 0;
-            pin(z);     // not a wave-uniform address to the compiler, which would wait for the result at once
-            drawn = __hip_atomic_fetch_add(a.next_chain + z, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    };
     auto walk_on = [&](int t) {       // publishes item t, the one after the walk's present one
         bool fresh = false;
         if (live) {
-            if (wk.c + 1 < wk.c_end) ++wk.c;
-            else live = fresh = open_chain((int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn));
-            draw_behind_last();
+            if (wk.c + 1 < wk.c_end) {
+                ++wk.c;
+            } else {
+                if (draw_pending) reserve = 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn);
+                live = fresh = open_chain(reserve);
+                draw_pending = live;
+                if (live && lane_ == 0) {
+                    int z = 0;
+                    pin(z);     // not a wave-uniform address to the compiler, which would wait for the result at once
+                    drawn = __hip_atomic_fetch_add(a.next_chain + z, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
         }
         publish(t, live, fresh);
     };
@@ -173,7 +177,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (prep && wave == 1) {
         if (lane_ < 32) items[lane_] = (lane_ & 7) == 7 ? SAME_CHAIN : (lane_ & 7) == 6 ? -1 : 0;    // none
         live = open_chain((int)blockIdx.x);
-        draw_behind_last();
         publish(0, live, true);
     }
     __syncthreads();
