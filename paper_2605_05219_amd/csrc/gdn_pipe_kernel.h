@@ -13,8 +13,12 @@
 // 345 chunks, 100 k units 2280 -> 1860; 96 chains of 128 chunks 648 -> 455; 8192 chains, 230 k units 4120 -> 4110.  With all compute units busy
 // the clock is held at 1.8 to 1.95 GHz by the power limit (2.4 with half of them): the same 7.8 k clocks are 4.2 to 4.6 us or 3.3.
 //
-// Pipeline.  A workgroup's items are the chunks of one chain after the other (the chains come longest first and are drawn as
-// in the fused kernel).  In step t
+// Pipeline.  A workgroup's items are the chunks of one chain after the other.  The chains come longest first: workgroup b begins with
+// chain b and draws each further one from a counter in memory, when the item of its present chain's last chunk is made out: a step
+// before the draw's result is needed and three before the recurrence is done with that chunk, so no workgroup keeps a chain that another could
+// start.  (Held in reserve a whole chain ahead, as the fused kernel does, the fullest of 256 workgroups got 76 chunks of 1024 chains with
+// 60 on average and 66 in the longest, against 66: 293 -> 276 us; 458 of 391 on average and 345 in the longest, against 437: 1803 -> 1757.)
+// In step t
 //     the recurrence waves work on item t - 3: substitution, outputs, state update, emission,
 //     the preparation waves prepare item t - 2 out of LDS, stage item t - 1 from registers to LDS (fp16) and fetch item t,
 // and one barrier ends the step.  K and Q are held for three items in turn, pair tiles for two, gate vectors for three.  V is the
@@ -117,9 +121,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     // the walk over the workgroup's items, by one wave (wave 1 of the preparation): the present chain and chunk
     struct Walk { int c, c_end, l, hv, hq, src; };
     Walk wk;
-    int reserve = 2 * (int)gridDim.x - 1 - (int)blockIdx.x;     // the chain to open next, or
-    bool draw_pending = false;                                  // on its way,
-    int drawn = 0;                                              // in lane 0
+    int drawn = 0;                                              // in lane 0: the next chain less gridDim.x, drawn with the present one's last chunk
     auto publish = [&](int t, bool live, bool fresh) {          // item t as the walk stands
         int w[8] = {0, 0, 0, 0, 0, 0, -1, SAME_CHAIN};
         if (live) {
@@ -150,21 +152,19 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         return true;
     };
     bool live = true;
+    auto draw_behind_last = [&] {     // a step ahead of its use
+        if (live && wk.c + 1 == wk.c_end && lane_ == 0) {
+            int z = 0;
+            pin(z);     // not a wave-uniform address to the compiler, which would wait for the result at once
+            drawn = __hip_atomic_fetch_add(a.next_chain + z, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
     auto walk_on = [&](int t) {       // publishes item t, the one after the walk's present one
         bool fresh = false;
         if (live) {
-            if (wk.c + 1 < wk.c_end) {
-                ++wk.c;
-            } else {
-                if (draw_pending) reserve = 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn);
-                live = fresh = open_chain(reserve);
-                draw_pending = live;
-                if (live && lane_ == 0) {
-                    int z = 0;
-                    pin(z);     // not a wave-uniform address to the compiler, which would wait for the result at once
-                    drawn = __hip_atomic_fetch_add(a.next_chain + z, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
+            if (wk.c + 1 < wk.c_end) ++wk.c;
+            else live = fresh = open_chain((int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn));
+            draw_behind_last();
         }
         publish(t, live, fresh);
     };
@@ -177,6 +177,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (prep && wave == 1) {
         if (lane_ < 32) items[lane_] = (lane_ & 7) == 7 ? SAME_CHAIN : (lane_ & 7) == 6 ? -1 : 0;    // none
         live = open_chain((int)blockIdx.x);
+        draw_behind_last();
         publish(0, live, true);
     }
     __syncthreads();
