@@ -33,6 +33,12 @@ int32_t check_shape(const gdn_layer_shape* s) {
 // emit_req, emit_pos, emit_slot (n_emit each)
 inline int64_t plan_ints(int32_t n_req, int32_t n_emit) { return 4 * (int64_t)n_req + 2 + 3 * (int64_t)n_emit; }
 
+// Tokens per wave of the convolution role: 8, or 4 where that leaves at most ten waves to a compute unit and the rows' latency is the time.
+// Kernel us, 3 layers of 6144 channels, runs of 4 / 8 / 16 / 32: 16 tokens 5.3 / 6.6 / 9.2 / 9.2, 256 8.7 / 9.6 / 10.7 / 15.6, 512 13.7 / 13.4 / 15.1 /
+// 17.1, 1024 20.4 / 18.6 / 20.0 / 23.5, 8192 151 / 122 / 124 / 125 (604 MB: 5 TB/s; in runs of 32 with each thread's taps read for
+// itself 10.6, 17.4, 18.7, 27.9 and 143).
+inline int32_t run_tokens(int64_t token_groups) { return token_groups / (4 * 64) <= 10 * 256 ? 4 : 8; }
+
 template <typename In, typename Out>
 hipError_t launch_inputs(const LayerArgs& a, int64_t blocks, int layers, hipStream_t stream) {
     hipLaunchKernelGGL((gdn_layer_inputs_kernel<In, Out>), dim3((unsigned)blocks, (unsigned)layers), dim3(LAYER_THREADS), 0, stream, a);
@@ -152,10 +158,11 @@ int32_t gdn_layer_inputs(const gdn_layer_shape* s, const void* x_qkv, const floa
     std::memcpy(p_cu, cu_seqlens, sizeof(int32_t) * (n_req + 1));
     std::memcpy(p_start, start_pos, sizeof(int32_t) * n_req);
     std::memcpy(p_src, src_slot, sizeof(int32_t) * n_req);
+    const int32_t run = run_tokens(T * (C / 8) * s->L);
     int64_t runs = 0;
     for (int32_t r = 0; r < n_req; ++r) {
         p_run[r] = (int32_t)runs;
-        runs += (cu_seqlens[r + 1] - cu_seqlens[r] + LAYER_RUN - 1) / LAYER_RUN;
+        runs += (cu_seqlens[r + 1] - cu_seqlens[r] + run - 1) / run;
     }
     p_run[n_req] = (int32_t)runs;
     if (n_emit > 0) {
@@ -164,7 +171,7 @@ int32_t gdn_layer_inputs(const gdn_layer_shape* s, const void* x_qkv, const floa
         std::memcpy(p_eslot, emit_slot, sizeof(int32_t) * n_emit);
     }
     const int64_t CG = C / 8;
-    const int64_t conv_blocks = (runs * CG + LAYER_THREADS - 1) / LAYER_THREADS;
+    const int64_t conv_blocks = (runs + 3) / 4 * ((CG + 63) / 64);
     const int64_t gate_blocks = (T * s->H_v + LAYER_THREADS - 1) / LAYER_THREADS;
     const int64_t emit_blocks = ((int64_t)n_emit * K1 * CG + LAYER_THREADS - 1) / LAYER_THREADS;
     const int64_t blocks = conv_blocks + gate_blocks + emit_blocks;
@@ -181,6 +188,7 @@ int32_t gdn_layer_inputs(const gdn_layer_shape* s, const void* x_qkv, const floa
     a.cu = d; a.start = d + (p_start - p_cu); a.src_slot = d + (p_src - p_cu); a.run_cu = d + (p_run - p_cu);
     a.emit_req = d + (p_ereq - p_cu); a.emit_pos = d + (p_epos - p_cu); a.emit_slot = d + (p_eslot - p_cu);
     a.n_req = n_req; a.n_emit = n_emit; a.n_runs = (int32_t)runs;
+    a.run = run;
     a.C = (int32_t)C; a.nq = s->H_qk * s->d_k; a.d_k = s->d_k; a.H_v = s->H_v; a.K = s->conv_k;
     a.T = T; a.qk_eps = s->qk_eps;
     a.conv_blocks = (int32_t)conv_blocks; a.gate_blocks = (int32_t)gate_blocks;

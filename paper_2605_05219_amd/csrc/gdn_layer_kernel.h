@@ -14,7 +14,6 @@
 namespace gdn {
 
 constexpr int LAYER_THREADS = 256;
-constexpr int LAYER_RUN = 32;   // tokens per thread of the convolution role
 
 struct LayerArgs {
     const void* x;          // [T][C]
@@ -37,6 +36,7 @@ struct LayerArgs {
     const int32_t* emit_pos;  // n_emit (absolute)
     const int32_t* emit_slot; // n_emit
     int32_t n_req, n_emit, n_runs;
+    int32_t run;              // tokens per thread of the convolution role
     int32_t C, nq, d_k, H_v, K;       // nq = H_qk d_k; channels [0,nq) q, [nq,2nq) k, rest v
     int64_t T;
     float qk_eps;
@@ -167,36 +167,38 @@ __global__ void __launch_bounds__(LAYER_THREADS) gdn_layer_inputs_kernel(LayerAr
     const int CG = a.C / 8;   // channel groups per row
     const int K1 = a.K - 1;
     if ((int)blockIdx.x < a.conv_blocks) {
-        // ---- short convolution + SiLU (+ L2 normalisation of q and k) over one run of tokens
-        const int64_t gi = (int64_t)blockIdx.x * LAYER_THREADS + threadIdx.x;
-        const int run = (int)(gi / CG);
-        const int ch = (int)(gi % CG) * 8;
-        if (run >= a.n_runs) return;   // whole heads leave together: C/8 is a multiple of the lanes of a head
+        // ---- short convolution + SiLU (+ L2 normalisation of q and k): a wave takes 64 channel groups over one run of tokens, a block the
+        // same channels over four runs.  The taps go through LDS: read by each thread for itself they were eight loads of 64 lines
+        // each, which is as much as a run of eight rows (see run_tokens for what that and short runs give).
+        __shared__ float4 taps[8 * 64];            // channel c of group l at 8 l + (c ^ (l & 7)): lanes read across the banks
+        const int tiles = (CG + 63) / 64;
+        const int lane = threadIdx.x & 63;
+        const int ch0 = (int)blockIdx.x % tiles * 512;
+        const int run = (int)blockIdx.x / tiles * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int ch = ch0 + 8 * lane;
+#pragma unroll
+        for (int i = threadIdx.x; i < 512; i += LAYER_THREADS) {
+            if (ch0 + i >= a.C) break;
+            float4 t;      // four weights per channel, older taps of a shorter convolution are zero
+            if (a.K == 4) {
+                t = reinterpret_cast<const float4*>(a.w)[ch0 + i];
+            } else {
+                const float* const wc = a.w + (int64_t)(ch0 + i) * a.K;
+                t = make_float4(0.f, a.K > 2 ? wc[0] : 0.f, wc[a.K - 2], wc[a.K - 1]);
+            }
+            taps[(i & ~7) | ((i ^ (i >> 3)) & 7)] = t;
+        }
+        __syncthreads();
+        if (run >= a.n_runs || ch >= a.C) return;   // whole heads leave together: C/8 is a multiple of the lanes of a head
         int lo = 0, hi = a.n_req;      // request of the run: last r with run_cu[r] <= run
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (a.run_cu[mid] <= run) lo = mid; else hi = mid;
         }
         const int r = lo;
-        const int t_first = (run - a.run_cu[r]) * LAYER_RUN;          // local index of the run's first token
+        const int t_first = (run - a.run_cu[r]) * a.run;          // local index of the run's first token
         const int64_t row0 = a.cu[r];
-        const int n = min(LAYER_RUN, a.cu[r + 1] - a.cu[r] - t_first);
-        // taps as four weights per channel, older taps of a shorter convolution are zero
-        float w4[8][4], bias[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            if (a.K == 4) {
-                const float4 t = reinterpret_cast<const float4*>(a.w)[ch + c];
-                w4[c][0] = t.x; w4[c][1] = t.y; w4[c][2] = t.z; w4[c][3] = t.w;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int jj = j - (4 - a.K);
-                    w4[c][j] = jj >= 0 ? a.w[(int64_t)(ch + c) * a.K + jj] : 0.f;
-                }
-            }
-            bias[c] = a.bias ? a.bias[ch + c] : 0.f;
-        }
+        const int n = min(a.run, a.cu[r + 1] - a.cu[r] - t_first);
         // the three inputs before the run: from the sequence, else from the stored state, else zero
         F8 win[3];
         const int slot = a.src_slot[r];
@@ -222,6 +224,14 @@ __global__ void __launch_bounds__(LAYER_THREADS) gdn_layer_inputs_kernel(LayerAr
         decltype(load_raw8(src)) nxt[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) nxt[u] = load_raw8(src + (int64_t)min(u, n - 1) * a.C);
+        float w4[8][4];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const float4 t = taps[8 * lane + (c ^ (lane & 7))];
+            w4[c][0] = t.x; w4[c][1] = t.y; w4[c][2] = t.z; w4[c][3] = t.w;
+        }
+        F8 bias = {{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}};
+        if (a.bias) bias = load8(a.bias + ch);
         for (int t0 = 0; t0 < n; t0 += 4) {
             decltype(load_raw8(src)) cur[4];
 #pragma unroll
@@ -238,7 +248,7 @@ __global__ void __launch_bounds__(LAYER_THREADS) gdn_layer_inputs_kernel(LayerAr
                 float ss = 0.f;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    float acc = bias[c];
+                    float acc = bias.f[c];
                     acc = fmaf(w4[c][0], win[0].f[c], acc);
                     acc = fmaf(w4[c][1], win[1].f[c], acc);
                     acc = fmaf(w4[c][2], win[2].f[c], acc);

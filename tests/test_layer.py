@@ -244,6 +244,18 @@ def test_stacked_layers_in_one_call_equal_one_call_per_layer_bitwise(dtype, out_
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("K,lens", [(4, [1, 4, 5, 0, 9, 3]), (3, [7, 8]), (4, [2301, 2303, 9]), (2, [4600])])   # runs of 4 and, from 4552 tokens, of 8
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_layer_inputs_with_channels_and_runs_that_fill_no_block(K, lens, dtype):
+    """144 channel groups of 8 (two blocks of 64 and one of 16), runs and groups of four runs that end anywhere, against the oracle."""
+    c = wl.layer_case(2700 + K, 3, 3, 128, 128, K, dtype, lens, [64] * len(lens), [[64 + n] if n else [] for n in lens])
+    ref = oracle_inputs(c, 1e-6)
+    got, _, _ = gpu_inputs(c, "f32", 1e-6)
+    for name, x, r in zip(("q", "k", "v", "beta", "gate"), got, ref[:5]):
+        check_tensor(x, r, "f32", name)
+
+
+@pytest.mark.gpu
 def test_layer_inputs_resume_equals_full_replay_bitwise_on_the_gpu():
     """A request resumed from the convolution state the full run stored reproduces the full run's outputs bit for bit."""
     H, d, K, N, p = 2, 128, 4, 300, 131
