@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(ATT_THREADS * NH, 2) attn_suffix_kernel(AttnAr
 
     const int lane = threadIdx.x & 63;
     const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = wg_wave & 3;   // of the four that share a head block
+    const int wave = NH == 1 ? wg_wave : wg_wave & 3;   // of the four that share a head block
     const int col = lane & 31;      // query column of this lane
     const int g = lane >> 5;        // half-wave
 
@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(ATT_THREADS * NH, 2) attn_suffix_kernel(AttnAr
         hb = blockIdx.x % HB;
     }
     const int kvh = hb / per;
-    hb = hb * NH + (wg_wave >> 2);
+    if (NH == 2) hb = 2 * hb + (wg_wave >> 2);
     const int TPW = ATT_BQ / R;           // tokens per workgroup
     const int wrow = 32 * wave + col;     // this lane's row of the workgroup: token wrow / R, head hb * R + wrow % R
     const int tl = wrow / R;

@@ -148,27 +148,21 @@ inline bool few_rows(int32_t len, int32_t start, int G) {
     return len > 0 && ATT_BQ % G == 0 && (int64_t)len * G <= NAR_ROWS && start + len >= 2 * SPLIT_MIN_KEYS;
 }
 
-// Whether a workgroup of the 128-row kernel takes two head blocks (see attn_kernel.h): 16 query heads on 2 key/value heads, one / two,
-// 8192 tokens 295 / 268 us, 64 suffixes of 200 to 1000 tokens behind 3000 to 5000 1572 / 1560, four of 300 to 700 139 / 139.
-inline bool pairs(const attn_shape& s, int pack) { return s.d == 128 && s.H_q / s.H_kv / pack % 2 == 0; }
-
 // Rows of a workgroup of the 128-row kernel: 128 tokens of one query head (1), or, where that would leave too many of all
-// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).  Too many: a twentieth (64 suffixes of 200 to 1000
-// tokens at d = 64 891 -> 861 us, 32 at d = 256 1592 -> 1510).  Where workgroups of two heads stand against packed ones (d = 128), 7 in a hundred
-// (the 64 suffixes, 0.926 of the rows, 1560 -> 1530; four of 300 to 700, 0.947 of them, 139 -> 141; 16 of 900 to 1900, 0.96, 727 -> 747), or a fifth
-// where no suffix has more than one row tile, whose waves then nearly all have rows (64 of 100 tokens, 0.875 of the rows, 288 -> 297).
+// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).  Too many: a fifth, and in calls of many rounds of
+// workgroups 7 in a hundred (64 suffixes of 200 to 1000 tokens behind 3000 to 5000, 0.926 of the rows, 1572 -> 1530 us, at d = 64 891 -> 861, 32 at d = 256
+// 1592 -> 1510; 0.96 of them 727 -> 747).  In smaller calls the cut of the walks and the last round decide (d = 256, one suffix of 430 to 860 tokens 57 / 77,
+// three 111 / 101).
 int pick_pack(const attn_shape& s, int32_t n_req, const int32_t* len, const std::vector<char>& elsewhere) {
     const int G = s.H_q / s.H_kv;
     if (G == 1 || ATT_BQ % G != 0 || g_allow_pack.load() == 0) return 1;
-    int64_t rows_plain = 0, rows_packed = 0, n_live = 0;
+    int64_t rows_plain = 0, rows_packed = 0;
     for (int32_t r = 0; r < n_req; ++r) {
         if (elsewhere[r]) continue;
-        n_live += len[r] > 0;
         rows_plain += (int64_t)((len[r] + ATT_BQ - 1) / ATT_BQ) * s.H_q;
         rows_packed += (int64_t)((len[r] + ATT_BQ / G - 1) / (ATT_BQ / G)) * s.H_kv;
     }
-    const bool one_tile = rows_plain <= (int64_t)n_live * s.H_q;
-    return rows_packed * 100 <= rows_plain * (!pairs(s, 1) ? 95 : one_tile ? 80 : 93) ? G : 1;
+    return rows_packed * 100 <= rows_plain * (rows_packed >= 4 * SPLIT_BELOW ? 93 : 80) ? G : 1;      // (in workgroups: 128 rows each)
 }
 
 // Which kernel walks the few-rows requests.  What is in a call beside such a request must not change the bits of its whole walk,
@@ -274,6 +268,37 @@ void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const 
         out.n_units[k] = (int64_t)out.units.size() - (k ? out.n_units[0] : 0);
     }
     std::stable_sort(out.units.begin(), out.units.end(), [](const Unit& x, const Unit& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
+}
+
+// Whether the workgroups of the 128-row kernel take two head blocks each (see attn_kernel.h): at d = 128, in calls of at most two rounds of them, one to a
+// compute unit, that balance over the chip as well as workgroups of half the size, two to one.  That is estimated by the key tiles of the fullest place when
+// the units, longest first, are dealt back and forth; a single-head workgroup that has a compute unit to itself goes through its tiles faster,
+// so its side counts half way to the mean.  Single / pairs, 16 heads on 2: 8192 tokens 295 / 268 us; on 4, 1354 tokens behind 1872 (300 pairs where 256 fit) 60 / 69; more
+// rounds: six suffixes of 1289 to 2578 tokens 330 / 342, five with 32 heads on 4 386 / 422, 29 of 915 to 1830 486 / 497, 16 of 900 to 1900 751 / 727.
+inline bool pairs_pay(const attn_shape& s, const UnitPlan& plan, int head_blocks) {
+    if (s.d != 128 || s.H_q / s.H_kv / plan.pack % 2 != 0) return false;
+    std::vector<int32_t> tiles;
+    int64_t sum = 0;
+    for (const Unit& u : plan.units) {
+        if (u.few && plan.apart) continue;
+        tiles.push_back(u.t1 - u.t0);
+        sum += u.t1 - u.t0;
+    }
+    constexpr int CUS = SPLIT_BELOW / 2;
+    if ((int64_t)tiles.size() * head_blocks > 4 * CUS) return false;
+    auto fullest = [&](int per_unit, int places) {
+        std::vector<int32_t> load(places, 0);
+        int j = 0, most = 0;
+        for (int32_t n : tiles)
+            for (int h = 0; h < per_unit; ++h, ++j) {
+                int32_t& x = load[j / places % 2 ? places - 1 - j % places : j % places];
+                x += n;
+                most = std::max(most, (int)x);
+            }
+        return (double)most;
+    };
+    const double mean = (double)sum * head_blocks / (2 * CUS);
+    return fullest(head_blocks / 2, CUS) <= 1.06 * 0.5 * (fullest(head_blocks, 2 * CUS) + mean);
 }
 
 }  // namespace
@@ -420,7 +445,7 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     build_units(*s, n_req, len.data(), start_pos, plan);
     const int G = s->H_q / s->H_kv;
     const int pack = plan.pack, HB = s->H_q / pack;
-    const int NH = pairs(*s, pack) ? 2 : 1;   // head blocks per workgroup
+    const int NH = pairs_pay(*s, plan, HB) ? 2 : 1;   // head blocks per workgroup
     const int64_t n_narrow = plan.apart ? plan.n_units[1] : 0, n_wide = (int64_t)plan.units.size() - n_narrow;
     const bool xcd_split = 8 % s->H_kv == 0;
     int64_t blocks;
