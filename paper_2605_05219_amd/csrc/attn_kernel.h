@@ -6,7 +6,7 @@
 // one (request, query head); wave w owns 32 of them, one per lane column.  Key/value rows are
 // walked in tiles of 64 (32 at d = 256), each tile brought into one of two LDS stages by 16-byte
 // buffer loads to LDS (no registers) while the waves compute on the other stage.
-// At d = 128, where a key/value head has an even number of head blocks, a workgroup has eight waves and takes two of these (the
+// At d = 128, where a key/value head has an even number of head blocks and the call is small (pairs_pay in attn_resume.hip), a workgroup has eight waves and takes two of these (the
 // same tokens of two query heads): they walk the same keys, which then cross from the L2 to the LDS once for 256 rows instead of once for
 // 128 (7 TB/s of such traffic at 900 TFLOP/s; the clock is held by the power limit, at 1.9 GHz, and 16 heads over 8192 tokens
 // go from 295 to 268 us).  At d = 256 eight waves that wait for each other at every tile cost more than the traffic (1592 -> 1650 us).
