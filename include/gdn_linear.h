@@ -60,13 +60,14 @@ int32_t gdn_linear_split(const void *x, int64_t ldx, const void *w, int64_t ldw,
 /*
  * The launches gdn_linear and gdn_linear_split make for a problem (host only; for tests and for callers that want to see
  * them): outputs 0 .. *cols - 1 in tile shape *shape and, where *cols < N, the others in a second launch in *rest_shape (shape
- * numbers as for gdn_linear_tune; the two forms of shape 0, 4 and 5, are reported as 0).  T, N, K positive (else GDN_ERR_COUNT), K a multiple of 64 (else GDN_ERR_SHAPE).
+ * numbers as for gdn_linear_tune).  T, N, K positive (else GDN_ERR_COUNT), K a multiple of 64 (else GDN_ERR_SHAPE).
  */
 int32_t gdn_linear_plan(int64_t T, int32_t N, int32_t K, int32_t *shape, int32_t *cols, int32_t *rest_shape);
 
 /*
  * Tuning knob, not a method step: fixes the workgroup tile gdn_linear uses (0: 128 x 128; 1: 256 x 256 with four
- * waves; 2: 256 x 256 with eight waves; 3: 64 x 64; 4: 128 x 128 with more k steps in flight; 5: 4 with 160 outputs; anything else: chosen per call from T, N and K, the default, which
+ * waves; 2: 256 x 256 with eight waves; 3: 64 x 64; 4: 128 x 128 with three k steps in flight instead of one; 5: 128 x 160
+ * like 4; anything else: chosen per call from T, N and K, the default, which
  * may also cut a large problem into two column ranges, a launch each).  Every shape computes the same
  * sums in the same order, so the results do not depend on it.  Process-wide; returns the previous setting (-1 = per
  * call).

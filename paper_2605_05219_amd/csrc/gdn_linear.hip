@@ -567,10 +567,9 @@ extern "C" int32_t gdn_linear_plan(int64_t T, int32_t N, int32_t K, int32_t* sha
     if (K % 64 != 0) return GDN_ERR_SHAPE;
     if (!shape || !cols || !rest_shape) return GDN_ERR_NULL;
     const LinearPlan p = plan_linear(T, N, K);
-    auto family = [](int shape) { return shape >= 4 ? 0 : shape; };   // (the deep and the wide form of shape 0)
-    *shape = family(p.shape);
+    *shape = p.shape;
     *cols = p.cols;
-    *rest_shape = family(p.rest_shape);
+    *rest_shape = p.rest_shape;
     return GDN_OK;
 }
 

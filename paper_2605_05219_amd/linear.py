@@ -59,14 +59,14 @@ def gdn_linear(x, w, bias, y, stream=None) -> None:
 
 
 def gdn_linear_plan(T: int, N: int, K: int):
-    """(tile shape, outputs it covers, tile shape of the other outputs) of a projection; host only."""
+    """(tile shape, outputs it covers, tile shape of the other outputs) of a projection, in gdn_linear_tune's numbers; host only."""
     shape, cols, rest = _i32(0), _i32(0), _i32(0)
     _check(_lib().gdn_linear_plan(int(T), int(N), int(K), ctypes.byref(shape), ctypes.byref(cols), ctypes.byref(rest)), "gdn_linear_plan")
     return shape.value, cols.value, rest.value
 
 
 def gdn_linear_tune(shape: int) -> int:
-    """Fixes the workgroup tile (0, 1, 2, 3) or returns the choice to the library (-1); returns the previous setting."""
+    """Fixes the workgroup tile (0 to 5, see include/gdn_linear.h) or returns the choice to the library (-1); returns the previous setting."""
     return int(_lib().gdn_linear_tune(int(shape)))
 
 

@@ -97,10 +97,10 @@ def test_plan_covers_the_outputs_and_follows_the_knob():
     for _ in range(200):
         T, N, K = int(np.exp(rng.uniform(0, 12))) , int(np.exp(rng.uniform(0, 9.5))), 64 * int(rng.integers(1, 65))
         shape, cols, rest = LN.gdn_linear_plan(T, N, K)
-        assert shape in (0, 2, 3) and 0 < cols <= N
+        assert shape in (0, 2, 3, 4, 5) and 0 < cols <= N
         if cols < N:                           # whole tile columns of the large shape, the rest in a smaller one
-            assert shape == 2 and cols % 256 == 0 and rest in (0, 3)
-    for knob in (0, 1, 2, 3):
+            assert shape == 2 and cols % 256 == 0 and rest in (0, 3, 4, 5)
+    for knob in range(6):
         prev = LN.gdn_linear_tune(knob)
         try:
             assert LN.gdn_linear_plan(8192, 8224, 2048)[:2] == (knob, 8224)
@@ -110,6 +110,17 @@ def test_plan_covers_the_outputs_and_follows_the_knob():
         with pytest.raises(B.GdnError) as ei:
             LN.gdn_linear_plan(T, N, K)
         assert ei.value.code == code
+
+
+@pytest.mark.parametrize("T,N,plan", [
+    (384, 8224, (4, 8224, 0)), (1400, 2048, (4, 2048, 0)),     # one round of 128 x 128 tiles
+    (512, 8224, (5, 8224, 0)),                                 # four such tiles too many, one round of 128 x 160
+    (8192, 2560, (2, 2048, 4)), (6000, 6144, (2, 5376, 5)),    # rounds of large tiles, and a rest of one round in either
+    (512, 2048, (3, 2048, 0)), (8192, 8224, (2, 8192, 3)),
+])
+def test_plan_names_the_shape_that_runs(T, N, plan):
+    """The plan's numbers are the knob's: the shapes with four stages are told from the one with two."""
+    assert LN.gdn_linear_plan(T, N, 2048) == plan
 
 
 def test_python_binding_rejects_mismatched_tensors():
@@ -294,6 +305,7 @@ def test_split_outputs_equal_the_whole_projection(shape, out):
     (8192, [6144, 2048, 16, 16], 8192),        # 33 columns of large tiles where 32 fill four rounds: the rest is two whole segments
     (8100, [2048, 256, 256], 2048),            # eight columns of large tiles and a rest; a ragged last tile row
     (8192, [2000, 304, 256], 2048),            # the cut inside the second segment
+    (6000, [2048, 4096], 5376),                # the rest in 128 x 160 tiles, 768 columns: the last of five is 128 wide
 ])
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_large_projection_cut_into_two_column_ranges(T, widths, cut, out):
