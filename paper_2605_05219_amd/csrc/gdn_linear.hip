@@ -251,8 +251,11 @@ gdn_linear_kernel(LinearArgs a) {
         __builtin_amdgcn_sched_barrier(0);
         {
             // The last k step of the stage (fragment set 1; KK is even), written out in issue order and pinned there: a load
-            // to LDS takes tens of cycles to issue, so one goes out behind every few matrix instructions, which covers it;
-            // the fragments of the next stage's first k step are read in between as well.
+            // to LDS takes tens of cycles to issue, so one goes out in each slot of a few matrix instructions, which cover it, from
+            // the first slot on: a load has from here to the hand-over STAGES - 1 stages on to arrive, and with two stages one that goes out in
+            // the last slot has half a stage.  (Spread over all slots, cold weights, shape 2: 4096 x 2560 x 2048 49.9 us
+            // against 47.3, 3000 x 4096 x 4096 90.4 / 85.9, 1000 x 8224 x 2048 50.4 / 48.7; warm 8192 x 8192 x 2048 189 / 191; two loads a slot: 48.0, 87.1, 49.1, 192.)
+            // The fragments of the next stage's first k step are read in between as well.
             const bool live = step + STAGES < n_steps;
             const int xbytes = live ? x_bytes : 0, wbytes = live ? w_bytes : 0, k_ahead = live ? (step + STAGES) * BK : 0;
             const char* xs = smem + next_stage * CFG::STAGE_BYTES;
@@ -260,6 +263,7 @@ gdn_linear_kernel(LinearArgs a) {
             const int pos = (g ^ sw) * 16;
             constexpr int NM = TI * TJ, NL = CFG::LPS, NR = TI + TJ;
             constexpr int SLOTS = NM < (NL > NR ? NL : NR) ? NM : (NL > NR ? NL : NR);   // interleave slots
+            static_assert(NL <= SLOTS, "every load has a slot");
 #pragma unroll
             for (int i = 0; i < SLOTS; ++i) {
 #pragma unroll
@@ -270,9 +274,7 @@ gdn_linear_kernel(LinearArgs a) {
                     if (r < TI) xf[0][r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xs + xrow + 16 * r * RB + pos));
                     else wf[0][r - TI] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ws + wrow + 16 * (r - TI) * RB + pos));
                 }
-#pragma unroll
-                for (int j = i * NL / SLOTS; j < (i + 1) * NL / SLOTS; ++j)
-                    LinLoad<CFG>::one(j, smem, stage, k_ahead, wave, xb, xbytes, wb, wbytes, xoff, woff);
+                if (i < NL) LinLoad<CFG>::one(i, smem, stage, k_ahead, wave, xb, xbytes, wb, wbytes, xoff, woff);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
