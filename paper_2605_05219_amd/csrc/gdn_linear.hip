@@ -395,22 +395,31 @@ int chip_cus_linear() {
     return n;
 }
 
-// The estimated time of a problem in a tile shape, in us at K = 2048: full rounds of workgroups over the chip, and a last one that
-// costs its latency (a workgroup alone walks k no faster) and more the fuller it is: the compute units share power and memory.
-// Fitted to T = 64 .. 8192, N = 2048 .. 8224, all shapes at each, the weights of the larger N not in the caches (a round then takes 4
-// to 7 us more, in every shape).  us, in shapes 3 / 0 / 4 / 5 / 2: 512 x 2048 9.9 / 21 / 16 / 20 / 39, 1400 x 2048 21 / 24 / 18 /
-// 21 / 40, 700 x 6144 38 / 32 / 34 / 25 / 50, 384 x 8224 31 / 31 / 23 / 27 / 50, 512 x 8224 40 / 32 / 36 / 27 / 51, 2048 x 6144
-// 78 / 58 / 63 / 67 / 51, 8192 x 2048 101 / 60 / 73 / 85 / 52, 8192 x 6144 299 / 181 / 217 / 219 / 154.
-struct ShapeCost { int id, bm, bn, per_cu; double full, alone; bool square; };
-constexpr ShapeCost SHAPES[5] = {{3, 64, 64, 2, 15.5, 10.0, false},
-                                 {0, 128, 128, 2, 32.0, 24.0, false},
-                                 {4, 128, 128, 1, 20.0, 16.5, false},
-                                 {5, 128, 160, 1, 24.0, 20.0, false},
-                                 {2, 256, 256, 1, 51.5, 38.0, true}};
-double shape_cost(const ShapeCost& c, int64_t T, int64_t N) {
+// The estimated time of a problem in a tile shape, in us: full rounds of workgroups over the chip, and a last one that costs its latency (a
+// workgroup alone walks k no faster) and more the fuller it is, since the compute units share power and memory.  A round has a part that
+// grows with k and a part that does not (first loads, outputs): at K = 64 the second is the larger, and the more so
+// the larger the tile, so a choice made at K = 2048 is up to 24 % off there (3000 x 6144 x 64 16.3 us in shape 2, 13.8 in shape 0; 8192 x 2560 x 256 22.9 / 19.9).
+// Fitted to T = 1 .. 12000, N = 32 .. 8224, K = 64 .. 8192, all shapes at each, weights in the caches and not: the shape
+// chosen is 0.5 % from the best of the five on average, 4 % and more in one case of twenty, at K >= 512 7 % at most, below (all of them calls
+// of 4 to 7 us) 25 %; its estimate is within 14 % in nine of ten.  us, cold weights, K = 2048, in shapes 3 / 0 / 4 / 5 / 2:
+// 512 x 2048 9.5 / 21 / 16 / 19 / 38, 1400 x 2048 20 / 23 / 18 / 21 / 39, 384 x 8224 31 / 31 / 22 / 27 / 47, 512 x 8224 39 / 31 / 36 / 27 / 49,
+// 1000 x 8224 60 / 54 / 53 / 49 / 47, 700 x 6144 36 / 31 / 33 / 24 / 47, 2048 x 6144 76 / 58 / 57 / 63 / 47, 8192 x 2048 92 / 57 / 67 / 77 / 50,
+// 8192 x 6144 283 / 173 / 205 / 204 / 147.
+struct ShapeCost {
+    int id, bm, bn, per_cu;
+    double full_k, full, alone_k, alone;      // us of a full round, of a workgroup alone: per 2048 of k, and whatever k
+    bool square;                              // the fullness of the last round counts squared
+};
+constexpr ShapeCost SHAPES[5] = {{3, 64, 64, 2, 10.4, 1.8, 3.9, 2.0, false},
+                                 {0, 128, 128, 2, 26.0, 3.3, 14.4, 1.8, false},
+                                 {4, 128, 128, 1, 14.2, 2.6, 10.4, 2.1, false},
+                                 {5, 128, 160, 1, 15.9, 5.0, 12.9, 3.9, false},
+                                 {2, 256, 256, 1, 41.9, 6.9, 32.6, 4.0, true}};
+double shape_cost(const ShapeCost& c, int64_t T, int64_t N, int32_t K) {
     const int64_t tiles = ((T + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), slots = (int64_t)chip_cus_linear() * c.per_cu;
-    const double f = (double)(tiles % slots) / (double)slots;
-    return (double)(tiles / slots) * c.full + (f > 0 ? c.alone + (c.full - c.alone) * (c.square ? f * f : f) : 0.0);
+    const double k = (double)K / 2048.0, f = (double)(tiles % slots) / (double)slots;
+    const double full = c.full_k * k + c.full, alone = c.alone_k * k + c.alone;
+    return (double)(tiles / slots) * full + (f > 0 ? alone + (full - alone) * (c.square ? f * f : f) : 0.0);
 }
 
 // Which tile shape a problem gets, and how many of its columns: a problem whose tiles leave a last round nearly empty may be cut
@@ -423,14 +432,14 @@ LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
     auto best_of = [&](int64_t n, int shapes, double* t) {
         int best = 0;
         for (int i = 0; i < shapes; ++i) {
-            const double ti = shape_cost(SHAPES[i], T, n);
+            const double ti = shape_cost(SHAPES[i], T, n, K);
             if (i == 0 || ti < *t) { best = SHAPES[i].id; *t = ti; }
         }
         return best;
     };
     double whole = 0.0;
     LinearPlan p = {best_of(N, 5, &whole), 0, N};
-    const double launch = 4.0 * 2048.0 / (double)K;      // a second launch: about 4 us whatever K
+    const double launch = 2.5;                           // a launch beyond its estimate
     double least = 0.97 * whole;                         // (a cut has to be worth it)
     const int64_t tiles_m = (T + 255) / 256, cus = chip_cus_linear();
     for (int64_t r = 1; r <= 64; ++r) {                  // the most columns that r rounds of 256 x 256 tiles hold
@@ -439,7 +448,7 @@ LinearPlan plan_linear(int64_t T, int32_t N, int32_t K) {
         if (cols == 0) continue;
         double rest = 0.0;
         const int rest_shape = best_of(N - cols, 4, &rest);
-        const double t = shape_cost(SHAPES[4], T, cols) + rest + launch;
+        const double t = shape_cost(SHAPES[4], T, cols, K) + rest + launch;
         if (t < least) { least = t; p = {2, rest_shape, (int32_t)cols}; }
     }
     return p;

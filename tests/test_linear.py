@@ -112,15 +112,17 @@ def test_plan_covers_the_outputs_and_follows_the_knob():
         assert ei.value.code == code
 
 
-@pytest.mark.parametrize("T,N,plan", [
-    (384, 8224, (4, 8224, 0)), (1400, 2048, (4, 2048, 0)),     # one round of 128 x 128 tiles
-    (512, 8224, (5, 8224, 0)),                                 # four such tiles too many, one round of 128 x 160
-    (8192, 2560, (2, 2048, 4)), (6000, 6144, (2, 5376, 5)),    # rounds of large tiles, and a rest of one round in either
-    (512, 2048, (3, 2048, 0)), (8192, 8224, (2, 8192, 3)),
+@pytest.mark.parametrize("T,N,K,plan", [
+    (384, 8224, 2048, (4, 8224, 0)), (1400, 2048, 2048, (4, 2048, 0)),     # one round of 128 x 128 tiles
+    (512, 8224, 2048, (5, 8224, 0)),                                       # four such tiles too many, one round of 128 x 160
+    (8192, 2560, 2048, (2, 2048, 4)), (6000, 6144, 2048, (2, 5376, 5)),    # rounds of large tiles, and a rest of one round in either
+    (512, 2048, 2048, (3, 2048, 0)), (8192, 8224, 2048, (2, 8192, 3)),
+    (512, 8224, 64, (0, 8224, 0)), (3000, 6144, 64, (0, 6144, 0)),         # few k steps: outputs weigh, two workgroups to a compute unit
+    (2048, 2560, 256, (0, 2560, 0)), (8192, 2560, 256, (0, 2560, 0)),
 ])
-def test_plan_names_the_shape_that_runs(T, N, plan):
+def test_plan_names_the_shape_that_runs(T, N, K, plan):
     """The plan's numbers are the knob's: the shapes with four stages are told from the one with two."""
-    assert LN.gdn_linear_plan(T, N, 2048) == plan
+    assert LN.gdn_linear_plan(T, N, K) == plan
 
 
 def test_python_binding_rejects_mismatched_tensors():
