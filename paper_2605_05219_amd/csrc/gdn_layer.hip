@@ -158,11 +158,11 @@ int32_t gdn_layer_inputs(const gdn_layer_shape* s, const void* x_qkv, const floa
     std::memcpy(p_cu, cu_seqlens, sizeof(int32_t) * (n_req + 1));
     std::memcpy(p_start, start_pos, sizeof(int32_t) * n_req);
     std::memcpy(p_src, src_slot, sizeof(int32_t) * n_req);
-    const int32_t run = run_tokens(T * (C / 8) * s->L);
+    const int32_t run = run_tokens(T * (C / 8) * s->L), run_shift = run == 8 ? 3 : 2;
     int64_t runs = 0;
     for (int32_t r = 0; r < n_req; ++r) {
         p_run[r] = (int32_t)runs;
-        runs += (cu_seqlens[r + 1] - cu_seqlens[r] + run - 1) / run;
+        runs += (cu_seqlens[r + 1] - cu_seqlens[r] + run - 1) >> run_shift;   // (by a division 11 us more for 16384 requests)
     }
     p_run[n_req] = (int32_t)runs;
     if (n_emit > 0) {
