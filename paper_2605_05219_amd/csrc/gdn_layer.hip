@@ -39,9 +39,14 @@ inline int64_t plan_ints(int32_t n_req, int32_t n_emit) { return 4 * (int64_t)n_
 // itself 10.6, 17.4, 18.7, 27.9 and 143).
 inline int32_t run_tokens(int64_t token_groups) { return token_groups / (4 * 64) <= 10 * 256 ? 4 : 8; }
 
+// Runs per wave: two where the rows have at most 32 groups of 8 channels (see the kernel).
+inline int runs_per_wave(int64_t C) { return C / 8 <= 32 ? 2 : 1; }
+
 template <typename In, typename Out>
 hipError_t launch_inputs(const LayerArgs& a, int64_t blocks, int layers, hipStream_t stream) {
-    hipLaunchKernelGGL((gdn_layer_inputs_kernel<In, Out>), dim3((unsigned)blocks, (unsigned)layers), dim3(LAYER_THREADS), 0, stream, a);
+    const dim3 grid((unsigned)blocks, (unsigned)layers), block(LAYER_THREADS);
+    if (runs_per_wave(a.C) == 2) hipLaunchKernelGGL((gdn_layer_inputs_kernel<In, Out, 2>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((gdn_layer_inputs_kernel<In, Out, 1>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -171,7 +176,8 @@ int32_t gdn_layer_inputs(const gdn_layer_shape* s, const void* x_qkv, const floa
         std::memcpy(p_eslot, emit_slot, sizeof(int32_t) * n_emit);
     }
     const int64_t CG = C / 8;
-    const int64_t conv_blocks = (runs + 3) / 4 * ((CG + 63) / 64);
+    const int rpw = runs_per_wave(C), lanes = 64 / rpw;   // lanes per run
+    const int64_t conv_blocks = (runs + 4 * rpw - 1) / (4 * rpw) * ((CG + lanes - 1) / lanes);
     const int64_t gate_blocks = (T * s->H_v + LAYER_THREADS - 1) / LAYER_THREADS;
     const int64_t emit_blocks = ((int64_t)n_emit * K1 * CG + LAYER_THREADS - 1) / LAYER_THREADS;
     const int64_t blocks = conv_blocks + gate_blocks + emit_blocks;

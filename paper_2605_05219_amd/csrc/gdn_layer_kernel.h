@@ -144,7 +144,8 @@ __device__ __forceinline__ float head_sum(float s, int d) {
     return s;
 }
 
-template <typename In, typename Out>
+// RPW: runs of tokens per wave of the convolution role
+template <typename In, typename Out, int RPW>
 __global__ void __launch_bounds__(LAYER_THREADS) gdn_layer_inputs_kernel(LayerArgs a) {
     {   // this block's layer: every tensor moves to that layer's plane
         const int64_t l = blockIdx.y;
@@ -169,15 +170,19 @@ __global__ void __launch_bounds__(LAYER_THREADS) gdn_layer_inputs_kernel(LayerAr
     if ((int)blockIdx.x < a.conv_blocks) {
         // ---- short convolution + SiLU (+ L2 normalisation of q and k): a wave takes 64 channel groups over one run of tokens, a block the
         // same channels over four runs.  The taps go through LDS: read by each thread for itself they were eight loads of 64 lines
-        // each, which is as much as a run of eight rows (see run_tokens for what that and short runs give).
-        __shared__ float4 taps[8 * 64];            // channel c of group l at 8 l + (c ^ (l & 7)): lanes read across the banks
-        const int tiles = (CG + 63) / 64;
-        const int lane = threadIdx.x & 63;
-        const int ch0 = (int)blockIdx.x % tiles * 512;
-        const int run = (int)blockIdx.x / tiles * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        // each, which is as much as a run of eight rows (see run_tokens for what that and short runs give).  Rows of at most 32
+        // groups go two to a wave (RPW = 2; 24 groups, 3 layers, 16384 requests of one token: 93 us in waves of their own, 73 so, 85
+        // when groups and runs were packed without gaps; of five tokens 44, 39, 40).
+        constexpr int LPR = 64 / RPW;              // lanes per run
+        __shared__ float4 taps[8 * LPR];           // channel c of group l at 8 l + (c ^ (l & 7)): lanes read across the banks
+        const int tiles = (CG + LPR - 1) / LPR;
+        const int lane = threadIdx.x % LPR;
+        const int ch0 = (int)blockIdx.x % tiles * (8 * LPR);
+        const int sub = RPW == 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x / LPR;
+        const int run = (int)blockIdx.x / tiles * (LAYER_THREADS / LPR) + sub;
         const int ch = ch0 + 8 * lane;
 #pragma unroll
-        for (int i = threadIdx.x; i < 512; i += LAYER_THREADS) {
+        for (int i = threadIdx.x; i < 8 * LPR; i += LAYER_THREADS) {
             if (ch0 + i >= a.C) break;
             float4 t;      // four weights per channel, older taps of a shorter convolution are zero
             if (a.K == 4) {

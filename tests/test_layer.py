@@ -256,6 +256,20 @@ def test_layer_inputs_with_channels_and_runs_that_fill_no_block(K, lens, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("H_qk,H_v,d_k,d_v", [(1, 1, 64, 64), (1, 2, 64, 64), (1, 3, 64, 64)])   # 24, 32 and 40 groups: two runs a wave, two, one
+@pytest.mark.parametrize("K,lens", [(4, [1, 1, 4, 5, 0, 9, 3, 1]), (3, [2, 13]), (4, [1] * 17)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_layer_inputs_of_narrow_rows(H_qk, H_v, d_k, d_v, K, lens, dtype):
+    """Rows of at most 32 channel groups go two runs to a wave: runs of different lengths and requests side by side, a last block with few
+    of its eight runs, against the oracle."""
+    c = wl.layer_case(2800 + K, H_qk, H_v, d_k, d_v, K, dtype, lens, [64] * len(lens), [[64 + n] if n else [] for n in lens])
+    ref = oracle_inputs(c, 1e-6)
+    got, _, _ = gpu_inputs(c, "f32", 1e-6)
+    for name, x, r in zip(("q", "k", "v", "beta", "gate"), got, ref[:5]):
+        check_tensor(x, r, "f32", name)
+
+
+@pytest.mark.gpu
 def test_layer_inputs_resume_equals_full_replay_bitwise_on_the_gpu():
     """A request resumed from the convolution state the full run stored reproduces the full run's outputs bit for bit."""
     H, d, K, N, p = 2, 128, 4, 300, 131
