@@ -90,7 +90,6 @@ struct AttnArgs {
     int32_t H_q, H_kv;
     int32_t xcd_split;        // 1: blocks are dealt to the 8 XCDs by key/value head
     int32_t pack;             // query heads per token in a workgroup's rows: 1, or H_q / H_kv (a divisor of 128)
-    int32_t pair;             // 1: a workgroup takes two head blocks of a key/value head
     float scale_log2e;        // scale * log2(e)
 };
 

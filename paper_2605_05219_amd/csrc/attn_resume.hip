@@ -80,19 +80,20 @@ inline int64_t plan_bytes(int32_t n_req, int64_t T, int G) {
 inline int64_t part_ml_bytes() { return (int64_t)SPLIT_MAX_WGS * ATT_BQ * 2 * sizeof(float); }
 inline int64_t part_o_bytes(int d) { return (int64_t)SPLIT_MAX_WGS * ATT_BQ * d * sizeof(float); }
 
-template <int D, typename OT>
+template <int D, typename OT, int NH>
 hipError_t launch_attn(const AttnArgs& a, unsigned blocks, hipStream_t stream) {
-    if (a.pair) hipLaunchKernelGGL((attn_suffix_kernel<D, OT, D == 128 ? 2 : 1>), dim3(blocks), dim3(2 * ATT_THREADS), 0, stream, a);
-    else hipLaunchKernelGGL((attn_suffix_kernel<D, OT, 1>), dim3(blocks), dim3(ATT_THREADS), 0, stream, a);
+    hipLaunchKernelGGL((attn_suffix_kernel<D, OT, NH>), dim3(blocks), dim3(ATT_THREADS * NH), 0, stream, a);
     return hipGetLastError();
 }
 
+// NH: head blocks per workgroup; 2 is built for d = 128 only
 template <typename OT>
-hipError_t launch_attn_d(int d, const AttnArgs& a, unsigned blocks, hipStream_t stream) {
+hipError_t launch_attn_d(int d, int NH, const AttnArgs& a, unsigned blocks, hipStream_t stream) {
+    if (NH != 1 && d != 128) return hipErrorInvalidValue;
     switch (d) {
-        case 64: return launch_attn<64, OT>(a, blocks, stream);
-        case 128: return launch_attn<128, OT>(a, blocks, stream);
-        default: return launch_attn<256, OT>(a, blocks, stream);
+        case 64: return launch_attn<64, OT, 1>(a, blocks, stream);
+        case 128: return NH == 2 ? launch_attn<128, OT, 2>(a, blocks, stream) : launch_attn<128, OT, 1>(a, blocks, stream);
+        default: return launch_attn<256, OT, 1>(a, blocks, stream);
     }
 }
 
@@ -561,9 +562,8 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     }
     if (n_wide > 0) {
         a.pack = pack;
-        a.pair = NH == 2;
-        e = s->o_dtype == GDN_F32 ? launch_attn_d<float>(s->d, a, (unsigned)blocks, stream)
-                                  : launch_attn_d<uint16_t>(s->d, a, (unsigned)blocks, stream);
+        e = s->o_dtype == GDN_F32 ? launch_attn_d<float>(s->d, NH, a, (unsigned)blocks, stream)
+                                  : launch_attn_d<uint16_t>(s->d, NH, a, (unsigned)blocks, stream);
         if (e != hipSuccess) return hip_err(e);
     }
 
