@@ -140,14 +140,25 @@ int32_t attn_plan(const attn_shape *shape, int32_t n_req, const int32_t *cu_seql
                   int32_t *key_tile_rows);
 
 /*
+ * How many head blocks (a query head, or with packed rows the heads of a key/value group) a workgroup
+ * of the 128-row kernel takes in such a call: 1, or 2 (d = 128 only; the workgroup then has eight waves).
+ * Host only; the errors of attn_plan.
+ */
+int32_t attn_plan_heads(const attn_shape *shape, int32_t n_req, const int32_t *cu_seqlens,
+                        const int32_t *start_pos);
+
+/*
  * Tuning knobs (not steps of the method; for tests and experiments).  attn_tune_split(0) forbids
  * cutting long key walks into parts, attn_tune_pack(0) forbids packing the query heads of a
  * key/value group into one workgroup's rows, and either forbids the few-rows kernel; a non-zero
- * argument restores the automatic choice.
+ * argument restores the automatic choice.  attn_tune_pairs(0) keeps one head block per workgroup,
+ * attn_tune_pairs(2) takes two wherever that kernel is built (d = 128, an even number of head blocks per
+ * key/value head), anything else restores the automatic choice; the results are bitwise the same.
  * Each returns its previous setting (1 = automatic).  Process-wide; read at every call.
  */
 int32_t attn_tune_split(int32_t allow);
 int32_t attn_tune_pack(int32_t allow);
+int32_t attn_tune_pairs(int32_t mode);
 
 #ifdef __cplusplus
 }

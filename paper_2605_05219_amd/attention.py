@@ -7,8 +7,8 @@ from .binding import GDN_BF16, GDN_F32, _check, _dp, _h32, _hp, _stream_ptr, lib
 
 _i32, _i64, _vp, _f32 = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p, ctypes.c_float
 
-EXPORTS = ["attn_workspace_bytes", "attn_kv_restore", "attn_kv_spill", "attn_suffix_prefill", "attn_plan", "attn_tune_split",
-           "attn_tune_pack"]
+EXPORTS = ["attn_workspace_bytes", "attn_kv_restore", "attn_kv_spill", "attn_suffix_prefill", "attn_plan", "attn_plan_heads",
+           "attn_tune_split", "attn_tune_pack", "attn_tune_pairs"]
 
 
 class attn_shape(ctypes.Structure):
@@ -39,7 +39,9 @@ def _lib():
                                           + [_vp, _vp, _i64, _i32, _i32, _vp] + [_vp, _vp, _i64, _vp])
         L.attn_plan.restype = _i32
         L.attn_plan.argtypes = [ctypes.POINTER(attn_shape), _i32, _vp, _vp, _i32] + [_vp] * 8
-        for f in (L.attn_tune_split, L.attn_tune_pack):
+        L.attn_plan_heads.restype = _i32
+        L.attn_plan_heads.argtypes = [ctypes.POINTER(attn_shape), _i32, _vp, _vp]
+        for f in (L.attn_tune_split, L.attn_tune_pack, L.attn_tune_pairs):
             f.restype = _i32
             f.argtypes = [_i32]
         _ready = True
@@ -56,6 +58,11 @@ def attn_tune_pack(allow: bool) -> bool:
     return bool(_lib().attn_tune_pack(1 if allow else 0))
 
 
+def attn_tune_pairs(mode: int) -> int:
+    """0: a workgroup takes one head block always; 2: two wherever that kernel is built; 1: automatic.  Returns the previous setting."""
+    return int(_lib().attn_tune_pairs(int(mode)))
+
+
 def attn_workspace_bytes(shape: attn_shape, n_req: int, total_tokens: int) -> int:
     return _check(int(_lib().attn_workspace_bytes(ctypes.byref(shape), int(n_req), int(total_tokens))), "attn_workspace_bytes")
 
@@ -70,6 +77,12 @@ def attn_plan(shape: attn_shape, cu_seqlens, start_pos, capacity: int = 1 << 16)
     _check(_lib().attn_plan(ctypes.byref(shape), int(sp.size), _hp(cu), _hp(sp), int(capacity), *[_vp(a.ctypes.data) for a in arrs],
                             ctypes.byref(n), ctypes.byref(pack), ctypes.byref(kt)), "attn_plan")
     return np.stack([a[:n.value] for a in arrs], axis=1), pack.value, kt.value
+
+
+def attn_plan_heads(shape: attn_shape, cu_seqlens, start_pos) -> int:
+    """Head blocks per workgroup of the 128-row kernel in such a call (1 or 2).  Host only."""
+    cu, sp = _h32(cu_seqlens), _h32(start_pos)
+    return _check(int(_lib().attn_plan_heads(ctypes.byref(shape), int(sp.size), _hp(cu), _hp(sp))), "attn_plan_heads")
 
 
 def _pool_geometry(pool):

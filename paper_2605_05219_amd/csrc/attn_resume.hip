@@ -126,6 +126,7 @@ hipError_t launch_combine_d(int d, const CombineArgs& a, hipStream_t stream) {
 // The work of one attn_suffix_prefill call (host, integer): how the rows of a workgroup are made up, the pieces
 // (row tiles of a request), the cut of long key walks into parts, and the units (whole walks or parts) in launch order.
 std::atomic<int32_t> g_allow_split{1}, g_allow_pack{1};   // attn_tune_split / attn_tune_pack
+std::atomic<int32_t> g_pairs{1};                           // attn_tune_pairs: 0 never, 1 per call, 2 wherever they are built
 struct Unit { int32_t req, tile, t0, t1, part; bool few; };      // part: slot among those of its kind of request, or -1
 struct Piece { int32_t req, tile, n_tiles, parts, base; };       // base: first slot
 struct UnitPlan {
@@ -276,8 +277,7 @@ void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const 
 // the units, longest first, are dealt back and forth; a single-head workgroup that has a compute unit to itself goes through its tiles faster,
 // so its side counts half way to the mean.  Single / pairs, 16 heads on 2: 8192 tokens 295 / 268 us; on 4, 1354 tokens behind 1872 (300 pairs where 256 fit) 60 / 69; more
 // rounds: six suffixes of 1289 to 2578 tokens 330 / 342, five with 32 heads on 4 386 / 422, 29 of 915 to 1830 486 / 497, 16 of 900 to 1900 751 / 727.
-inline bool pairs_pay(const attn_shape& s, const UnitPlan& plan, int head_blocks) {
-    if (s.d != 128 || s.H_q / s.H_kv / plan.pack % 2 != 0) return false;
+inline bool pairs_pay(const UnitPlan& plan, int head_blocks) {
     std::vector<int32_t> tiles;
     int64_t sum = 0;
     for (const Unit& u : plan.units) {
@@ -300,6 +300,26 @@ inline bool pairs_pay(const attn_shape& s, const UnitPlan& plan, int head_blocks
     };
     const double mean = (double)sum * head_blocks / (2 * CUS);
     return fullest(head_blocks / 2, CUS) <= 1.06 * 0.5 * (fullest(head_blocks, 2 * CUS) + mean);
+}
+
+// Head blocks per workgroup of the 128-row kernel.
+inline int heads_per_workgroup(const attn_shape& s, const UnitPlan& plan) {
+    const int mode = g_pairs.load();
+    if (mode == 0 || s.d != 128 || s.H_q / s.H_kv / plan.pack % 2 != 0) return 1;
+    return mode == 2 || pairs_pay(plan, s.H_q / plan.pack) ? 2 : 1;
+}
+
+// The requests of attn_plan and attn_plan_heads checked, and their suffix lengths.
+int32_t plan_lengths(int32_t n_req, const int32_t* cu_seqlens, const int32_t* start_pos, std::vector<int32_t>& len) {
+    len.resize(n_req);
+    if (!cu_seqlens || !start_pos) return GDN_ERR_NULL;
+    if (cu_seqlens[0] != 0) return GDN_ERR_SEQLENS;
+    for (int32_t r = 0; r < n_req; ++r) {
+        if (cu_seqlens[r + 1] < cu_seqlens[r]) return GDN_ERR_SEQLENS;
+        len[r] = cu_seqlens[r + 1] - cu_seqlens[r];
+        if (start_pos[r] < 0 || (int64_t)start_pos[r] + len[r] > INT32_MAX - 256) return GDN_ERR_START;
+    }
+    return GDN_OK;
 }
 
 }  // namespace
@@ -381,7 +401,7 @@ int32_t attn_kv_spill(const attn_shape* s, int32_t n_req, const int32_t* n_rows,
 int32_t attn_plan(const attn_shape* s, int32_t n_req, const int32_t* cu_seqlens, const int32_t* start_pos, int32_t capacity,
                   int32_t* unit_req, int32_t* unit_tile, int32_t* unit_t0, int32_t* unit_t1, int32_t* unit_part,
                   int32_t* n_units, int32_t* heads_per_row_group, int32_t* key_tile_rows) {
-    const int32_t rc = check_shape(s);
+    int32_t rc = check_shape(s);
     if (rc != GDN_OK) return rc;
     if (n_req < 0 || capacity < 0) return GDN_ERR_COUNT;
     if (!n_units || !heads_per_row_group || !key_tile_rows) return GDN_ERR_NULL;
@@ -389,14 +409,9 @@ int32_t attn_plan(const attn_shape* s, int32_t n_req, const int32_t* cu_seqlens,
     *heads_per_row_group = 1;
     *key_tile_rows = att_kt(s->d);
     if (n_req == 0) return GDN_OK;
-    if (!cu_seqlens || !start_pos) return GDN_ERR_NULL;
-    if (cu_seqlens[0] != 0) return GDN_ERR_SEQLENS;
-    std::vector<int32_t> len(n_req);
-    for (int32_t r = 0; r < n_req; ++r) {
-        if (cu_seqlens[r + 1] < cu_seqlens[r]) return GDN_ERR_SEQLENS;
-        len[r] = cu_seqlens[r + 1] - cu_seqlens[r];
-        if (start_pos[r] < 0 || (int64_t)start_pos[r] + len[r] > INT32_MAX - 256) return GDN_ERR_START;
-    }
+    std::vector<int32_t> len;
+    rc = plan_lengths(n_req, cu_seqlens, start_pos, len);
+    if (rc != GDN_OK) return rc;
     UnitPlan plan;
     build_units(*s, n_req, len.data(), start_pos, plan);
     *n_units = (int32_t)plan.units.size();
@@ -411,6 +426,19 @@ int32_t attn_plan(const attn_shape* s, int32_t n_req, const int32_t* cu_seqlens,
         unit_part[i] = plan.units[i].part < 0 ? -1 : plan.units[i].part + (plan.units[i].few ? plan.n_slots[0] : 0);
     }
     return GDN_OK;
+}
+
+int32_t attn_plan_heads(const attn_shape* s, int32_t n_req, const int32_t* cu_seqlens, const int32_t* start_pos) {
+    int32_t rc = check_shape(s);
+    if (rc != GDN_OK) return rc;
+    if (n_req < 0) return GDN_ERR_COUNT;
+    if (n_req == 0) return 1;
+    std::vector<int32_t> len;
+    rc = plan_lengths(n_req, cu_seqlens, start_pos, len);
+    if (rc != GDN_OK) return rc;
+    UnitPlan plan;
+    build_units(*s, n_req, len.data(), start_pos, plan);
+    return heads_per_workgroup(*s, plan);
 }
 
 int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_new, const void* v_new, const void* out_gate,
@@ -446,7 +474,7 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
     build_units(*s, n_req, len.data(), start_pos, plan);
     const int G = s->H_q / s->H_kv;
     const int pack = plan.pack, HB = s->H_q / pack;
-    const int NH = pairs_pay(*s, plan, HB) ? 2 : 1;   // head blocks per workgroup
+    const int NH = heads_per_workgroup(*s, plan);
     const int64_t n_narrow = plan.apart ? plan.n_units[1] : 0, n_wide = (int64_t)plan.units.size() - n_narrow;
     const bool xcd_split = 8 % s->H_kv == 0;
     int64_t blocks;
@@ -596,5 +624,7 @@ int32_t attn_suffix_prefill(const attn_shape* s, const void* q, const void* k_ne
 int32_t attn_tune_split(int32_t allow) { return g_allow_split.exchange(allow != 0); }
 
 int32_t attn_tune_pack(int32_t allow) { return g_allow_pack.exchange(allow != 0); }
+
+int32_t attn_tune_pairs(int32_t mode) { return g_pairs.exchange(mode == 0 || mode == 2 ? mode : 1); }
 
 }  // extern "C"

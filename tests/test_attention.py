@@ -236,6 +236,28 @@ def test_mixed_calls_walk_decode_rows_whole_only_as_calls_of_their_own_do(seed):
     assert 5 * parts[0] + (8 if apart else 5) * parts[1] <= 8 * 768
 
 
+def test_planner_tells_the_heads_of_a_workgroup():
+    heads = lambda H_q, H_kv, d, lens, starts: AT.attn_plan_heads(AT.make_attn_shape(H_q, H_kv, d), np.concatenate([[0], np.cumsum(lens)]), starts)
+    assert heads(16, 2, 128, [8192], [0]) == 2 and heads(16, 2, 128, [512], [7680]) == 2 and heads(16, 4, 128, [128] * 32, [64] * 32) == 2
+    assert heads(16, 4, 128, [1354], [1872]) == 1                      # 300 workgroups of two heads where 256 have a compute unit
+    assert heads(16, 2, 128, [], []) == 1 and heads(16, 2, 128, [0], [5]) in (1, 2)
+    for mode in (0, 2):
+        prev = AT.attn_tune_pairs(mode)
+        try:
+            assert prev == 1
+            for d in (64, 128, 256):                                   # built for d = 128 and an even number of head blocks only
+                assert heads(16, 2, d, [1000], [0]) == (2 if mode == 2 and d == 128 else 1)
+            assert heads(10, 2, 128, [1000], [0]) == 1 and heads(8, 8, 128, [1000], [0]) == 1
+            assert heads(16, 2, 128, [8], [3000]) == 1                 # packed rows: one head block per key/value head
+        finally:
+            assert AT.attn_tune_pairs(prev) == mode
+    assert AT.attn_tune_pairs(7) == 1 and AT.attn_tune_pairs(1) == 1   # anything else: automatic
+    for cu, sp, code in [([1, 100], [0], -4), ([0, 100, 90], [0, 0], -4), ([0, 5], [-1], -10)]:
+        with pytest.raises(B.GdnError) as ei:
+            AT.attn_plan_heads(AT.make_attn_shape(16, 2, 128), cu, sp)
+        assert ei.value.code == code
+
+
 # ----------------------------------------------------------------------------- GPU parity
 def f64(a):
     return wl.to_f32(a).astype(np.float64)
@@ -436,24 +458,68 @@ def test_split_key_walks_agree_with_whole_walks(monkeypatch):
 @pytest.mark.parametrize("split", [False, True])
 @pytest.mark.parametrize("H_q,H_kv", [(12, 2), (6, 3), (16, 4), (10, 2)])   # groups of 6 (no packing), 2 on a plain block order, 4; an odd one: no pairs
 def test_workgroups_of_two_query_heads(H_q, H_kv, split):
-    """d = 128, unpacked rows: a workgroup takes two heads of a key/value group.  Query tiles that end anywhere, waves without a row,
-    whole walks and parts of walks, some past a query's limit, against the oracle."""
+    """d = 128, unpacked rows: a workgroup is made to take two heads of a key/value group.  Query tiles that end anywhere, waves without
+    a row, whole walks and parts of walks, some past a query's limit, against the oracle and bit for bit against workgroups of one head."""
     lens, starts = [1, 127, 128, 129, 300], [700, 64, 513, 0, 1300]
     c = wl.attn_case(3900 + H_q, H_q, H_kv, 128, lens, starts, spare_slots=1)
+    got = {}
     AT.attn_tune_pack(False)
     AT.attn_tune_split(split)
     try:
-        got, k_after, v_after = gpu_prefill(c, gate=True)
-        bf, _, _ = gpu_prefill(c, "bf16")
+        for mode in (0, 2):
+            prev = AT.attn_tune_pairs(mode)
+            try:
+                heads = AT.attn_plan_heads(AT.make_attn_shape(H_q, H_kv, 128), c.cu_seqlens, c.start_pos)
+                assert heads == (2 if mode == 2 and H_q // H_kv % 2 == 0 else 1)
+                got[mode] = [gpu_prefill(c, gate=True), gpu_prefill(c, "bf16")]
+            finally:
+                AT.attn_tune_pairs(prev)
     finally:
         AT.attn_tune_pack(True)
         AT.attn_tune_split(True)
-    check_o(got, oracle_o(c, 128 ** -0.5, True), "f32")
-    check_o(bf, oracle_o(c, 128 ** -0.5), "bf16")
+    check_o(got[2][0][0], oracle_o(c, 128 ** -0.5, True), "f32")
+    check_o(got[2][1][0], oracle_o(c, 128 ** -0.5), "bf16")
     k_want, v_want = pools_with_prefix(c)
     for r, s in enumerate(c.seq_slot):
         k_want[s, :len(c.k_full[r])], v_want[s, :len(c.v_full[r])] = c.k_full[r], v_bits(c.v_full[r])
-    assert np.array_equal(k_after, k_want) and np.array_equal(v_after, v_want)
+    assert np.array_equal(got[2][0][1], k_want) and np.array_equal(got[2][0][2], v_want)
+    for one, two in zip(got[0], got[2]):
+        assert all(np.array_equal(x, y) for x, y in zip(one, two))
+
+
+@pytest.mark.gpu
+def test_decode_rows_beside_workgroups_of_two_query_heads():
+    """One launch for suffixes and decode rows (walks of these in parts, their slots behind the others'), two heads to a workgroup."""
+    lens, starts = [1, 512, 2, 255], [1500, 300, 3000, 1100]
+    c = wl.attn_case(3950, 4, 2, 128, lens, starts)
+    prev = AT.attn_tune_pairs(2)
+    try:
+        units, pack, _ = AT.attn_plan(AT.make_attn_shape(4, 2, 128), c.cu_seqlens, c.start_pos)
+        assert pack == 1 and AT.attn_plan_heads(AT.make_attn_shape(4, 2, 128), c.cu_seqlens, c.start_pos) == 2
+        assert (units[units[:, 0] == 0][:, 4] >= 0).all()              # the decode rows' walks are split
+        two = gpu_prefill(c, gate=True)
+        AT.attn_tune_pairs(0)
+        one = gpu_prefill(c, gate=True)
+    finally:
+        AT.attn_tune_pairs(prev)
+    check_o(two[0], oracle_o(c, 128 ** -0.5, True), "f32")
+    assert all(np.array_equal(x, y) for x, y in zip(one, two))
+
+
+@pytest.mark.gpu
+def test_calls_that_take_pairs_of_heads_by_themselves():
+    """32 prompts of 128 tokens behind 64: a unit a prompt, 256 workgroups of two heads, one to a compute unit."""
+    c = wl.attn_case(3960, 16, 4, 128, [128] * 32, [64] * 32)
+    sh = AT.make_attn_shape(16, 4, 128, "bf16")
+    assert AT.attn_plan_heads(sh, c.cu_seqlens, c.start_pos) == 2
+    two = gpu_prefill(c, "bf16")
+    prev = AT.attn_tune_pairs(0)
+    try:
+        one = gpu_prefill(c, "bf16")
+    finally:
+        AT.attn_tune_pairs(prev)
+    check_o(two[0], oracle_o(c, 128 ** -0.5), "bf16")
+    assert all(np.array_equal(x, y) for x, y in zip(one, two))
 
 
 @pytest.mark.gpu
