@@ -151,20 +151,34 @@ inline bool few_rows(int32_t len, int32_t start, int G) {
 }
 
 // Rows of a workgroup of the 128-row kernel: 128 tokens of one query head (1), or, where that would leave too many of all
-// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).  Too many: a fifth, and in calls of many rounds of
-// workgroups 7 in a hundred (64 suffixes of 200 to 1000 tokens behind 3000 to 5000, 0.926 of the rows, 1572 -> 1530 us, at d = 64 891 -> 861, 32 at d = 256
-// 1592 -> 1510; 0.96 of them 727 -> 747).  In smaller calls the cut of the walks and the last round decide (d = 256, one suffix of 430 to 860 tokens 57 / 77,
-// three 111 / 101).
-int pick_pack(const attn_shape& s, int32_t n_req, const int32_t* len, const std::vector<char>& elsewhere) {
+// rows empty (short suffixes), 128 / G tokens of the G heads of a key/value group (G).  Too many: a fifth.  In calls of many rounds of
+// workgroups fewer will do, down to 7 in a hundred at G >= 8 and 9.5 below (64 suffixes of 200 to 1000 tokens behind 3000 to 5000, G = 8, 0.926 of the
+// rows, 1572 -> 1530 us, at d = 64 891 -> 861; at G = 4 and 0.915 to 0.926 of them 0.93 to 1.13 of the time, 1.00 on average), if the
+// key tiles this saves weigh more than the plan it costs: G times the units, some 25 ns each to list, sort and send.  (64 suffixes of 110 to 440
+// behind 64 to 128, G = 8, d = 64, 0.834 of the rows but 1108 units for 166: 54 -> 66 us; of 250 to 500 behind 3000 to 6000, d = 256, 0.868 of them
+// 2061 -> 1871.  Over 530 calls of G = 4 and 8 that are less than a fifth empty this rule is 0.5 % from the better form on average, 6 % at worst; packing all of
+// them 0.7 and 17 %, and 1.3 % where each call is waited for before the next; packing none 2.9 %.)
+// In smaller calls the cut of the walks and the last round decide (d = 256, one suffix of 430 to 860 tokens 57 / 77, three 111 / 101).
+int pick_pack(const attn_shape& s, int32_t n_req, const int32_t* len, const int32_t* start_pos, const std::vector<char>& elsewhere) {
     const int G = s.H_q / s.H_kv;
     if (G == 1 || ATT_BQ % G != 0 || g_allow_pack.load() == 0) return 1;
-    int64_t rows_plain = 0, rows_packed = 0;
+    const int KT = att_kt(s.d);
+    int64_t units[2] = {0, 0};           // plain, packed
+    double tiles[2] = {0.0, 0.0};        // key tiles of one head block's workgroups
     for (int32_t r = 0; r < n_req; ++r) {
         if (elsewhere[r]) continue;
-        rows_plain += (int64_t)((len[r] + ATT_BQ - 1) / ATT_BQ) * s.H_q;
-        rows_packed += (int64_t)((len[r] + ATT_BQ / G - 1) / (ATT_BQ / G)) * s.H_kv;
+        for (int k = 0; k < 2; ++k) {
+            const int TPW = k ? ATT_BQ / G : ATT_BQ;
+            const int64_t n = (len[r] + TPW - 1) / TPW;
+            units[k] += n;
+            tiles[k] += (double)n * (0.5 + ((double)start_pos[r] + 0.5 * (len[r] + TPW)) / KT);
+        }
     }
-    return rows_packed * 100 <= rows_plain * (rows_packed >= 4 * SPLIT_BELOW ? 93 : 80) ? G : 1;      // (in workgroups: 128 rows each)
+    const int64_t rows_plain = units[0] * s.H_q, rows_packed = units[1] * s.H_kv;      // (in workgroups: 128 rows each)
+    if (rows_packed * 100 <= rows_plain * 80) return G;
+    if (rows_packed < 4 * SPLIT_BELOW || rows_packed * 1000 > rows_plain * (G >= 8 ? 930 : 905)) return 1;
+    const double tile_ns = s.d == 64 ? 2.2 : 3.9, plain_ns = tile_ns * tiles[0] * s.H_q, packed_ns = tile_ns * tiles[1] * s.H_kv;   // a workgroup's tile, the chip full
+    return plain_ns - packed_ns >= 25.0 * (double)(units[1] - units[0]) ? G : 1;
 }
 
 // Which kernel walks the few-rows requests.  What is in a call beside such a request must not change the bits of its whole walk,
@@ -186,7 +200,7 @@ void pick_kernels(const attn_shape& s, int32_t n_req, const int32_t* len, const 
         n_few += out.few[r];
         n_live += len[r] > 0;
     }
-    out.pack = pick_pack(s, n_req, len, std::vector<char>(n_req, 0));
+    out.pack = pick_pack(s, n_req, len, start_pos, std::vector<char>(n_req, 0));
     if (n_few == 0) return;
     const int TPW = ATT_BQ / out.pack, HB = s.H_q / out.pack;
     int64_t others = 0;
@@ -195,7 +209,7 @@ void pick_kernels(const attn_shape& s, int32_t n_req, const int32_t* len, const 
     const bool one_launch = n_few < n_live && ((others + n_few) * HB < SPLIT_BELOW || others * HB >= SPLIT_BELOW);
     const bool room = 2 * n_few * HB * NAR_ROWS <= SPLIT_MAX_WGS * ATT_BQ && 2 * n_few * WIDE_INTS <= UNIT_INTS * SPLIT_MAX_WGS;   // two parts each
     out.apart = !(one_launch && room);
-    if (out.apart) out.pack = pick_pack(s, n_req, len, out.few);
+    if (out.apart) out.pack = pick_pack(s, n_req, len, start_pos, out.few);
 }
 
 void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const int32_t* start_pos, UnitPlan& out) {

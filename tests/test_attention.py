@@ -236,6 +236,22 @@ def test_mixed_calls_walk_decode_rows_whole_only_as_calls_of_their_own_do(seed):
     assert 5 * parts[0] + (8 if apart else 5) * parts[1] <= 8 * 768
 
 
+@pytest.mark.parametrize("H_q,H_kv,d,n,lo,hi,start,packed", [
+    (16, 2, 64, 64, 110, 440, 64, False),        # short walks: seven times the units cost the host more than the sixth of the rows they spare
+    (16, 2, 128, 48, 250, 500, 64, False),
+    (16, 2, 128, 64, 200, 1000, 3000, True), (16, 2, 256, 64, 250, 500, 3000, True), (16, 4, 64, 64, 250, 400, 3000, True),
+    (16, 4, 256, 96, 400, 800, 800, False),      # groups of four, a thirteenth of the rows empty
+])
+def test_rows_are_packed_where_the_walks_outweigh_the_plan(H_q, H_kv, d, n, lo, hi, start, packed):
+    """Calls of many workgroups, less than a fifth of whose rows would stay empty."""
+    lens = [lo + (hi - lo) * i // (n - 1) for i in range(n)]
+    G = H_q // H_kv
+    rows = [sum(-(-x // 128) for x in lens) * H_q, sum(-(-x // (128 // G)) for x in lens) * H_kv]
+    assert 0.80 * rows[0] < rows[1] <= 0.93 * rows[0] and rows[1] >= 2048
+    _, pack, _ = AT.attn_plan(AT.make_attn_shape(H_q, H_kv, d), np.concatenate([[0], np.cumsum(lens)]), [start + 7 * i for i in range(n)])
+    assert pack == (G if packed else 1)
+
+
 def test_planner_tells_the_heads_of_a_workgroup():
     heads = lambda H_q, H_kv, d, lens, starts: AT.attn_plan_heads(AT.make_attn_shape(H_q, H_kv, d), np.concatenate([[0], np.cumsum(lens)]), starts)
     assert heads(16, 2, 128, [8192], [0]) == 2 and heads(16, 2, 128, [512], [7680]) == 2 and heads(16, 4, 128, [128] * 32, [64] * 32) == 2
