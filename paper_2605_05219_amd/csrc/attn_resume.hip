@@ -286,11 +286,17 @@ void build_units(const attn_shape& sh, int32_t n_req, const int32_t* len, const 
     std::stable_sort(out.units.begin(), out.units.end(), [](const Unit& x, const Unit& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
 }
 
-// Whether the workgroups of the 128-row kernel take two head blocks each (see attn_kernel.h): at d = 128, in calls of at most two rounds of them, one to a
-// compute unit, that balance over the chip as well as workgroups of half the size, two to one.  That is estimated by the key tiles of the fullest place when
-// the units, longest first, are dealt back and forth; a single-head workgroup that has a compute unit to itself goes through its tiles faster,
-// so its side counts half way to the mean.  Single / pairs, 16 heads on 2: 8192 tokens 295 / 268 us; on 4, 1354 tokens behind 1872 (300 pairs where 256 fit) 60 / 69; more
-// rounds: six suffixes of 1289 to 2578 tokens 330 / 342, five with 32 heads on 4 386 / 422, 29 of 915 to 1830 486 / 497, 16 of 900 to 1900 751 / 727.
+// Whether the workgroups of the 128-row kernel take two head blocks each (see attn_kernel.h), where that kernel is built: in calls of at most two rounds
+// of such workgroups, one to a compute unit, whose walks are long enough and that balance over the chip as well as workgroups of half the size, two to one.
+// Balance is estimated by the key tiles of the fullest place when the units, longest first, are dealt back and forth; a single-head workgroup that has a
+// compute unit to itself goes through its tiles faster, so its side counts half way to the mean.  Single / pairs, 16 heads on 2, one suffix: 8192 tokens 303 /
+// 280 us, 7936 288 / 265; 3000 68 / 79 and 4096 100 / 115 (unbalanced); 32 heads on 4, 4096 tokens 161 / 153.
+// Walks: a pair starts when both its heads' first tiles have come and ends when both are done, which a short walk does not make up for.  Two rounds, by mean tiles of
+// a walk: below 6 6 % slower on average (64 prompts of 128 tokens 37 / 42, behind 64 to 96 45 / 49), 6 to 16 4 %, 16 to 24 2 %, 28 to 34 even,
+// 34 to 50 1.5 % faster, more 3 %; one round: below 12 2 % slower (512 tokens of 32 heads behind 2048 44 / 45), 16 2 % faster (512 of 16 behind 8000 58 / 57).
+// Beyond two rounds it goes either way: 8320 tokens 310 / 292, behind 2048 441 / 460, behind 8000 894 / 941, 10240 437 / 451, 12288 620 / 623, 16384 1060 / 1029; five with
+// 32 heads on 4 386 / 422, 29 of 915 to 1830 486 / 497, 16 of 900 to 1900 751 / 727; over 141 calls of more than 1024 workgroups between 0.94 and 1.19,
+// 1.01 on average.  These keep one head.
 inline bool pairs_pay(const UnitPlan& plan, int head_blocks) {
     std::vector<int32_t> tiles;
     int64_t sum = 0;
@@ -300,7 +306,8 @@ inline bool pairs_pay(const UnitPlan& plan, int head_blocks) {
         sum += u.t1 - u.t0;
     }
     constexpr int CUS = SPLIT_BELOW / 2;
-    if ((int64_t)tiles.size() * head_blocks > 4 * CUS) return false;
+    const int64_t wgs = (int64_t)tiles.size() * head_blocks;
+    if (wgs > 4 * CUS || sum < (int64_t)tiles.size() * (wgs <= 2 * CUS ? 14 : 28)) return false;
     auto fullest = [&](int per_unit, int places) {
         std::vector<int32_t> load(places, 0);
         int j = 0, most = 0;

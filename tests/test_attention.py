@@ -254,7 +254,8 @@ def test_rows_are_packed_where_the_walks_outweigh_the_plan(H_q, H_kv, d, n, lo, 
 
 def test_planner_tells_the_heads_of_a_workgroup():
     heads = lambda H_q, H_kv, d, lens, starts: AT.attn_plan_heads(AT.make_attn_shape(H_q, H_kv, d), np.concatenate([[0], np.cumsum(lens)]), starts)
-    assert heads(16, 2, 128, [8192], [0]) == 2 and heads(16, 2, 128, [512], [7680]) == 2 and heads(16, 4, 128, [128] * 32, [64] * 32) == 2
+    assert heads(16, 2, 128, [8192], [0]) == 2 and heads(16, 2, 128, [512], [7680]) == 2 and heads(32, 4, 128, [1024] * 4, [2000] * 4) == 2
+    assert heads(16, 4, 128, [128] * 64, [64] * 64) == 1 and heads(32, 4, 128, [512], [2048]) == 1          # short walks
     assert heads(16, 4, 128, [1354], [1872]) == 1                      # 300 workgroups of two heads where 256 have a compute unit
     assert heads(16, 2, 128, [], []) == 1 and heads(16, 2, 128, [0], [5]) in (1, 2)
     for mode in (0, 2):
@@ -524,9 +525,9 @@ def test_decode_rows_beside_workgroups_of_two_query_heads():
 
 @pytest.mark.gpu
 def test_calls_that_take_pairs_of_heads_by_themselves():
-    """32 prompts of 128 tokens behind 64: a unit a prompt, 256 workgroups of two heads, one to a compute unit."""
-    c = wl.attn_case(3960, 16, 4, 128, [128] * 32, [64] * 32)
-    sh = AT.make_attn_shape(16, 4, 128, "bf16")
+    """32 suffixes of 120 to 128 tokens behind 1900 to 2000: a whole walk of 32 tiles for each, 512 workgroups of two heads."""
+    c = wl.attn_case(3960, 32, 4, 128, [128, 120, 127, 128] * 8, [1900 + 3 * i for i in range(32)])
+    sh = AT.make_attn_shape(32, 4, 128, "bf16")
     assert AT.attn_plan_heads(sh, c.cu_seqlens, c.start_pos) == 2
     two = gpu_prefill(c, "bf16")
     prev = AT.attn_tune_pairs(0)
