@@ -63,7 +63,8 @@ struct FusedArgs {
     const int32_t* req_chunk_cu;
     const int32_t* req_src_slot;
     const int32_t* req_order;        // requests, longest chain first
-    int32_t* next_chain;             // one word, zero when the kernel starts: chains handed out beyond the first two rounds
+    int32_t* next_chain;             // one word, zero when the kernel starts: chains handed out beyond the first two rounds of gridDim.x (fused kernel,
+                                     // which holds a chain in reserve) or beyond the first (pipelined kernel)
     const float* state_src;
     float* state_dst;
     int64_t src_slot_stride, dst_slot_stride;

@@ -25,7 +25,7 @@
 // same piece of 16 consecutive rows hit 16 different 16-byte bank groups.  Rows past the end of x or w read as
 // zeros (the buffer descriptor ends with the matrix); they only feed outputs that are never stored.  The products
 // are taken transposed (w rows as the left operand), so that a lane holds four consecutive outputs of ONE token
-// and stores them with one 8- or 16-byte store.
+// and writes them to LDS, for the turn to whole rows, with one 8- or 16-byte store.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -286,13 +286,14 @@ gdn_linear_kernel(LinearArgs a) {
         mma_all(kk & 1);
     }
 
-    // ---- epilogue: bias, one rounding, and out through LDS.  A lane holds runs of four outputs of ONE token, 32 tokens per
-    //      instruction: stored from there, every instruction would touch 32 rows of the output with 8 or 16 bytes each.
-    //      Each wave turns its quarter around in its own quarter of the (now idle) stage ring instead: rows of 256 bytes (128
-    //      with the small tile), the 16-byte pieces of a row XOR-swizzled with the token so that both the writes (lane = token)
-    //      and the reads (lane = piece) spread over the banks; then 16 lanes store one row's 256 contiguous bytes.  A wave's LDS
-    //      operations execute in order, so no barrier stands between its writes and reads; the one barrier before keeps the
-    //      other waves' last fragment reads out of the way.
+    // ---- epilogue: bias, one rounding, and out through LDS.  A lane holds runs of four outputs of ONE token, 16 tokens per product:
+    //      stored from there, every instruction would touch 16 rows of the output with 32 or 64 bytes each.  Each wave turns its
+    //      outputs around in its own share (REGION) of the now idle stage ring instead: rows of 64, 128 or 256 bytes, one for a token,
+    //      with as many of the wave's outputs as 256 bytes hold (of shape 5's 80 all in bf16, in a pitch of 256 bytes, and 16 in
+    //      fp32), the 16-byte pieces of a row XOR-swizzled with the token so that both the writes (lane = token) and the reads (lane =
+    //      piece) spread over the banks; then 4, 8 or 16 lanes store one row's contiguous bytes.  A wave's LDS operations execute in
+    //      order, so no barrier stands between its writes and reads; the one barrier before keeps the other waves' last
+    //      fragment reads out of the way.
     constexpr int ES = OUT_BF16 ? 2 : 4;
     constexpr int WN = CFG::WN, WM = CFG::WM;                      // the wave's outputs and tokens
     constexpr int REGION = CFG::SMEM / CFG::NW;                    // the wave's part of the ring
