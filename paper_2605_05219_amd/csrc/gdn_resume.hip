@@ -494,11 +494,11 @@ hipError_t launch_fused(const FusedArgs& fa, int d, int gv, bool piped, bool one
 // which then reads and stages that head's q and k rows once for both (a fifth of a call's bytes with fp32 outputs).  It
 // needs an even group size.  The eight waves move in step through preparation and recurrence, so a chain takes longer than on the pipelined kernel that runs
 // single heads, and calls bound by their longest chain lose: at d = 128, 8 query/key heads under 16 value heads, fp32 / bf16 outputs, single against pairs in us, volume
-// over longest chain at 0.0186 us a unit and 4.6 a chunk: ratio 0.8 (11 k units, longest 56) 247 / 236 against 431 / 413, 1.4 (14 k, 42) 270 / 258 against 359 / 350, 2.6 (72 k,
-// 113) 1196 / 1142 against 1205 / 1135.  From there on the two are equal within 2 %, the pairs' fewer bytes worth a little with short chains or bf16 outputs, the single heads' pace with long
-// ones: 4.0 (94 k, 95) 1556 / 1483 against 1564 / 1484, 4.0 (281 k, 287) 4589 / 4452 against 4692 / 4430, 7.6 (206 k, 110) 3406 / 3249 against 3394 / 3207, 28 (866 k, 126) 14254 / 13531
-// against 14258 / 13530, 61 (121 k, 8) 2433 / 2324 against 2381 / 2256.  Even chains lose more, since pairs make half as many, longer pieces to deal out: 1152 of 125 chunks (ratio
-// 4.7) 2468 against 3045, 1792 (7.3) 3588 against 4109, 2304 of 64 (9.3) 2391 against 2630, 3328 of 64 (13) 3448 against 3721, 4096 of 64 (17) 4220 against 4253.  Pairs from a ratio of
+// over longest chain at 0.0186 us a unit and 4.6 a chunk: ratio 1.1 (14 k units, longest 51) 258 / 244 against 402 / 401, 1.9 (53 k, 113) 912 / 866 against 979 / 966, 2.4 (23 k,
+// 39) 427 / 404 against 430 / 408.  From there on the two are equal within 2 %, the pairs' fewer bytes worth a little with bf16 outputs: 3.3 (102 k, 126) 1735 / 1654 against 1721 /
+// 1634, 5.7 (90 k, 64) 1536 / 1457 against 1525 / 1440, 6.7 (183 k, 110) 3111 / 2959 against 3097 / 2917, 13 (366 k, 110, two layers) 6200 / 5898 against 6213 / 5825, 17 (201 k, 48) 3515 / 3346
+// against 3515 / 3324, 32 (63 k, 8) 1283 / 1235 against 1262 / 1190.  Even chains lose more, since pairs make half as many, longer pieces to deal out: 1152 of 125 chunks (ratio
+// 4.7) 2502 against 2977, 1792 (7.3) 3737 against 4193, 2304 of 64 (9.3) 2480 against 2667, 3328 of 64 (13) 3568 against 3760, 4096 of 64 (17) 4359 against 4438, 8192 of 16 (33) 2286 against 2282.  Pairs from a ratio of
 // 16 on.  At d = 64 a pair's 81 KB of LDS leave a compute unit one workgroup where three single-head ones fit, and pairs never
 // won (9.47 against 9.56 ms on 32768 chains, 1.39 against 1.17 on 4096): forced only.  gdn_tune_fused_pair forces the choice.
 std::atomic<int32_t> g_forced_pair{-1};
@@ -617,15 +617,18 @@ inline double fused_us(bool big, const CallSize& c) {
 }
 // Single heads on the pipelined kernel?  It takes a chain through 1.5 times as fast as the fused kernel with a compute unit to itself, but its first three steps only fill
 // the pipeline, and the fused kernel's workgroups, two to a compute unit at d = 128, three at 64, overlap each other's phases.  Measured, fused / pipelined (us):
-//   d = 128, chains x chunks   192 x 1 21 / 25, x 2 23 / 28, x 4 34 / 35, x 6 45 / 42, x 8 55 / 48; 288 x 1 23 / 31, x 4 47 / 52; 512 x 1 27 / 36, x 4 54 / 59, x 16 158 / 158; 1600 x 1 66 / 78, x 4 163 / 161,
-//       3200 x 1 145 / 140, x 4 307 / 290; ragged 768 of up to 8 (2.3 k units) 70 / 65, 1024 (3.3 k) 88 / 91, 1600 (5.5 k) 136 / 141, 1600 of up to 16 (8.3 k) 189 / 183, of up to 128 (39 k) 896 / 691
-//   d = 64   192 x 4 23 / 25, x 8 38 / 33, x 16 66 / 52; 288 x 2 20 / 25, x 8 48 / 53, x 16 89 / 92; 512 x 8 53 / 57, x 126 644 / 636; 1600 x 4 80 / 97, x 16 276 / 293; ragged 1024 of up to 16 (4.4 k) 76 / 64,
-//       1600 of up to 16 (8.7 k) 98 / 108, of up to 64 (24 k) 293 / 259, 3200 of up to 32 (27 k) 255 / 296; 8192 of up to 126 (232 k) 2064 / 2256
+//   d = 128, chains x chunks   192 x 2 21 / 28, x 4 33 / 35, x 6 44 / 41, x 8 54 / 48; 288 x 1 22 / 30, x 4 46 / 50, x 8 76 / 75; 512 x 1 24 / 35, x 4 53 / 57, x 16 165 / 163; 1600 x 1 69 / 79,
+//       x 4 161 / 160, 3200 x 1 142 / 138, x 4 303 / 290.  Ragged, at most 5 chunks a chain on average, by the volume's time over the longest chain's (0.0186 us a unit, 4.6 a chunk): 0.8 (512 chains, 2.3 k
+//       units, longest 12) 84 / 60, 1.1 (608, 2.7 k, 10) 77 / 67, 1.2 (608, 2.3 k, 8) 63 / 61, (592, 1.8 k, 6) 53 / 56, 1.4 (640, 2 k, 6) 56 / 60, (576, 2.8 k, 8) 70 / 79, 2.2 (960, 3.3 k, 6) 81 / 89, 2.8
+//       (2048, 5.6 k, 8) 143 / 144.  Longer ones: 1600 of up to 115 (31 k units) 779 / 568.  Over 122 calls of 120 to 2048 chains the lines at 5 chunks and 1.2 are 0.12 % from the better kernel on average, 9 % at
+//       most; at 4.5 and 1.5 0.8 and 13 %.
+//   d = 64   192 x 4 22 / 24, x 8 37 / 33, x 16 65 / 51; 288 x 2 18 / 24, x 8 48 / 50, x 16 88 / 86; 512 x 8 52 / 55, x 126 660 / 647; 1600 x 4 75 / 92, x 16 271 / 294; ragged 1024 of up to 16 (4.7 k units) 73 / 63,
+//       1600 of up to 16 (7.2 k) 84 / 94, of up to 64 (20 k) 283 / 226, 3200 of up to 32 (23 k) 235 / 262, of up to 126 (68 k) 683 / 688; 8192 of up to 126 (166 k) 1533 / 1663
 // gdn_tune_fused_per_cu, which has a meaning for the fused kernel only, forces that one.
 inline bool fused_piped(const gdn_shape& s, int gv, const CallSize& c) {
     if (gv != 1 || g_forced_per_cu.load() >= 1) return false;
     if (s.d_k != 128) return pipelined_us(false, c) < fused_us(false, c);
-    const bool short_on_average = 2 * c.units <= 9 * c.n_chains && per_256(0.0186) * (double)c.units >= 1.5 * 4.6 * c.longest;
+    const bool short_on_average = c.units <= 5 * c.n_chains && per_256(0.0186) * (double)c.units >= 1.2 * 4.6 * c.longest;
     return c.n_chains > 8 * chip_cus() || (c.longest > 4 && !short_on_average);
 }
 // The operand blocks of a call that may run the split launches take at most this much of the workspace: 1 GiB (72 k units), the throughput variants' slab, or what

@@ -390,6 +390,19 @@ def test_short_chains_get_the_fused_kernel_and_long_ones_the_pipelined(n_req, d,
     assert resume_path([64 * chunks] * n_req, 1, 16, d, 1 << 32) == path
 
 
+@pytest.mark.parametrize("lens,path", [
+    ([320] * 16 + [128] * 12 + [64] * 8, "fused"),                    # 576 chains, 1.8 k units, longest 5: volume over longest chain 1.45
+    ([384] * 12 + [128] * 24, "fused"),                               # longest 6: 1.3
+    ([512] * 18 + [128] * 18, "fused"),                               # longest 8, five chunks a chain on average: 1.46
+    ([384] * 12 + [64] * 24, "pipelined"),                            # 1.03
+    ([640] * 13 + [128] * 24, "pipelined"),                           # longest 10: 1.15
+    ([512] * 30 + [320] * 6, "pipelined"),                            # more than five chunks a chain on average
+])
+def test_ragged_calls_of_short_chains_get_the_fused_kernel_where_volume_outweighs_the_longest(lens, path):
+    """d = 128, 16 heads: at most five chunks a chain on average, and a volume that takes 1.2 times as long as the longest chain."""
+    assert resume_path(lens, 1, 16, 128, 1 << 32) == path
+
+
 def test_pairs_of_value_heads_only_where_volume_outweighs_the_longest_chain_by_far():
     """8 query/key heads under 16 value heads: 1152 even chains of 125 chunks 2.47 ms with single heads, 3.05 in pairs; 32768 chains of 8 2.43 and 2.38."""
     def path(lens, L):
