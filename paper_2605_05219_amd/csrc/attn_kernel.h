@@ -8,8 +8,8 @@
 // buffer loads to LDS (no registers) while the waves compute on the other stage.
 // At d = 128, where a key/value head has an even number of head blocks and the call is small (pairs_pay in attn_resume.hip), a workgroup has eight waves and takes two of these (the
 // same tokens of two query heads): they walk the same keys, which then cross from the L2 to the LDS once for 256 rows instead of once for
-// 128 (7 TB/s of such traffic at 900 TFLOP/s; the clock is held by the power limit, at 1.9 GHz, and 16 heads over 8192 tokens
-// go from 295 to 268 us).  At d = 256 eight waves that wait for each other at every tile cost more than the traffic (1592 -> 1650 us).
+// 128 (7 TB/s of such traffic at 900 TFLOP/s; the clock is held by the power limit, at 1.75 GHz, and 16 heads over 8192 tokens
+// go from 303 to 280 us, 517 to 493 k clocks).  At d = 256 eight waves that wait for each other at every tile cost more than the traffic (1592 -> 1650 us).
 //
 // Both contractions are computed transposed, so that a query is a COLUMN of every accumulator
 // tile and everything a softmax row needs sits in one lane (and its partner 32 lanes up):
