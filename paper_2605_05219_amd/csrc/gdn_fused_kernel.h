@@ -65,6 +65,7 @@ struct FusedArgs {
     const int32_t* req_order;        // requests, longest chain first
     int32_t* next_chain;             // one word, zero when the kernel starts: chains handed out beyond the first two rounds of gridDim.x (fused kernel,
                                      // which holds a chain in reserve) or beyond the first (pipelined kernel)
+    int32_t deal_back;               // pipelined kernel, at most two rounds: 1: the second is dealt backwards, not drawn (pairs_fit in gdn_resume.hip)
     const float* state_src;
     float* state_dst;
     int64_t src_slot_stride, dst_slot_stride;

@@ -18,6 +18,9 @@
 // before the draw's result is needed and three before the recurrence is done with that chunk, so no workgroup keeps a chain that another could
 // start.  (Held in reserve a whole chain ahead, as the fused kernel does, the fullest of 256 workgroups got 76 chunks of 1024 chains with
 // 60 on average and 66 in the longest, against 66: 293 -> 276 us; 458 of 391 on average and 345 in the longest, against 437: 1803 -> 1757.)
+// Where a second round dealt backwards, chain 2 gridDim.x - 1 - b to workgroup b, keeps every pair within the longest chain, it is dealt so (deal_back): no
+// deal is better, and draws among chains of a few chunks follow the order in which the workgroups happen to start (432 chains of up to 5 chunks, 2 on average, 42 us
+// drawn, 37 dealt; 448 of up to 10 57 / 54; 256 of 3 32 / 31).
 // In step t
 //     the recurrence waves work on item t - 3: substitution, outputs, state update, emission,
 //     the preparation waves prepare item t - 2 out of LDS, stage item t - 1 from registers to LDS (fp16) and fetch item t,
@@ -122,6 +125,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     struct Walk { int c, c_end, l, hv, hq, src; };
     Walk wk;
     int drawn = 0;                                              // in lane 0: the next chain less gridDim.x, drawn with the present one's last chunk
+    const bool deal_back = a.deal_back && a.n_chains <= 2 * (int)gridDim.x;
+    if (deal_back) drawn = (int)gridDim.x - 1 - (int)blockIdx.x;
     auto publish = [&](int t, bool live, bool fresh) {          // item t as the walk stands
         int w[8] = {0, 0, 0, 0, 0, 0, -1, SAME_CHAIN};
         if (live) {
@@ -153,7 +158,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     };
     bool live = true;
     auto draw_behind_last = [&] {     // a step ahead of its use
-        if (live && wk.c + 1 == wk.c_end && lane_ == 0) {
+        if (live && !deal_back && wk.c + 1 == wk.c_end && lane_ == 0) {
             int z = 0;
             pin(z);     // not a wave-uniform address to the compiler, which would wait for the result at once
             drawn = __hip_atomic_fetch_add(a.next_chain + z, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -162,8 +167,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     auto walk_on = [&](int t) {       // publishes item t, the one after the walk's present one
         bool fresh = false;
         if (live) {
-            if (wk.c + 1 < wk.c_end) ++wk.c;
-            else live = fresh = open_chain((int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn));
+            if (wk.c + 1 < wk.c_end) {
+                ++wk.c;
+            } else {
+                live = fresh = open_chain((int)gridDim.x + __builtin_amdgcn_readfirstlane(drawn));
+                if (deal_back) drawn = a.n_chains;      // (no third)
+            }
             draw_behind_last();
         }
         publish(t, live, fresh);

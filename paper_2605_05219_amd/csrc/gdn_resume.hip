@@ -576,6 +576,8 @@ inline double most_chunks(const CallSize& c, int64_t blocks, double spread) {
     }
     return chunks;
 }
+// Whether the chains of a call are at most two rounds that, the second dealt backwards, leave no compute unit more than the longest chain.
+inline bool pairs_fit(const CallSize& c) { return c.n_chains <= 2 * chip_cus() && most_chunks(c, 1, 1.0) <= c.longest; }
 // Split launches, cw columns to a workgroup: the blocks of all units, then the chunks of the fullest compute unit.  At d = 64 the chunks slow down as the call's data outgrow the
 // memory-side cache (1.03 us each up to 6.4 k units, 1.44 from 12 k), at d = 128, with twice the time for a chunk's data, hardly.
 struct SplitRates { double start, per_chunk, per_unit; };
@@ -1327,6 +1329,7 @@ static int32_t prefill_impl(const gdn_shape* shape, const void* q, const void* k
         fa.src_slot_stride = ra.src_slot_stride; fa.dst_slot_stride = dst_slot_stride;
         const int gv = fused_heads_per_wg(s, n_units, plan.max_chunks_per_req);
         fa.n_chains = (int32_t)((int64_t)n_live * s.L * s.H_v / gv);
+        fa.deal_back = pairs_fit(route.size);
         fa.next_chain = reinterpret_cast<int32_t*>(workspace) + (3 * (int64_t)n_chunks + 4 * (int64_t)n_req + 1);
         fa.L = s.L; fa.H_qk = s.H_qk; fa.H_v = s.H_v;
         fa.T_alloc = s.T_alloc;

@@ -1012,6 +1012,41 @@ def test_pipelined_kernel_hands_short_chains_over(d, o_dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("lens", [
+    [400] + [70, 64, 1, 128] * 6,                       # 400 chains, every pair within the longest chain: the second round is dealt
+    [330, 0, 300] + [130] * 14 + [60, 0, 190] * 5,      # 416 and two empty requests, full pairs
+    [540] * 2 + [350] * 14 + [340] * 16,                # 512 chains, pairs longer than the longest: drawn
+    [330] * 16, [330] + [30] * 16,                      # one round; one round and one request
+])
+@pytest.mark.parametrize("d", [128, 64])
+def test_pipelined_kernel_deals_or_draws_a_second_round(lens, d):
+    """At most two chains to a compute unit, on the pipelined kernel: every chain is run, once, whichever way the second round is handed out.  Against the
+    oracle, and bit for bit against the fused kernel."""
+    from paper_2605_05219_amd import binding as B
+    rng = np.random.default_rng(7150 + len(lens))
+    starts = [64 * (i % 3) for i in range(len(lens))]
+    per_req = [wl.token_streams(rng, 1, ln, 16, 16, d, d, "bf16") for ln in lens]
+    src = [-1 if s0 == 0 else i % 3 for i, s0 in enumerate(starts)]
+    emits = [[s0 + ln] if ln else [] for s0, ln in zip(starts, lens)]
+    call = wl.pack_call(1, 16, 16, d, d, "bf16", per_req, starts, src, emits, [[3 + i] if e else [] for i, e in enumerate(emits)], len(lens) + 3)
+    pool = rng.standard_normal((len(lens) + 3,) + call.slot_shape).astype(np.float32) * 0.1
+    prev = B.gdn_tune_fused(1)
+    prev_n = B.gdn_tune_fused_per_cu(-1)
+    try:
+        if d == 128:
+            assert call_path(call) == "pipelined"
+        check_call(call, pool, TOL["bf16"])
+        o1, p1 = run_call_gpu(call, pool)
+        B.gdn_tune_fused_per_cu(8)
+        assert call_path(call) == "fused"
+        o2, p2 = run_call_gpu(call, pool)
+        assert np.array_equal(o1.view(np.uint32), o2.view(np.uint32)) and np.array_equal(p1.view(np.uint32), p2.view(np.uint32))
+    finally:
+        B.gdn_tune_fused(prev)
+        B.gdn_tune_fused_per_cu(prev_n)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d,H_qk,H_v,o_dtype,columns", [(128, 3, 3, "f32", 32), (128, 3, 3, "f32", 64), (128, 1, 2, "bf16", 32), (128, 1, 2, "bf16", 64),
                                                         (64, 5, 5, "f32", 32), (64, 2, 4, "bf16", 32)])
 def test_split_launches_equal_the_fused_kernel_bitwise(d, H_qk, H_v, o_dtype, columns):
