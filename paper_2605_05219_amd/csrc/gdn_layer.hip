@@ -39,8 +39,13 @@ inline int64_t plan_ints(int32_t n_req, int32_t n_emit) { return 4 * (int64_t)n_
 // itself 10.6, 17.4, 18.7, 27.9 and 143).
 inline int32_t run_tokens(int64_t token_groups) { return token_groups / (4 * 64) <= 10 * 256 ? 4 : 8; }
 
-// Runs per wave: two where the rows have at most 32 groups of 8 channels (see the kernel).
-inline int runs_per_wave(int64_t C) { return C / 8 <= 32 ? 2 : 1; }
+// Runs per wave: two where that halves the empty lanes of a row's last wave and these weigh, in rows of fewer than 256 groups of 8 channels.  One / two runs a
+// wave, 3 layers, us: 72 groups, 16384 tokens 36.7 / 29.1 (29.7 when groups and runs were packed without gaps), 96 36.7 / 31.3, 208 80 / 72, 1000 requests of five tokens 63 / 62; 24
+// groups see the kernel; wider rows lose in calls of single tokens, whose requests two runs look up apart: 288 groups, 2048 of them 102 / 105, 528 188 / 209; 16384 tokens 98 / 96, 180 / 176.
+inline int runs_per_wave(int64_t C) {
+    const int64_t CG = C / 8;
+    return CG < 256 && (CG + 31) / 32 % 2 == 1 ? 2 : 1;
+}
 
 template <typename In, typename Out>
 hipError_t launch_inputs(const LayerArgs& a, int64_t blocks, int layers, hipStream_t stream) {

@@ -170,8 +170,8 @@ __global__ void __launch_bounds__(LAYER_THREADS) gdn_layer_inputs_kernel(LayerAr
     if ((int)blockIdx.x < a.conv_blocks) {
         // ---- short convolution + SiLU (+ L2 normalisation of q and k): a wave takes 64 channel groups over one run of tokens, a block the
         // same channels over four runs.  The taps go through LDS: read by each thread for itself they were eight loads of 64 lines
-        // each, which is as much as a run of eight rows (see run_tokens for what that and short runs give).  Rows of at most 32
-        // groups go two to a wave (RPW = 2; 24 groups, 3 layers, 16384 requests of one token: 93 us in waves of their own, 73 so, 85
+        // each, which is as much as a run of eight rows (see run_tokens for what that and short runs give).  Rows whose last
+        // 64 groups are half empty go two to a wave, 32 groups of each (RPW = 2, see runs_per_wave; 24 groups, 3 layers, 16384 requests of one token: 93 us in waves of their own, 73 so, 85
         // when groups and runs were packed without gaps; of five tokens 44, 39, 40).
         constexpr int LPR = 64 / RPW;              // lanes per run
         __shared__ float4 taps[8 * LPR];           // channel c of group l at 8 l + (c ^ (l & 7)): lanes read across the banks

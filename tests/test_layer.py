@@ -256,11 +256,12 @@ def test_layer_inputs_with_channels_and_runs_that_fill_no_block(K, lens, dtype):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("H_qk,H_v,d_k,d_v", [(1, 1, 64, 64), (1, 2, 64, 64), (1, 3, 64, 64)])   # 24, 32 and 40 groups: two runs a wave, two, one
+@pytest.mark.parametrize("H_qk,H_v,d_k,d_v", [(1, 1, 64, 64), (1, 2, 64, 64), (1, 3, 64, 64),   # 24, 32 and 40 groups: two runs a wave, two, one
+                                             (3, 3, 64, 64), (1, 3, 128, 128), (4, 4, 64, 64)])   # 72, 80 and 96: two
 @pytest.mark.parametrize("K,lens", [(4, [1, 1, 4, 5, 0, 9, 3, 1]), (3, [2, 13]), (4, [1] * 17)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_layer_inputs_of_narrow_rows(H_qk, H_v, d_k, d_v, K, lens, dtype):
-    """Rows of at most 32 channel groups go two runs to a wave: runs of different lengths and requests side by side, a last block with few
+    """Rows whose last wave would be half empty go two runs to a wave: runs of different lengths and requests side by side, a last block with few
     of its eight runs, against the oracle."""
     c = wl.layer_case(2800 + K, H_qk, H_v, d_k, d_v, K, dtype, lens, [64] * len(lens), [[64 + n] if n else [] for n in lens])
     ref = oracle_inputs(c, 1e-6)
